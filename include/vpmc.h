@@ -170,9 +170,10 @@ typedef struct {
                                (the CSR queue runs at most 1024 threads in physics mode, 768 in
                                straight mode, and its LDS tile shrinks with the workgroup) */
     int grid_blocks;        /* 0 = tuned default */
-    int hist_per_lane;      /* CSR work-queue chunk = 64 * hist_per_lane histories; 0 = default 4 */
+    int hist_per_lane;      /* CSR work queue: a wavefront draws 64 * min(hist_per_lane, 32) particles of its
+                               row at a time; 0 = default 1 */
     int max_slots;          /* CSR rows resident at once (<= 1024); 0 = sized from memory */
-    uint64_t queue_cap;     /* CSR work queue: iterations (chunks drawn, row picks, waits) a
+    uint64_t queue_cap;     /* CSR work queue: iterations (draws, row picks, waits) a
                                wavefront may make before it gives up and the run returns
                                VPMC_E_ABORTED with no rows written; 0 = 2^40 (no practical cap) */
 } vpmc_opts;

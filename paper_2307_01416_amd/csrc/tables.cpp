@@ -134,13 +134,14 @@ void split_pair(double x, float *hi, float *lo) {
 void pack_device_tables(float *blob) {
     const HostTables &t = host_tables();
     memset(blob, 0, sizeof(float) * TAB_FLOATS);
+    float *const low = blob + TAB_HI_FLOATS;
     for (int i = 0; i < NE; ++i) {
-        split_pair(t.E[i], blob + TAB_E + i, blob + TAB_EL + i);
-        if (i + 1 < NE) split_pair(t.E[i + 1] - t.E[i], blob + TAB_DWH + i, blob + TAB_DWL + i);
+        split_pair(t.E[i], blob + TAB_E + i, low + TABL_E + i);
+        if (i + 1 < NE) split_pair(t.E[i + 1] - t.E[i], blob + TAB_DWH + i, low + TABL_DW + i);
     }
     for (int m = 0; m < NMAT; ++m) {
-        float *b = blob + TAB_MAT0 + m * TAB_PER_MAT;
-        float *bl = blob + TAB_LMAT0 + m * TAB_PER_LMAT;
+        float *b = blob + TAB_SHARED + kTabSlot[m] * TAB_PER_MAT;
+        float *bl = low + TABL_SHARED + kTabSlot[m] * TAB_PER_LMAT;
         for (int i = 0; i < NE; ++i) {
             b[T_R * NE + i] = (float)(10.0 * t.R[m][i]);
             if (i + 1 < NE) {

@@ -185,11 +185,11 @@ struct vpmc_ctx {
     vpmc_stats last_stats{};
     std::vector<hipEvent_t> events;
     // influence-matrix builder
-    DevBuf slot_grid, slot_mark, slot_cnt, slot_coff, slot_rowcnt, q_stage, q_rownext;
+    DevBuf slot_grid, slot_mark, slot_cnt, slot_coff, slot_rowcnt, q_stage, q_ctl;
     int n_slots = 0;
     size_t slot_nvox = 0;
     bool slots_dirty = false;
-    DevBuf rows, chunk_off, heads, row_off, row_nnz, used, flags, fields_tab, poly_off, polys, scen_tab, csr_col, csr_q;
+    DevBuf rows, grp_off, heads, row_off, row_nnz, used, flags, fields_tab, poly_off, polys, scen_tab, csr_col, csr_q;
     unsigned long long csr_cap = 0, csr_total = 0, csr_cap_hint = 0;
     int csr_rows = 0;
     bool csr_valid = false;
@@ -408,69 +408,12 @@ int grow_keep(vpmc_ctx *c, DevBuf &b, size_t keep_bytes, size_t bytes, size_t ca
     return VPMC_OK;
 }
 
-// LDS tile box of a row (voxel indices, x fastest): the voxels along the
-// spot's central ray from its CT entry to 1.15 x its CSDA range in water
-// (less the range shifter) + 10 mm,
-// widened laterally by the largest half-width (<= 15 mm, 0.5 mm steps) that
-// keeps the box within cap voxels.  No box (tn = 0) when the ray misses the
-// grid or no width fits.
-static void tile_box(const FieldDev &f, const SpotDev &sp, const ScenDev &sc, const GeomDev &g, int cap, int lo[3],
-                     int n[3]) {
-    lo[0] = lo[1] = lo[2] = 0;
-    n[0] = n[1] = n[2] = 0;
-    if (cap <= 0) return;
-    const int gn[3] = {g.nx, g.ny, g.nz};
-    double p0[3], d[3], glo[3], ghi[3];
-    for (int k = 0; k < 3; ++k) {
-        p0[k] = (double)f.iso[k] + sp.x * (double)f.ex[k] + sp.y * (double)f.ey[k] - (double)sc.shift[k];
-        d[k] = f.ez[k];
-        glo[k] = g.lo[k];
-        ghi[k] = g.lo[k] + gn[k] * (double)g.sp[k];
-    }
-    double tn = -1e30, tf = 1e30;
-    for (int k = 0; k < 3; ++k) {
-        if (std::fabs(d[k]) < 1e-12) {
-            if (p0[k] < glo[k] || p0[k] >= ghi[k]) return;
-            continue;
-        }
-        const double t1 = (glo[k] - p0[k]) / d[k], t2 = (ghi[k] - p0[k]) / d[k];
-        tn = std::max(tn, std::min(t1, t2));
-        tf = std::min(tf, std::max(t1, t2));
-    }
-    if (!(tf > tn)) return;
-    // water range left after the range shifter (its water-equivalent
-    // thickness taken low, 0.95 x rho x t), with 15 % and 10 mm to spare
+// Water-equivalent range (mm) left to a spot's particles at the CT entry: the
+// CSDA range in water less the range shifter's (its thickness taken low).
+float spot_range_we(const FieldDev &f, const SpotDev &sp) {
     double rw = 10.0 * range_host(MAT_WATER, std::min((double)sp.e0, E_HI));
     if (f.has_rs) rw -= 0.95 * (double)f.rs_rho * (double)f.rs_t;
-    const double reach = 1.15 * std::max(rw, 0.0) + 10.0;
-    const double t1 = std::min(tf, tn + reach);
-    int mn[3], mx[3], a = 0;
-    for (int k = 0; k < 3; ++k) {
-        auto cell = [&](double t) {
-            const int i = (int)std::floor((p0[k] + t * d[k] - glo[k]) / g.sp[k]);
-            return std::min(std::max(i, 0), gn[k] - 1);
-        };
-        mn[k] = std::min(cell(tn), cell(t1));
-        mx[k] = std::max(cell(tn), cell(t1));
-        if (std::fabs(d[k]) > std::fabs(d[a])) a = k;
-    }
-    for (double h = 15.0; h >= 0.0; h -= 0.5) {
-        int l[3], w[3];
-        size_t vol = 1;
-        for (int k = 0; k < 3; ++k) {
-            const int hk = k == a ? 0 : (int)std::floor(h / g.sp[k]);
-            l[k] = std::max(0, mn[k] - hk);
-            w[k] = std::min(gn[k] - 1, mx[k] + hk) - l[k] + 1;
-            vol *= (size_t)w[k];
-        }
-        if (vol <= (size_t)cap) {
-            for (int k = 0; k < 3; ++k) {
-                lo[k] = l[k];
-                n[k] = w[k];
-            }
-            return;
-        }
-    }
+    return (float)std::max(rw, 0.0);
 }
 
 int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario *scen, int n_scen, const vpmc_opts *o,
@@ -480,11 +423,11 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     const size_t cap = o->max_device_bytes;
     hipStream_t st = (hipStream_t)o->hip_stream;
     // histories per lane: the caller's, else the one tuned for a field, else
-    // the last tuned one, else 4 (per epoch: the field with most of its rows)
+    // the last tuned one, else 1 (per epoch: the field with most of its rows)
     auto field_hpl = [&](uint32_t field_id) {
         if (o->hist_per_lane > 0) return o->hist_per_lane;
         if (field_id < VPMC_MAX_FIELDS && c->tuned_csr_hpl_field[field_id]) return c->tuned_csr_hpl_field[field_id];
-        return c->tuned_csr_hpl ? c->tuned_csr_hpl : 4;
+        return c->tuned_csr_hpl ? c->tuned_csr_hpl : 1;
     };
     int rc;
 
@@ -494,6 +437,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     std::vector<int> poff(nf);
     std::vector<float2> polys;
     std::vector<SpotDev> sd;
+    std::vector<float> range_we;
     std::vector<int> spot_base(nf);
     for (int f = 0; f < nf; ++f) {
         const FieldState &fs = c->fields[bf[f].field_id];
@@ -509,6 +453,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
             d.nh = s.n_histories;
             d.scale = s.n_histories ? (float)ldexp((double)s.weight / (double)s.n_histories, k) : 0.0f;
             sd.push_back(d);
+            range_we.push_back(spot_range_we(ftab[f], d));
         }
     }
     if (polys.size() > (size_t)POLY_LDS)
@@ -526,6 +471,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
                 r.spot_global = (uint32_t)(spot_base[f] + i);
                 r.scen = sc;
                 r.n_hist = bf[f].spots[i].n_histories;
+                r.range_we = range_we[r.spot_global];
                 rows.push_back(r);
             }
     const int R = (int)rows.size();
@@ -553,11 +499,9 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
                                                 : std::max(1, dev_cus * (o->physics == 0 ? 12 : 16) / (q_threads / 64)));
     int tile_cap = queue_tile_cap(o->physics, q_threads);
     {
-        const size_t stat = (o->physics == 0 ? TAB_FLOATS : TAB_HI_FLOATS) * 4 + POLY_LDS * 8 + 256;
-        tile_cap = (int)std::min<size_t>((size_t)tile_cap, lds_wg > stat ? (lds_wg - stat) / 8 : 0);
+        const size_t stat = queue_static_lds(o->physics);
+        tile_cap = (int)std::min<size_t>((size_t)tile_cap, lds_wg > stat ? (lds_wg - stat) / 4 : 0);
     }
-    for (RowDev &r : rows)
-        tile_box(ftab[r.field], sd[r.spot_global], stab[r.scen], c->geom, tile_cap, r.tlo, r.tn);
 
     // slots: dense int64 grid + touched-block bytes per resident row
     const size_t nblk = (nvox + 31) / 32, nchunk = (nblk + 255) / 256;
@@ -591,13 +535,14 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
         c->slots_dirty = false;
     }
 
-    // epochs, their histories per lane and chunk prefixes
+    // epochs, their histories per lane and the rows' groups of 64 histories
     const int E = (R + G - 1) / std::max(G, 1);
-    std::vector<unsigned long long> choff;
-    std::vector<size_t> ep_choff(E);
-    std::vector<unsigned long long> ep_chunks(E);
+    std::vector<unsigned long long> goff((size_t)R + 1);
+    goff[0] = 0;
+    for (int r = 0; r < R; ++r) goff[(size_t)r + 1] = goff[(size_t)r] + ((unsigned long long)rows[r].n_hist + 63) / 64;
     std::vector<int> ep_hpl(E);
     int hpl_max = 1;
+    unsigned long long ep_groups = 0;   // of the largest epoch
     for (int e = 0; e < E; ++e) {
         const int r0 = e * G, r1 = std::min(R, r0 + G);
         int best_f = -1, best_n = 0;
@@ -609,19 +554,43 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
         }
         ep_hpl[e] = field_hpl(best_f < 0 ? 0u : (uint32_t)best_f);
         hpl_max = std::max(hpl_max, ep_hpl[e]);
-        const unsigned long long chunk = 64ull * (unsigned long long)ep_hpl[e];
-        ep_choff[e] = choff.size();
-        unsigned long long acc = 0;
-        choff.push_back(0);
-        for (int r = r0; r < r1; ++r) {
-            acc += (rows[r].n_hist + chunk - 1) / chunk;
-            choff.push_back(acc);
-        }
-        ep_chunks[e] = acc;
+        ep_groups = std::max(ep_groups, goff[(size_t)r1] - goff[(size_t)r0]);
     }
+    // staging buffer: a whole epoch's histories up to kMaxStage; with a cap on
+    // device memory, or when the memory is not there, down to one refill of
+    // every wave (the epoch is then transported in several rounds)
+    const unsigned long long stage_min = queue_stage_min(q_blocks, q_threads, hpl_max);
+    unsigned long long stage_n = std::max<unsigned long long>(64, std::min(ep_groups * 64ull, cap ? stage_min : std::max(kMaxStage, stage_min)));
+    for (;;) {
+        rc = ensure(c, c->q_stage, stage_n * kStageFields * sizeof(float), cap);
+        if (rc != VPMC_E_OOM || cap || stage_n <= stage_min) break;
+        (void)hipGetLastError();
+        stage_n = std::max(stage_min, stage_n / 2 / 64 * 64);
+    }
+    if (rc) return rc;
+    // rounds: (epoch, first group, first row, one past the last row)
+    struct Round {
+        unsigned long long g0, g1;
+        int r0, r1;
+    };
+    std::vector<Round> rounds;
+    std::vector<size_t> ep_round((size_t)E + 1);
+    for (int e = 0; e < E; ++e) {
+        ep_round[e] = rounds.size();
+        const int r0 = e * G, r1 = std::min(R, r0 + G);
+        const unsigned long long per = std::max(1ull, stage_n / 64);
+        for (unsigned long long g0 = goff[(size_t)r0]; g0 < goff[(size_t)r1]; g0 += per) {
+            Round q{g0, std::min(goff[(size_t)r1], g0 + per), 0, 0};
+            const auto b = goff.begin();
+            q.r0 = (int)(std::upper_bound(b, goff.end(), q.g0) - b) - 1;       // the row of its first group
+            q.r1 = (int)(std::lower_bound(b, goff.end(), q.g1) - b);           // past the row of its last
+            rounds.push_back(q);
+        }
+    }
+    ep_round[(size_t)E] = rounds.size();
     if ((rc = ensure(c, c->rows, std::max<size_t>(1, rows.size()) * sizeof(RowDev), cap))) return rc;
-    if ((rc = ensure(c, c->chunk_off, std::max<size_t>(1, choff.size()) * 8, cap))) return rc;
-    if ((rc = ensure(c, c->heads, std::max(1, E) * 8, cap))) return rc;
+    if ((rc = ensure(c, c->grp_off, goff.size() * 8, cap))) return rc;
+    if ((rc = ensure(c, c->heads, std::max<size_t>(1, rounds.size()) * 8, cap))) return rc;
     if ((rc = ensure(c, c->row_off, std::max(1, R) * 8, cap))) return rc;
     if ((rc = ensure(c, c->row_nnz, std::max(1, R) * 8, cap))) return rc;
     if ((rc = ensure(c, c->used, 8, cap))) return rc;
@@ -634,12 +603,14 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     if ((rc = ensure(c, c->ledger, (size_t)n_scen * NLEDGER * 8, cap))) return rc;
     if ((rc = ensure(c, c->stats, 16, cap))) return rc;
     if (rows.size()) HIP_TRY(hipMemcpyAsync(c->rows.ptr, rows.data(), rows.size() * sizeof(RowDev), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(c->chunk_off.ptr, choff.data(), choff.size() * 8, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(c->grp_off.ptr, goff.data(), goff.size() * 8, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(c->fields_tab.ptr, ftab.data(), nf * sizeof(FieldDev), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(c->poly_off.ptr, poff.data(), nf * sizeof(int), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(c->polys.ptr, polys.data(), polys.size() * sizeof(float2), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(c->spots.ptr, sd.data(), sd.size() * sizeof(SpotDev), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(c->scen_tab.ptr, stab.data(), n_scen * sizeof(ScenDev), hipMemcpyHostToDevice, st));
+    HIP_TRY(launch_tile_box(c->geom, (RowDev *)c->rows.ptr, R, (const FieldDev *)c->fields_tab.ptr,
+                            (const SpotDev *)c->spots.ptr, (const ScenDev *)c->scen_tab.ptr, tile_cap, st));
     // initial CSR capacity: the previous run's total, else a per-row guess
     unsigned long long want = c->csr_cap_hint ? c->csr_cap_hint : (unsigned long long)std::max(R, 1) * 16384ull;
     want = std::min<unsigned long long>(want, (unsigned long long)std::max(R, 1) * nvox);
@@ -699,8 +670,8 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     Q.iter_cap = o->queue_cap ? (unsigned long long)o->queue_cap : kDefaultQueueCap;
     Q.flags = (unsigned int *)c->flags.ptr;
 
-    if ((rc = ensure(c, c->q_stage, queue_stage_floats(q_blocks, q_threads, hpl_max) * sizeof(float), cap))) return rc;
-    if ((rc = ensure(c, c->q_rownext, (size_t)std::max(R, 1) * 8, cap))) return rc;
+    if ((rc = ensure(c, c->q_ctl, (size_t)std::max(R, 1) * sizeof(RowCtl), cap))) return rc;
+    Q.grp_off = (const unsigned long long *)c->grp_off.ptr;
     Q.stage = (float *)c->q_stage.ptr;
     Q.refill_min = kRefillMin;
     Q.tile_cap = tile_cap;
@@ -713,8 +684,8 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     auto clear_counters = [&]() -> int {
         HIP_TRY(launch_fill_u64((unsigned long long *)c->ledger.ptr, (size_t)n_scen * NLEDGER, 0ull, st));
         HIP_TRY(launch_fill_u64((unsigned long long *)c->stats.ptr, 2, 0ull, st));
-        HIP_TRY(launch_fill_u64((unsigned long long *)c->heads.ptr, (size_t)std::max(1, E), 0ull, st));
-        HIP_TRY(launch_fill_u64((unsigned long long *)c->q_rownext.ptr, (size_t)std::max(1, R), 0ull, st));
+        HIP_TRY(launch_fill_u64((unsigned long long *)c->heads.ptr, std::max<size_t>(1, rounds.size()), 0ull, st));
+        HIP_TRY(launch_fill_u64((unsigned long long *)c->q_ctl.ptr, (size_t)std::max(1, R), 0ull, st));
         HIP_TRY(launch_fill_u64((unsigned long long *)c->used.ptr, 1, 0ull, st));
         HIP_TRY(launch_fill_u64((unsigned long long *)c->flags.ptr, 1, 0ull, st));
         return VPMC_OK;
@@ -723,12 +694,30 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
         QueueDev Qe = Q;
         Qe.row_begin = e * G;
         Qe.n_rows = std::min(R, (e + 1) * G) - e * G;
-        Qe.chunk_off = (const unsigned long long *)c->chunk_off.ptr + ep_choff[e];
-        Qe.n_chunks = ep_chunks[e];
         Qe.hist_per_lane = ep_hpl[e];
-        Qe.head = (unsigned long long *)c->heads.ptr + e;
-        Qe.row_next = (unsigned long long *)c->q_rownext.ptr + Qe.row_begin;
         return Qe;
+    };
+    // beam line and patient transport of an epoch, round by round
+    auto transport_epoch = [&](const QueueDev &Qe, int e) -> hipError_t {
+        hipError_t he = hipSuccess;
+        for (size_t i = ep_round[e]; i < ep_round[(size_t)e + 1] && he == hipSuccess; ++i) {
+            const Round &rd = rounds[i];
+            QueueDev Qr = Qe;
+            Qr.row_begin = rd.r0;
+            Qr.n_rows = rd.r1 - rd.r0;
+            Qr.slot0 = (uint32_t)(rd.r0 - Qe.row_begin);
+            Qr.grid = Qe.grid + (size_t)Qr.slot0 * gstride;
+            Qr.mark = Qe.mark + (size_t)Qr.slot0 * mstride;
+            Qr.g_begin = rd.g0;
+            Qr.g_end = rd.g1;
+            Qr.head = (unsigned long long *)c->heads.ptr + i;
+            Qr.ctl = (RowCtl *)c->q_ctl.ptr;
+            // (the counters of a row that a previous round began)
+            if (i > ep_round[e]) he = launch_fill_u64((unsigned long long *)c->q_ctl.ptr + rd.r0, 1, 0ull, st);
+            if (he == hipSuccess) he = launch_beam(c->geom, Qr, dev_cus, st);
+            if (he == hipSuccess) he = launch_queue(c->geom, Qr, q_blocks, q_threads, st);
+        }
+        return he;
     };
     // compaction passes of one epoch (count per chunk, scan per row; emit)
     auto count_rows = [&](const QueueDev &Qe) -> hipError_t {
@@ -763,8 +752,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
         int crc = clear_counters();
         for (int e = 0; e < E && crc == VPMC_OK; ++e) {
             const QueueDev Qe = epoch_queue(e);
-            hipError_t he = hipSuccess;
-            if (Qe.n_chunks) he = launch_queue(c->geom, Qe, q_blocks, q_threads, st);
+            hipError_t he = transport_epoch(Qe, e);
             if (he == hipSuccess) he = count_rows(Qe);
             if (he == hipSuccess)
                 he = launch_csr_offsets((const unsigned int *)c->slot_rowcnt.ptr, Qe.n_rows, Qe.row_begin,
@@ -809,8 +797,8 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
             const QueueDev Qe = epoch_queue(e);
             if (sur_on) HIP_TRY(launch_fill_u64((unsigned long long *)c->sur_cnt.ptr, 1, 0ull, st));
             HIP_TRY(hipEventRecord(c->events[2], st));
-            if (Qe.n_chunks) HIP_TRY(launch_queue(c->geom, Qe, q_blocks, q_threads, st));
-            if (sur_on && Qe.n_chunks) {
+            HIP_TRY(transport_epoch(Qe, e));
+            if (sur_on && ep_round[(size_t)e + 1] > ep_round[e]) {
                 // deferred brass entries of this epoch: network, then resume
                 unsigned long long cnt = 0;
                 HIP_TRY(hipMemcpyAsync(&cnt, c->sur_cnt.ptr, sizeof cnt, hipMemcpyDeviceToHost, st));
@@ -1214,7 +1202,7 @@ void vpmc_destroy(vpmc_ctx *c) {
         }
         for (DevBuf *b : {&c->tallies, &c->let_tallies, &c->qbatch, &c->s2, &c->ledger, &c->spots, &c->offsets,
                           &c->stage_dose, &c->stage_sigma, &c->stats, &c->slot_grid, &c->slot_mark, &c->slot_cnt,
-                          &c->slot_coff, &c->slot_rowcnt, &c->q_stage, &c->q_rownext, &c->rows, &c->chunk_off, &c->heads, &c->row_off, &c->row_nnz, &c->used,
+                          &c->slot_coff, &c->slot_rowcnt, &c->q_stage, &c->q_ctl, &c->rows, &c->grp_off, &c->heads, &c->row_off, &c->row_nnz, &c->used,
                           &c->flags, &c->fields_tab, &c->poly_off, &c->polys, &c->scen_tab, &c->csr_col,
                           &c->csr_q, &c->mlp_w, &c->mlp_wb, &c->mlp_m, &c->mlp_v, &c->mlp_g, &c->mlp_act,
                           &c->mlp_io, &c->mlp_dx, &c->mlp_dy, &c->mlp_dt, &c->mlp_idx, &c->sur_rec,

@@ -14,20 +14,24 @@ constexpr double E_LO = 1.0;
 constexpr double E_HI = 256.0;
 enum Material { MAT_WATER = 0, MAT_AIR = 1, MAT_PMMA = 2, MAT_BRASS = 3, MAT_BONE = 4 };
 
-// FP32 device blob, high parts first.  Shared: energy nodes, segment energy
-// widths E_i+1 - E_i.  Per material: R, dE/dR per segment, R_i+1 - R_i,
+// FP32 device blob, high parts first.  Shared: segment energy widths
+// E_i+1 - E_i, energy nodes.  Per material: R, dE/dR per segment, R_i+1 - R_i,
 // omega^2, T, Sigma_nuc; NE floats each, all per unit of density x path
 // length in mm (10 x g/cm^2).  Then the low parts that make the node, width,
 // slope and range-width tables (high, low) FP32 pairs of the FP64 values, for
-// the double-float bookkeeping of the deterministic mode; the physics-mode
-// kernels stage only the high block (32 KiB) in LDS.
-enum { TAB_E = 0, TAB_DWH = NE, TAB_MAT0 = 2 * NE, TAB_PER_MAT = 6 * NE };
+// the double-float bookkeeping of the deterministic mode.  The materials of
+// the patient come first, those of the beam line last: each kernel stages in
+// LDS the shared tables and the materials it meets.
+enum { TAB_DWH = 0, TAB_E = NE, TAB_SHARED = 2 * NE, TAB_PER_MAT = 6 * NE };
 enum { T_R = 0, T_SH = 1, T_DH = 2, T_W2 = 3, T_T = 4, T_SN = 5 };
-constexpr int TAB_HI_FLOATS = 2 * NE + NMAT * 6 * NE;    // 8192 floats = 32 KiB
-enum { TAB_EL = TAB_HI_FLOATS, TAB_DWL = TAB_HI_FLOATS + NE, TAB_LMAT0 = TAB_HI_FLOATS + 2 * NE,
-       TAB_PER_LMAT = 2 * NE };
+enum { TABL_E = 0, TABL_DW = NE, TABL_SHARED = 2 * NE, TAB_PER_LMAT = 2 * NE };
 enum { L_SL = 0, L_DL = 1 };
-constexpr int TAB_FLOATS = TAB_HI_FLOATS + 2 * NE + NMAT * 2 * NE;   // 11264 floats = 44 KiB
+enum { DM_WATER = 0, DM_AIR = 1, DM_BONE = 2, DM_PMMA = 3, DM_BRASS = 4 };   // order of the materials in the blob
+constexpr int kTabSlot[NMAT] = {DM_WATER, DM_AIR, DM_PMMA, DM_BRASS, DM_BONE};
+constexpr int tab_hi_floats(int nm) { return TAB_SHARED + nm * TAB_PER_MAT; }
+constexpr int tab_lo_floats(int nm) { return TABL_SHARED + nm * TAB_PER_LMAT; }
+constexpr int TAB_HI_FLOATS = tab_hi_floats(NMAT);
+constexpr int TAB_FLOATS = TAB_HI_FLOATS + tab_lo_floats(NMAT);
 
 struct MaterialDef {
     double z_over_a, mean_exc_ev, rad_len_gcm2, nuc_coeff, density;
@@ -150,7 +154,8 @@ struct RowDev {
     uint32_t spot_global; // index into the flattened spot table
     int scen;
     uint32_t n_hist;
-    int tlo[3], tn[3];    // LDS tile box of the row in voxel indices (tn = 0: none)
+    float range_we;       // water-equivalent range at the CT entry, mm
+    int tlo[3], tn[3];    // LDS tile box of the row in voxel indices (tn = 0: none; tile_box_kernel)
 };
 
 struct ScenDev {
@@ -158,17 +163,27 @@ struct ScenDev {
     float range_scale;
 };
 
+// Per row of the run: particles staged by the beam line and records drawn by
+// the patient loop (a row's part of one round, at most kMaxStage records).
+struct RowCtl {
+    unsigned int staged, next;
+};
+
+// An epoch's histories are transported in rounds: as many groups of 64
+// histories (of one row each) as the staging buffer holds, normally all.
 struct QueueDev {
     const RowDev *rows;
-    const unsigned long long *chunk_off;  // [n_rows + 1] chunk prefix of this epoch's rows
-    int row_begin, n_rows;
-    unsigned long long n_chunks;
-    unsigned long long *head;             // fresh-row counter of this epoch
-    unsigned long long *row_next;         // [n_rows] chunk counter per row of this epoch
-    int tile_cap;                         // int64 entries of the workgroup's LDS tile
-    int hist_per_lane;                    // one chunk = 64 * hist_per_lane histories
+    const unsigned long long *grp_off;    // [rows of the run + 1] prefix of the rows' groups
+    unsigned long long g_begin, g_end;    // groups of this round
+    int row_begin, n_rows;                // rows of this round (of the epoch in the compaction passes)
+    uint32_t slot0;                       // slot of the round's first row (grid and mark start there)
+    unsigned long long *head;             // fresh-row counter of this round
+    RowCtl *ctl;                          // [rows of the run]
+    int tile_cap;                         // 32-bit entries of the workgroup's LDS tile (< 2^16)
+    int hist_per_lane;                    // one draw = 64 * hist_per_lane staged records
+    int beam_groups;                      // consecutive groups a wave of the beam line takes at a time
     int refill_min;                       // idle lanes that trigger a refill in the patient loop
-    float *stage;                         // [waves of the launch][64 * min(hist_per_lane, kStageHpl)] staged VPs (64 B)
+    float *stage;                         // [64 * (g_end - g_begin)] staged VPs (64 B)
     const FieldDev *fields;
     const int *poly_off;                  // per field: offset into polys
     const float2 *polys;
@@ -192,16 +207,23 @@ struct QueueDev {
 constexpr unsigned long long kDefaultQueueCap = 1ull << 40;   // far above any run's chunk count
 constexpr unsigned int kFlagAborted = 4u;
 
-// staging floats the queue kernel needs for a launch shape (per wave up to
-// 64 * kStageHpl VPs of 16 words)
+// staging records of a round: all histories of an epoch up to kMaxStage
+// (2 GiB of 64 B records: a head epoch of 1000 rows x 2e4 histories fits); with
+// a cap on device memory what queue_stage_min gives, one refill of every wave
 constexpr size_t kStageFields = 16;
 constexpr int kStageHpl = 32;
-constexpr int kRefillMin = 8;   // idle lanes that trigger a refill of the patient loop
-inline size_t queue_stage_floats(int blocks, int threads, int hist_per_lane) {
-    const size_t hps = (size_t)(hist_per_lane < kStageHpl ? hist_per_lane : kStageHpl);
-    return (size_t)blocks * (size_t)((threads + 63) / 64) * kStageFields * 64 * hps;
+constexpr unsigned long long kMaxStage = 1ull << 25;
+constexpr int kBeamGroups = 16;  // consecutive groups a wave of the beam line takes at a time, at most
+constexpr int kRefillMin = 8;    // idle lanes that trigger a refill of the patient loop
+inline unsigned long long queue_stage_min(int blocks, int threads, int hist_per_lane) {
+    const int hps = hist_per_lane < kStageHpl ? hist_per_lane : kStageHpl;
+    return (unsigned long long)blocks * (unsigned long long)((threads + 63) / 64) * 64ull * (unsigned long long)hps;
 }
+hipError_t launch_tile_box(const GeomDev &g, RowDev *rows, int n, const FieldDev *fields, const SpotDev *spots,
+                           const ScenDev *scen, int cap, hipStream_t s);
+hipError_t launch_beam(const GeomDev &g, QueueDev Q, int cus, hipStream_t s);
 hipError_t launch_queue(const GeomDev &g, const QueueDev &Q, int blocks, int threads, hipStream_t s);
+size_t queue_static_lds(unsigned physics);
 // workgroup size the queue kernel runs with for a requested size, and the
 // LDS tile entries that leave the CU its full wave occupancy
 int queue_threads(unsigned physics, int threads);

@@ -121,6 +121,27 @@ __device__ __forceinline__ void box_muller_fast(uint32_t a, uint32_t b, float &z
 }
 
 // ------------------------------------------------------------ table lookups
+// The staged tables of a kernel: high parts, low parts (deterministic mode
+// only) and, in the kernels that stage them, where the beam line's materials are.
+struct Tabs {
+    const float *hi, *lo;
+    int pmma, brass;
+};
+
+// Stages the shared tables and materials [m0, m0 + NM) of the blob in LDS.
+template <bool X, int NM>
+__device__ __forceinline__ void stage_tables(float *hi, float *lo, const float *blob, int m0) {
+    constexpr int n0 = TAB_SHARED / 4, n1 = NM * TAB_PER_MAT / 4, l0 = TABL_SHARED / 4, l1 = NM * TAB_PER_LMAT / 4;
+    const float4 *b = reinterpret_cast<const float4 *>(blob), *bm = b + n0 + m0 * (TAB_PER_MAT / 4);
+    for (int i = threadIdx.x; i < n0 + n1; i += blockDim.x)
+        reinterpret_cast<float4 *>(hi)[i] = i < n0 ? b[i] : bm[i - n0];
+    if constexpr (X) {
+        const float4 *l = b + TAB_HI_FLOATS / 4, *lm = l + l0 + m0 * (TAB_PER_LMAT / 4);
+        for (int i = threadIdx.x; i < l0 + l1; i += blockDim.x)
+            reinterpret_cast<float4 *>(lo)[i] = i < l0 ? l[i] : lm[i - l0];
+    }
+}
+
 // segment i with E_i <= E < E_i+1, clamped to [0, NE-2]
 __device__ __forceinline__ int seg_of(const float *tab, float E) {
     int i = (int)(__log2f(fmaxf(E, kELo)) * kSegPerLog2);
@@ -312,7 +333,7 @@ __device__ __forceinline__ void sub_energy(Lane &v, DF dE) {
 
 // tm: the material's high tables, tl: its low tables (read only when X)
 template <bool X>
-__device__ __forceinline__ DF csda_loss(const float *tab, const float *tm, const float *tl, int i, DF x, DF rem,
+__device__ __forceinline__ DF csda_loss(const Tabs &T, const float *tm, const float *tl, int i, DF x, DF rem,
                                         DF r) {
     using A = Ar<X>;
     if (A::le(r, rem)) return A::mul(r, A::pair(tm[T_SH * NE + i], X ? tl[L_SL * NE + i] : 0.0f));
@@ -321,7 +342,7 @@ __device__ __forceinline__ DF csda_loss(const float *tab, const float *tm, const
     for (int j = i - 1; j >= 0; --j) {
         const DF dRj = A::pair(tm[T_DH * NE + j], X ? tl[L_DL * NE + j] : 0.0f);
         if (A::le(r, dRj)) return A::add(dE, A::mul(r, A::pair(tm[T_SH * NE + j], X ? tl[L_SL * NE + j] : 0.0f)));
-        dE = A::add(dE, A::pair(tab[TAB_DWH + j], X ? tab[TAB_DWL + j] : 0.0f));
+        dE = A::add(dE, A::pair(T.hi[TAB_DWH + j], X ? T.lo[TABL_DW + j] : 0.0f));
         r = A::sub(r, dRj);
     }
     return dE;
@@ -339,28 +360,29 @@ __device__ __forceinline__ DF csda_loss(const float *tab, const float *tm, const
 // stops, its energy over its residual path (E rho / R); at the cut-off, the
 // slope of the CSDA relation's first segment times the density.
 template <bool Slab, bool X>
-__device__ int phys_step(Lane &v, const float *tab, int m, DF rho_loss, float rho, DF dg, float &dep,
+__device__ int phys_step(Lane &v, const Tabs &T, int m, DF rho_loss, float rho, DF dg, float &dep,
                          float &esc, float &let) {
     using A = Ar<X>;
     dep = 0.0f;
     esc = 0.0f;
     let = 0.0f;
     v.nsteps++;
-    const float *tm = tab + TAB_MAT0 + m * TAB_PER_MAT;
+    const float *tab = T.hi;
+    const float *tm = tab + TAB_SHARED + m * TAB_PER_MAT;
     if (v.E + v.Elo <= kELo) {
         let = rho_loss.h * tm[T_SH * NE];
         dep = v.E + v.Elo;
         v.E = v.Elo = 0.0f;
         return ST_STOP;
     }
-    const float *tl = tab + TAB_LMAT0 + m * TAB_PER_LMAT;
+    const float *tl = T.lo + TABL_SHARED + m * TAB_PER_LMAT;
     int i = seg_of(tab, v.E);
     // E - E_i: the high parts subtract exactly (same binade), the low parts add
-    DF x = X ? two_sum(v.E - tab[TAB_E + i], v.Elo - tab[TAB_EL + i])
+    DF x = X ? two_sum(v.E - tab[TAB_E + i], v.Elo - T.lo[TABL_E + i])
              : DF{(v.E - tab[TAB_E + i]) + v.Elo, 0.0f};
     if (x.h < 0.0f && i > 0) {
         --i;
-        x = X ? two_sum(v.E - tab[TAB_E + i], v.Elo - tab[TAB_EL + i])
+        x = X ? two_sum(v.E - tab[TAB_E + i], v.Elo - T.lo[TABL_E + i])
               : DF{(v.E - tab[TAB_E + i]) + v.Elo, 0.0f};
     }
     const DF S = A::pair(tm[T_SH * NE + i], X ? tl[L_SL * NE + i] : 0.0f);
@@ -376,7 +398,7 @@ __device__ int phys_step(Lane &v, const float *tab, int m, DF rho_loss, float rh
     const bool geo = dg.h <= smax;
     const DF s = geo ? dg : DF{smax, 0.0f};
     const DF r = A::mul(rho_loss, s);   // density x mm (the tables' unit)
-    DF dE = csda_loss<X>(tab, tm, tl, i, x, rem, r);
+    DF dE = csda_loss<X>(T, tm, tl, i, x, rem, r);
     if (s.h > 0.0f) let = (dE.h + dE.l) / (s.h + s.l);
     const float Ebar = v.E - 0.5f * dE.h;
     uint4 w = make_uint4(0u, 0u, 0u, 0xFFFFFFFFu);
@@ -472,15 +494,20 @@ struct SparseSink {
     }
 };
 
-// Row tile of the influence-matrix builder: a dense int64 box of the CT grid
-// in LDS around the spot's central ray, shared by the waves of a workgroup
-// that work on the same row.  Deposits inside the box are LDS atomics, the
-// others go to the row's slot grid; the box is added into the slot grid once
-// when its last user leaves.  On this GPU the int64 tally atomics to device
-// memory are performed on the memory side, beyond the XCD's L2, and their
-// rate bounds the step loop; the tile takes most of them off that path.
+// Row tile of the influence-matrix builder: a dense box of the CT grid in LDS
+// around the spot's central ray, shared by the waves of a workgroup that work
+// on the same row.  Deposits inside the box are LDS atomics, the others go to
+// the row's slot grid; the box is added into the slot grid once when its last
+// user leaves.  On this GPU the int64 tally atomics to device memory are
+// performed on the memory side, beyond the XCD's L2, and their rate bounds
+// the step loop; the tile takes most of them off that path.  An entry holds
+// the low 32 bits of its voxel's sum: the deposit's high half and the carry
+// out of the entry (the returned old value tells) go to the slot grid, where
+// the entry's bits are added once at the end, so the int64 sum is exact.  At
+// 4 bytes a voxel the box is twice as large as with int64 entries, and a
+// carry comes once per few hundred deposits.
 struct TileSink {
-    long long *tile;     // nullptr: this batch does not use the tile
+    uint32_t *tile;     // nullptr: this wave does not use the tile
     int lo0, lo1, lo2;
     uint32_t n0, n1, n2;
     SparseSink gs;
@@ -491,8 +518,10 @@ struct TileSink {
         if (tile) {
             const uint32_t u0 = (uint32_t)(idx[0] - lo0), u1 = (uint32_t)(idx[1] - lo1), u2 = (uint32_t)(idx[2] - lo2);
             if (u0 < n0 && u1 < n1 && u2 < n2) {
-                atomicAdd(reinterpret_cast<unsigned long long *>(tile) + (u0 + n0 * (u1 + n1 * u2)),
-                          (unsigned long long)q);
+                const uint32_t ql = (uint32_t)q;
+                const uint32_t old = atomicAdd(tile + (u0 + n0 * (u1 + n1 * u2)), ql);
+                const int qh = (int)(q >> 32) + (old + ql < ql ? 1 : 0);
+                if (qh != 0) gs.put(v, (long long)qh << 32);
                 return;
             }
         }
@@ -679,7 +708,7 @@ enum { EX_DOWN = 0, EX_GONE = 1 };
 // homogeneous slab (range shifter): local depth 0 .. thick; on return the
 // depth is the global plane z the VP left through
 template <bool X>
-__device__ int slab_transport(Lane &v, Acc &acc, float scale, const float *tab, int m, DF rho,
+__device__ int slab_transport(Lane &v, Acc &acc, float scale, const Tabs &T, int m, DF rho,
                               float zu, float zd, DF thick, int ledger) {
     v.pz = 0.0f;
     v.pzlo = 0.0f;
@@ -688,7 +717,7 @@ __device__ int slab_transport(Lane &v, Acc &acc, float scale, const float *tab, 
         const DF tp = plane_distance<X>(v, thick, down);
         float dep, esc;
         float let;
-        const int st = phys_step<true, X>(v, tab, m, rho, rho.h, tp, dep, esc, let);
+        const int st = phys_step<true, X>(v, T, m, rho, rho.h, tp, dep, esc, let);
         ledger_add(acc, ledger, dep, scale);
         ledger_add(acc, L_NUC, esc, scale);
         if (st == ST_STOP) return EX_GONE;
@@ -705,97 +734,231 @@ __device__ int slab_transport(Lane &v, Acc &acc, float scale, const float *tab, 
     return EX_GONE;
 }
 
-// Methods B: between the block's entrance and exit planes the crossing
-// number at the VP's projected position decides, at every step, opening
-// (straight transport, no random numbers) or brass (brass tables).  D = false
-// compiles the plain (non-divergent) geometry only; D = true adds the
-// divergent block's.  A non-divergent block takes the same code, and so gives
-// the same bits, in both.
-template <bool X, bool D = true>
-__device__ int block_transport(Lane &v, Acc &acc, float scale, const float *tab, const float2 *poly,
-                               int nv, float rho_b, float zu, float zd, DF thick, const FieldDev &f_sdf) {
-    v.pz = 0.0f;
-    v.pzlo = 0.0f;
-    for (int it = 0; it < MAX_BLOCK_ITER; ++it) {
-        bool down;
-        const DF tpp = plane_distance<X>(v, thick, down);
-        const float tp = tpp.h;
-        bool open = false;
-        float te = INFINITY;
-        if (nv >= 3 && !(D && f_sdf.div)) {
-            bool inside;
-            const float lb = sdf_bound(f_sdf, v.px, v.py, inside);
-            const float lat = sqrtf(v.dx * v.dx + v.dy * v.dy);
-            if (no_edge_within(lb, lat, tp)) {
-                open = inside;
-            } else {
-                const int ls = listed_edges(f_sdf, poly, nv, v.px, v.py, v.dx, v.dy, lat, tp, open, te);
-                if (ls == 0) open = in_polygon(poly, nv, v.px, v.py);
-                if (ls != 1) te = edge_distance(poly, nv, v.px, v.py, v.dx, v.dy);
-            }
-        } else if (nv >= 3) {
-            // divergent block: opening scale at this depth and its rate of
-            // change along the ray
-            const float sc = fmaf(v.pz, f_sdf.fs, f_sdf.fc0), kw = v.dz * f_sdf.fs;
-            const float isc = 1.0f / sc;
-            const float bx = v.px * isc, by = v.py * isc;
-            const float cx = v.dx - kw * bx, cy = v.dy - kw * by;
-            // far from every edge for the whole path to the exit plane: the
-            // side is known and the exact edge distance exceeds tp, so the
-            // decisions below are those of the exact loops (the scaled
-            // position moves by at most tp |d_xy - kw (bx, by)| / min s)
-            bool inside;
-            const float lb = sdf_bound(f_sdf, bx, by, inside);
-            if (no_edge_within(lb, sqrtf(cx * cx + cy * cy) / fminf(sc, fmaf(tp, kw, sc)), tp)) {
-                open = inside;
-            } else {
-                open = in_polygon(poly, nv, bx, by);
-                te = edge_distance_div(poly, nv, v.px, v.py, v.dx, v.dy, sc, kw);
-            }
-        }
-        if (open) {
-            if (tp <= te) {
-                v.px = fmaf(tp, v.dx, v.px);
-                v.py = fmaf(tp, v.dy, v.py);
-                v.pz = down ? zd : zu;
-                v.pzlo = 0.0f;
-                if (down) return EX_DOWN;
-                ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
-                return EX_GONE;
-            }
-            move<true, X>(v, {te, 0.0f});
-            if constexpr (D) edge_push_blk(v, f_sdf);
-            else edge_push(v);
-            continue;
-        }
-        const DF dg = te < tp ? DF{te, 0.0f} : tpp;
-        float dep, esc;
-        float let;
-        const int st = phys_step<true, X>(v, tab, MAT_BRASS, {rho_b, 0.0f}, rho_b, dg, dep, esc, let);
-        ledger_add(acc, L_BLOCK, dep, scale);
-        ledger_add(acc, L_NUC, esc, scale);
-        if (st == ST_STOP) return EX_GONE;
-        if (st == ST_GEO && tp <= te) {
-            v.pz = down ? zd : zu;
-            v.pzlo = 0.0f;
-            if (down) return EX_DOWN;
-            ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
-            return EX_GONE;
-        }
-        if (st == ST_GEO) {
-            if constexpr (D) edge_push_blk(v, f_sdf);
-            else edge_push(v);
-        }
-        if (v.pz >= thick.h) { v.pz = zd; v.pzlo = 0.0f; return EX_DOWN; }
-        if (v.pz <= 0.0f) {
-            v.pz = zu;
-            v.pzlo = 0.0f;
-            ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
-            return EX_GONE;
-        }
+// Searches over every edge of the polygon for the lanes with `need`, one such
+// lane at a time: its point and direction are broadcast and the edges are
+// divided among the lanes of the wave that are here (a lane alone would walk
+// all edges with the others waiting: 128 edges of ~27 instructions against
+// ~80 per searching lane this way; with more than 40 lanes in need each takes
+// its own loop again).  Each edge's arithmetic and the minimum (parity) over
+// the edges are those of the loops above, so the results are the same bits.
+// DIV: the divergent block's walls at opening scale s0, rate kw.
+template <bool DIV>
+__device__ __forceinline__ float wave_edge_distance(const float2 *poly, int nv, float x, float y, float u, float v,
+                                                    float s0, float kw, bool need) {
+    float res = INFINITY;
+    unsigned long long todo = __ballot(need);
+    if (todo == 0ull) return res;
+    if (__popcll(todo) > 40) {
+        if (need) res = DIV ? edge_distance_div(poly, nv, x, y, u, v, s0, kw) : edge_distance(poly, nv, x, y, u, v);
+        return res;
     }
-    ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
-    return EX_GONE;
+    const unsigned long long here = __ballot(true);
+    const int lane = threadIdx.x & 63, n = __popcll(here), rank = __popcll(here & ((1ull << lane) - 1ull));
+    auto bc = [](float f, int l) {
+        return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(f), l));
+    };
+    for (; todo; todo &= todo - 1ull) {
+        const int l = __ffsll((long long)todo) - 1;
+        const float xs = bc(x, l), ys = bc(y, l), us = bc(u, l), vs = bc(v, l);
+        const float ss = DIV ? bc(s0, l) : 1.0f, ks = DIV ? bc(kw, l) : 0.0f;
+        float best = INFINITY;
+        for (int i = rank; i < nv; i += n) {
+            const float2 a = poly[i ? i - 1 : nv - 1], b = poly[i];
+            const float ex = b.x - a.x, ey = b.y - a.y;
+            const float ux = DIV ? us - ks * a.x : us, uy = DIV ? vs - ks * a.y : vs;
+            const float den = ux * ey - uy * ex;
+            if (den != 0.0f) {
+                const float wx = DIV ? ss * a.x - xs : a.x - xs, wy = DIV ? ss * a.y - ys : a.y - ys;
+                const float inv = 1.0f / den;
+                const float t = (wx * ey - wy * ex) * inv;
+                const float mu = (wx * uy - wy * ux) * inv;
+                const float st = DIV ? fmaf(t, ks, ss) : 1.0f;
+                if (t > 0.0f && (!DIV || st > 0.0f) && mu >= 0.0f && mu <= st) best = fminf(best, t);
+            }
+        }
+        float m = INFINITY;
+        for (unsigned long long hits = __ballot(best < INFINITY); hits; hits &= hits - 1ull)
+            m = fminf(m, bc(best, __ffsll((long long)hits) - 1));
+        if (lane == l) res = m;
+    }
+    return res;
+}
+
+__device__ __forceinline__ bool wave_in_polygon(const float2 *poly, int nv, float x, float y, bool need) {
+    bool res = false;
+    unsigned long long todo = __ballot(need);
+    if (todo == 0ull) return res;
+    if (__popcll(todo) > 40) {
+        if (need) res = in_polygon(poly, nv, x, y);
+        return res;
+    }
+    const unsigned long long here = __ballot(true);
+    const int lane = threadIdx.x & 63, n = __popcll(here), rank = __popcll(here & ((1ull << lane) - 1ull));
+    for (; todo; todo &= todo - 1ull) {
+        const int l = __ffsll((long long)todo) - 1;
+        const float xs = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(x), l));
+        const float ys = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(y), l));
+        bool c = false;
+        for (int i = rank; i < nv; i += n) {
+            const float2 a = poly[i], b = poly[i ? i - 1 : nv - 1];
+            if ((a.y > ys) != (b.y > ys)) {
+                const float xc = a.x + (ys - a.y) * (b.x - a.x) / (b.y - a.y);
+                if (xs < xc) c = !c;
+            }
+        }
+        const bool in = (__popcll(__ballot(c)) & 1) != 0;
+        if (lane == l) res = in;
+    }
+    return res;
+}
+
+// Where a point in the block stands: its side of the opening and the path
+// length te to the first wall, exact wherever it is below the path length t
+// that matters.  `on` lanes only; every lane of the wave that calls takes
+// part in the searches.  In the brass (`R` > 0: the residual range times
+// 1.001 over the density) no wall beyond R matters either: the particle
+// stops or steps short of it, with the same result wherever it is.
+template <bool D>
+__device__ __forceinline__ void block_side(const FieldDev &f, const float2 *poly, bool on, float x, float y, float dx,
+                                           float dy, float dz, float z, float t, float R, bool far_side, bool &open,
+                                           float &te) {
+    const int nv = f.nv;
+    open = false;
+    te = INFINITY;
+    if (nv < 3) return;   // closed block
+    if (!(D && f.div)) {
+        bool need = false, inside;
+        const float lat = sqrtf(dx * dx + dy * dy);
+        if (on) {
+            const float lb = sdf_bound(f, x, y, inside);
+            if (no_edge_within(lb, lat, t)) {
+                open = inside;
+            } else {
+                const int ls = listed_edges(f, poly, nv, x, y, dx, dy, lat, t, open, te);
+                if (ls == 0) open = lb > 0.0f ? inside : in_polygon(poly, nv, x, y);
+                // (far_side: the caller does not use te in the brass)
+                need = ls != 1 && !(far_side && !open);
+                if (need && !open && R > 0.0f) {
+                    const float tr = fminf(t, R);
+                    if (no_edge_within(lb, lat, tr)) { te = INFINITY; need = false; }
+                    else if (ls == 2 && lat * fminf(te, tr) <= f.list_reach) need = false;
+                }
+            }
+        }
+        const float full = wave_edge_distance<false>(poly, nv, x, y, dx, dy, 1.0f, 0.0f, need);
+        if (need) te = full;
+    } else {
+        // divergent block: opening scale at this depth and its rate of change
+        // along the ray; far from every edge for the whole path to the exit
+        // plane the side is known and the exact edge distance exceeds t (the
+        // scaled position moves by at most t |d_xy - kw (bx, by)| / min s)
+        const float sc = fmaf(z, f.fs, f.fc0), kw = dz * f.fs;
+        const float isc = 1.0f / sc;
+        const float bx = x * isc, by = y * isc;
+        const float cx = dx - kw * bx, cy = dy - kw * by;
+        bool side = false, need = false, inside;
+        if (on) {
+            const float lb = sdf_bound(f, bx, by, inside);
+            if (no_edge_within(lb, sqrtf(cx * cx + cy * cy) / fminf(sc, fmaf(t, kw, sc)), t)) {
+                open = inside;
+            } else {
+                need = true;
+                side = !(lb > 0.0f);
+                open = lb > 0.0f && inside;
+            }
+        }
+        const bool in = wave_in_polygon(poly, nv, bx, by, side);
+        if (side) open = in;
+        if (far_side && !open) need = false;
+        const float full = wave_edge_distance<true>(poly, nv, x, y, dx, dy, sc, kw, need);
+        if (need) te = full;
+    }
+}
+
+// CSDA range of the particle's energy in a material (density x mm), as
+// phys_step finds it up to rounding
+__device__ __forceinline__ float residual_range(const Lane &v, const Tabs &T, int m) {
+    const int i = seg_of(T.hi, v.E);
+    const float *tm = T.hi + TAB_SHARED + m * TAB_PER_MAT;
+    return tm[T_R * NE + i] + (v.E - T.hi[TAB_E + i]) * __builtin_amdgcn_rcpf(tm[T_SH * NE + i]);
+}
+
+enum { BK_IN = 0, BK_DOWN = 1, BK_GONE = 2 };
+
+// One step of a traversal of the aperture block (Methods B: between the
+// block's entrance and exit planes the crossing number at the particle's
+// projected position decides, at every step, opening (straight transport, no
+// random numbers) or brass).  The depth is local to the block.  `on` lanes
+// step; every lane of the wave that calls takes part in the edge searches.
+// D = false compiles the plain (non-divergent) geometry only; D = true adds
+// the divergent block's.  A non-divergent block takes the same code, and so
+// gives the same bits, in both.
+template <bool X, bool D>
+__device__ __forceinline__ int block_step(Lane &v, bool on, uint32_t &it, Acc &acc, float scale, const Tabs &T,
+                                          const float2 *poly, const FieldDev &f) {
+    const DF thick = {f.blk_t, f.blk_tl};
+    bool down = true, open = false;
+    DF tpp = {0.0f, 0.0f};
+    float te = INFINITY, R = 0.0f;
+    if (on && it++ >= (uint32_t)MAX_BLOCK_ITER) {
+        ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
+        return BK_GONE;
+    }
+    if (on) {
+        tpp = plane_distance<X>(v, thick, down);
+        // (E_LO: at the cut-off the particle stops whatever the distance)
+        R = v.E > kELo ? 1.001f * residual_range(v, T, T.brass) / f.blk_rho : 0.0f;
+    }
+    block_side<D>(f, poly, on, v.px, v.py, v.dx, v.dy, v.dz, v.pz, tpp.h, R, false, open, te);
+    if (!on) return BK_IN;
+    const float tp = tpp.h;
+    auto leave = [&](bool out_down) {
+        v.pz = out_down ? f.blk_zd : f.blk_zu;
+        v.pzlo = 0.0f;
+        if (out_down) return (int)BK_DOWN;
+        ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
+        return (int)BK_GONE;
+    };
+    if (open) {
+        if (tp <= te) {
+            v.px = fmaf(tp, v.dx, v.px);
+            v.py = fmaf(tp, v.dy, v.py);
+            return leave(down);
+        }
+        move<true, X>(v, {te, 0.0f});
+        if constexpr (D) edge_push_blk(v, f);
+        else edge_push(v);
+        return BK_IN;
+    }
+    const DF dg = te < tp ? DF{te, 0.0f} : tpp;
+    float dep, esc, let;
+    const int st = phys_step<true, X>(v, T, T.brass, {f.blk_rho, 0.0f}, f.blk_rho, dg, dep, esc, let);
+    ledger_add(acc, L_BLOCK, dep, scale);
+    ledger_add(acc, L_NUC, esc, scale);
+    if (st == ST_STOP) return BK_GONE;
+    if (st == ST_GEO && tp <= te) return leave(down);
+    if (st == ST_GEO) {
+        if constexpr (D) edge_push_blk(v, f);
+        else edge_push(v);
+    }
+    if (v.pz >= thick.h) { v.pz = f.blk_zd; v.pzlo = 0.0f; return BK_DOWN; }
+    if (v.pz <= 0.0f) return leave(false);
+    return BK_IN;
+}
+
+// Whole traversals of the lanes with `on` (depth local to the block); true
+// for those that leave through the downstream face.
+template <bool X, bool D>
+__device__ bool block_transport(Lane &v, bool on, Acc &acc, float scale, const Tabs &T, const float2 *poly,
+                                const FieldDev &f) {
+    uint32_t it = 0;
+    int st = on ? BK_IN : BK_GONE;
+    while (__ballot(st == BK_IN) != 0ull) {
+        const bool in = st == BK_IN;
+        const int s = block_step<X, D>(v, in, it, acc, scale, T, poly, f);
+        if (in) st = s;
+    }
+    return st == BK_DOWN;
 }
 
 // distance from (x, y) to the polygon's boundary (minimum over edges of the
@@ -817,109 +980,94 @@ __device__ float dist_to_polygon(const float2 *poly, int nv, float x, float y) {
     return sqrtf(best);
 }
 
-// range shifter then aperture block, in the beam frame; on success (p, d) is
-// on the VP's ray and tmin is the ray parameter of the last exit plane
-enum { BL_STOP = 0, BL_PATIENT = 1, BL_DEFER = 2 };
+// Range shifter, then the block's upstream face, in the beam frame, for the
+// lanes with `on`: BL_PATIENT with tmin the ray parameter of the last exit
+// plane ((p, d) is then on the particle's ray), BL_BLOCK when the block's
+// brass or walls are met (the particle is on the upstream face, depth local),
+// BL_DEFER when the surrogate takes the traversal, else BL_STOP.
+enum { BL_STOP = 0, BL_PATIENT = 1, BL_DEFER = 2, BL_BLOCK = 3 };
 
-template <bool X, bool D = true>
-__device__ int beamline(Lane &v, Acc &acc, float scale, const float *tab, const float2 *poly,
-                        const FieldDev &f, float &tmin, const SurDev *sur = nullptr, uint32_t tag = 0u) {
+template <bool X, bool D>
+__device__ __forceinline__ int beam_entry(Lane &v, bool on, Acc &acc, float scale, const Tabs &T, const float2 *poly,
+                                          const FieldDev &f, float &tmin, const SurDev *sur, uint32_t tag) {
     tmin = -INFINITY;
-    if (f.has_rs) {
+    int st = on ? BL_PATIENT : BL_STOP;
+    if (on && f.has_rs) {
         const float t = (f.rs_zu - v.pz) / v.dz;
         const float qx = fmaf(t, v.dx, v.px), qy = fmaf(t, v.dy, v.py);
         if (qx * qx + qy * qy <= f.rs_r2) {
             v.px = qx;
             v.py = qy;
             v.pz = f.rs_zu;
-            if (slab_transport<X>(v, acc, scale, tab, MAT_PMMA, {f.rs_rho, f.rs_rhol}, f.rs_zu, f.rs_zd,
-                               {f.rs_t, f.rs_tl}, L_RS) != EX_DOWN)
-                return BL_STOP;
-            tmin = 0.0f;
+            if (slab_transport<X>(v, acc, scale, T, T.pmma, {f.rs_rho, f.rs_rhol}, f.rs_zu, f.rs_zd,
+                                  {f.rs_t, f.rs_tl}, L_RS) == EX_DOWN)
+                tmin = 0.0f;
+            else
+                st = BL_STOP;
         }
     }
-    if (f.has_block) {
-        if (!(v.dz > 0.0f)) {
-            ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
-            return BL_STOP;
-        }
-        const float t = (f.blk_zu - v.pz) / v.dz;
-        const float qx = fmaf(t, v.dx, v.px), qy = fmaf(t, v.dy, v.py);
-        const int nv = f.nv;
-        bool open = false, through = false;
-        if (nv >= 3 && !(D && f.div)) {
-            const float tx = f.blk_t / v.dz;
-            bool inside;
-            const float lb = sdf_bound(f, qx, qy, inside);
-            const float lat = sqrtf(v.dx * v.dx + v.dy * v.dy);
-            float te = INFINITY;
-            if (no_edge_within(lb, lat, tx)) {
-                open = inside;
-                through = inside;
-            } else {
-                const int ls = listed_edges(f, poly, nv, qx, qy, v.dx, v.dy, lat, tx, open, te);
-                if (ls == 0) open = in_polygon(poly, nv, qx, qy);
-                if (open && ls != 1) te = edge_distance(poly, nv, qx, qy, v.dx, v.dy);
-                through = open && te >= tx;
-            }
-        } else if (nv >= 3) {
-            const float tx = f.blk_t / v.dz;
-            // divergent block: opening scale on the upstream face
-            const float sc = f.fc0, kw = v.dz * f.fs;
-            const float isc = 1.0f / sc;
-            const float bx = qx * isc, by = qy * isc;
-            const float cx = v.dx - kw * bx, cy = v.dy - kw * by;
-            bool inside;
-            const float lb = sdf_bound(f, bx, by, inside);
-            if (no_edge_within(lb, sqrtf(cx * cx + cy * cy) / fminf(sc, fmaf(tx, kw, sc)), tx)) {
-                open = inside;
-                through = inside;
-            } else {
-                open = in_polygon(poly, nv, bx, by);
-                through = open && edge_distance_div(poly, nv, qx, qy, v.dx, v.dy, sc, kw) >= tx;
-            }
-        }
-        if (through) {
-            tmin = (f.blk_zd - v.pz) / v.dz;
-            return BL_PATIENT;
-        }
-        if (!open && sur && sur->enabled && !(D && f.div)) {
-            // enters through brass: far enough from the opening's edge, the
-            // learned surrogate takes over the traversal (queued for it)
-            const float de = nv >= 3 ? dist_to_polygon(poly, nv, qx, qy) : 1000.0f;
-            if (de >= sur->d_fallback) {
-                const unsigned long long slot = atomicAdd(sur->count, 1ull);
-                if (slot < sur->capacity) {
-                    DeferRec r;
-                    r.spot = v.spot;
-                    r.hist = v.hist;
-                    r.nblk = v.nblk;
-                    r.tag = tag;
-                    r.x = qx;
-                    r.y = qy;
-                    r.u = v.dx;
-                    r.v = v.dy;
-                    r.w = v.dz;
-                    r.E = v.E;
-                    r.Elo = v.Elo;
-                    r.pzlo = v.pzlo;
-                    r.d_edge = de;
-                    r.thick = f.blk_t;
-                    r.pad[0] = r.pad[1] = 0.0f;
-                    sur->rec[slot] = r;
-                    return BL_DEFER;
-                }
-            }
-        }
-        v.px = qx;
-        v.py = qy;
-        v.pz = f.blk_zu;
-        if (block_transport<X, D>(v, acc, scale, tab, poly, nv, f.blk_rho, f.blk_zu, f.blk_zd, {f.blk_t, f.blk_tl}, f) !=
-            EX_DOWN)
-            return BL_STOP;
-        tmin = 0.0f;
+    if (!f.has_block) return st;
+    if (st == BL_PATIENT && !(v.dz > 0.0f)) {
+        ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
+        st = BL_STOP;
     }
-    return BL_PATIENT;
+    const bool face = st == BL_PATIENT;
+    const float t = (f.blk_zu - v.pz) / v.dz;
+    const float qx = fmaf(t, v.dx, v.px), qy = fmaf(t, v.dy, v.py);
+    const float tx = f.blk_t / v.dz;
+    bool open;
+    float te;
+    block_side<D>(f, poly, face, qx, qy, v.dx, v.dy, v.dz, 0.0f, tx, 0.0f, true, open, te);
+    if (!face) return st;
+    if (open && te >= tx) {   // straight through the opening
+        tmin = (f.blk_zd - v.pz) / v.dz;
+        return BL_PATIENT;
+    }
+    if (!open && sur && sur->enabled && !(D && f.div)) {
+        // enters through brass: far enough from the opening's edge, the
+        // learned surrogate takes over the traversal (queued for it)
+        const float de = f.nv >= 3 ? dist_to_polygon(poly, f.nv, qx, qy) : 1000.0f;
+        if (de >= sur->d_fallback) {
+            const unsigned long long slot = atomicAdd(sur->count, 1ull);
+            if (slot < sur->capacity) {
+                DeferRec r;
+                r.spot = v.spot;
+                r.hist = v.hist;
+                r.nblk = v.nblk;
+                r.tag = tag;
+                r.x = qx;
+                r.y = qy;
+                r.u = v.dx;
+                r.v = v.dy;
+                r.w = v.dz;
+                r.E = v.E;
+                r.Elo = v.Elo;
+                r.pzlo = v.pzlo;
+                r.d_edge = de;
+                r.thick = f.blk_t;
+                r.pad[0] = r.pad[1] = 0.0f;
+                sur->rec[slot] = r;
+                return BL_DEFER;
+            }
+        }
+    }
+    v.px = qx;
+    v.py = qy;
+    v.pz = 0.0f;
+    v.pzlo = 0.0f;
+    return BL_BLOCK;
+}
+
+// range shifter and block of one lane's particle: true when it goes on to
+// the patient with tmin set
+template <bool X, bool D>
+__device__ bool beamline(Lane &v, bool on, Acc &acc, float scale, const Tabs &T, const float2 *poly, const FieldDev &f,
+                         float &tmin, const SurDev *sur) {
+    const int st = beam_entry<X, D>(v, on, acc, scale, T, poly, f, tmin, sur, 0u);
+    if (!f.has_block) return st == BL_PATIENT;
+    const bool down = block_transport<X, D>(v, st == BL_BLOCK, acc, scale, T, poly, f);
+    if (down) tmin = 0.0f;
+    return down || st == BL_PATIENT;
 }
 
 // ------------------------------------------------------------ patient
@@ -939,7 +1087,7 @@ constexpr float kCalX[4] = {-1000.0f, 0.0f, 1000.0f, 1500.0f};
 template <bool X>
 __device__ __forceinline__ DF hu_density(int hu, int &m) {
     const int hc = min(max(hu, -1000), 3071);
-    m = hu < -900 ? MAT_AIR : hu < 150 ? MAT_WATER : MAT_BONE;
+    m = hu < -900 ? DM_AIR : hu < 150 ? DM_WATER : DM_BONE;
     if (!X) {
         // physics mode: the same piecewise-linear calibration as a sum of
         // clamped segments (register arithmetic; a per-segment lookup of the
@@ -1056,7 +1204,7 @@ __device__ bool patient_enter(Lane &v, Acc &acc, float scale, const GeomDev &g, 
 // One condensed-history step of a VP inside the CT grid; false once its
 // transport has ended (stopped, or left the grid: then the escaped ledger).
 template <class Sink, bool X>
-__device__ bool patient_step(Lane &v, Acc &acc, float scale, const float *tab, const GeomDev &g, float range_scale,
+__device__ bool patient_step(Lane &v, Acc &acc, float scale, const Tabs &T, const GeomDev &g, float range_scale,
                              const Sink &sink, PState &ps) {
     if (v.nsteps >= (uint32_t)MAX_STEPS) {
         ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
@@ -1067,7 +1215,7 @@ __device__ bool patient_step(Lane &v, Acc &acc, float scale, const float *tab, c
     uint32_t &vox = ps.vox;
     int &hu = ps.hu;
     {
-        int m = MAT_WATER;
+        int m = DM_WATER;
         DF rho = {1.0f, 0.0f};
         if (g.kind == 1) rho = hu_density<X>(hu, m);
         const DF rho_loss = Ar<X>::mul_f(rho, range_scale);
@@ -1111,7 +1259,7 @@ __device__ bool patient_step(Lane &v, Acc &acc, float scale, const float *tab, c
             }
         }
         float dep, esc, let;
-        const int st = phys_step<false, X>(v, tab, m, rho_loss, rho.h, dg, dep, esc, let);
+        const int st = phys_step<false, X>(v, T, m, rho_loss, rho.h, dg, dep, esc, let);
         const long long qd = to_fixed(dep, scale);
         if (qd != 0) sink.add(vox, idx, qd);
         if constexpr (Sink::kLet) {
@@ -1153,12 +1301,12 @@ __device__ bool patient_step(Lane &v, Acc &acc, float scale, const float *tab, c
 }
 
 template <class Sink, bool X>
-__device__ void patient(Lane &v, Acc &acc, float scale, const float *tab, const GeomDev &g,
+__device__ void patient(Lane &v, Acc &acc, float scale, const Tabs &T, const GeomDev &g,
                         const FieldDev &f, const float *shift, float range_scale, const Sink &sink,
                         float tmin) {
     PState ps;
     if (!patient_enter<X>(v, acc, scale, g, f, shift, tmin, ps)) return;
-    while (patient_step<Sink, X>(v, acc, scale, tab, g, range_scale, sink, ps)) {
+    while (patient_step<Sink, X>(v, acc, scale, T, g, range_scale, sink, ps)) {
     }
 }
 
@@ -1200,10 +1348,10 @@ __device__ __forceinline__ int find_spot(const unsigned long long *off, int n, u
 
 template <bool X>
 __global__ __launch_bounds__(512) void transport_kernel(GeomDev g, FieldDev f, LaunchDev L) {
-    __shared__ float tab[X ? TAB_FLOATS : TAB_HI_FLOATS];
+    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS], lo[X ? tab_lo_floats(NMAT) : 4];
     __shared__ float2 poly[POLY_LDS];
-    for (int i = threadIdx.x; i < (X ? TAB_FLOATS : TAB_HI_FLOATS) / 4; i += blockDim.x)
-        reinterpret_cast<float4 *>(tab)[i] = reinterpret_cast<const float4 *>(L.tables)[i];
+    stage_tables<X, NMAT>(hi, lo, L.tables, 0);
+    const Tabs T{hi, lo, DM_PMMA, DM_BRASS};
     if (f.has_block)
         for (int i = threadIdx.x; i < f.nv; i += blockDim.x) poly[i] = f.poly[i];
     __syncthreads();
@@ -1227,8 +1375,8 @@ __global__ __launch_bounds__(512) void transport_kernel(GeomDev g, FieldDev f, L
         v.physics = L.physics;
         source(v, sp, f.vsad);
         float tmin;
-        if (beamline<X>(v, acc, sp.scale, tab, poly, f, tmin, &L.sur) == BL_PATIENT)
-            patient<DenseSink, X>(v, acc, sp.scale, tab, g, f, L.shift, L.range_scale, DenseSink{L.tally, L.let_tally},
+        if (beamline<X, true>(v, true, acc, sp.scale, T, poly, f, tmin, &L.sur))
+            patient<DenseSink, X>(v, acc, sp.scale, T, g, f, L.shift, L.range_scale, DenseSink{L.tally, L.let_tally},
                                   tmin);
         acc.steps += v.nsteps;
         acc.hist += 1;
@@ -1272,57 +1420,377 @@ __device__ __forceinline__ unsigned long long rd_lds64(const unsigned long long 
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Adds the tile of row rl (epoch-local) into its slot grid and clears it; one wave.
-__device__ void tile_flush(long long *tile, const RowDev &row, const QueueDev &Q, const GeomDev &g, uint32_t rl,
+// Adds the tile of row rl (round-local) into its slot grid and clears it; one wave.
+__device__ void tile_flush(uint32_t *tile, const RowDev &row, const QueueDev &Q, const GeomDev &g, uint32_t rl,
                            int lane) {
-    const uint32_t n0 = (uint32_t)row.tn[0], n1 = (uint32_t)row.tn[1], n2 = (uint32_t)row.tn[2];
+    const uint32_t n0 = (uint32_t)row.tn[0], n1 = (uint32_t)row.tn[1];
+    const uint32_t tn = n0 * n1 * (uint32_t)row.tn[2];
     const SparseSink gs{Q.grid + (size_t)rl * Q.gstride, Q.mark + (size_t)rl * Q.mstride};
-    uint32_t e = 0;
-    for (uint32_t u2 = 0; u2 < n2; ++u2)
-        for (uint32_t u1 = 0; u1 < n1; ++u1, e += n0)
-            for (uint32_t u0 = (uint32_t)lane; u0 < n0; u0 += 64) {
-                const long long q = tile[e + u0];
-                if (q != 0) {
-                    tile[e + u0] = 0;
-                    gs.put((uint32_t)(row.tlo[0] + (int)u0) +
-                               (uint32_t)g.nx * ((uint32_t)(row.tlo[1] + (int)u1) + (uint32_t)g.ny * (uint32_t)(row.tlo[2] + (int)u2)),
-                           q);
-                }
-            }
+    // e / n0 and e / (n0 n1) by FP32 reciprocals: exact, entries < 2^16
+    const float i0 = 1.0f / (float)n0, i1 = 1.0f / (float)n1;
+    for (uint32_t e0 = (uint32_t)lane; e0 < tn; e0 += 256) {
+        uint32_t q[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) q[j] = e0 + 64u * j < tn ? tile[e0 + 64u * j] : 0u;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (q[j] == 0u) continue;
+            const uint32_t e = e0 + 64u * j;
+            tile[e] = 0u;
+            const uint32_t e1 = (uint32_t)(((float)e + 0.5f) * i0), u0 = e - n0 * e1;
+            const uint32_t u2 = (uint32_t)(((float)e1 + 0.5f) * i1), u1 = e1 - n1 * u2;
+            gs.put((uint32_t)row.tlo[0] + u0 +
+                       (uint32_t)g.nx * ((uint32_t)row.tlo[1] + u1 + (uint32_t)g.ny * ((uint32_t)row.tlo[2] + u2)),
+                   (long long)q[j]);
+        }
+    }
 }
 
-// Influence-matrix transport of an epoch's rows.  Each row has a chunk
-// counter (chunk = 64 * hist_per_lane histories); a workgroup works on one
-// current row at a time, its waves drawing chunks of it, and when the row is
-// exhausted one wave picks the next: a fresh row from the epoch's row head,
-// else (work stealing) any row with chunks left, else the end.  The
-// workgroup's LDS tile holds one row's box at a time (RowDev::tlo/tn): a
-// wave joins it for a chunk of that row, and the last wave to leave adds
-// it into the slot grid; chunks of another row go straight to the slot
-// grid.  Per chunk, in stage fills of up to 64 * kStageHpl histories:
-// phase 1 runs source, beam line and CT entry with the lanes in lock step
-// and stages the VPs that enter the grid (compacted with a ballot); phase 2
-// is the patient step loop, where a lane whose VP has ended takes the next
-// staged VP as soon as refill_min lanes are idle (or all remaining VPs fit).
+// Wave-wide ledger sums into one scenario's ledger, one atomic per entry and
+// wave; clears the accumulators.
+__device__ __forceinline__ void flush_ledger(Acc &acc, unsigned long long *ledger, int lane) {
+#pragma unroll
+    for (int k = 0; k < NLEDGER; ++k) {
+        long long x = acc.led[k];
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+        if (lane == 0 && x != 0) atomicAdd(ledger + k, (unsigned long long)x);
+        acc.led[k] = 0;
+    }
+}
+
+__device__ __forceinline__ void flush_stats(Acc &acc, unsigned long long *stats, int lane) {
+    unsigned long long st = acc.steps, hs = acc.hist;
+    for (int o = 32; o > 0; o >>= 1) {
+        st += __shfl_xor(st, o, 64);
+        hs += __shfl_xor(hs, o, 64);
+    }
+    if (lane == 0 && (st | hs) != 0) {
+        atomicAdd(stats + 0, st);
+        atomicAdd(stats + 1, hs);
+    }
+    acc.steps = acc.hist = 0;
+}
+
+// First staged record of a row in this round (its groups start at g_begin).
+__device__ __forceinline__ size_t stage_base(const QueueDev &Q, uint32_t r) {
+    const unsigned long long a = Q.grp_off[r];
+    return (size_t)((a > Q.g_begin ? a : Q.g_begin) - Q.g_begin) * 64u;
+}
+
+// Appends the particles of the lanes with `in` to the staged lists of their
+// rows: ballot compaction per row, one returning atomic per row and wave.
+__device__ __forceinline__ void stage_out(const QueueDev &Q, bool in, uint32_t r, const Lane &v, const PState &ps,
+                                          int lane) {
+    for (unsigned long long todo = __ballot(in); todo;) {
+        const uint32_t rr = (uint32_t)__builtin_amdgcn_readlane((int)r, __ffsll((long long)todo) - 1);
+        const bool mine = in && r == rr;
+        const unsigned long long m = __ballot(mine);
+        unsigned int at = 0;
+        if (lane == 0) at = atomicAdd(&Q.ctl[rr].staged, (unsigned int)__popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (mine) {
+            StagedVP s;
+            s.px = v.px; s.py = v.py; s.pz = v.pz; s.dx = v.dx;
+            s.dy = v.dy; s.dz = v.dz; s.E = v.E; s.Elo = v.Elo;
+            s.nblk = v.nblk; s.hist = v.hist; s.nsteps = v.nsteps; s.vox = ps.vox;
+            s.i0 = ps.idx[0]; s.i1 = ps.idx[1]; s.i2 = ps.idx[2]; s.hu = ps.hu;
+            reinterpret_cast<StagedVP *>(Q.stage)[stage_base(Q, rr) + at +
+                                                  (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = s;
+        }
+        todo &= ~m;
+    }
+}
+
+// Beam line of a round's histories: source, range shifter, aperture block and
+// CT entry; the particles that enter the grid are appended to their row's
+// staged list.  A wave takes runs of groups of 64 histories of one row, the
+// lanes in lock step through source and range shifter.  Most particles are
+// then through the opening or stop; those that meet the block's brass or walls
+// are pushed onto a small stack of the wave in LDS, and whenever it holds a
+// wavefull they are stepped through the block together, until half of them
+// are out and the rest goes back onto the stack.  So the block, whose
+// traversals take from one to dozens of steps, runs with at least half of its
+// lanes busy instead of the one or two that a group of 64 has left at its
+// end, and the CT entries of a wavefull are done at once.  Bound by VALU issue
+// and the table reads' latency at 12 waves per CU.  Measured on the 13-scenario
+// matrix of the 0.4 cc head case (4.0e7 histories): 33.6 ms with each group's
+// traversals run to their end in the group (12 % of the lanes busy), 9.3 ms
+// this way with the edge searches divided among the lanes (47 %).
+constexpr int kBlkStack = 128;   // up to 63 waiting + 64 pushed by a group
+
+template <bool X, bool D>
+__global__ __launch_bounds__(256, 3) void beam_kernel(GeomDev g, QueueDev Q) {
+    constexpr int kW = X ? 14 : 13;   // words of a waiting particle (the low part of the depth only when X)
+    __shared__ __attribute__((aligned(16))) float hi[tab_hi_floats(2)], lo[X ? tab_lo_floats(2) : 4];
+    __shared__ float2 poly[POLY_LDS];
+    __shared__ uint32_t stacks[4][kW][kBlkStack];
+    stage_tables<X, 2>(hi, lo, Q.tables, DM_PMMA);   // PMMA and brass
+    const Tabs T{hi, lo, 0, 1};
+    for (int i = threadIdx.x; i < Q.n_poly_total; i += blockDim.x) poly[i] = Q.polys[i];
+    __syncthreads();
+
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned long long below = (1ull << lane) - 1ull;
+    uint32_t(*const stk)[kBlkStack] = stacks[wv];
+    const unsigned long long nwave = (unsigned long long)gridDim.x * (blockDim.x >> 6);
+    unsigned long long run = (unsigned long long)blockIdx.x * (blockDim.x >> 6) + wv;
+    const uint32_t row_end = (uint32_t)(Q.row_begin + Q.n_rows);
+    Acc acc;
+#pragma unroll
+    for (int k = 0; k < NLEDGER; ++k) acc.led[k] = 0;
+    acc.steps = acc.hist = 0;
+    int cur_scen = -1, cur_field = -1;
+    unsigned long long G = 0, G1 = 0;   // groups left of the current run
+    uint32_t r = 0;                     // row of group G
+    int nst = 0;                        // particles on the stack
+    bool more = true;
+    // moves on to the next group's row; the run's first row by bisection
+    auto advance = [&]() {
+        if (G >= G1) {
+            G = Q.g_begin + run * (unsigned long long)Q.beam_groups;
+            run += nwave;
+            G1 = min(G + (unsigned long long)Q.beam_groups, Q.g_end);
+            more = G < Q.g_end;
+            if (!more) return;
+            r = (uint32_t)Q.row_begin;
+            for (uint32_t h = row_end; h - r > 1u;) {   // grp_off[r] <= G < grp_off[r + 1]
+                const uint32_t mid = (r + h) >> 1;
+                if (Q.grp_off[mid] <= G) r = mid;
+                else h = mid;
+            }
+        }
+        while (G >= Q.grp_off[r + 1]) ++r;   // (rows without histories have no group)
+    };
+    advance();
+    for (;;) {
+        bool same = false;   // the next group's row shares the field and the scenario of what waits
+        if (more) same = Q.rows[r].scen == cur_scen && Q.rows[r].field == cur_field;
+        if (more && (nst == 0 || (same && nst < 64))) {
+            const RowDev row = Q.rows[r];
+            if (row.scen != cur_scen) {
+                if (cur_scen >= 0) flush_ledger(acc, Q.ledger + (size_t)cur_scen * NLEDGER, lane);
+                cur_scen = row.scen;
+            }
+            cur_field = row.field;
+            const SpotDev sp = Q.spots[row.spot_global];
+            const FieldDev &f = Q.fields[row.field];
+            const unsigned long long h = (G - Q.grp_off[r]) * 64ull + lane;
+            const bool on = h < row.n_hist;
+            Lane v;
+            PState ps;
+            v.k0 = Q.key0;
+            v.k1 = Q.seed_hi ^ row.field_id;
+            v.spot = row.spot;
+            v.physics = Q.physics;
+            v.hist = (uint32_t)h;
+            v.nblk = 0;
+            v.nsteps = 0;
+            float tmin;
+            if (on) source(v, sp, D ? f.vsad : 0.0f);
+            const int st = beam_entry<X, D>(v, on, acc, sp.scale, T, poly + Q.poly_off[row.field], f, tmin, &Q.sur,
+                                            (uint32_t)(r - Q.row_begin) + Q.slot0);
+            const unsigned long long blk = __ballot(st == BL_BLOCK);
+            if (st == BL_BLOCK) {
+                const int at = nst + __popcll(blk & below);
+                stk[0][at] = __float_as_uint(v.px); stk[1][at] = __float_as_uint(v.py);
+                stk[2][at] = __float_as_uint(v.pz); stk[3][at] = __float_as_uint(v.dx);
+                stk[4][at] = __float_as_uint(v.dy); stk[5][at] = __float_as_uint(v.dz);
+                stk[6][at] = __float_as_uint(v.E); stk[7][at] = __float_as_uint(v.Elo);
+                stk[8][at] = v.nblk; stk[9][at] = v.hist; stk[10][at] = v.nsteps;
+                stk[11][at] = 0u; stk[12][at] = r;
+                if constexpr (X) stk[13][at] = __float_as_uint(v.pzlo);
+            }
+            nst += __popcll(blk);
+            const bool in = st == BL_PATIENT && patient_enter<X>(v, acc, sp.scale, g, f, Q.scen[row.scen].shift, tmin, ps);
+            if (on) {
+                if (!in && st != BL_BLOCK) acc.steps += v.nsteps;
+                acc.hist += 1;
+            }
+            stage_out(Q, in, r, v, ps, lane);
+            ++G;
+            advance();
+            continue;
+        }
+        if (nst == 0) break;
+        // the top of the stack through the block
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const int take = min(nst, 64);
+        nst -= take;
+        const bool on = lane < take;
+        const FieldDev &f = Q.fields[cur_field];
+        const float2 *fpoly = poly + Q.poly_off[cur_field];
+        Lane v;
+        uint32_t it = 0, vr = 0;
+        float scale = 0.0f;
+        if (on) {
+            const int at = nst + lane;
+            v.px = __uint_as_float(stk[0][at]); v.py = __uint_as_float(stk[1][at]);
+            v.pz = __uint_as_float(stk[2][at]); v.dx = __uint_as_float(stk[3][at]);
+            v.dy = __uint_as_float(stk[4][at]); v.dz = __uint_as_float(stk[5][at]);
+            v.E = __uint_as_float(stk[6][at]); v.Elo = __uint_as_float(stk[7][at]);
+            v.nblk = stk[8][at]; v.hist = stk[9][at]; v.nsteps = stk[10][at];
+            it = stk[11][at];
+            vr = stk[12][at];
+            v.pzlo = 0.0f;
+            if constexpr (X) v.pzlo = __uint_as_float(stk[13][at]);
+            const RowDev &row = Q.rows[vr];
+            v.spot = row.spot;
+            v.k0 = Q.key0;
+            v.k1 = Q.seed_hi ^ row.field_id;
+            v.physics = Q.physics;
+            scale = Q.spots[row.spot_global].scale;
+        }
+        // half of a wavefull may go back when more can follow it
+        const int park = nst > 0 || (more && same) ? 32 : 0;
+        int st = on ? BK_IN : BK_GONE;
+        do {
+            const bool in = st == BK_IN;
+            const int s = block_step<X, D>(v, in, it, acc, scale, T, fpoly, f);
+            if (in) st = s;
+        } while (__popcll(__ballot(st == BK_IN)) > park);
+        PState ps;
+        const bool in = st == BK_DOWN && patient_enter<X>(v, acc, scale, g, f, Q.scen[cur_scen].shift, 0.0f, ps);
+        if (on && st != BK_IN && !in) acc.steps += v.nsteps;
+        stage_out(Q, in, vr, v, ps, lane);
+        const unsigned long long back = __ballot(st == BK_IN);
+        if (st == BK_IN) {
+            const int at = nst + __popcll(back & below);
+            stk[0][at] = __float_as_uint(v.px); stk[1][at] = __float_as_uint(v.py);
+            stk[2][at] = __float_as_uint(v.pz); stk[3][at] = __float_as_uint(v.dx);
+            stk[4][at] = __float_as_uint(v.dy); stk[5][at] = __float_as_uint(v.dz);
+            stk[6][at] = __float_as_uint(v.E); stk[7][at] = __float_as_uint(v.Elo);
+            stk[8][at] = v.nblk; stk[9][at] = v.hist; stk[10][at] = v.nsteps;
+            stk[11][at] = it;
+            stk[12][at] = vr;
+            if constexpr (X) stk[13][at] = __float_as_uint(v.pzlo);
+        }
+        nst += __popcll(back);
+    }
+    if (cur_scen >= 0) flush_ledger(acc, Q.ledger + (size_t)cur_scen * NLEDGER, lane);
+    flush_stats(acc, Q.stats, lane);
+}
+
+// LDS tile box of every row (voxel indices, x fastest), one lane per row: the
+// voxels along the spot's central ray from its CT entry to 5 mm of water past
+// 1.05 x its residual range (RowDev::range_we, water-equivalent) in the CT
+// under the row's scenario, widened laterally by the largest half-width (<= 20
+// mm, 0.5 mm steps) that keeps the box within cap voxels.  The air before the
+// head uses up no range, so a length taken from the range alone would end the
+// box short of the Bragg peak.  No box (tn = 0) when the ray misses the grid or
+// no width fits.  (Any box gives the same sums.)
+__global__ __launch_bounds__(64) void tile_box_kernel(GeomDev g, RowDev *rows, int n, const FieldDev *fields,
+                                                      const SpotDev *spots, const ScenDev *scen, int cap) {
+    const int r = blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= n) return;
+    RowDev row = rows[r];
+    const FieldDev &f = fields[row.field];
+    const SpotDev sp = spots[row.spot_global];
+    const ScenDev sc = scen[row.scen];
+    const int gn[3] = {g.nx, g.ny, g.nz};
+    float p0[3], d[3], tn = -1e30f, tf = 1e30f;
+    bool hit = cap > 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        p0[k] = f.iso[k] + sp.x * f.ex[k] + sp.y * f.ey[k] - sc.shift[k] - g.lo[k];
+        d[k] = f.ez[k];
+        const float hi = gn[k] * g.sp[k];
+        if (fabsf(d[k]) < 1e-6f) {
+            hit = hit && p0[k] >= 0.0f && p0[k] < hi;
+        } else {
+            const float t1 = -p0[k] / d[k], t2 = (hi - p0[k]) / d[k];
+            tn = fmaxf(tn, fminf(t1, t2));
+            tf = fminf(tf, fmaxf(t1, t2));
+        }
+    }
+    auto cell = [&](int k, float t) {
+        return min(max((int)floorf((p0[k] + t * d[k]) / g.sp[k]), 0), gn[k] - 1);
+    };
+    for (int k = 0; k < 3; ++k) row.tlo[k] = row.tn[k] = 0;
+    if (hit && tf > tn) {
+        const float need = 1.05f * fmaxf(row.range_we, 0.0f) + 5.0f;
+        const float ds = fminf(fminf(g.sp[0], g.sp[1]), g.sp[2]);
+        float t1 = tn;
+        if (g.kind == 1) {
+            float we = 0.0f;
+            for (int i = 0; i < 65536 && we < need && t1 < tf; ++i, t1 += ds) {
+                const float tm = t1 + 0.5f * ds;
+                const size_t v = (size_t)cell(0, tm) + (size_t)g.nx * ((size_t)cell(1, tm) + (size_t)g.ny * (size_t)cell(2, tm));
+                int m;
+                float rho;
+                hu_material(g.hu[v], m, rho);
+                we += rho * sc.range_scale * ds;
+            }
+            t1 = fminf(t1, tf);
+        } else {
+            t1 = fminf(tf, tn + need / sc.range_scale);
+        }
+        int mn[3], mx[3], a = 0;
+        for (int k = 0; k < 3; ++k) {
+            mn[k] = min(cell(k, tn), cell(k, t1));
+            mx[k] = max(cell(k, tn), cell(k, t1));
+            if (fabsf(d[k]) > fabsf(d[a])) a = k;
+        }
+        for (float h = 20.0f; h >= 0.0f; h -= 0.5f) {
+            int l[3], w[3];
+            unsigned long long vol = 1;
+            for (int k = 0; k < 3; ++k) {
+                const int hk = k == a ? 0 : (int)floorf(h / g.sp[k]);
+                l[k] = max(0, mn[k] - hk);
+                w[k] = min(gn[k] - 1, mx[k] + hk) - l[k] + 1;
+                vol *= (unsigned long long)w[k];   // (each factor < 2^31; stops growing past cap below)
+                if (vol > (1ull << 32)) vol = 1ull << 32;
+            }
+            if (vol <= (unsigned long long)cap) {
+                for (int k = 0; k < 3; ++k) {
+                    row.tlo[k] = l[k];
+                    row.tn[k] = w[k];
+                }
+                break;
+            }
+        }
+    }
+    for (int k = 0; k < 3; ++k) {
+        rows[r].tlo[k] = row.tlo[k];
+        rows[r].tn[k] = row.tn[k];
+    }
+}
+
+// Patient transport of a round's staged particles.  Each row has a counter of
+// drawn records; a workgroup works on one current row at a time, its waves
+// drawing 64 * hist_per_lane records of it at a time, and when the row is
+// exhausted one wave picks the next: a fresh row from the round's row head,
+// else (work stealing) any row with records left, else the end.  A lane whose
+// particle has ended takes the next drawn record as soon as refill_min lanes
+// are idle (or all remaining records fit), and the wave draws again while its
+// other lanes are in flight: lanes run dry only when the row does, once per
+// row instead of once per chunk.  The workgroup's LDS tile holds one row's box
+// at a time (RowDev::tlo/tn): a wave joins it at a draw if it holds that row
+// or is free, and the last wave to leave adds it into the slot grid; waves
+// that did not get it deposit straight into the slot grid.
+// Draws are of one wavefull by default: more keep waves longer on rows other
+// than the tile's (0.4 cc head matrix, transport of all epochs: 137, 123 and
+// 114 ms at 256, 128 and 64 records a draw).  Bound by VALU issue, and next by
+// the memory-side atomics: of 1.07e9 deposits outside the tile per 0.4 cc head
+// matrix (2.0e9 with int64 entries, boxes sized from the range alone and the
+// tile joined only at a draw) at 1.5e10 of 2.0e10 per second; 71.5 ms against
+// 105 ms with source and beam line inside and a drain after every chunk.
 // Each history's arithmetic and random stream are those of a lane running it
 // alone, and the tallies are integer sums: the result does not depend on
 // the schedule.  The only waits between waves are for the wave that is
 // replacing the current row, which does so without waiting on anyone.
-template <bool X, bool D>
+template <bool X>
 // Physics mode: up to 1024 threads (16 waves at <= 128 VGPRs, one workgroup
 // per CU with a ~120 KiB tile); double-float mode: up to 768 (12 waves at
-// <= 168 VGPRs).  D: some field of the batch is divergent (virtual source or
-// divergent block); without, the plain geometry is compiled alone.
+// <= 168 VGPRs).
 __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueDev Q) {
-    __shared__ float tab[X ? TAB_FLOATS : TAB_HI_FLOATS];
-    __shared__ float2 poly[POLY_LDS];
+    __shared__ __attribute__((aligned(16))) float hi[tab_hi_floats(3)], lo[X ? tab_lo_floats(3) : 4];
     __shared__ unsigned long long s_row;    // current row (high word; kRowNone while replaced)
     __shared__ unsigned long long s_tile;   // (row of the tile << 32) | users, kTileBusy while flushed
-    extern __shared__ __attribute__((aligned(16))) long long tile[];   // Q.tile_cap int64
-    for (int i = threadIdx.x; i < (X ? TAB_FLOATS : TAB_HI_FLOATS) / 4; i += blockDim.x)
-        reinterpret_cast<float4 *>(tab)[i] = reinterpret_cast<const float4 *>(Q.tables)[i];
-    for (int i = threadIdx.x; i < Q.n_poly_total; i += blockDim.x) poly[i] = Q.polys[i];
-    for (int i = threadIdx.x; i < Q.tile_cap; i += blockDim.x) tile[i] = 0;
+    extern __shared__ __attribute__((aligned(16))) uint32_t tile[];   // Q.tile_cap entries
+    stage_tables<X, 3>(hi, lo, Q.tables, DM_WATER);   // water, air, bone
+    const Tabs T{hi, lo, -1, -1};
+    for (int i = threadIdx.x; i < Q.tile_cap; i += blockDim.x) tile[i] = 0u;
     if (threadIdx.x == 0) {
         s_row = (unsigned long long)kRowNone << 32;
         s_tile = (unsigned long long)kRowNone << 32;
@@ -1331,35 +1799,37 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
 
     const int lane = threadIdx.x & 63;
     const unsigned long long below = (1ull << lane) - 1ull;
-    const int hps = min(Q.hist_per_lane, kStageHpl);   // histories per lane per stage fill
-    StagedVP *const stg = reinterpret_cast<StagedVP *>(Q.stage) +
-                          ((size_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * (size_t)(hps * 64);
-    const unsigned long long chunk_h = 64ull * (unsigned long long)Q.hist_per_lane;
+    RowCtl *const ctl = Q.ctl + Q.row_begin;
+    const uint32_t draw_n = 64u * (uint32_t)min(Q.hist_per_lane, kStageHpl);   // (few enough for the 32-bit counters)
     unsigned long long iters = 0;
     for (;;) {
         // ---- bounded queue: a wavefront that has made iter_cap iterations
-        // (chunks, row picks, waits) leaves and reports it; it holds no row
+        // (draws, row picks, waits) leaves and reports it; it holds no row
         // pick and no tile here, so the other waves finish as before
         if (++iters > Q.iter_cap) {
             if (lane == 0) atomicOr(Q.flags, kFlagAborted);
             break;
         }
-        // ---- the workgroup's current row, and a chunk of it
+        // ---- the workgroup's current row, and records of it
         const uint32_t cur = __builtin_amdgcn_readfirstlane((uint32_t)(rd_lds64(&s_row) >> 32));
         if (cur == kRowEnd) break;
         if (cur == kRowPick) {   // another wave is picking the next row (it waits on nobody)
             __builtin_amdgcn_s_sleep(2);
             continue;
         }
-        unsigned long long cj = ~0ull;
-        uint32_t nch = 0;
+        uint32_t next = 0, end = 0, n_staged = 0;
+        auto draw = [&]() {
+            unsigned int at = 0;
+            if (lane == 0) at = atomicAdd(&ctl[cur].next, draw_n);
+            next = __builtin_amdgcn_readfirstlane(at);
+            // a counter past its row's end means the row is exhausted
+            end = next < n_staged ? min(n_staged, next + draw_n) : next;
+        };
         if (cur != kRowNone) {
-            nch = (uint32_t)((Q.rows[Q.row_begin + cur].n_hist + chunk_h - 1) / chunk_h);
-            if (lane == 0) cj = atomicAdd(Q.row_next + cur, 1ull);
-            cj = ((unsigned long long)__builtin_amdgcn_readfirstlane((uint32_t)(cj >> 32)) << 32) |
-                 __builtin_amdgcn_readfirstlane((uint32_t)cj);
+            n_staged = __builtin_amdgcn_readfirstlane(ctl[cur].staged);
+            draw();
         }
-        if (cj >= nch) {
+        if (next >= end) {
             // no row yet, or this one is exhausted: the one wave that swaps
             // the row word from cur to kRowPick picks the next row
             bool mine = false;
@@ -1370,8 +1840,8 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
                                                             __HIP_MEMORY_SCOPE_WORKGROUP);
             }
             if (__builtin_amdgcn_readfirstlane((uint32_t)mine) != 0u) {
-                // a fresh row from the epoch's head, else the first row with
-                // chunks left (64 rows per probe), else the end
+                // a fresh row from the round's head, else the first row with
+                // records left (64 rows per probe), else the end
                 unsigned long long f = 0;
                 if (lane == 0) f = atomicAdd(Q.head, 1ull);
                 f = __builtin_amdgcn_readfirstlane((uint32_t)f);   // < 2^32 rows
@@ -1382,10 +1852,9 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
                     for (int r0 = 0; r0 < Q.n_rows; r0 += 64) {
                         const int r = r0 + lane;
                         bool left = false;
-                        if (r < Q.n_rows) {
-                            const unsigned long long nc = (Q.rows[Q.row_begin + r].n_hist + chunk_h - 1) / chunk_h;
-                            left = __hip_atomic_load(Q.row_next + r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < nc;
-                        }
+                        if (r < Q.n_rows)
+                            left = __hip_atomic_load(&ctl[r].next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                                   ctl[r].staged;
                         const unsigned long long m = __ballot(left);
                         if (m) {
                             nr = (uint32_t)(r0 + __ffsll((long long)m) - 1);
@@ -1400,15 +1869,18 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
             continue;
         }
         const uint32_t rl = cur;
-        const unsigned long long j = cj;
         const RowDev row = Q.rows[Q.row_begin + rl];
         const SpotDev sp = Q.spots[row.spot_global];
         const ScenDev sc = Q.scen[row.scen];
+        const StagedVP *const stg = reinterpret_cast<const StagedVP *>(Q.stage) + stage_base(Q, Q.row_begin + rl);
         const SparseSink gsink{Q.grid + (size_t)rl * Q.gstride, Q.mark + (size_t)rl * Q.mstride};
-        // ---- join the tile for this chunk if it holds this row (or is free)
-        bool joined = false;
+        TileSink sink{nullptr, row.tlo[0], row.tlo[1], row.tlo[2],
+                      (uint32_t)row.tn[0], (uint32_t)row.tn[1], (uint32_t)row.tn[2], gsink};
+        // join the tile if it holds this row (or is free and clear)
         const uint32_t tn = (uint32_t)row.tn[0] * (uint32_t)row.tn[1] * (uint32_t)row.tn[2];
-        if (tn != 0u && tn <= (uint32_t)Q.tile_cap) {
+        const bool boxed = tn != 0u && tn <= (uint32_t)Q.tile_cap;
+        auto join = [&]() {
+            bool joined = false;
             if (lane == 0) {
                 for (;;) {
                     unsigned long long t = rd_lds64(&s_tile);
@@ -1416,7 +1888,7 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
                     unsigned long long want;
                     if (us == kTileBusy) break;
                     if (tr == rl) want = t + 1ull;
-                    else if (us == 0u) want = ((unsigned long long)rl << 32) | 1ull;   // free (and clear): take it
+                    else if (us == 0u) want = ((unsigned long long)rl << 32) | 1ull;
                     else break;
                     if (__hip_atomic_compare_exchange_strong(&s_tile, &t, want, __ATOMIC_ACQUIRE, __ATOMIC_RELAXED,
                                                              __HIP_MEMORY_SCOPE_WORKGROUP)) {
@@ -1425,10 +1897,9 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
                     }
                 }
             }
-            joined = __builtin_amdgcn_readfirstlane((uint32_t)joined) != 0u;
-        }
-        const TileSink sink{joined ? tile : nullptr, row.tlo[0], row.tlo[1], row.tlo[2],
-                            (uint32_t)row.tn[0], (uint32_t)row.tn[1], (uint32_t)row.tn[2], gsink};
+            if (__builtin_amdgcn_readfirstlane((uint32_t)joined) != 0u) sink.tile = tile;
+        };
+        if (boxed) join();
         Acc acc;
 #pragma unroll
         for (int k = 0; k < NLEDGER; ++k) acc.led[k] = 0;
@@ -1438,83 +1909,53 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
         v.k1 = Q.seed_hi ^ row.field_id;
         v.spot = row.spot;
         v.physics = Q.physics;
-        for (int t0 = 0; t0 < Q.hist_per_lane; t0 += hps) {
-            if ((j * (unsigned long long)Q.hist_per_lane + t0) * 64ull >= row.n_hist) break;
-            // phase 1
-            uint32_t nst = 0;
-            {
-                const FieldDev &f = Q.fields[row.field];
-                const float2 *fpoly = poly + Q.poly_off[row.field];
-                for (int t = t0; t < min(Q.hist_per_lane, t0 + hps); ++t) {
-                    const unsigned long long h0 = (j * (unsigned long long)Q.hist_per_lane + t) * 64ull;
-                    if (h0 >= row.n_hist) break;
-                    const unsigned long long h = h0 + lane;
-                    bool in = false;
-                    PState ps;
-                    if (h < row.n_hist) {
-                        v.hist = (uint32_t)h;
-                        v.nblk = 0;
-                        v.nsteps = 0;
-                        source(v, sp, D ? f.vsad : 0.0f);
-                        float tmin;
-                        in = beamline<X, D>(v, acc, sp.scale, tab, fpoly, f, tmin, &Q.sur, (uint32_t)rl) == BL_PATIENT &&
-                             patient_enter<X>(v, acc, sp.scale, g, f, sc.shift, tmin, ps);
-                        if (!in) acc.steps += v.nsteps;
-                        acc.hist += 1;
-                    }
-                    const unsigned long long rb = __ballot(in);
-                    if (in) {
-                        StagedVP r;
-                        r.px = v.px; r.py = v.py; r.pz = v.pz; r.dx = v.dx;
-                        r.dy = v.dy; r.dz = v.dz; r.E = v.E; r.Elo = v.Elo;
-                        r.nblk = v.nblk; r.hist = v.hist; r.nsteps = v.nsteps; r.vox = ps.vox;
-                        r.i0 = ps.idx[0]; r.i1 = ps.idx[1]; r.i2 = ps.idx[2]; r.hu = ps.hu;
-                        stg[nst + (uint32_t)__popcll(rb & below)] = r;
-                    }
-                    nst += (uint32_t)__popcll(rb);
+        bool active = false;
+        uint32_t since = 0;
+        PState ps;
+        for (;;) {
+            const unsigned long long idle = __ballot(!active);
+            const uint32_t nidle = (uint32_t)__popcll(idle);
+            if (next >= end && end < n_staged && nidle >= (uint32_t)Q.refill_min) {
+                if (++iters > Q.iter_cap) {   // no further draw: the lanes in flight finish, then the wave leaves
+                    n_staged = end;
+                } else {
+                    draw();
+                    if (next >= end) n_staged = end = next = 0;   // the row is exhausted
                 }
             }
-            // the staged entries are read back by other lanes of this wave
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-            // phase 2
-            uint32_t next = 0;
-            bool active = false;
-            PState ps;
-            for (;;) {
-                const unsigned long long idle = __ballot(!active);
-                const uint32_t nidle = (uint32_t)__popcll(idle);
-                const bool refill = next < nst && nidle >= min((uint32_t)Q.refill_min, nst - next);
-                if (!refill && nidle == 64u) break;
-                const uint32_t k = next + (uint32_t)__popcll(idle & below);
-                if (refill && !active && k < nst) {
-                    // word by word (single-word loads are not merged into
-                    // 4-register tuples, so each field can land in the
-                    // register the loop carries it in)
-                    const uint32_t *rw = reinterpret_cast<const uint32_t *>(stg + k);
-                    auto ld = [&](int i) {
-                        return __hip_atomic_load(rw + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                    };
-                    v.px = __uint_as_float(ld(0)); v.py = __uint_as_float(ld(1));
-                    v.pz = __uint_as_float(ld(2)); v.dx = __uint_as_float(ld(3));
-                    v.dy = __uint_as_float(ld(4)); v.dz = __uint_as_float(ld(5));
-                    v.E = __uint_as_float(ld(6)); v.Elo = __uint_as_float(ld(7));
-                    v.pxlo = v.pylo = v.pzlo = 0.0f;
-                    v.nblk = ld(8); v.hist = ld(9); v.nsteps = ld(10);
-                    ps.vox = ld(11);
-                    ps.idx[0] = (int)ld(12); ps.idx[1] = (int)ld(13); ps.idx[2] = (int)ld(14);
-                    ps.hu = (int)ld(15);
-                    active = true;
-                }
-                if (refill) next = min(nst, next + nidle);
-                if (active) {
-                    active = patient_step<TileSink, X>(v, acc, sp.scale, tab, g, sc.range_scale, sink, ps);
-                    if (!active) acc.steps += v.nsteps;
-                }
+            // a wave that started beside the previous row's stragglers gets
+            // the tile soon after they have left it
+            if (boxed && sink.tile == nullptr && (++since & 3u) == 0u) join();
+            const bool refill = next < end && nidle >= min((uint32_t)Q.refill_min, end - next);
+            if (!refill && nidle == 64u) break;
+            const uint32_t k = next + (uint32_t)__popcll(idle & below);
+            if (refill && !active && k < end) {
+                // word by word (single-word loads are not merged into
+                // 4-register tuples, so each field can land in the
+                // register the loop carries it in)
+                const uint32_t *rw = reinterpret_cast<const uint32_t *>(stg + k);
+                auto ld = [&](int i) {
+                    return __hip_atomic_load(rw + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+                };
+                v.px = __uint_as_float(ld(0)); v.py = __uint_as_float(ld(1));
+                v.pz = __uint_as_float(ld(2)); v.dx = __uint_as_float(ld(3));
+                v.dy = __uint_as_float(ld(4)); v.dz = __uint_as_float(ld(5));
+                v.E = __uint_as_float(ld(6)); v.Elo = __uint_as_float(ld(7));
+                v.pxlo = v.pylo = v.pzlo = 0.0f;
+                v.nblk = ld(8); v.hist = ld(9); v.nsteps = ld(10);
+                ps.vox = ld(11);
+                ps.idx[0] = (int)ld(12); ps.idx[1] = (int)ld(13); ps.idx[2] = (int)ld(14);
+                ps.hu = (int)ld(15);
+                active = true;
+            }
+            if (refill) next = min(end, next + nidle);
+            if (active) {
+                active = patient_step<TileSink, X>(v, acc, sp.scale, T, g, sc.range_scale, sink, ps);
+                if (!active) acc.steps += v.nsteps;
             }
         }
         // ---- leave the tile; the last user adds it out and frees it
-        if (joined) {
+        if (sink.tile != nullptr) {
             bool flusher = false;
             if (lane == 0) {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -1539,21 +1980,8 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
             }
         }
-#pragma unroll
-        for (int k = 0; k < NLEDGER; ++k) {
-            long long x = acc.led[k];
-            for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-            if (lane == 0 && x != 0) atomicAdd(Q.ledger + (size_t)row.scen * NLEDGER + k, (unsigned long long)x);
-        }
-        unsigned long long sx = acc.steps, hx = acc.hist;
-        for (int o = 32; o > 0; o >>= 1) {
-            sx += __shfl_xor(sx, o, 64);
-            hx += __shfl_xor(hx, o, 64);
-        }
-        if (lane == 0 && hx != 0) {
-            atomicAdd(Q.stats + 0, sx);
-            atomicAdd(Q.stats + 1, hx);
-        }
+        flush_ledger(acc, Q.ledger + (size_t)row.scen * NLEDGER, lane);
+        flush_stats(acc, Q.stats, lane);
     }
 }
 
@@ -1960,10 +2388,10 @@ __global__ __launch_bounds__(256) void surrogate_sample_kernel(FieldDev f, const
                                                                uint32_t key0, uint32_t key1, unsigned physics,
                                                                const float *tables, float *xo, float *yo,
                                                                float *to) {
-    __shared__ float tab[TAB_HI_FLOATS];
+    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS];
     __shared__ float2 poly[POLY_LDS];
-    for (int i = threadIdx.x; i < TAB_HI_FLOATS / 4; i += blockDim.x)
-        reinterpret_cast<float4 *>(tab)[i] = reinterpret_cast<const float4 *>(tables)[i];
+    stage_tables<false, NMAT>(hi, nullptr, tables, 0);
+    const Tabs T{hi, nullptr, DM_PMMA, DM_BRASS};
     for (int i = threadIdx.x; i < f.nv; i += blockDim.x) poly[i] = f.poly[i];
     __syncthreads();
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
@@ -2008,9 +2436,8 @@ __global__ __launch_bounds__(256) void surrogate_sample_kernel(FieldDev f, const
         Acc acc;
 #pragma unroll
         for (int k = 0; k < NLEDGER; ++k) acc.led[k] = 0;
-        const int ex =
-            block_transport<false>(v, acc, 1.0f, tab, poly, nv, f.blk_rho, f.blk_zu, f.blk_zd, {f.blk_t, f.blk_tl}, f);
-        if (ex != EX_DOWN) {
+        v.pz = 0.0f;   // depth local to the block
+        if (!block_transport<false, true>(v, true, acc, 1.0f, T, poly, f)) {
             to[i] = 0.0f;
             continue;
         }
@@ -2032,14 +2459,15 @@ __global__ __launch_bounds__(256) void surrogate_sample_kernel(FieldDev f, const
 // and offset); otherwise the plain brass transport runs from the recorded
 // state.  Then the patient.
 template <class Sink, bool X>
-__device__ void resume_deferred(Lane &v, Acc &acc, float scale, const float *tab, const float2 *poly,
+__device__ void resume_deferred(Lane &v, Acc &acc, float scale, const Tabs &T, const float2 *poly,
                                 const FieldDev &f, const float *o, float p_lo, float p_hi, const GeomDev &g,
                                 const float *shift, float range_scale, const Sink &sink) {
     const float ptrans = 1.0f / (1.0f + __expf(-o[0]));
     bool go = true;
     if (!(ptrans < p_lo || ptrans > p_hi)) {
-        go = block_transport<X>(v, acc, scale, tab, poly, f.nv, f.blk_rho, f.blk_zu, f.blk_zd, {f.blk_t, f.blk_tl}, f) ==
-             EX_DOWN;
+        v.pz = 0.0f;   // depth local to the block
+        v.pzlo = 0.0f;
+        go = block_transport<X, true>(v, true, acc, scale, T, poly, f);
     } else {
         v.E += v.Elo;
         v.Elo = 0.0f;
@@ -2083,7 +2511,7 @@ __device__ void resume_deferred(Lane &v, Acc &acc, float scale, const float *tab
             }
         }
     }
-    if (go) patient<Sink, X>(v, acc, scale, tab, g, f, shift, range_scale, sink, 0.0f);
+    if (go) patient<Sink, X>(v, acc, scale, T, g, f, shift, range_scale, sink, 0.0f);
 }
 
 __device__ __forceinline__ void lane_from_record(Lane &v, const DeferRec &r, uint32_t k0, uint32_t k1,
@@ -2126,10 +2554,10 @@ template <bool X>
 __global__ __launch_bounds__(256) void sur_resume_kernel(GeomDev g, FieldDev f, LaunchDev L, const DeferRec *rec,
                                                          const float *out, unsigned long long n, float p_lo,
                                                          float p_hi) {
-    __shared__ float tab[X ? TAB_FLOATS : TAB_HI_FLOATS];
+    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS], lo[X ? tab_lo_floats(NMAT) : 4];
     __shared__ float2 poly[POLY_LDS];
-    for (int i = threadIdx.x; i < (X ? TAB_FLOATS : TAB_HI_FLOATS) / 4; i += blockDim.x)
-        reinterpret_cast<float4 *>(tab)[i] = reinterpret_cast<const float4 *>(L.tables)[i];
+    stage_tables<X, NMAT>(hi, lo, L.tables, 0);
+    const Tabs T{hi, lo, DM_PMMA, DM_BRASS};
     for (int i = threadIdx.x; i < f.nv; i += blockDim.x) poly[i] = f.poly[i];
     __syncthreads();
     Acc acc;
@@ -2141,7 +2569,7 @@ __global__ __launch_bounds__(256) void sur_resume_kernel(GeomDev g, FieldDev f, 
         const DeferRec r = rec[i];
         Lane v;
         lane_from_record(v, r, L.key0, L.key1, L.physics, f.blk_zu);
-        resume_deferred<DenseSink, X>(v, acc, L.spots[r.spot].scale, tab, poly, f, out + i * MLP_OUT, p_lo, p_hi, g, L.shift,
+        resume_deferred<DenseSink, X>(v, acc, L.spots[r.spot].scale, T, poly, f, out + i * MLP_OUT, p_lo, p_hi, g, L.shift,
                         L.range_scale, DenseSink{L.tally, L.let_tally});
         acc.steps += v.nsteps;
     }
@@ -2154,10 +2582,10 @@ template <bool X>
 __global__ __launch_bounds__(256) void sur_resume_csr_kernel(GeomDev g, QueueDev Q, const DeferRec *rec,
                                                              const float *out, unsigned long long n, float p_lo,
                                                              float p_hi) {
-    __shared__ float tab[X ? TAB_FLOATS : TAB_HI_FLOATS];
+    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS], lo[X ? tab_lo_floats(NMAT) : 4];
     __shared__ float2 poly[POLY_LDS];
-    for (int i = threadIdx.x; i < (X ? TAB_FLOATS : TAB_HI_FLOATS) / 4; i += blockDim.x)
-        reinterpret_cast<float4 *>(tab)[i] = reinterpret_cast<const float4 *>(Q.tables)[i];
+    stage_tables<X, NMAT>(hi, lo, Q.tables, 0);
+    const Tabs T{hi, lo, DM_PMMA, DM_BRASS};
     for (int i = threadIdx.x; i < Q.n_poly_total; i += blockDim.x) poly[i] = Q.polys[i];
     __syncthreads();
     Acc acc;
@@ -2186,7 +2614,7 @@ __global__ __launch_bounds__(256) void sur_resume_csr_kernel(GeomDev g, QueueDev
         }
         Lane v;
         lane_from_record(v, r, Q.key0, Q.seed_hi ^ row.field_id, Q.physics, f.blk_zu);
-        resume_deferred<SparseSink, X>(v, acc, Q.spots[row.spot_global].scale, tab, poly + Q.poly_off[row.field], f,
+        resume_deferred<SparseSink, X>(v, acc, Q.spots[row.spot_global].scale, T, poly + Q.poly_off[row.field], f,
                         out + i * MLP_OUT, p_lo, p_hi, g, sc.shift, sc.range_scale, sink);
         acc.steps += v.nsteps;
     }
@@ -2272,21 +2700,44 @@ int queue_tile_cap(unsigned physics, int threads) {
     threads = queue_threads(physics, threads);
     const int waves_cu = physics == 0 ? 12 : 16;
     const int wgs = std::max(1, waves_cu / (threads / 64));
-    const int stat = (physics == 0 ? TAB_FLOATS : TAB_HI_FLOATS) * 4 + POLY_LDS * 8 + 256;
-    const int per_wg = 160 * 1024 / wgs - stat;
-    return std::max(0, per_wg / 8);
+    const int per_wg = 160 * 1024 / wgs - (int)queue_static_lds(physics);
+    return std::max(0, per_wg / 4);
+}
+
+size_t queue_static_lds(unsigned physics) { return (tab_hi_floats(3) + (physics == 0 ? tab_lo_floats(3) : 4)) * 4 + 256; }
+
+hipError_t launch_tile_box(const GeomDev &g, RowDev *rows, int n, const FieldDev *fields, const SpotDev *spots,
+                           const ScenDev *scen, int cap, hipStream_t s) {
+    if (n > 0)
+        hipLaunchKernelGGL(tile_box_kernel, dim3((n + 63) / 64), dim3(64), 0, s, g, rows, n, fields, spots, scen, cap);
+    return hipGetLastError();
+}
+
+// beam line of a round: a resident set of workgroups (3 of 256 threads per
+// CU), each wave striding over runs of Q.beam_groups groups
+hipError_t launch_beam(const GeomDev &g, QueueDev Q, int cus, hipStream_t s) {
+    const unsigned long long groups = Q.g_end - Q.g_begin;
+    if (groups == 0) return hipSuccess;
+    // runs as long as kBeamGroups, shorter where that leaves waves without one
+    const unsigned long long waves = (unsigned long long)cus * 12;
+    Q.beam_groups = (int)std::max<unsigned long long>(1, std::min<unsigned long long>(kBeamGroups, groups / waves));
+    const unsigned long long runs = (groups + Q.beam_groups - 1) / Q.beam_groups;
+    const int blocks = (int)std::min<unsigned long long>((runs + 3) / 4, waves / 4);
+    if (Q.physics == 0) {
+        if (Q.div) hipLaunchKernelGGL((beam_kernel<true, true>), dim3(blocks), dim3(256), 0, s, g, Q);
+        else hipLaunchKernelGGL((beam_kernel<true, false>), dim3(blocks), dim3(256), 0, s, g, Q);
+    } else {
+        if (Q.div) hipLaunchKernelGGL((beam_kernel<false, true>), dim3(blocks), dim3(256), 0, s, g, Q);
+        else hipLaunchKernelGGL((beam_kernel<false, false>), dim3(blocks), dim3(256), 0, s, g, Q);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_queue(const GeomDev &g, const QueueDev &Q, int blocks, int threads, hipStream_t s) {
     threads = queue_threads(Q.physics, threads);
-    const size_t tile_bytes = (size_t)Q.tile_cap * sizeof(long long);
-    if (Q.physics == 0) {
-        if (Q.div) hipLaunchKernelGGL((queue_kernel<true, true>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
-        else hipLaunchKernelGGL((queue_kernel<true, false>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
-    } else {
-        if (Q.div) hipLaunchKernelGGL((queue_kernel<false, true>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
-        else hipLaunchKernelGGL((queue_kernel<false, false>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
-    }
+    const size_t tile_bytes = (size_t)Q.tile_cap * sizeof(uint32_t);
+    if (Q.physics == 0) hipLaunchKernelGGL(queue_kernel<true>, dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
+    else hipLaunchKernelGGL(queue_kernel<false>, dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
     return hipGetLastError();
 }
 
