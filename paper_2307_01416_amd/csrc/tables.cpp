@@ -139,6 +139,7 @@ void pack_device_tables(float *blob) {
         split_pair(t.E[i], blob + TAB_E + i, low + TABL_E + i);
         if (i + 1 < NE) split_pair(t.E[i + 1] - t.E[i], blob + TAB_DWH + i, low + TABL_DW + i);
     }
+    blob[TAB_DWH + NE - 1] = -INFINITY;   // before the energy nodes
     for (int m = 0; m < NMAT; ++m) {
         float *b = blob + TAB_SHARED + kTabSlot[m] * TAB_PER_MAT;
         float *bl = low + TABL_SHARED + kTabSlot[m] * TAB_PER_LMAT;
@@ -149,6 +150,7 @@ void pack_device_tables(float *blob) {
                 split_pair((t.E[i + 1] - t.E[i]) / dR, b + T_SH * NE + i, bl + L_SL * NE + i);
                 split_pair(dR, b + T_DH * NE + i, bl + L_DL * NE + i);
             }
+            else b[T_SH * NE + i] = INFINITY;   // before the range widths
             b[T_W2 * NE + i] = (float)(0.1 * t.W2[m][i]);
             b[T_T * NE + i] = (float)(0.1 * t.T[m][i]);
             b[T_SN * NE + i] = (float)(0.1 * t.SN[m][i]);

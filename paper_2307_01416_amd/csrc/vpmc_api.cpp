@@ -174,6 +174,7 @@ struct vpmc_ctx {
     bool has_geom = false;
     GeomDev geom{};
     DevBuf hu_buf;
+    DevBuf rho_buf;   // densities derived from the CT numbers (not counted against max_device_bytes)
     size_t nvox = 0;
     FieldState fields[VPMC_MAX_FIELDS];
     // scratch (grow-only)
@@ -408,14 +409,6 @@ int grow_keep(vpmc_ctx *c, DevBuf &b, size_t keep_bytes, size_t bytes, size_t ca
     return VPMC_OK;
 }
 
-// Water-equivalent range (mm) left to a spot's particles at the CT entry: the
-// CSDA range in water less the range shifter's (its thickness taken low).
-float spot_range_we(const FieldDev &f, const SpotDev &sp) {
-    double rw = 10.0 * range_host(MAT_WATER, std::min((double)sp.e0, E_HI));
-    if (f.has_rs) rw -= 0.95 * (double)f.rs_rho * (double)f.rs_t;
-    return (float)std::max(rw, 0.0);
-}
-
 int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario *scen, int n_scen, const vpmc_opts *o,
             int k, float *dose_gy, double *ledger_mev, int64_t *row_ptr) {
     const size_t nvox = c->nvox;
@@ -437,7 +430,6 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     std::vector<int> poff(nf);
     std::vector<float2> polys;
     std::vector<SpotDev> sd;
-    std::vector<float> range_we;
     std::vector<int> spot_base(nf);
     for (int f = 0; f < nf; ++f) {
         const FieldState &fs = c->fields[bf[f].field_id];
@@ -453,7 +445,6 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
             d.nh = s.n_histories;
             d.scale = s.n_histories ? (float)ldexp((double)s.weight / (double)s.n_histories, k) : 0.0f;
             sd.push_back(d);
-            range_we.push_back(spot_range_we(ftab[f], d));
         }
     }
     if (polys.size() > (size_t)POLY_LDS)
@@ -471,7 +462,6 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
                 r.spot_global = (uint32_t)(spot_base[f] + i);
                 r.scen = sc;
                 r.n_hist = bf[f].spots[i].n_histories;
-                r.range_we = range_we[r.spot_global];
                 rows.push_back(r);
             }
     const int R = (int)rows.size();
@@ -609,8 +599,6 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     HIP_TRY(hipMemcpyAsync(c->polys.ptr, polys.data(), polys.size() * sizeof(float2), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(c->spots.ptr, sd.data(), sd.size() * sizeof(SpotDev), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(c->scen_tab.ptr, stab.data(), n_scen * sizeof(ScenDev), hipMemcpyHostToDevice, st));
-    HIP_TRY(launch_tile_box(c->geom, (RowDev *)c->rows.ptr, R, (const FieldDev *)c->fields_tab.ptr,
-                            (const SpotDev *)c->spots.ptr, (const ScenDev *)c->scen_tab.ptr, tile_cap, st));
     // initial CSR capacity: the previous run's total, else a per-row guess
     unsigned long long want = c->csr_cap_hint ? c->csr_cap_hint : (unsigned long long)std::max(R, 1) * 16384ull;
     want = std::min<unsigned long long>(want, (unsigned long long)std::max(R, 1) * nvox);
@@ -715,6 +703,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
             // (the counters of a row that a previous round began)
             if (i > ep_round[e]) he = launch_fill_u64((unsigned long long *)c->q_ctl.ptr + rd.r0, 1, 0ull, st);
             if (he == hipSuccess) he = launch_beam(c->geom, Qr, dev_cus, st);
+            if (he == hipSuccess) he = launch_tile_box(c->geom, Qr, (RowDev *)c->rows.ptr, st);
             if (he == hipSuccess) he = launch_queue(c->geom, Qr, q_blocks, q_threads, st);
         }
         return he;
@@ -1169,7 +1158,9 @@ int vpmc_create(vpmc_ctx **out, int hip_device) {
         if ((e = hipSetDevice(hip_device)) != hipSuccess ||
             (e = hipMalloc(&c->d_tables, sizeof(float) * TAB_FLOATS)) != hipSuccess ||
             (e = hipMemcpy(c->d_tables, blob.data(), sizeof(float) * TAB_FLOATS, hipMemcpyHostToDevice)) !=
-                hipSuccess) {
+                hipSuccess ||
+            (e = launch_derive_tables(c->d_tables, nullptr)) != hipSuccess ||
+            (e = hipStreamSynchronize(nullptr)) != hipSuccess) {
             if (c->d_tables) (void)hipFree(c->d_tables);
             delete c;
             return fail(VPMC_E_DEVICE, "table upload failed: %s", hipGetErrorString(e));
@@ -1193,6 +1184,7 @@ void vpmc_destroy(vpmc_ctx *c) {
         (void)hipDeviceSynchronize();
         if (c->d_tables) (void)hipFree(c->d_tables);
         release(c->hu_buf);
+        release(c->rho_buf);
         for (auto &f : c->fields) {
             release(f.poly_buf);
             release(f.sdf_buf);
@@ -1298,6 +1290,18 @@ int vpmc_load_geometry(vpmc_ctx *c, int kind, const int16_t *hu, int nx, int ny,
         HIP_TRY(hipMemcpy(c->hu_buf.ptr, hu, nvox * sizeof(int16_t),
                           (flags & VPMC_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice));
         g.hu = (const int16_t *)c->hu_buf.ptr;
+        const size_t margin = (size_t)nx * ny, total = nvox + 2 * margin;
+        if (c->rho_buf.cap < total * sizeof(float)) {
+            release(c->rho_buf);
+            HIP_TRY(hipMalloc(&c->rho_buf.ptr, total * sizeof(float)));
+            c->rho_buf.cap = total * sizeof(float);
+        }
+        float *rho = (float *)c->rho_buf.ptr;
+        HIP_TRY(hipMemset(rho, 0, margin * sizeof(float)));
+        HIP_TRY(hipMemset(rho + margin + nvox, 0, margin * sizeof(float)));
+        HIP_TRY(launch_density(g.hu, rho + margin, nvox, nullptr));
+        HIP_TRY(hipStreamSynchronize(nullptr));   // runs may use any stream
+        g.rho = rho + margin;
     }
     c->geom = g;
     c->nvox = nvox;

@@ -15,15 +15,20 @@ constexpr double E_HI = 256.0;
 enum Material { MAT_WATER = 0, MAT_AIR = 1, MAT_PMMA = 2, MAT_BRASS = 3, MAT_BONE = 4 };
 
 // FP32 device blob, high parts first.  Shared: segment energy widths
-// E_i+1 - E_i, energy nodes.  Per material: R, dE/dR per segment, R_i+1 - R_i,
-// omega^2, T, Sigma_nuc; NE floats each, all per unit of density x path
-// length in mm (10 x g/cm^2).  Then the low parts that make the node, width,
-// slope and range-width tables (high, low) FP32 pairs of the FP64 values, for
-// the double-float bookkeeping of the deterministic mode.  The materials of
-// the patient come first, those of the beam line last: each kernel stages in
-// LDS the shared tables and the materials it meets.
-enum { TAB_DWH = 0, TAB_E = NE, TAB_SHARED = 2 * NE, TAB_PER_MAT = 6 * NE };
-enum { T_R = 0, T_SH = 1, T_DH = 2, T_W2 = 3, T_T = 4, T_SN = 5 };
+// E_i+1 - E_i, energy nodes, reciprocal widths.  Per material: R, reciprocal
+// slopes, slopes dE/dR, R_i+1 - R_i, omega^2, T, Sigma_nuc; NE floats each, all
+// per unit of density x path length in mm (10 x g/cm^2).  Tables per segment
+// use NE - 1 entries; the last one is a sentinel for the table behind it, read
+// at index -1 by the walks down the segments: -inf before the energy nodes, 0
+// before the slopes, +inf before the range widths.  The reciprocals are
+// computed on the device (derive_tables_kernel), by the instructions the step
+// would use.  Then the low parts that make the node, width, slope and
+// range-width tables (high, low) FP32 pairs of the FP64 values, for the
+// double-float bookkeeping of the deterministic mode.  The materials of the
+// patient come first, those of the beam line last: each kernel stages in LDS
+// the shared tables and the materials it meets.
+enum { TAB_DWH = 0, TAB_E = NE, TAB_RDW = 2 * NE, TAB_SHARED = 3 * NE, TAB_PER_MAT = 7 * NE };
+enum { T_R = 0, T_RS = 1, T_SH = 2, T_DH = 3, T_W2 = 4, T_T = 5, T_SN = 6 };
 enum { TABL_E = 0, TABL_DW = NE, TABL_SHARED = 2 * NE, TAB_PER_LMAT = 2 * NE };
 enum { L_SL = 0, L_DL = 1 };
 enum { DM_WATER = 0, DM_AIR = 1, DM_BONE = 2, DM_PMMA = 3, DM_BRASS = 4 };   // order of the materials in the blob
@@ -68,6 +73,11 @@ struct GeomDev {
     int kind, nx, ny, nz;
     float sp[3], lo[3];
     const int16_t *hu;
+    // density per voxel (CT geometry), the value the calibration gives in
+    // physics mode; nx * ny entries before the first and behind the last voxel
+    // are readable, so the next voxel's density is fetched before it is known
+    // to be inside the grid
+    const float *rho;
 };
 
 struct FieldDev {
@@ -154,7 +164,6 @@ struct RowDev {
     uint32_t spot_global; // index into the flattened spot table
     int scen;
     uint32_t n_hist;
-    float range_we;       // water-equivalent range at the CT entry, mm
     int tlo[3], tn[3];    // LDS tile box of the row in voxel indices (tn = 0: none; tile_box_kernel)
 };
 
@@ -214,13 +223,15 @@ constexpr size_t kStageFields = 16;
 constexpr int kStageHpl = 32;
 constexpr unsigned long long kMaxStage = 1ull << 25;
 constexpr int kBeamGroups = 16;  // consecutive groups a wave of the beam line takes at a time, at most
+constexpr uint32_t kLeaveIdle = 32;   // idle lanes at which a wave of an exhausted row leaves the tile
 constexpr int kRefillMin = 8;    // idle lanes that trigger a refill of the patient loop
 inline unsigned long long queue_stage_min(int blocks, int threads, int hist_per_lane) {
     const int hps = hist_per_lane < kStageHpl ? hist_per_lane : kStageHpl;
     return (unsigned long long)blocks * (unsigned long long)((threads + 63) / 64) * 64ull * (unsigned long long)hps;
 }
-hipError_t launch_tile_box(const GeomDev &g, RowDev *rows, int n, const FieldDev *fields, const SpotDev *spots,
-                           const ScenDev *scen, int cap, hipStream_t s);
+hipError_t launch_derive_tables(float *blob, hipStream_t s);
+hipError_t launch_density(const int16_t *hu, float *rho, size_t n, hipStream_t s);
+hipError_t launch_tile_box(const GeomDev &g, const QueueDev &Q, RowDev *rows, hipStream_t s);
 hipError_t launch_beam(const GeomDev &g, QueueDev Q, int cus, hipStream_t s);
 hipError_t launch_queue(const GeomDev &g, const QueueDev &Q, int blocks, int threads, hipStream_t s);
 size_t queue_static_lds(unsigned physics);

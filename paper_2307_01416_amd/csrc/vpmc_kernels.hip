@@ -37,9 +37,19 @@ __device__ __forceinline__ uint4 philox4x32_10(uint4 c, uint32_t k0, uint32_t k1
     return c;
 }
 
-// top 23 bits + 1/2, times 2^-23: exact in FP32, strictly inside (0, 1)
+// (top 23 bits + 1/2) times 2^-23, strictly inside (0, 1): the bits as the
+// mantissa of a float in [1, 2), less 1 - 2^-24 (exact: an odd multiple of
+// 2^-24 below 2^24 of them)
 __device__ __forceinline__ float unit_open(uint32_t w) {
-    return ((float)(w >> 9) + 0.5f) * 0x1p-23f;
+    return __uint_as_float(__builtin_amdgcn_alignbit(127u, w, 9u)) - 0x1.fffffep-1f;
+}
+
+// natural logarithm of a positive finite number: hardware log2 and a two-part
+// product with ln 2
+__device__ __forceinline__ float ln_pos(float x) {
+    const float y = __builtin_amdgcn_logf(x);
+    const float r = y * 0x1.62e42ep-1f;
+    return r + fmaf(y, 0x1.efa39ep-25f, fmaf(y, 0x1.62e42ep-1f, -r));
 }
 
 struct Lane {
@@ -114,7 +124,7 @@ __device__ __forceinline__ float sqrt_hw(float x) { return __builtin_amdgcn_sqrt
 
 // step normals: hardware sin/cos take the angle in turns
 __device__ __forceinline__ void box_muller_fast(uint32_t a, uint32_t b, float &z1, float &z2) {
-    const float r = sqrt_hw(-2.0f * __logf(unit_open(a)));
+    const float r = sqrt_hw(-2.0f * ln_pos(unit_open(a)));
     const float t = unit_open(b);
     z1 = r * __builtin_amdgcn_cosf(t);
     z2 = r * __builtin_amdgcn_sinf(t);
@@ -142,13 +152,15 @@ __device__ __forceinline__ void stage_tables(float *hi, float *lo, const float *
     }
 }
 
-// segment i with E_i <= E < E_i+1, clamped to [0, NE-2]
+// segment i with E_i <= E < E_i+1, clamped to [0, NE-2].  The nodes are
+// log-spaced, so the hardware logarithm (error below 1e-4 of a segment)
+// misses it by one at most.
 __device__ __forceinline__ int seg_of(const float *tab, float E) {
-    int i = (int)(__log2f(fmaxf(E, kELo)) * kSegPerLog2);
+    int i = (int)(__builtin_amdgcn_logf(E) * kSegPerLog2);
     i = min(max(i, 0), NE - 2);
-    while (i > 0 && E < tab[TAB_E + i]) --i;
-    while (i < NE - 2 && E >= tab[TAB_E + i + 1]) ++i;
-    return i;
+    const float a = tab[TAB_E + i], b = tab[TAB_E + i + 1];
+    i += (E >= b ? 1 : 0) - (E < a ? 1 : 0);
+    return min(max(i, 0), NE - 2);
 }
 
 // position of E on the node grid: segment and clamped fraction, shared by
@@ -159,10 +171,12 @@ struct NodePos {
 };
 
 // position of an energy E < E_i+1 known to lie at or below segment i (the
-// search walks down from i to the unique segment with E_j <= E < E_j+1)
+// search walks down from i to the unique segment with E_j <= E < E_j+1; the
+// sentinel before the first node ends it)
 __device__ __forceinline__ NodePos node_pos_below(const float *tab, float E, int i) {
-    while (i > 0 && E < tab[TAB_E + i]) --i;
-    const float f = (E - tab[TAB_E + i]) * __builtin_amdgcn_rcpf(tab[TAB_DWH + i]);
+    while (E < tab[TAB_E + i]) --i;
+    i = max(i, 0);
+    const float f = (E - tab[TAB_E + i]) * tab[TAB_RDW + i];
     return {i, fminf(fmaxf(f, 0.0f), 1.0f)};
 }
 
@@ -176,7 +190,7 @@ __device__ __forceinline__ NodePos node_pos_below(const float *tab, float E, int
 // grid u = (k + 1/2) 2^-23.
 __device__ __forceinline__ float normal_quantile(float u) {
     const float t = 2.0f * u - 1.0f;
-    const float w = -__logf(4.0f * u * (1.0f - u));
+    const float w = -ln_pos(4.0f * u * (1.0f - u));
     float p;
     if (w < 5.0f) {   // central part (all but 0.34 % of the draws)
         const float s1 = w - 2.5f;
@@ -331,7 +345,8 @@ __device__ __forceinline__ void sub_energy(Lane &v, DF dE) {
     v.Elo = e.l;
 }
 
-// tm: the material's high tables, tl: its low tables (read only when X)
+// tm: the material's high tables, tl: its low tables (read only when X).  The
+// walk ends at the latest at index -1, whose width is infinite and slope zero.
 template <bool X>
 __device__ __forceinline__ DF csda_loss(const Tabs &T, const float *tm, const float *tl, int i, DF x, DF rem,
                                         DF r) {
@@ -339,13 +354,13 @@ __device__ __forceinline__ DF csda_loss(const Tabs &T, const float *tm, const fl
     if (A::le(r, rem)) return A::mul(r, A::pair(tm[T_SH * NE + i], X ? tl[L_SL * NE + i] : 0.0f));
     DF dE = x;
     r = A::sub(r, rem);
-    for (int j = i - 1; j >= 0; --j) {
-        const DF dRj = A::pair(tm[T_DH * NE + j], X ? tl[L_DL * NE + j] : 0.0f);
-        if (A::le(r, dRj)) return A::add(dE, A::mul(r, A::pair(tm[T_SH * NE + j], X ? tl[L_SL * NE + j] : 0.0f)));
-        dE = A::add(dE, A::pair(T.hi[TAB_DWH + j], X ? T.lo[TABL_DW + j] : 0.0f));
-        r = A::sub(r, dRj);
+    for (--i;; --i) {
+        const DF dR = A::pair(tm[T_DH * NE + i], X ? tl[L_DL * NE + i] : 0.0f);
+        if (A::le(r, dR)) break;
+        dE = A::add(dE, A::pair(T.hi[TAB_DWH + i], X ? T.lo[TABL_DW + i] : 0.0f));
+        r = A::sub(r, dR);
     }
-    return dE;
+    return A::add(dE, A::mul(r, A::pair(tm[T_SH * NE + i], X ? tl[L_SL * NE + i] : 0.0f)));
 }
 
 // One condensed-history step in a homogeneous region: CSDA loss from the
@@ -359,23 +374,19 @@ __device__ __forceinline__ DF csda_loss(const Tabs &T, const float *tm, const fl
 // the mean CSDA stopping power over the step (dE_csda / s); for a VP that
 // stops, its energy over its residual path (E rho / R); at the cut-off, the
 // slope of the CSDA relation's first segment times the density.
-template <bool Slab, bool X>
-__device__ int phys_step(Lane &v, const Tabs &T, int m, DF rho_loss, float rho, DF dg, float &dep,
-                         float &esc, float &let) {
+// P: the processes, compiled in (-1: read from the lane).
+template <bool Slab, bool X, int P = X ? 0 : -1>
+__device__ __forceinline__ int phys_step(Lane &v, const Tabs &T, int m, DF rho_loss, float rho, DF dg, float &dep,
+                                         float &esc, float &let) {
     using A = Ar<X>;
-    dep = 0.0f;
+    const unsigned phys = P >= 0 ? (unsigned)P : v.physics;
     esc = 0.0f;
     let = 0.0f;
     v.nsteps++;
     const float *tab = T.hi;
     const float *tm = tab + TAB_SHARED + m * TAB_PER_MAT;
-    if (v.E + v.Elo <= kELo) {
-        let = rho_loss.h * tm[T_SH * NE];
-        dep = v.E + v.Elo;
-        v.E = v.Elo = 0.0f;
-        return ST_STOP;
-    }
     const float *tl = T.lo + TABL_SHARED + m * TAB_PER_LMAT;
+    const float tot = v.E + v.Elo;
     int i = seg_of(tab, v.E);
     // E - E_i: the high parts subtract exactly (same binade), the low parts add
     DF x = X ? two_sum(v.E - tab[TAB_E + i], v.Elo - T.lo[TABL_E + i])
@@ -385,12 +396,15 @@ __device__ int phys_step(Lane &v, const Tabs &T, int m, DF rho_loss, float rho, 
         x = X ? two_sum(v.E - tab[TAB_E + i], v.Elo - T.lo[TABL_E + i])
               : DF{(v.E - tab[TAB_E + i]) + v.Elo, 0.0f};
     }
-    const DF S = A::pair(tm[T_SH * NE + i], X ? tl[L_SL * NE + i] : 0.0f);
-    const DF rem = A::div(x, S);
+    DF rem;
+    if constexpr (X) rem = A::div(x, {tm[T_SH * NE + i], tl[L_SL * NE + i]});
+    else rem = {x.h * tm[T_RS * NE + i], 0.0f};
     const float R = tm[T_R * NE + i] + rem.h;
-    if (rho_loss.h * dg.h >= R) {
-        let = (v.E + v.Elo) * rho_loss.h * __builtin_amdgcn_rcpf(R);
-        dep = v.E + v.Elo;
+    // at the cut-off, or without the range to reach the boundary: stops here
+    const bool cut = tot <= kELo;
+    if (cut || rho_loss.h * dg.h >= R) {
+        let = cut ? rho_loss.h * tm[T_SH * NE] : tot * rho_loss.h * __builtin_amdgcn_rcpf(R);
+        dep = tot;
         v.E = v.Elo = 0.0f;
         return ST_STOP;
     }
@@ -403,21 +417,20 @@ __device__ int phys_step(Lane &v, const Tabs &T, int m, DF rho_loss, float rho, 
     const float Ebar = v.E - 0.5f * dE.h;
     uint4 w = make_uint4(0u, 0u, 0u, 0xFFFFFFFFu);
     NodePos pb{0, 0.0f};
-    if (v.physics) {
+    if (phys) {
         w = draw(v);
         pb = node_pos_below(tab, Ebar, i);
     }
-    if (v.physics & PH_STRAGGLE) {
+    if (phys & PH_STRAGGLE) {
         const float var = r.h * node_lerp(tm + T_W2 * NE, pb);
         const float z = normal_quantile(unit_open(w.z));
         dE = A::add(dE, {-(sqrt_hw(var) * z), 0.0f});
-        const float tot = v.E + v.Elo;
         if (!(dE.h + dE.l > 0.0f)) dE = {0.0f, 0.0f};
         else if (dE.h + dE.l > tot) dE = {v.E, v.Elo};
     }
     dep = dE.h + dE.l;
     sub_energy<X>(v, dE);
-    if (v.physics & PH_MCS) {
+    if (phys & PH_MCS) {
         const float th0 = sqrt_hw(rho * s.h * node_lerp(tm + T_T * NE, pb));
         float z1, z2;
         box_muller_fast(w.x, w.y, z1, z2);
@@ -428,9 +441,10 @@ __device__ int phys_step(Lane &v, const Tabs &T, int m, DF rho_loss, float rho, 
     } else {
         move<Slab, X>(v, s);
     }
-    if (v.physics & PH_NUCLEAR) {
-        const float P = one_minus_exp_neg(rho * s.h * node_lerp(tm + T_SN * NE, pb));
-        if (unit_open(w.w) < P) {
+    if (phys & PH_NUCLEAR) {
+        // 1 - exp(-x) <= x: the few lanes with u below x look closer
+        const float xn = rho * s.h * node_lerp(tm + T_SN * NE, pb), u = unit_open(w.w);
+        if (u < xn && u < one_minus_exp_neg(xn)) {
             const uint4 w2 = draw(v);
             const float E1 = v.E + v.Elo;
             const float loc = NUC_F_LOCAL * E1, out = NUC_F_ESCAPE * E1;
@@ -454,6 +468,14 @@ struct Acc {
 
 __device__ __forceinline__ long long to_fixed(float e, float scale) {
     return (long long)rintf(e * scale);
+}
+
+// the same, quick where the result lies in [0, 2^32) (as the float's bits
+// tell: positive floats order like their bits, negative ones come after)
+__device__ __forceinline__ long long to_fixed_deposit(float e, float scale) {
+    const float r = rintf(e * scale);
+    if (__float_as_uint(r) < 0x4F800000u) return (long long)(uint32_t)r;
+    return (long long)r;
 }
 
 __device__ __forceinline__ void ledger_add(Acc &a, int j, float e, float scale) {
@@ -1111,18 +1133,28 @@ __device__ __forceinline__ void hu_material(int hu, int &m, float &rho) {
     rho = d.h + d.l;
 }
 
-// keep a voxel-local coordinate pair inside [0, sp]
-__device__ __forceinline__ void clamp_pair(float &h, float &l, float sp) {
-    if (h < 0.0f || (h == 0.0f && l < 0.0f)) { h = 0.0f; l = 0.0f; }
-    else if (h > sp || (h == sp && l > 0.0f)) { h = sp; l = 0.0f; }
+// keep a voxel-local coordinate inside [0, sp]
+template <bool X>
+__device__ __forceinline__ void clamp_local(float &h, float &l, float sp) {
+    if constexpr (!X) {
+        h = __builtin_amdgcn_fmed3f(h, 0.0f, sp);
+    } else {
+        if (h < 0.0f || (h == 0.0f && l < 0.0f)) { h = 0.0f; l = 0.0f; }
+        else if (h > sp || (h == sp && l > 0.0f)) { h = sp; l = 0.0f; }
+    }
 }
 
 // position of a VP inside the CT grid between steps
 struct PState {
     int idx[3];
     uint32_t vox;   // linear index of voxel idx
-    int hu;         // its CT number (CT geometry)
+    uint32_t cell;  // its CT number (X) or the bits of its density (CT geometry)
 };
+
+// Between two CT numbers that the calibration assigns to different materials
+// (-901 | -900 and 149 | 150): it grows with the CT number, so in physics mode
+// the density tells the material.
+constexpr float kRhoTissue = 0.1006f, kRhoBone = 1.0897f;
 
 // Entry into the CT grid: beam frame -> CT frame with the scenario shift,
 // ray-box intersection from the last exit plane (tmin), voxel-local
@@ -1197,106 +1229,109 @@ __device__ bool patient_enter(Lane &v, Acc &acc, float scale, const GeomDev &g, 
     ps.idx[1] = idx[1];
     ps.idx[2] = idx[2];
     ps.vox = (uint32_t)idx[0] + (uint32_t)g.nx * ((uint32_t)idx[1] + (uint32_t)g.ny * (uint32_t)idx[2]);
-    ps.hu = g.kind == 1 ? (int)g.hu[ps.vox] : 0;
+    if constexpr (X) ps.cell = g.kind == 1 ? (uint32_t)(int)g.hu[ps.vox] : 0u;
+    else ps.cell = __float_as_uint(g.kind == 1 ? g.rho[ps.vox] : 1.0f);
     return true;
 }
 
 // One condensed-history step of a VP inside the CT grid; false once its
 // transport has ended (stopped, or left the grid: then the escaped ledger).
-template <class Sink, bool X>
-__device__ bool patient_step(Lane &v, Acc &acc, float scale, const Tabs &T, const GeomDev &g, float range_scale,
-                             const Sink &sink, PState &ps) {
+// Written for instruction count (the work queue issues VALU instructions
+// without a gap): the exit face is a pair of lane masks rather than an axis
+// number, per-axis updates are selects and carry-ins on those masks, the next
+// voxel's density is fetched without a bounds check, and only what a lane
+// rarely needs is branched over.
+template <class Sink, bool X, int P = X ? 0 : -1>
+__device__ __forceinline__ bool patient_step(Lane &v, Acc &acc, float scale, const Tabs &T, const GeomDev &g,
+                                             float range_scale, const Sink &sink, PState &ps) {
     if (v.nsteps >= (uint32_t)MAX_STEPS) {
         ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
         return false;
     }
-    const int n[3] = {g.nx, g.ny, g.nz};
-    int *idx = ps.idx;
-    uint32_t &vox = ps.vox;
-    int &hu = ps.hu;
-    {
-        int m = DM_WATER;
-        DF rho = {1.0f, 0.0f};
-        if (g.kind == 1) rho = hu_density<X>(hu, m);
-        const DF rho_loss = Ar<X>::mul_f(rho, range_scale);
-        // exit face: the axis with the shortest FP32 distance, then that
-        // distance as a pair from the pair coordinate
-        float dgf = INFINITY;
-        int ax = -1, sgn = 0;
-        {
-            const float pp[3] = {v.px, v.py, v.pz}, pl[3] = {v.pxlo, v.pylo, v.pzlo}, dd[3] = {v.dx, v.dy, v.dz};
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                if (dd[k] == 0.0f) continue;
-                const bool up = dd[k] > 0.0f;
-                const float t = fmaxf((((up ? g.sp[k] : 0.0f) - pp[k]) - pl[k]) * __builtin_amdgcn_rcpf(dd[k]), 0.0f);
-                if (t < dgf) { dgf = t; ax = k; sgn = up ? 1 : -1; }
-            }
-        }
-        DF dg = {dgf, 0.0f};
-        if (X && ax >= 0) {
-            // selects, not indexing: the per-axis values stay in registers
-            const float pa = ax == 0 ? v.px : ax == 1 ? v.py : v.pz;
-            const float la = ax == 0 ? v.pxlo : ax == 1 ? v.pylo : v.pzlo;
-            const float da = ax == 0 ? v.dx : ax == 1 ? v.dy : v.dz;
-            const float spa = ax == 0 ? g.sp[0] : ax == 1 ? g.sp[1] : g.sp[2];
-            dg = df_div_f(df_sub({sgn > 0 ? spa : 0.0f, 0.0f}, {pa, la}), da);
+    int m = DM_WATER;
+    DF rho = {1.0f, 0.0f};
+    if constexpr (X) {
+        if (g.kind == 1) rho = hu_density<true>((int)ps.cell, m);
+    } else {
+        rho.h = __uint_as_float(ps.cell);
+        m = rho.h < kRhoTissue ? DM_AIR : rho.h < kRhoBone ? DM_WATER : DM_BONE;
+    }
+    const DF rho_loss = Ar<X>::mul_f(rho, range_scale);
+    // exit face: the axis with the shortest FP32 distance (the first of equal
+    // ones), then in pairs that distance from the pair coordinate
+    const bool u0 = v.dx > 0.0f, u1 = v.dy > 0.0f, u2 = v.dz > 0.0f;
+    const float a0 = u0 ? g.sp[0] : 0.0f, a1 = u1 ? g.sp[1] : 0.0f, a2 = u2 ? g.sp[2] : 0.0f;
+    auto dist = [](float a, float p, float l, float d) {
+        float t = a - p;
+        if constexpr (X) t -= l;
+        return fmaxf(t * __builtin_amdgcn_rcpf(d), 0.0f);
+    };
+    float t0 = dist(a0, v.px, v.pxlo, v.dx), t1 = dist(a1, v.py, v.pylo, v.dy), t2 = dist(a2, v.pz, v.pzlo, v.dz);
+    if (v.dx == 0.0f) t0 = INFINITY;
+    if (v.dy == 0.0f) t1 = INFINITY;
+    if (v.dz == 0.0f) t2 = INFINITY;
+    const bool c1 = t1 < t0;
+    const float t01 = c1 ? t1 : t0;
+    const bool is2 = t2 < t01, is1 = !is2 && c1, is0 = !is2 && !c1;
+    const bool up = (is0 && u0) || (is1 && u1) || (is2 && u2);
+    DF dg = {is2 ? t2 : t01, 0.0f};
+    if constexpr (X) {
+        const float pa = is0 ? v.px : is1 ? v.py : v.pz;
+        const float la = is0 ? v.pxlo : is1 ? v.pylo : v.pzlo;
+        const float da = is0 ? v.dx : is1 ? v.dy : v.dz;
+        const float aa = is0 ? a0 : is1 ? a1 : a2;
+        if (dg.h < INFINITY) {
+            dg = df_div_f(df_sub({aa, 0.0f}, {pa, la}), da);
             if (!(dg.h > 0.0f)) dg = {0.0f, 0.0f};
         }
-        // the CT number behind the face this step may cross is fetched now,
-        // so its latency overlaps the step's arithmetic
-        int nidx = -1;
-        uint32_t nvox = vox;
-        int hu_next = hu;
-        if (ax >= 0) {
-            const int ia = ax == 0 ? idx[0] : ax == 1 ? idx[1] : idx[2];
-            const int na = ax == 0 ? n[0] : ax == 1 ? n[1] : n[2];
-            const int sa = ax == 0 ? 1 : ax == 1 ? g.nx : g.nx * g.ny;
-            nidx = ia + sgn;
-            if (nidx >= 0 && nidx < na) {
-                nvox = vox + (uint32_t)(sgn * sa);
-                if (g.kind == 1) hu_next = (int)g.hu[nvox];
-            }
-        }
-        float dep, esc, let;
-        const int st = phys_step<false, X>(v, T, m, rho_loss, rho.h, dg, dep, esc, let);
-        const long long qd = to_fixed(dep, scale);
-        if (qd != 0) sink.add(vox, idx, qd);
-        if constexpr (Sink::kLet) {
-            if (sink.let != nullptr) {
-                // numerator of the dose-averaged LET: rne(dep * LET * w/N * 2^(k - kLetShift))
-                const long long ql = to_fixed(dep * let, scale * (1.0f / (float)(1 << kLetShift)));
-                if (ql != 0) sink.add_let(vox, ql);
-            }
-        }
-        acc.led[L_GRID] += qd;
-        if (esc != 0.0f) ledger_add(acc, L_NUC, esc, scale);
-        if (st == ST_STOP) return false;
-        if (st == ST_GEO) {
-            bool out = false;
-#pragma unroll
-            for (int k = 0; k < 3; ++k) {
-                if (k == ax) {
-                    idx[k] = nidx;
-                    out = nidx < 0 || nidx >= n[k];
-                }
-            }
-            if (out) {
-                ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
-                return false;
-            }
-            // near face of the next voxel, exactly
-            const float face_next = sgn > 0 ? 0.0f : (ax == 0 ? g.sp[0] : ax == 1 ? g.sp[1] : g.sp[2]);
-            if (ax == 0) { v.px = face_next; v.pxlo = 0.0f; }
-            else if (ax == 1) { v.py = face_next; v.pylo = 0.0f; }
-            else { v.pz = face_next; v.pzlo = 0.0f; }
-            vox = nvox;
-            hu = hu_next;
-        }
-        clamp_pair(v.px, v.pxlo, g.sp[0]);
-        clamp_pair(v.py, v.pylo, g.sp[1]);
-        clamp_pair(v.pz, v.pzlo, g.sp[2]);
     }
+    // what lies behind the face this step may cross is fetched now, so its
+    // latency overlaps the step's arithmetic
+    const int stride = is2 ? g.nx * g.ny : is1 ? g.nx : 1;
+    const int nvox = up ? (int)ps.vox + stride : (int)ps.vox - stride;
+    uint32_t ncell = ps.cell;
+    if (g.kind == 1) {
+        if constexpr (X) {
+            // (an index of the grid: the CT numbers have no margin)
+            const int ia = is0 ? ps.idx[0] : is1 ? ps.idx[1] : ps.idx[2];
+            const int na = is0 ? g.nx : is1 ? g.ny : g.nz;
+            if (up ? ia + 1 < na : ia > 0) ncell = (uint32_t)(int)g.hu[nvox];
+        } else {
+            ncell = __float_as_uint(g.rho[nvox]);
+        }
+    }
+    float dep, esc, let;
+    const int st = phys_step<false, X, P>(v, T, m, rho_loss, rho.h, dg, dep, esc, let);
+    const long long qd = to_fixed_deposit(dep, scale);
+    if (qd != 0) sink.add(ps.vox, ps.idx, qd);
+    if constexpr (Sink::kLet) {
+        if (sink.let != nullptr) {
+            // numerator of the dose-averaged LET: rne(dep * LET * w/N * 2^(k - kLetShift))
+            const long long ql = to_fixed(dep * let, scale * (1.0f / (float)(1 << kLetShift)));
+            if (ql != 0) sink.add_let(ps.vox, ql);
+        }
+    }
+    acc.led[L_GRID] += qd;
+    if (esc != 0.0f) ledger_add(acc, L_NUC, esc, scale);
+    if (st == ST_STOP) return false;
+    const bool geo = st == ST_GEO, g0 = geo && is0, g1 = geo && is1, g2 = geo && is2;
+    ps.idx[0] += (g0 && u0 ? 1 : 0) - (g0 && !u0 ? 1 : 0);
+    ps.idx[1] += (g1 && u1 ? 1 : 0) - (g1 && !u1 ? 1 : 0);
+    ps.idx[2] += (g2 && u2 ? 1 : 0) - (g2 && !u2 ? 1 : 0);
+    if ((uint32_t)ps.idx[0] >= (uint32_t)g.nx || (uint32_t)ps.idx[1] >= (uint32_t)g.ny ||
+        (uint32_t)ps.idx[2] >= (uint32_t)g.nz) {
+        ledger_add(acc, L_ESCAPED, v.E + v.Elo, scale);
+        return false;
+    }
+    // near face of the next voxel, exactly
+    if (g0) { v.px = g.sp[0] - a0; v.pxlo = 0.0f; }
+    if (g1) { v.py = g.sp[1] - a1; v.pylo = 0.0f; }
+    if (g2) { v.pz = g.sp[2] - a2; v.pzlo = 0.0f; }
+    ps.vox = geo ? (uint32_t)nvox : ps.vox;
+    ps.cell = geo ? ncell : ps.cell;
+    clamp_local<X>(v.px, v.pxlo, g.sp[0]);
+    clamp_local<X>(v.py, v.pylo, g.sp[1]);
+    clamp_local<X>(v.pz, v.pzlo, g.sp[2]);
     return true;
 }
 
@@ -1402,14 +1437,40 @@ __global__ __launch_bounds__(512) void transport_kernel(GeomDev g, FieldDev f, L
 // ------------------------------------------------------------ CSR mode
 // A VP staged at its entry into the CT grid (64 B, four 16-byte words):
 // voxel-local position, direction in the CT frame, energy pair, Philox block
-// counter, history, step count, voxel (linear, per axis) and its CT number.
+// counter, history, step count, voxel (linear, per axis) and its CT number or density.
 struct alignas(16) StagedVP {
     float px, py, pz, dx;
     float dy, dz, E, Elo;
     uint32_t nblk, hist, nsteps, vox;
-    int i0, i1, i2, hu;
+    int i0, i1, i2;
+    uint32_t cell;
 };
 static_assert(sizeof(StagedVP) == 4 * kStageFields, "staging record");
+
+__device__ __forceinline__ void store_staged(StagedVP *to, const Lane &v, const PState &ps) {
+    StagedVP s;
+    s.px = v.px; s.py = v.py; s.pz = v.pz; s.dx = v.dx;
+    s.dy = v.dy; s.dz = v.dz; s.E = v.E; s.Elo = v.Elo;
+    s.nblk = v.nblk; s.hist = v.hist; s.nsteps = v.nsteps; s.vox = ps.vox;
+    s.i0 = ps.idx[0]; s.i1 = ps.idx[1]; s.i2 = ps.idx[2]; s.cell = ps.cell;
+    *to = s;
+}
+
+// Word by word: single-word loads are not merged into 4-register tuples, so
+// each field can land in the register the step loop carries it in.
+__device__ __forceinline__ void load_staged(const StagedVP *from, Lane &v, PState &ps) {
+    const uint32_t *rw = reinterpret_cast<const uint32_t *>(from);
+    auto ld = [&](int i) { return __hip_atomic_load(rw + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); };
+    v.px = __uint_as_float(ld(0)); v.py = __uint_as_float(ld(1));
+    v.pz = __uint_as_float(ld(2)); v.dx = __uint_as_float(ld(3));
+    v.dy = __uint_as_float(ld(4)); v.dz = __uint_as_float(ld(5));
+    v.E = __uint_as_float(ld(6)); v.Elo = __uint_as_float(ld(7));
+    v.pxlo = v.pylo = v.pzlo = 0.0f;
+    v.nblk = ld(8); v.hist = ld(9); v.nsteps = ld(10);
+    ps.vox = ld(11);
+    ps.idx[0] = (int)ld(12); ps.idx[1] = (int)ld(13); ps.idx[2] = (int)ld(14);
+    ps.cell = ld(15);
+}
 
 constexpr uint32_t kRowNone = 0xFFFFFFFFu;   // workgroup row word: no row yet
 constexpr uint32_t kRowPick = 0xFFFFFFFDu;   // a wave is picking the next row
@@ -1488,15 +1549,10 @@ __device__ __forceinline__ void stage_out(const QueueDev &Q, bool in, uint32_t r
         unsigned int at = 0;
         if (lane == 0) at = atomicAdd(&Q.ctl[rr].staged, (unsigned int)__popcll(m));
         at = __builtin_amdgcn_readfirstlane(at);
-        if (mine) {
-            StagedVP s;
-            s.px = v.px; s.py = v.py; s.pz = v.pz; s.dx = v.dx;
-            s.dy = v.dy; s.dz = v.dz; s.E = v.E; s.Elo = v.Elo;
-            s.nblk = v.nblk; s.hist = v.hist; s.nsteps = v.nsteps; s.vox = ps.vox;
-            s.i0 = ps.idx[0]; s.i1 = ps.idx[1]; s.i2 = ps.idx[2]; s.hu = ps.hu;
-            reinterpret_cast<StagedVP *>(Q.stage)[stage_base(Q, rr) + at +
-                                                  (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = s;
-        }
+        if (mine)
+            store_staged(reinterpret_cast<StagedVP *>(Q.stage) + stage_base(Q, rr) + at +
+                             (uint32_t)__popcll(m & ((1ull << lane) - 1ull)),
+                         v, ps);
         todo &= ~m;
     }
 }
@@ -1671,89 +1727,128 @@ __global__ __launch_bounds__(256, 3) void beam_kernel(GeomDev g, QueueDev Q) {
     flush_stats(acc, Q.stats, lane);
 }
 
-// LDS tile box of every row (voxel indices, x fastest), one lane per row: the
-// voxels along the spot's central ray from its CT entry to 5 mm of water past
-// 1.05 x its residual range (RowDev::range_we, water-equivalent) in the CT
-// under the row's scenario, widened laterally by the largest half-width (<= 20
-// mm, 0.5 mm steps) that keeps the box within cap voxels.  The air before the
-// head uses up no range, so a length taken from the range alone would end the
-// box short of the Bragg peak.  No box (tn = 0) when the ray misses the grid or
-// no width fits.  (Any box gives the same sums.)
-__global__ __launch_bounds__(64) void tile_box_kernel(GeomDev g, RowDev *rows, int n, const FieldDev *fields,
-                                                      const SpotDev *spots, const ScenDev *scen, int cap) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= n) return;
-    RowDev row = rows[r];
-    const FieldDev &f = fields[row.field];
-    const SpotDev sp = spots[row.spot_global];
-    const ScenDev sc = scen[row.scen];
+// LDS tile box of a round's rows (voxel indices, x fastest), one wave per row,
+// from up to 256 of the particles that the beam line staged for it: along the
+// main axis of their mean direction from the CT entry to 5 mm of water past
+// 1.05 x the range of the most energetic one in the CT along the mean ray (the
+// air before the head uses up no range), and across it around the mean ray's
+// middle, as many standard deviations of the particles' spread there (with 3 %
+// of the depth for the scattering in the patient) as fit into cap voxels, 4 at
+// most.  The particles know what the spot's parameters do not: the aperture
+// cuts an edge spot's beam to one side, and the range shifter's scattering
+// widens it.  No box (tn = 0) when nothing fits.  (Any box gives the same sums.)
+__global__ __launch_bounds__(256) void tile_box_kernel(GeomDev g, QueueDev Q, RowDev *rows) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t rl = blockIdx.x * (blockDim.x >> 6) + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (rl >= (uint32_t)Q.n_rows) return;
+    const uint32_t r = (uint32_t)Q.row_begin + rl;
+    const uint32_t n = Q.ctl[r].staged;
+    const StagedVP *stg = reinterpret_cast<const StagedVP *>(Q.stage) + stage_base(Q, r);
     const int gn[3] = {g.nx, g.ny, g.nz};
-    float p0[3], d[3], tn = -1e30f, tf = 1e30f;
-    bool hit = cap > 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        p0[k] = f.iso[k] + sp.x * f.ex[k] + sp.y * f.ey[k] - sc.shift[k] - g.lo[k];
-        d[k] = f.ez[k];
-        const float hi = gn[k] * g.sp[k];
-        if (fabsf(d[k]) < 1e-6f) {
-            hit = hit && p0[k] >= 0.0f && p0[k] < hi;
-        } else {
-            const float t1 = -p0[k] / d[k], t2 = (hi - p0[k]) / d[k];
-            tn = fmaxf(tn, fminf(t1, t2));
-            tf = fminf(tf, fmaxf(t1, t2));
-        }
-    }
-    auto cell = [&](int k, float t) {
-        return min(max((int)floorf((p0[k] + t * d[k]) / g.sp[k]), 0), gn[k] - 1);
+    auto sum = [](float x) {
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+        return x;
     };
-    for (int k = 0; k < 3; ++k) row.tlo[k] = row.tn[k] = 0;
-    if (hit && tf > tn) {
-        const float need = 1.05f * fmaxf(row.range_we, 0.0f) + 5.0f;
+    // sums over the sample: directions, positions (mm from the grid's corner), largest energy
+    const uint32_t ns = min(n, 256u), step = ns ? max(n / ns, 1u) : 1u;
+    float d[3] = {0, 0, 0}, p[3] = {0, 0, 0}, emax = 0.0f;
+    for (uint32_t j = (uint32_t)lane; j < ns; j += 64) {
+        const StagedVP q = stg[j * step];
+        d[0] += q.dx; d[1] += q.dy; d[2] += q.dz;
+        p[0] += q.i0 * g.sp[0] + q.px; p[1] += q.i1 * g.sp[1] + q.py; p[2] += q.i2 * g.sp[2] + q.pz;
+        emax = fmaxf(emax, q.E);
+    }
+    for (int o = 32; o > 0; o >>= 1) emax = fmaxf(emax, __shfl_xor(emax, o, 64));
+    const float in = ns ? 1.0f / (float)ns : 0.0f;
+    for (int k = 0; k < 3; ++k) {
+        d[k] = sum(d[k]) * in;
+        p[k] = sum(p[k]) * in;
+    }
+    int a = 0;
+    for (int k = 1; k < 3; ++k)
+        if (fabsf(d[k]) > fabsf(d[a])) a = k;
+    int tlo[3] = {0, 0, 0}, tn[3] = {0, 0, 0};
+    if (ns != 0u && fabsf(d[a]) > 1e-3f && Q.tile_cap > 0) {
+        // depth along the mean ray
+        const float *tab = Q.tables;
+        const int i = seg_of(tab, emax);
+        const float R = tab[TAB_SHARED + T_R * NE + i] + (emax - tab[TAB_E + i]) / tab[TAB_SHARED + T_SH * NE + i];
+        const float need = 1.05f * R + 5.0f, rs = Q.scen[rows[r].scen].range_scale;
         const float ds = fminf(fminf(g.sp[0], g.sp[1]), g.sp[2]);
-        float t1 = tn;
+        auto cell = [&](int k, float x) { return min(max((int)floorf(x / g.sp[k]), 0), gn[k] - 1); };
+        float t = 0.0f;
         if (g.kind == 1) {
+            // 64 samples of the ray at a time, one per lane
             float we = 0.0f;
-            for (int i = 0; i < 65536 && we < need && t1 < tf; ++i, t1 += ds) {
-                const float tm = t1 + 0.5f * ds;
-                const size_t v = (size_t)cell(0, tm) + (size_t)g.nx * ((size_t)cell(1, tm) + (size_t)g.ny * (size_t)cell(2, tm));
-                int m;
-                float rho;
-                hu_material(g.hu[v], m, rho);
-                we += rho * sc.range_scale * ds;
+            for (int it = 0; it < 4096 && we < need; ++it) {
+                const float tm = t + ((float)lane + 0.5f) * ds;
+                float x[3];
+                bool ok = true;
+                for (int k = 0; k < 3; ++k) {
+                    x[k] = p[k] + tm * d[k];
+                    ok = ok && x[k] >= 0.0f && x[k] < gn[k] * g.sp[k];
+                }
+                float w = 0.0f;
+                if (ok)
+                    w = g.rho[(size_t)cell(0, x[0]) +
+                              (size_t)g.nx * ((size_t)cell(1, x[1]) + (size_t)g.ny * (size_t)cell(2, x[2]))] * rs * ds;
+                for (int o = 1; o < 64; o <<= 1) {   // inclusive prefix over the lanes
+                    const float y = __shfl_up(w, o, 64);
+                    if (lane >= o) w += y;
+                }
+                const unsigned long long past = __ballot(!ok || we + w >= need);
+                if (past) {
+                    t += (float)__ffsll((long long)past) * ds;
+                    break;
+                }
+                we += __shfl(w, 63, 64);
+                t += 64.0f * ds;
             }
-            t1 = fminf(t1, tf);
         } else {
-            t1 = fminf(tf, tn + need / sc.range_scale);
+            t = need / rs;
         }
-        int mn[3], mx[3], a = 0;
-        for (int k = 0; k < 3; ++k) {
-            mn[k] = min(cell(k, tn), cell(k, t1));
-            mx[k] = max(cell(k, tn), cell(k, t1));
-            if (fabsf(d[k]) > fabsf(d[a])) a = k;
+        // spread across the main axis at 60 % of the depth
+        float var[3] = {0, 0, 0};
+        for (uint32_t j = (uint32_t)lane; j < ns; j += 64) {
+            const StagedVP q = stg[j * step];
+            const float e[3] = {q.dx - d[0], q.dy - d[1], q.dz - d[2]};
+            const float y[3] = {q.i0 * g.sp[0] + q.px - p[0], q.i1 * g.sp[1] + q.py - p[1], q.i2 * g.sp[2] + q.pz - p[2]};
+            for (int k = 0; k < 3; ++k) {
+                const float z = y[k] + 0.6f * t * e[k];
+                var[k] += z * z;
+            }
         }
-        for (float h = 20.0f; h >= 0.0f; h -= 0.5f) {
+        float sd[3];
+        for (int k = 0; k < 3; ++k) sd[k] = sqrtf(sum(var[k]) * in) + 0.03f * 0.6f * t + 0.1f;
+        for (float kap = 4.0f; kap > 0.0f; kap -= 0.1f) {
             int l[3], w[3];
             unsigned long long vol = 1;
             for (int k = 0; k < 3; ++k) {
-                const int hk = k == a ? 0 : (int)floorf(h / g.sp[k]);
-                l[k] = max(0, mn[k] - hk);
-                w[k] = min(gn[k] - 1, mx[k] + hk) - l[k] + 1;
-                vol *= (unsigned long long)w[k];   // (each factor < 2^31; stops growing past cap below)
+                const float e0 = p[k], e1 = p[k] + t * d[k];
+                float x0 = fminf(e0, e1), x1 = fmaxf(e0, e1);
+                if (k != a) {
+                    x0 -= kap * sd[k];
+                    x1 += kap * sd[k];
+                }
+                l[k] = cell(k, x0);
+                w[k] = cell(k, x1) - l[k] + 1;
+                vol *= (unsigned long long)w[k];
                 if (vol > (1ull << 32)) vol = 1ull << 32;
             }
-            if (vol <= (unsigned long long)cap) {
+            if (vol <= (unsigned long long)Q.tile_cap) {
                 for (int k = 0; k < 3; ++k) {
-                    row.tlo[k] = l[k];
-                    row.tn[k] = w[k];
+                    tlo[k] = l[k];
+                    tn[k] = w[k];
                 }
                 break;
             }
         }
     }
-    for (int k = 0; k < 3; ++k) {
-        rows[r].tlo[k] = row.tlo[k];
-        rows[r].tn[k] = row.tn[k];
-    }
+    if (lane == 0)
+        for (int k = 0; k < 3; ++k) {
+            rows[r].tlo[k] = tlo[k];
+            rows[r].tn[k] = tn[k];
+        }
 }
 
 // Patient transport of a round's staged particles.  Each row has a counter of
@@ -1770,16 +1865,18 @@ __global__ __launch_bounds__(64) void tile_box_kernel(GeomDev g, RowDev *rows, i
 // that did not get it deposit straight into the slot grid.
 // Draws are of one wavefull by default: more keep waves longer on rows other
 // than the tile's (0.4 cc head matrix, transport of all epochs: 137, 123 and
-// 114 ms at 256, 128 and 64 records a draw).  Bound by VALU issue, and next by
-// the memory-side atomics: of 1.07e9 deposits outside the tile per 0.4 cc head
-// matrix (2.0e9 with int64 entries, boxes sized from the range alone and the
-// tile joined only at a draw) at 1.5e10 of 2.0e10 per second; 71.5 ms against
-// 105 ms with source and beam line inside and a drain after every chunk.
+// 114 ms at 256, 128 and 64 records a draw).  Bound by VALU issue (384
+// instructions a wave-step; 89 % of the launch) and next by the memory-side
+// atomics (1.4e10 of 2.0e10 per second).  Measured on the 13-scenario matrices,
+// 0.4 cc / 8 cc head: 110 / 546 ms as one kernel with source and beam line, a
+// drain after every chunk and int64 tile entries; 71.5 / 399 ms with staged
+// draws, 32-bit entries and the tile joined in flight; 57 / 311 ms with the
+// step rewritten for instruction count and exhausted rows leaving the tile.
 // Each history's arithmetic and random stream are those of a lane running it
 // alone, and the tallies are integer sums: the result does not depend on
 // the schedule.  The only waits between waves are for the wave that is
 // replacing the current row, which does so without waiting on anyone.
-template <bool X>
+template <bool X, int P>
 // Physics mode: up to 1024 threads (16 waves at <= 128 VGPRs, one workgroup
 // per CU with a ~120 KiB tile); double-float mode: up to 768 (12 waves at
 // <= 168 VGPRs).
@@ -1899,6 +1996,33 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
             }
             if (__builtin_amdgcn_readfirstlane((uint32_t)joined) != 0u) sink.tile = tile;
         };
+        // leaves the tile; the last user adds it out and frees it
+        auto leave = [&]() {
+            sink.tile = nullptr;
+            bool flusher = false;
+            if (lane == 0) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                for (;;) {
+                    unsigned long long t = rd_lds64(&s_tile);
+                    const bool last = (uint32_t)t == 1u;
+                    const unsigned long long want = last ? (((unsigned long long)rl << 32) | kTileBusy) : t - 1ull;
+                    if (__hip_atomic_compare_exchange_strong(&s_tile, &t, want, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
+                                                             __HIP_MEMORY_SCOPE_WORKGROUP)) {
+                        flusher = last;
+                        break;
+                    }
+                }
+            }
+            flusher = __builtin_amdgcn_readfirstlane((uint32_t)flusher) != 0u;
+            if (flusher) {
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+                tile_flush(tile, row, Q, g, rl, lane);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                if (lane == 0)
+                    __hip_atomic_store(&s_tile, (unsigned long long)rl << 32, __ATOMIC_RELEASE,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        };
         if (boxed) join();
         Acc acc;
 #pragma unroll
@@ -1925,61 +2049,25 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
             }
             // a wave that started beside the previous row's stragglers gets
             // the tile soon after they have left it
-            if (boxed && sink.tile == nullptr && (++since & 3u) == 0u) join();
+            if (boxed && sink.tile == nullptr && n_staged != 0u && (++since & 3u) == 0u) join();
             const bool refill = next < end && nidle >= min((uint32_t)Q.refill_min, end - next);
             if (!refill && nidle == 64u) break;
+            // an exhausted row's last particles (those that miss the head cross
+            // the whole grid in air, 2.5 times the mean steps) do not hold the
+            // tile: the wave leaves it once kLeaveIdle lanes are idle
+            if (n_staged == 0u && nidle >= kLeaveIdle && sink.tile != nullptr) leave();
             const uint32_t k = next + (uint32_t)__popcll(idle & below);
             if (refill && !active && k < end) {
-                // word by word (single-word loads are not merged into
-                // 4-register tuples, so each field can land in the
-                // register the loop carries it in)
-                const uint32_t *rw = reinterpret_cast<const uint32_t *>(stg + k);
-                auto ld = [&](int i) {
-                    return __hip_atomic_load(rw + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                };
-                v.px = __uint_as_float(ld(0)); v.py = __uint_as_float(ld(1));
-                v.pz = __uint_as_float(ld(2)); v.dx = __uint_as_float(ld(3));
-                v.dy = __uint_as_float(ld(4)); v.dz = __uint_as_float(ld(5));
-                v.E = __uint_as_float(ld(6)); v.Elo = __uint_as_float(ld(7));
-                v.pxlo = v.pylo = v.pzlo = 0.0f;
-                v.nblk = ld(8); v.hist = ld(9); v.nsteps = ld(10);
-                ps.vox = ld(11);
-                ps.idx[0] = (int)ld(12); ps.idx[1] = (int)ld(13); ps.idx[2] = (int)ld(14);
-                ps.hu = (int)ld(15);
+                load_staged(stg + k, v, ps);
                 active = true;
             }
             if (refill) next = min(end, next + nidle);
             if (active) {
-                active = patient_step<TileSink, X>(v, acc, sp.scale, T, g, sc.range_scale, sink, ps);
+                active = patient_step<TileSink, X, P>(v, acc, sp.scale, T, g, sc.range_scale, sink, ps);
                 if (!active) acc.steps += v.nsteps;
             }
         }
-        // ---- leave the tile; the last user adds it out and frees it
-        if (sink.tile != nullptr) {
-            bool flusher = false;
-            if (lane == 0) {
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                for (;;) {
-                    unsigned long long t = rd_lds64(&s_tile);
-                    const bool last = (uint32_t)t == 1u;
-                    const unsigned long long want = last ? (((unsigned long long)rl << 32) | kTileBusy) : t - 1ull;
-                    if (__hip_atomic_compare_exchange_strong(&s_tile, &t, want, __ATOMIC_ACQ_REL, __ATOMIC_RELAXED,
-                                                             __HIP_MEMORY_SCOPE_WORKGROUP)) {
-                        flusher = last;
-                        break;
-                    }
-                }
-            }
-            flusher = __builtin_amdgcn_readfirstlane((uint32_t)flusher) != 0u;
-            if (flusher) {
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                tile_flush(tile, row, Q, g, rl, lane);
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                if (lane == 0)
-                    __hip_atomic_store(&s_tile, (unsigned long long)rl << 32, __ATOMIC_RELEASE,
-                                       __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-        }
+        if (sink.tile != nullptr) leave();
         flush_ledger(acc, Q.ledger + (size_t)row.scen * NLEDGER, lane);
         flush_stats(acc, Q.stats, lane);
     }
@@ -2642,6 +2730,24 @@ __global__ __launch_bounds__(256) void sur_resume_csr_kernel(GeomDev g, QueueDev
     if ((threadIdx.x & 63) == 0 && st != 0) atomicAdd(Q.stats + 0, st);
 }
 
+// Reciprocal tables of a blob: segment widths (hardware estimate) and slopes
+// (estimate and one Newton step), as the steps used to compute them; the last
+// entries stay (sentinels).
+__global__ void derive_tables_kernel(float *blob) {
+    const int i = threadIdx.x;
+    if (i >= NE - 1) return;
+    if (blockIdx.x == 0) blob[TAB_RDW + i] = __builtin_amdgcn_rcpf(blob[TAB_DWH + i]);
+    float *tm = blob + TAB_SHARED + blockIdx.x * TAB_PER_MAT;
+    tm[T_RS * NE + i] = rcp_nr(tm[T_SH * NE + i]);
+}
+
+__global__ void density_kernel(const int16_t *hu, float *rho, size_t n) {
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        int m;
+        rho[i] = hu_density<false>((int)hu[i], m).h;
+    }
+}
+
 // ------------------------------------------------------------ batches, dose
 // fold one batch: total += q_b, sum of squares += q_b^2 (FP64), clear q_b
 __global__ void fold_batch_kernel(unsigned long long *qb, long long *qt, double *s2, size_t n) {
@@ -2706,10 +2812,20 @@ int queue_tile_cap(unsigned physics, int threads) {
 
 size_t queue_static_lds(unsigned physics) { return (tab_hi_floats(3) + (physics == 0 ? tab_lo_floats(3) : 4)) * 4 + 256; }
 
-hipError_t launch_tile_box(const GeomDev &g, RowDev *rows, int n, const FieldDev *fields, const SpotDev *spots,
-                           const ScenDev *scen, int cap, hipStream_t s) {
-    if (n > 0)
-        hipLaunchKernelGGL(tile_box_kernel, dim3((n + 63) / 64), dim3(64), 0, s, g, rows, n, fields, spots, scen, cap);
+hipError_t launch_derive_tables(float *blob, hipStream_t s) {
+    hipLaunchKernelGGL(derive_tables_kernel, dim3(NMAT), dim3(NE), 0, s, blob);
+    return hipGetLastError();
+}
+
+hipError_t launch_density(const int16_t *hu, float *rho, size_t n, hipStream_t s) {
+    const int blocks = (int)std::min<size_t>((n + 255) / 256, 8192);
+    hipLaunchKernelGGL(density_kernel, dim3(blocks), dim3(256), 0, s, hu, rho, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_tile_box(const GeomDev &g, const QueueDev &Q, RowDev *rows, hipStream_t s) {
+    if (Q.n_rows > 0)
+        hipLaunchKernelGGL(tile_box_kernel, dim3((Q.n_rows + 3) / 4), dim3(256), 0, s, g, Q, rows);
     return hipGetLastError();
 }
 
@@ -2736,8 +2852,14 @@ hipError_t launch_beam(const GeomDev &g, QueueDev Q, int cus, hipStream_t s) {
 hipError_t launch_queue(const GeomDev &g, const QueueDev &Q, int blocks, int threads, hipStream_t s) {
     threads = queue_threads(Q.physics, threads);
     const size_t tile_bytes = (size_t)Q.tile_cap * sizeof(uint32_t);
-    if (Q.physics == 0) hipLaunchKernelGGL(queue_kernel<true>, dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
-    else hipLaunchKernelGGL(queue_kernel<false>, dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
+    // all processes together are compiled in; a part of them is read per launch
+    if (Q.physics == 0)
+        hipLaunchKernelGGL((queue_kernel<true, 0>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
+    else if (Q.physics == (PH_STRAGGLE | PH_MCS | PH_NUCLEAR))
+        hipLaunchKernelGGL((queue_kernel<false, PH_STRAGGLE | PH_MCS | PH_NUCLEAR>), dim3(blocks), dim3(threads),
+                           tile_bytes, s, g, Q);
+    else
+        hipLaunchKernelGGL((queue_kernel<false, -1>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
     return hipGetLastError();
 }
 
