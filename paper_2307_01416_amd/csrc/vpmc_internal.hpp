@@ -164,6 +164,9 @@ struct RowDev {
     uint32_t spot_global; // index into the flattened spot table
     int scen;
     uint32_t n_hist;
+    // dense runs: a row is a range of a batch's items in one scenario
+    uint32_t batch, dest;           // batch, and the tally its deposits go to
+    unsigned long long item0;       // first item of the batch's items
     int tlo[3], tn[3];    // LDS tile box of the row in voxel indices (tn = 0: none; tile_box_kernel)
 };
 
@@ -193,6 +196,12 @@ struct QueueDev {
     int beam_groups;                      // consecutive groups a wave of the beam line takes at a time
     int refill_min;                       // idle lanes that trigger a refill in the patient loop
     float *stage;                         // [64 * (g_end - g_begin)] staged VPs (64 B)
+    // dense runs: items of batch b = histories of all spots in spot_order, spot
+    // spot_order[s] from item_off[b * (n_spots + 1) + s] on
+    int dense, n_spots, n_batches;
+    const unsigned long long *item_off;
+    const uint32_t *spot_order;
+    unsigned long long *let;              // [n_scen][gstride] LET numerators, or null
     const FieldDev *fields;
     const int *poly_off;                  // per field: offset into polys
     const float2 *polys;
@@ -382,8 +391,10 @@ hipError_t opt_update(const OptDev &O, int mode, double beta, int it, double *hi
 // launchers (vpmc_kernels.hip)
 hipError_t launch_transport(const GeomDev &g, const FieldDev &f, const LaunchDev &L, int blocks,
                             int threads, hipStream_t s);
-hipError_t launch_fold_batch(unsigned long long *q_batch, long long *q_total, double *s2, size_t n,
+hipError_t launch_fold_batch(unsigned long long *q_batch, int nb, long long *q_total, double *s2, size_t n,
                              hipStream_t s);
+hipError_t launch_fold_dose(unsigned long long *q_batch, int n_batches, long long *q_total, const GeomDev &g,
+                            double mev_scale, float *dose, float *sigma, size_t n, hipStream_t s);
 hipError_t launch_dose(const long long *q, const double *s2, int n_batches, const GeomDev &g,
                        double mev_scale, float *dose, float *sigma, size_t n, hipStream_t s);
 

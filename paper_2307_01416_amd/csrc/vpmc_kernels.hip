@@ -487,7 +487,7 @@ struct DenseSink {
     unsigned long long *tally;
     unsigned long long *let = nullptr;   // dose-averaged LET numerator, or none
     static constexpr bool kLet = true;
-    __device__ __forceinline__ void add_let(uint32_t v, long long q) const {
+    __device__ __forceinline__ void add_let(uint32_t v, const int *, long long q) const {
         atomicAdd(let + v, (unsigned long long)q);
     }
     __device__ __forceinline__ void add(uint32_t v, const int *, long long q) const {
@@ -506,7 +506,7 @@ struct SparseSink {
     uint8_t *mark;
     static constexpr bool kLet = false;
     unsigned long long *let = nullptr;
-    __device__ __forceinline__ void add_let(uint32_t, long long) const {}
+    __device__ __forceinline__ void add_let(uint32_t, const int *, long long) const {}
     __device__ __forceinline__ void add(uint32_t v, const int *, long long q) const {
         put(v, q);
     }
@@ -516,38 +516,55 @@ struct SparseSink {
     }
 };
 
-// Row tile of the influence-matrix builder: a dense box of the CT grid in LDS
-// around the spot's central ray, shared by the waves of a workgroup that work
-// on the same row.  Deposits inside the box are LDS atomics, the others go to
-// the row's slot grid; the box is added into the slot grid once when its last
-// user leaves.  On this GPU the int64 tally atomics to device memory are
-// performed on the memory side, beyond the XCD's L2, and their rate bounds
-// the step loop; the tile takes most of them off that path.  An entry holds
-// the low 32 bits of its voxel's sum: the deposit's high half and the carry
-// out of the entry (the returned old value tells) go to the slot grid, where
-// the entry's bits are added once at the end, so the int64 sum is exact.  At
-// 4 bytes a voxel the box is twice as large as with int64 entries, and a
-// carry comes once per few hundred deposits.
+// Row tile of the work queue: a dense box of the CT grid in LDS around the
+// row's particles, shared by the waves of a workgroup that work on the same
+// row.  Deposits inside the box are LDS atomics, the others go to the row's
+// grid; the box is added into the grid once when its last user leaves.  On
+// this GPU the int64 tally atomics to device memory are performed on the
+// memory side, beyond the XCD's L2, and their rate bounds the step loop; the
+// tile takes most of them off that path.  An entry holds the low 32 bits of its
+// voxel's sum: the deposit's high half and the carry out of the entry (the
+// returned old value tells) go to the grid, where the entry's bits are added
+// once at the end, so the int64 sum is exact.  At 4 bytes a voxel the box is
+// twice as large as with int64 entries, and a carry comes once per few hundred
+// deposits.  MARKS: influence-matrix slots with their touched-block marks, else
+// dense tallies.  LET: a second box behind the first for the numerator of the
+// dose-averaged LET.
+template <bool MARKS, bool LET>
 struct TileSink {
     uint32_t *tile;     // nullptr: this wave does not use the tile
     int lo0, lo1, lo2;
     uint32_t n0, n1, n2;
     SparseSink gs;
-    unsigned long long *let = nullptr;   // (no LET tally in influence matrices)
-    static constexpr bool kLet = false;
-    __device__ __forceinline__ void add_let(uint32_t, long long) const {}
+    unsigned long long *let;   // dense LET numerator, or none
+    uint32_t let_off;          // entries from a voxel's tally to its LET entry
+    static constexpr bool kLet = LET;
+    __device__ __forceinline__ void put(uint32_t v, long long q) const {
+        if constexpr (MARKS) gs.put(v, q);
+        else atomicAdd(gs.grid + v, (unsigned long long)q);
+    }
+    // the low half into a tile entry; true when the rest (in q) is not zero
+    static __device__ __forceinline__ bool carry(uint32_t *e, long long &q) {
+        const uint32_t ql = (uint32_t)q;
+        const uint32_t old = atomicAdd(e, ql);
+        const int qh = (int)(q >> 32) + (old + ql < ql ? 1 : 0);
+        q = (long long)qh << 32;
+        return qh != 0;
+    }
+    __device__ __forceinline__ bool inside(const int *idx, uint32_t &at) const {
+        const uint32_t u0 = (uint32_t)(idx[0] - lo0), u1 = (uint32_t)(idx[1] - lo1), u2 = (uint32_t)(idx[2] - lo2);
+        at = u0 + n0 * (u1 + n1 * u2);
+        return u0 < n0 && u1 < n1 && u2 < n2;
+    }
+    __device__ __forceinline__ void add_let(uint32_t v, const int *idx, long long q) const {
+        uint32_t at;
+        if (tile && inside(idx, at) && !carry(tile + let_off + at, q)) return;
+        atomicAdd(let + v, (unsigned long long)q);
+    }
     __device__ __forceinline__ void add(uint32_t v, const int *idx, long long q) const {
-        if (tile) {
-            const uint32_t u0 = (uint32_t)(idx[0] - lo0), u1 = (uint32_t)(idx[1] - lo1), u2 = (uint32_t)(idx[2] - lo2);
-            if (u0 < n0 && u1 < n1 && u2 < n2) {
-                const uint32_t ql = (uint32_t)q;
-                const uint32_t old = atomicAdd(tile + (u0 + n0 * (u1 + n1 * u2)), ql);
-                const int qh = (int)(q >> 32) + (old + ql < ql ? 1 : 0);
-                if (qh != 0) gs.put(v, (long long)qh << 32);
-                return;
-            }
-        }
-        gs.put(v, q);
+        uint32_t at;
+        if (tile && inside(idx, at) && !carry(tile + at, q)) return;
+        put(v, q);
     }
 };
 
@@ -1156,6 +1173,12 @@ struct PState {
 // the density tells the material.
 constexpr float kRhoTissue = 0.1006f, kRhoBone = 1.0897f;
 
+template <bool X>
+__device__ __forceinline__ uint32_t cell_of(const GeomDev &g, uint32_t vox) {
+    if constexpr (X) return g.kind == 1 ? (uint32_t)(int)g.hu[vox] : 0u;
+    return __float_as_uint(g.kind == 1 ? g.rho[vox] : 1.0f);
+}
+
 // Entry into the CT grid: beam frame -> CT frame with the scenario shift,
 // ray-box intersection from the last exit plane (tmin), voxel-local
 // coordinates.  Returns false when the VP misses the grid (its energy goes
@@ -1229,8 +1252,7 @@ __device__ bool patient_enter(Lane &v, Acc &acc, float scale, const GeomDev &g, 
     ps.idx[1] = idx[1];
     ps.idx[2] = idx[2];
     ps.vox = (uint32_t)idx[0] + (uint32_t)g.nx * ((uint32_t)idx[1] + (uint32_t)g.ny * (uint32_t)idx[2]);
-    if constexpr (X) ps.cell = g.kind == 1 ? (uint32_t)(int)g.hu[ps.vox] : 0u;
-    else ps.cell = __float_as_uint(g.kind == 1 ? g.rho[ps.vox] : 1.0f);
+    ps.cell = cell_of<X>(g, ps.vox);
     return true;
 }
 
@@ -1308,7 +1330,7 @@ __device__ __forceinline__ bool patient_step(Lane &v, Acc &acc, float scale, con
         if (sink.let != nullptr) {
             // numerator of the dose-averaged LET: rne(dep * LET * w/N * 2^(k - kLetShift))
             const long long ql = to_fixed(dep * let, scale * (1.0f / (float)(1 << kLetShift)));
-            if (ql != 0) sink.add_let(ps.vox, ql);
+            if (ql != 0) sink.add_let(ps.vox, ps.idx, ql);
         }
     }
     acc.led[L_GRID] += qd;
@@ -1437,7 +1459,8 @@ __global__ __launch_bounds__(512) void transport_kernel(GeomDev g, FieldDev f, L
 // ------------------------------------------------------------ CSR mode
 // A VP staged at its entry into the CT grid (64 B, four 16-byte words):
 // voxel-local position, direction in the CT frame, energy pair, Philox block
-// counter, history, step count, voxel (linear, per axis) and its CT number or density.
+// counter, history, step count, voxel (linear, per axis) and its CT number or density
+// (in dense runs, whose rows hold several spots, the spot instead).
 struct alignas(16) StagedVP {
     float px, py, pz, dx;
     float dy, dz, E, Elo;
@@ -1447,18 +1470,20 @@ struct alignas(16) StagedVP {
 };
 static_assert(sizeof(StagedVP) == 4 * kStageFields, "staging record");
 
+template <bool DENSE>
 __device__ __forceinline__ void store_staged(StagedVP *to, const Lane &v, const PState &ps) {
     StagedVP s;
     s.px = v.px; s.py = v.py; s.pz = v.pz; s.dx = v.dx;
     s.dy = v.dy; s.dz = v.dz; s.E = v.E; s.Elo = v.Elo;
     s.nblk = v.nblk; s.hist = v.hist; s.nsteps = v.nsteps; s.vox = ps.vox;
-    s.i0 = ps.idx[0]; s.i1 = ps.idx[1]; s.i2 = ps.idx[2]; s.cell = ps.cell;
+    s.i0 = ps.idx[0]; s.i1 = ps.idx[1]; s.i2 = ps.idx[2]; s.cell = DENSE ? v.spot : ps.cell;
     *to = s;
 }
 
 // Word by word: single-word loads are not merged into 4-register tuples, so
 // each field can land in the register the step loop carries it in.
-__device__ __forceinline__ void load_staged(const StagedVP *from, Lane &v, PState &ps) {
+template <bool DENSE, bool X>
+__device__ __forceinline__ void load_staged(const StagedVP *from, const GeomDev &g, Lane &v, PState &ps) {
     const uint32_t *rw = reinterpret_cast<const uint32_t *>(from);
     auto ld = [&](int i) { return __hip_atomic_load(rw + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT); };
     v.px = __uint_as_float(ld(0)); v.py = __uint_as_float(ld(1));
@@ -1469,40 +1494,56 @@ __device__ __forceinline__ void load_staged(const StagedVP *from, Lane &v, PStat
     v.nblk = ld(8); v.hist = ld(9); v.nsteps = ld(10);
     ps.vox = ld(11);
     ps.idx[0] = (int)ld(12); ps.idx[1] = (int)ld(13); ps.idx[2] = (int)ld(14);
-    ps.cell = ld(15);
+    if constexpr (DENSE) {
+        v.spot = ld(15);
+        ps.cell = cell_of<X>(g, ps.vox);
+    } else {
+        ps.cell = ld(15);
+    }
 }
 
 constexpr uint32_t kRowNone = 0xFFFFFFFFu;   // workgroup row word: no row yet
 constexpr uint32_t kRowPick = 0xFFFFFFFDu;   // a wave is picking the next row
 constexpr uint32_t kRowEnd = 0xFFFFFFFEu;    // no work left in the epoch
 constexpr uint32_t kTileBusy = 0xFFFFFFFFu;  // tile users field while it is added out
+constexpr int kStealRows = 2048;             // last rows of a round that are looked through for work
 
 __device__ __forceinline__ unsigned long long rd_lds64(const unsigned long long *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-// Adds the tile of row rl (round-local) into its slot grid and clears it; one wave.
-__device__ void tile_flush(uint32_t *tile, const RowDev &row, const QueueDev &Q, const GeomDev &g, uint32_t rl,
-                           int lane) {
-    const uint32_t n0 = (uint32_t)row.tn[0], n1 = (uint32_t)row.tn[1];
-    const uint32_t tn = n0 * n1 * (uint32_t)row.tn[2];
-    const SparseSink gs{Q.grid + (size_t)rl * Q.gstride, Q.mark + (size_t)rl * Q.mstride};
+// Adds the tile into its row's grid and clears it; one wave.
+template <bool MARKS, bool LET>
+__device__ void tile_flush(uint32_t *tile, const TileSink<MARKS, LET> &sink, const GeomDev &g, int lane) {
+    const uint32_t n0 = sink.n0, n1 = sink.n1, tn = n0 * n1 * sink.n2;
     // e / n0 and e / (n0 n1) by FP32 reciprocals: exact, entries < 2^16
     const float i0 = 1.0f / (float)n0, i1 = 1.0f / (float)n1;
     for (uint32_t e0 = (uint32_t)lane; e0 < tn; e0 += 256) {
-        uint32_t q[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) q[j] = e0 + 64u * j < tn ? tile[e0 + 64u * j] : 0u;
+        uint32_t q[4], ql[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if (q[j] == 0u) continue;
+            q[j] = e0 + 64u * j < tn ? tile[e0 + 64u * j] : 0u;
+            if constexpr (LET) ql[j] = e0 + 64u * j < tn ? tile[sink.let_off + e0 + 64u * j] : 0u;
+            else ql[j] = 0u;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if ((q[j] | ql[j]) == 0u) continue;
             const uint32_t e = e0 + 64u * j;
-            tile[e] = 0u;
             const uint32_t e1 = (uint32_t)(((float)e + 0.5f) * i0), u0 = e - n0 * e1;
             const uint32_t u2 = (uint32_t)(((float)e1 + 0.5f) * i1), u1 = e1 - n1 * u2;
-            gs.put((uint32_t)row.tlo[0] + u0 +
-                       (uint32_t)g.nx * ((uint32_t)row.tlo[1] + u1 + (uint32_t)g.ny * ((uint32_t)row.tlo[2] + u2)),
-                   (long long)q[j]);
+            const uint32_t v = (uint32_t)sink.lo0 + u0 + (uint32_t)g.nx * ((uint32_t)sink.lo1 + u1 +
+                                                                           (uint32_t)g.ny * ((uint32_t)sink.lo2 + u2));
+            if (q[j] != 0u) {
+                tile[e] = 0u;
+                sink.put(v, (long long)q[j]);
+            }
+            if constexpr (LET) {
+                if (ql[j] != 0u) {
+                    tile[sink.let_off + e] = 0u;
+                    atomicAdd(sink.let + v, (unsigned long long)ql[j]);
+                }
+            }
         }
     }
 }
@@ -1540,6 +1581,7 @@ __device__ __forceinline__ size_t stage_base(const QueueDev &Q, uint32_t r) {
 
 // Appends the particles of the lanes with `in` to the staged lists of their
 // rows: ballot compaction per row, one returning atomic per row and wave.
+template <bool DENSE>
 __device__ __forceinline__ void stage_out(const QueueDev &Q, bool in, uint32_t r, const Lane &v, const PState &ps,
                                           int lane) {
     for (unsigned long long todo = __ballot(in); todo;) {
@@ -1550,9 +1592,9 @@ __device__ __forceinline__ void stage_out(const QueueDev &Q, bool in, uint32_t r
         if (lane == 0) at = atomicAdd(&Q.ctl[rr].staged, (unsigned int)__popcll(m));
         at = __builtin_amdgcn_readfirstlane(at);
         if (mine)
-            store_staged(reinterpret_cast<StagedVP *>(Q.stage) + stage_base(Q, rr) + at +
-                             (uint32_t)__popcll(m & ((1ull << lane) - 1ull)),
-                         v, ps);
+            store_staged<DENSE>(reinterpret_cast<StagedVP *>(Q.stage) + stage_base(Q, rr) + at +
+                                    (uint32_t)__popcll(m & ((1ull << lane) - 1ull)),
+                                v, ps);
         todo &= ~m;
     }
 }
@@ -1574,9 +1616,10 @@ __device__ __forceinline__ void stage_out(const QueueDev &Q, bool in, uint32_t r
 // this way with the edge searches divided among the lanes (47 %).
 constexpr int kBlkStack = 128;   // up to 63 waiting + 64 pushed by a group
 
-template <bool X, bool D>
+template <bool X, bool D, bool DENSE>
 __global__ __launch_bounds__(256, 3) void beam_kernel(GeomDev g, QueueDev Q) {
-    constexpr int kW = X ? 14 : 13;   // words of a waiting particle (the low part of the depth only when X)
+    // words of a waiting particle (the spot only in dense runs, the low part of the depth only when X)
+    constexpr int kSpot = 13, kLow = DENSE ? 14 : 13, kW = kLow + (X ? 1 : 0);
     __shared__ __attribute__((aligned(16))) float hi[tab_hi_floats(2)], lo[X ? tab_lo_floats(2) : 4];
     __shared__ float2 poly[POLY_LDS];
     __shared__ uint32_t stacks[4][kW][kBlkStack];
@@ -1628,17 +1671,35 @@ __global__ __launch_bounds__(256, 3) void beam_kernel(GeomDev g, QueueDev Q) {
                 cur_scen = row.scen;
             }
             cur_field = row.field;
-            const SpotDev sp = Q.spots[row.spot_global];
             const FieldDev &f = Q.fields[row.field];
             const unsigned long long h = (G - Q.grp_off[r]) * 64ull + lane;
             const bool on = h < row.n_hist;
+            uint32_t spot = row.spot, hist = (uint32_t)h, spot_at = row.spot_global;
+            if constexpr (DENSE) {
+                // the row's items run through the batch's spots: the spot of
+                // the group's first item by bisection, the lanes' from there
+                const unsigned long long *off = Q.item_off + (size_t)row.batch * ((size_t)Q.n_spots + 1);
+                const unsigned long long i0 = row.item0 + (h - lane), item = row.item0 + h;
+                uint32_t s = 0;
+                for (uint32_t e = (uint32_t)Q.n_spots; e - s > 1u;) {   // off[s] <= i0 < off[e]
+                    const uint32_t mid = (s + e) >> 1;
+                    if (off[mid] <= i0) s = mid;
+                    else e = mid;
+                }
+                s = (uint32_t)__builtin_amdgcn_readfirstlane((int)s);
+                if (on)
+                    while (item >= off[s + 1]) ++s;
+                spot = spot_at = Q.spot_order[s];
+                hist = row.batch + (uint32_t)Q.n_batches * (uint32_t)(item - off[s]);
+            }
+            const SpotDev sp = Q.spots[spot_at];
             Lane v;
             PState ps;
             v.k0 = Q.key0;
             v.k1 = Q.seed_hi ^ row.field_id;
-            v.spot = row.spot;
+            v.spot = spot;
             v.physics = Q.physics;
-            v.hist = (uint32_t)h;
+            v.hist = hist;
             v.nblk = 0;
             v.nsteps = 0;
             float tmin;
@@ -1654,7 +1715,8 @@ __global__ __launch_bounds__(256, 3) void beam_kernel(GeomDev g, QueueDev Q) {
                 stk[6][at] = __float_as_uint(v.E); stk[7][at] = __float_as_uint(v.Elo);
                 stk[8][at] = v.nblk; stk[9][at] = v.hist; stk[10][at] = v.nsteps;
                 stk[11][at] = 0u; stk[12][at] = r;
-                if constexpr (X) stk[13][at] = __float_as_uint(v.pzlo);
+                if constexpr (DENSE) stk[kSpot][at] = v.spot;
+                if constexpr (X) stk[kLow][at] = __float_as_uint(v.pzlo);
             }
             nst += __popcll(blk);
             const bool in = st == BL_PATIENT && patient_enter<X>(v, acc, sp.scale, g, f, Q.scen[row.scen].shift, tmin, ps);
@@ -1662,7 +1724,7 @@ __global__ __launch_bounds__(256, 3) void beam_kernel(GeomDev g, QueueDev Q) {
                 if (!in && st != BL_BLOCK) acc.steps += v.nsteps;
                 acc.hist += 1;
             }
-            stage_out(Q, in, r, v, ps, lane);
+            stage_out<DENSE>(Q, in, r, v, ps, lane);
             ++G;
             advance();
             continue;
@@ -1689,13 +1751,13 @@ __global__ __launch_bounds__(256, 3) void beam_kernel(GeomDev g, QueueDev Q) {
             it = stk[11][at];
             vr = stk[12][at];
             v.pzlo = 0.0f;
-            if constexpr (X) v.pzlo = __uint_as_float(stk[13][at]);
+            if constexpr (X) v.pzlo = __uint_as_float(stk[kLow][at]);
             const RowDev &row = Q.rows[vr];
-            v.spot = row.spot;
+            v.spot = DENSE ? stk[kSpot][at] : row.spot;
             v.k0 = Q.key0;
             v.k1 = Q.seed_hi ^ row.field_id;
             v.physics = Q.physics;
-            scale = Q.spots[row.spot_global].scale;
+            scale = Q.spots[DENSE ? v.spot : row.spot_global].scale;
         }
         // half of a wavefull may go back when more can follow it
         const int park = nst > 0 || (more && same) ? 32 : 0;
@@ -1708,7 +1770,7 @@ __global__ __launch_bounds__(256, 3) void beam_kernel(GeomDev g, QueueDev Q) {
         PState ps;
         const bool in = st == BK_DOWN && patient_enter<X>(v, acc, scale, g, f, Q.scen[cur_scen].shift, 0.0f, ps);
         if (on && st != BK_IN && !in) acc.steps += v.nsteps;
-        stage_out(Q, in, vr, v, ps, lane);
+        stage_out<DENSE>(Q, in, vr, v, ps, lane);
         const unsigned long long back = __ballot(st == BK_IN);
         if (st == BK_IN) {
             const int at = nst + __popcll(back & below);
@@ -1719,7 +1781,8 @@ __global__ __launch_bounds__(256, 3) void beam_kernel(GeomDev g, QueueDev Q) {
             stk[8][at] = v.nblk; stk[9][at] = v.hist; stk[10][at] = v.nsteps;
             stk[11][at] = it;
             stk[12][at] = vr;
-            if constexpr (X) stk[13][at] = __float_as_uint(v.pzlo);
+            if constexpr (DENSE) stk[kSpot][at] = v.spot;
+            if constexpr (X) stk[kLow][at] = __float_as_uint(v.pzlo);
         }
         nst += __popcll(back);
     }
@@ -1876,7 +1939,7 @@ __global__ __launch_bounds__(256) void tile_box_kernel(GeomDev g, QueueDev Q, Ro
 // alone, and the tallies are integer sums: the result does not depend on
 // the schedule.  The only waits between waves are for the wave that is
 // replacing the current row, which does so without waiting on anyone.
-template <bool X, int P>
+template <bool X, int P, bool DENSE, bool LET>
 // Physics mode: up to 1024 threads (16 waves at <= 128 VGPRs, one workgroup
 // per CU with a ~120 KiB tile); double-float mode: up to 768 (12 waves at
 // <= 168 VGPRs).
@@ -1884,10 +1947,10 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
     __shared__ __attribute__((aligned(16))) float hi[tab_hi_floats(3)], lo[X ? tab_lo_floats(3) : 4];
     __shared__ unsigned long long s_row;    // current row (high word; kRowNone while replaced)
     __shared__ unsigned long long s_tile;   // (row of the tile << 32) | users, kTileBusy while flushed
-    extern __shared__ __attribute__((aligned(16))) uint32_t tile[];   // Q.tile_cap entries
+    extern __shared__ __attribute__((aligned(16))) uint32_t tile[];   // Q.tile_cap entries (twice with LET)
     stage_tables<X, 3>(hi, lo, Q.tables, DM_WATER);   // water, air, bone
     const Tabs T{hi, lo, -1, -1};
-    for (int i = threadIdx.x; i < Q.tile_cap; i += blockDim.x) tile[i] = 0u;
+    for (int i = threadIdx.x; i < Q.tile_cap * (LET ? 2 : 1); i += blockDim.x) tile[i] = 0u;
     if (threadIdx.x == 0) {
         s_row = (unsigned long long)kRowNone << 32;
         s_tile = (unsigned long long)kRowNone << 32;
@@ -1946,7 +2009,9 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
                 if (f < (unsigned long long)Q.n_rows) {
                     nr = (uint32_t)f;
                 } else {
-                    for (int r0 = 0; r0 < Q.n_rows; r0 += 64) {
+                    // (rows are handed out in order: those with records left
+                    // are among the last ones)
+                    for (int r0 = max(0, Q.n_rows - kStealRows); r0 < Q.n_rows; r0 += 64) {
                         const int r = r0 + lane;
                         bool left = false;
                         if (r < Q.n_rows)
@@ -1967,12 +2032,14 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
         }
         const uint32_t rl = cur;
         const RowDev row = Q.rows[Q.row_begin + rl];
-        const SpotDev sp = Q.spots[row.spot_global];
+        float scale = DENSE ? 0.0f : Q.spots[row.spot_global].scale;   // (dense rows: per lane)
         const ScenDev sc = Q.scen[row.scen];
         const StagedVP *const stg = reinterpret_cast<const StagedVP *>(Q.stage) + stage_base(Q, Q.row_begin + rl);
-        const SparseSink gsink{Q.grid + (size_t)rl * Q.gstride, Q.mark + (size_t)rl * Q.mstride};
-        TileSink sink{nullptr, row.tlo[0], row.tlo[1], row.tlo[2],
-                      (uint32_t)row.tn[0], (uint32_t)row.tn[1], (uint32_t)row.tn[2], gsink};
+        const SparseSink gsink{Q.grid + (size_t)(DENSE ? row.dest : rl) * Q.gstride,
+                               DENSE ? nullptr : Q.mark + (size_t)rl * Q.mstride};
+        TileSink<!DENSE, LET> sink{nullptr, row.tlo[0], row.tlo[1], row.tlo[2],
+                                   (uint32_t)row.tn[0], (uint32_t)row.tn[1], (uint32_t)row.tn[2], gsink,
+                                   LET ? Q.let + (size_t)row.scen * Q.gstride : nullptr, (uint32_t)Q.tile_cap};
         // join the tile if it holds this row (or is free and clear)
         const uint32_t tn = (uint32_t)row.tn[0] * (uint32_t)row.tn[1] * (uint32_t)row.tn[2];
         const bool boxed = tn != 0u && tn <= (uint32_t)Q.tile_cap;
@@ -2016,7 +2083,7 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
             flusher = __builtin_amdgcn_readfirstlane((uint32_t)flusher) != 0u;
             if (flusher) {
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                tile_flush(tile, row, Q, g, rl, lane);
+                tile_flush(tile, sink, g, lane);
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                 if (lane == 0)
                     __hip_atomic_store(&s_tile, (unsigned long long)rl << 32, __ATOMIC_RELEASE,
@@ -2058,12 +2125,13 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
             if (n_staged == 0u && nidle >= kLeaveIdle && sink.tile != nullptr) leave();
             const uint32_t k = next + (uint32_t)__popcll(idle & below);
             if (refill && !active && k < end) {
-                load_staged(stg + k, v, ps);
+                load_staged<DENSE, X>(stg + k, g, v, ps);
+                if constexpr (DENSE) scale = Q.spots[v.spot].scale;
                 active = true;
             }
             if (refill) next = min(end, next + nidle);
             if (active) {
-                active = patient_step<TileSink, X, P>(v, acc, sp.scale, T, g, sc.range_scale, sink, ps);
+                active = patient_step<TileSink<!DENSE, LET>, X, P>(v, acc, scale, T, g, sc.range_scale, sink, ps);
                 if (!active) acc.steps += v.nsteps;
             }
         }
@@ -2749,16 +2817,27 @@ __global__ void density_kernel(const int16_t *hu, float *rho, size_t n) {
 }
 
 // ------------------------------------------------------------ batches, dose
-// fold one batch: total += q_b, sum of squares += q_b^2 (FP64), clear q_b
-__global__ void fold_batch_kernel(unsigned long long *qb, long long *qt, double *s2, size_t n) {
+// fold nb batches, in order: total += q_b, sum of squares += q_b^2 (FP64), clear q_b
+__global__ void fold_batch_kernel(unsigned long long *qb, int nb, long long *qt, double *s2, size_t n) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
          i += (size_t)gridDim.x * blockDim.x) {
-        const long long q = (long long)qb[i];
-        if (q != 0) {
-            qt[i] += q;
-            const double d = (double)q;
-            s2[i] += d * d;
-            qb[i] = 0ull;
+        long long tot = 0;
+        double s = 0.0;
+        bool any = false;
+        for (int b = 0; b < nb; ++b) {
+            const long long q = (long long)qb[(size_t)b * n + i];
+            if (q == 0) continue;
+            if (!any) {
+                any = true;
+                s = s2[i];
+            }
+            tot += q;
+            s += (double)q * (double)q;
+            qb[(size_t)b * n + i] = 0ull;
+        }
+        if (any) {
+            qt[i] += tot;
+            s2[i] = s;
         }
     }
 }
@@ -2778,6 +2857,42 @@ __global__ void dose_kernel(const long long *q, const double *s2, int B, GeomDev
             // batch estimator of the standard error of the mean (FP64)
             const double D = (double)qi;
             const double var = fmax((double)B * s2[i] - D * D, 0.0) / (double)(B - 1);
+            sigma[i] = (float)sqrt(var) * conv;
+        }
+    }
+}
+
+// All batches of a scenario at once: fold_batch_kernel into nothing, then
+// dose_kernel, in one pass over the batch grids (8 B a voxel and batch read,
+// 16 B a voxel written; four batches' loads in flight).  HBM-bound.
+__global__ __launch_bounds__(256) void fold_dose_kernel(unsigned long long *qb, int B, long long *qt, GeomDev g,
+                                                        double mev_scale, float *dose, float *sigma, size_t n) {
+    const float vol_kg = g.sp[0] * g.sp[1] * g.sp[2] * 1e-6f;   // mm^3 -> cm^3 -> kg at 1 g/cm^3
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
+         i += (size_t)gridDim.x * blockDim.x) {
+        long long tot = 0;
+        double s = 0.0;
+        for (int b0 = 0; b0 < B; b0 += 4) {
+            long long q[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) q[j] = b0 + j < B ? (long long)qb[(size_t)(b0 + j) * n + i] : 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (q[j] == 0) continue;
+                tot += q[j];
+                s += (double)q[j] * (double)q[j];
+                qb[(size_t)(b0 + j) * n + i] = 0ull;
+            }
+        }
+        qt[i] = tot;
+        float rho = 1.0f;
+        int m;
+        if (g.kind == 1) hu_material(g.hu[i], m, rho);
+        const float conv = (float)mev_scale / (rho * vol_kg);   // Gy per (q unit)
+        if (dose) dose[i] = (float)tot * conv;
+        if (sigma) {
+            const double D = (double)tot;
+            const double var = fmax((double)B * s - D * D, 0.0) / (double)(B - 1);
             sigma[i] = (float)sqrt(var) * conv;
         }
     }
@@ -2839,27 +2954,38 @@ hipError_t launch_beam(const GeomDev &g, QueueDev Q, int cus, hipStream_t s) {
     Q.beam_groups = (int)std::max<unsigned long long>(1, std::min<unsigned long long>(kBeamGroups, groups / waves));
     const unsigned long long runs = (groups + Q.beam_groups - 1) / Q.beam_groups;
     const int blocks = (int)std::min<unsigned long long>((runs + 3) / 4, waves / 4);
-    if (Q.physics == 0) {
-        if (Q.div) hipLaunchKernelGGL((beam_kernel<true, true>), dim3(blocks), dim3(256), 0, s, g, Q);
-        else hipLaunchKernelGGL((beam_kernel<true, false>), dim3(blocks), dim3(256), 0, s, g, Q);
+    const bool x = Q.physics == 0, d = Q.div != 0, de = Q.dense != 0;
+#define VPMC_BEAM(X_, D_, E_) hipLaunchKernelGGL((beam_kernel<X_, D_, E_>), dim3(blocks), dim3(256), 0, s, g, Q)
+    if (x) {
+        if (d) { if (de) VPMC_BEAM(true, true, true); else VPMC_BEAM(true, true, false); }
+        else { if (de) VPMC_BEAM(true, false, true); else VPMC_BEAM(true, false, false); }
     } else {
-        if (Q.div) hipLaunchKernelGGL((beam_kernel<false, true>), dim3(blocks), dim3(256), 0, s, g, Q);
-        else hipLaunchKernelGGL((beam_kernel<false, false>), dim3(blocks), dim3(256), 0, s, g, Q);
+        if (d) { if (de) VPMC_BEAM(false, true, true); else VPMC_BEAM(false, true, false); }
+        else { if (de) VPMC_BEAM(false, false, true); else VPMC_BEAM(false, false, false); }
     }
+#undef VPMC_BEAM
     return hipGetLastError();
 }
 
 hipError_t launch_queue(const GeomDev &g, const QueueDev &Q, int blocks, int threads, hipStream_t s) {
     threads = queue_threads(Q.physics, threads);
-    const size_t tile_bytes = (size_t)Q.tile_cap * sizeof(uint32_t);
+    const bool let = Q.dense && Q.let;
+    const size_t tile_bytes = (size_t)Q.tile_cap * (let ? 2 : 1) * sizeof(uint32_t);
+    constexpr int kAll = PH_STRAGGLE | PH_MCS | PH_NUCLEAR;
+#define VPMC_QUEUE(X_, P_)                                                                                         \
+    do {                                                                                                           \
+        if (!Q.dense)                                                                                              \
+            hipLaunchKernelGGL((queue_kernel<X_, P_, false, false>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q); \
+        else if (let)                                                                                              \
+            hipLaunchKernelGGL((queue_kernel<X_, P_, true, true>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);   \
+        else                                                                                                       \
+            hipLaunchKernelGGL((queue_kernel<X_, P_, true, false>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);  \
+    } while (0)
     // all processes together are compiled in; a part of them is read per launch
-    if (Q.physics == 0)
-        hipLaunchKernelGGL((queue_kernel<true, 0>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
-    else if (Q.physics == (PH_STRAGGLE | PH_MCS | PH_NUCLEAR))
-        hipLaunchKernelGGL((queue_kernel<false, PH_STRAGGLE | PH_MCS | PH_NUCLEAR>), dim3(blocks), dim3(threads),
-                           tile_bytes, s, g, Q);
-    else
-        hipLaunchKernelGGL((queue_kernel<false, -1>), dim3(blocks), dim3(threads), tile_bytes, s, g, Q);
+    if (Q.physics == 0) VPMC_QUEUE(true, 0);
+    else if (Q.physics == kAll) VPMC_QUEUE(false, kAll);
+    else VPMC_QUEUE(false, -1);
+#undef VPMC_QUEUE
     return hipGetLastError();
 }
 
@@ -2979,9 +3105,16 @@ hipError_t launch_surrogate_sample(const FieldDev &f, const float *entries, int 
     return hipGetLastError();
 }
 
-hipError_t launch_fold_batch(unsigned long long *qb, long long *qt, double *s2, size_t n, hipStream_t s) {
+hipError_t launch_fold_batch(unsigned long long *qb, int nb, long long *qt, double *s2, size_t n, hipStream_t s) {
     const int blocks = (int)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
-    hipLaunchKernelGGL(fold_batch_kernel, dim3(blocks), dim3(256), 0, s, qb, qt, s2, n);
+    hipLaunchKernelGGL(fold_batch_kernel, dim3(blocks), dim3(256), 0, s, qb, nb, qt, s2, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_dose(unsigned long long *qb, int B, long long *qt, const GeomDev &g, double mev_scale,
+                            float *dose, float *sigma, size_t n, hipStream_t s) {
+    const int blocks = (int)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
+    hipLaunchKernelGGL(fold_dose_kernel, dim3(blocks), dim3(256), 0, s, qb, B, qt, g, mev_scale, dose, sigma, n);
     return hipGetLastError();
 }
 
