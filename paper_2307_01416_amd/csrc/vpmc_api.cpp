@@ -48,120 +48,24 @@ struct FieldState {
     bool set = false;
     FieldDev dev{};
     std::vector<float2> poly;
-    DevBuf poly_buf, sdf_buf, cell_off_buf, cell_edge_buf, cell_ref_buf;
+    DevBuf poly_buf, sdf_buf, cell_buf, cell_edge_buf, cell_ref_buf;
 };
 
-// Signed distance (FP64, + inside) from the cell centres of a raster over
-// the polygon's bounding box widened by `margin` to the polygon boundary;
-// the side follows the same half-open crossing-number rule as the kernels.
-struct Raster {
-    double x0, y0, h;
-    int nx, ny;
-    std::vector<float> d;
-};
-
+// Raster of a polygon's surroundings: its bounding box widened by `margin`.
 Raster polygon_raster(const std::vector<float2> &poly, double margin) {
     double xmin = 1e300, xmax = -1e300, ymin = 1e300, ymax = -1e300;
     for (const float2 &p : poly) {
         xmin = std::min(xmin, (double)p.x); xmax = std::max(xmax, (double)p.x);
         ymin = std::min(ymin, (double)p.y); ymax = std::max(ymax, (double)p.y);
     }
-    Raster r;
+    Raster r{};
     const double ext = std::max(xmax - xmin, ymax - ymin) + 2.0 * margin;
     r.h = std::max(0.25, ext / 512.0);
     r.x0 = xmin - margin;
     r.y0 = ymin - margin;
     r.nx = (int)std::ceil((xmax - xmin + 2.0 * margin) / r.h);
     r.ny = (int)std::ceil((ymax - ymin + 2.0 * margin) / r.h);
-    r.d.resize((size_t)r.nx * r.ny);
-    const int nv = (int)poly.size();
-    for (int j = 0; j < r.ny; ++j)
-        for (int i = 0; i < r.nx; ++i) {
-            const double x = r.x0 + (i + 0.5) * r.h, y = r.y0 + (j + 0.5) * r.h;
-            bool in = false;
-            double best = 1e300;
-            for (int a = nv - 1, b = 0; b < nv; a = b++) {
-                const double ax = poly[a].x, ay = poly[a].y, bx = poly[b].x, by = poly[b].y;
-                if ((ay > y) != (by > y)) {
-                    const double xc = ax + (y - ay) * (bx - ax) / (by - ay);
-                    if (x < xc) in = !in;
-                }
-                const double ex = bx - ax, ey = by - ay, l2 = ex * ex + ey * ey;
-                double t = l2 > 0.0 ? ((x - ax) * ex + (y - ay) * ey) / l2 : 0.0;
-                t = std::min(std::max(t, 0.0), 1.0);
-                const double dx = x - ax - t * ex, dy = y - ay - t * ey;
-                best = std::min(best, dx * dx + dy * dy);
-            }
-            r.d[(size_t)j * r.nx + i] = (float)(in ? std::sqrt(best) : -std::sqrt(best));
-        }
     return r;
-}
-
-// Per raster cell near the boundary: a reference point (FP32, at least
-// 1e-4 mm from every edge, within 0.01 mm of the cell centre) with its side
-// by the crossing-number rule, and the edges (k, k+1) within kListRadius of
-// it.  A point p of the cell is on the reference point's side unless listed
-// edges cross the segment from it to p, and a ray from p meets no unlisted
-// edge within kListRadius - |p - ref|, so the kernels test a handful of edges
-// instead of every edge there.  Cells farther than kListRadius + h from the
-// boundary get no reference point (the raster's distance bound decides them).
-// off[cell]: bits 0-29 the first entry of the cell in edge[], bit 30 a
-// reference point exists, bit 31 it is inside; the next cell's bits 0-29 end
-// the list.
-struct CellLists {
-    std::vector<uint32_t> off;
-    std::vector<uint16_t> edge;
-    std::vector<float2> ref;
-};
-
-bool crossing_inside(const std::vector<float2> &poly, double x, double y) {
-    const int nv = (int)poly.size();
-    bool in = false;
-    for (int a = nv - 1, b = 0; b < nv; a = b++) {
-        const double ax = poly[a].x, ay = poly[a].y, bx = poly[b].x, by = poly[b].y;
-        if ((ay > y) != (by > y)) {
-            const double xc = ax + (y - ay) * (bx - ax) / (by - ay);
-            if (x < xc) in = !in;
-        }
-    }
-    return in;
-}
-
-double segment_distance(const float2 &a, const float2 &b, double x, double y) {
-    const double ex = (double)b.x - a.x, ey = (double)b.y - a.y, l2 = ex * ex + ey * ey;
-    double t = l2 > 0.0 ? ((x - a.x) * ex + (y - a.y) * ey) / l2 : 0.0;
-    t = std::min(std::max(t, 0.0), 1.0);
-    const double dx = x - a.x - t * ex, dy = y - a.y - t * ey;
-    return std::sqrt(dx * dx + dy * dy);
-}
-
-CellLists cell_lists(const std::vector<float2> &poly, const Raster &r, double radius) {
-    const int nv = (int)poly.size();
-    CellLists L;
-    L.off.assign((size_t)r.nx * r.ny + 1, 0u);
-    L.ref.assign((size_t)r.nx * r.ny, make_float2(0.f, 0.f));
-    for (int j = 0; j < r.ny; ++j)
-        for (int i = 0; i < r.nx; ++i) {
-            const size_t cell = (size_t)j * r.nx + i;
-            L.off[cell] = (uint32_t)L.edge.size();
-            if (std::fabs((double)r.d[cell]) > radius + r.h) continue;   // no edge within reach of the cell
-            // reference point: the cell centre in FP32, moved (by at most
-            // 0.01 mm) off any edge it lies within 1e-4 mm of
-            float2 q = make_float2((float)(r.x0 + (i + 0.5) * r.h), (float)(r.y0 + (j + 0.5) * r.h));
-            for (int tries = 0; tries < 8; ++tries) {
-                double dmin = 1e300;
-                for (int k = 0; k < nv; ++k) dmin = std::min(dmin, segment_distance(poly[k], poly[(k + 1) % nv], q.x, q.y));
-                if (dmin > 1e-4) break;
-                q = make_float2(q.x + 0.0013f, q.y + 0.0009f);
-            }
-            L.ref[cell] = q;
-            L.off[cell] |= 0x40000000u;
-            if (crossing_inside(poly, q.x, q.y)) L.off[cell] |= 0x80000000u;
-            for (int k = 0; k < nv; ++k)
-                if (segment_distance(poly[k], poly[(k + 1) % nv], q.x, q.y) <= radius) L.edge.push_back((uint16_t)k);
-        }
-    L.off[(size_t)r.nx * r.ny] = (uint32_t)L.edge.size();
-    return L;
 }
 
 }  // namespace
@@ -1214,7 +1118,7 @@ void vpmc_destroy(vpmc_ctx *c) {
         for (auto &f : c->fields) {
             release(f.poly_buf);
             release(f.sdf_buf);
-            release(f.cell_off_buf);
+            release(f.cell_buf);
             release(f.cell_edge_buf);
             release(f.cell_ref_buf);
         }
@@ -1404,10 +1308,6 @@ int vpmc_set_aperture(vpmc_ctx *c, int field_id, const vpmc_beam *beam, const fl
         d.sdf_far = (float)(kSdfMargin - 1e-3);
         d.sdf_nx = ras.nx;
         d.sdf_ny = ras.ny;
-    }
-    CellLists lists;
-    if (poly.size() >= 3) {
-        lists = cell_lists(poly, ras, kListRadius);
         // a ray from p (within h sqrt(2) of its cell's reference point) meets
         // no unlisted edge within this path length in the BEV plane
         d.list_reach = (float)(kListRadius - (0.5 * ras.h * 1.4142135623730951 + 0.011) - 1e-3);
@@ -1416,27 +1316,38 @@ int vpmc_set_aperture(vpmc_ctx *c, int field_id, const vpmc_beam *beam, const fl
         HIP_TRY(hipSetDevice(c->device));
         if ((rc = ensure(c, f.poly_buf, poly.size() * sizeof(float2), 0))) return rc;
         HIP_TRY(hipMemcpy(f.poly_buf.ptr, poly.data(), poly.size() * sizeof(float2), hipMemcpyHostToDevice));
-        if (!ras.d.empty()) {
-            if ((rc = ensure(c, f.sdf_buf, ras.d.size() * sizeof(float), 0))) return rc;
-            HIP_TRY(hipMemcpy(f.sdf_buf.ptr, ras.d.data(), ras.d.size() * sizeof(float), hipMemcpyHostToDevice));
-            if ((rc = ensure(c, f.cell_off_buf, lists.off.size() * sizeof(uint32_t), 0)) ||
-                (rc = ensure(c, f.cell_ref_buf, lists.ref.size() * sizeof(float2), 0)) ||
-                (rc = ensure(c, f.cell_edge_buf, std::max<size_t>(1, lists.edge.size()) * sizeof(uint16_t), 0)))
+        if (ras.nx > 0) {
+            const size_t cells = (size_t)ras.nx * ras.ny;
+            const size_t had = f.cell_buf.cap;   // the two counters stand behind the cells
+            if ((rc = ensure(c, f.sdf_buf, cells * sizeof(float), 0)) ||
+                (rc = ensure(c, f.cell_buf, (cells + 2) * sizeof(uint2), 0)))
                 return rc;
-            HIP_TRY(hipMemcpy(f.cell_off_buf.ptr, lists.off.data(), lists.off.size() * sizeof(uint32_t),
-                              hipMemcpyHostToDevice));
-            HIP_TRY(hipMemcpy(f.cell_ref_buf.ptr, lists.ref.data(), lists.ref.size() * sizeof(float2),
-                              hipMemcpyHostToDevice));
-            if (!lists.edge.empty())
-                HIP_TRY(hipMemcpy(f.cell_edge_buf.ptr, lists.edge.data(), lists.edge.size() * sizeof(uint16_t),
-                                  hipMemcpyHostToDevice));
+            c->bytes -= (f.cell_buf.cap - had) / 2;   // max_device_bytes counts one offset a cell
+            if ((rc = ensure(c, f.cell_ref_buf, cells * sizeof(float2), 0))) return rc;
+            ras.poly = (const float2 *)f.poly_buf.ptr;
+            ras.nv = (int)poly.size();
+            ras.radius = kListRadius;
+            ras.d = (float *)f.sdf_buf.ptr;
+            ras.cell = (uint2 *)f.cell_buf.ptr;
+            ras.ref = (float2 *)f.cell_ref_buf.ptr;
+            ras.count = (unsigned long long *)(ras.cell + cells);
+            HIP_TRY(launch_fill_u64(ras.count, 2, 0ull, nullptr));
+            HIP_TRY(launch_raster(ras, nullptr));
+            unsigned long long n_edges = 0;
+            HIP_TRY(hipMemcpy(&n_edges, ras.count, sizeof n_edges, hipMemcpyDeviceToHost));
+            if (n_edges >= (1ull << 30)) return fail(VPMC_E_OOM, "aperture edge lists of %llu entries", n_edges);
+            if ((rc = ensure(c, f.cell_edge_buf, std::max<size_t>(1, n_edges) * sizeof(uint16_t), 0))) return rc;
+            ras.edge = (uint16_t *)f.cell_edge_buf.ptr;
+            HIP_TRY(launch_raster_lists(ras, nullptr));
+            HIP_TRY(hipStreamSynchronize(nullptr));   // runs may use any stream
         }
     }
+    const bool has = ras.nx > 0;
     d.poly = (const float2 *)f.poly_buf.ptr;
-    d.sdf = ras.d.empty() ? nullptr : (const float *)f.sdf_buf.ptr;
-    d.cell_off = ras.d.empty() ? nullptr : (const uint32_t *)f.cell_off_buf.ptr;
-    d.cell_ref = ras.d.empty() ? nullptr : (const float2 *)f.cell_ref_buf.ptr;
-    d.cell_edge = ras.d.empty() ? nullptr : (const uint16_t *)f.cell_edge_buf.ptr;
+    d.sdf = has ? (const float *)f.sdf_buf.ptr : nullptr;
+    d.cell = has ? (const uint2 *)f.cell_buf.ptr : nullptr;
+    d.cell_ref = has ? (const float2 *)f.cell_ref_buf.ptr : nullptr;
+    d.cell_edge = has ? (const uint16_t *)f.cell_edge_buf.ptr : nullptr;
     f.dev = d;
     f.poly = std::move(poly);
     f.set = true;
@@ -1599,8 +1510,6 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
         dense_spot_tables(spots, n_spots, k, 1, sd, off1);
     }
     auto items_of = [&](int b) { return off[(size_t)b * (n_spots + 1) + n_spots]; };
-    unsigned long long items = 0;   // of one scenario
-    for (int b = 0; b < B; ++b) items += items_of(b);
 
     const QueueShape shape = queue_shape(c, o->physics,
                                          o->block_threads ? o->block_threads

@@ -90,9 +90,11 @@ struct FieldDev {
     float sdf_x0, sdf_y0, sdf_ih, sdf_r, sdf_far;
     int sdf_nx, sdf_ny;
     // per raster cell near the boundary: edge lists around a reference point
-    // whose side is known (bit 31 of cell_off), for exact tests on a handful
-    // of edges; valid for BEV paths up to list_reach from the point
-    const uint32_t *cell_off;
+    // whose side is known, for exact tests on a handful of edges; valid for
+    // BEV paths up to list_reach from the point.  cell: x the first entry in
+    // cell_edge (bits 0-29), bit 30 a reference point exists, bit 31 it is
+    // inside; y one past the last entry
+    const uint2 *cell;
     const uint16_t *cell_edge;
     const float2 *cell_ref;
     float list_reach;
@@ -106,6 +108,22 @@ struct FieldDev {
     int div;
     float fs, fc0;
 };
+
+// Distance raster and edge lists of an aperture polygon while they are made.
+struct Raster {
+    double x0, y0, h;
+    int nx, ny;
+    const float2 *poly;
+    int nv;
+    double radius;                // edges listed around a cell's reference point
+    float *d;                     // [nx * ny] signed distance of the cell centres
+    uint2 *cell;                  // [nx * ny]
+    float2 *ref;                  // [nx * ny]
+    uint16_t *edge;
+    unsigned long long *count;    // [0] listed edges in all, [1] those placed so far
+};
+hipError_t launch_raster(const Raster &r, hipStream_t s);         // distances, reference points, counts
+hipError_t launch_raster_lists(const Raster &r, hipStream_t s);   // the lists
 
 struct SpotDev {
     float x, y, e0, sigma, esig, emax, scale;   // scale = w/N * 2^k

@@ -620,11 +620,12 @@ __device__ __forceinline__ bool no_edge_within(float lb, float lat, float t) {
 // Each listed edge's crossing arithmetic is edge_distance's.
 __device__ __forceinline__ int listed_edges(const FieldDev &f, const float2 *poly, int nv, float x, float y,
                                             float u, float v, float lat, float t, bool &inside, float &te) {
-    if (!f.cell_off) return 0;
+    if (!f.cell) return 0;
     const float fx = (x - f.sdf_x0) * f.sdf_ih, fy = (y - f.sdf_y0) * f.sdf_ih;
     if (!(fx >= 0.0f && fy >= 0.0f && fx < (float)f.sdf_nx && fy < (float)f.sdf_ny)) return 0;
     const int cell = (int)fy * f.sdf_nx + (int)fx;
-    const uint32_t o0 = f.cell_off[cell], o1 = f.cell_off[cell + 1] & 0x3fffffffu;
+    const uint2 oc = f.cell[cell];
+    const uint32_t o0 = oc.x, o1 = oc.y;
     if (!(o0 & 0x40000000u)) return 0;
     const float2 r = f.cell_ref[cell];
     bool in = (o0 & 0x80000000u) != 0u;
@@ -2816,6 +2817,110 @@ __global__ void density_kernel(const int16_t *hu, float *rho, size_t n) {
     }
 }
 
+// ------------------------------------------------------------ aperture raster
+// One wave per raster cell, its lanes over the polygon's edges (FP64).
+// Pass 1: signed distance (+ inside, by the kernels' half-open crossing-number
+// rule) from the cell centre to the boundary; for a cell within radius + h of
+// it a reference point (FP32, the cell centre moved by at most 0.01 mm off any
+// edge closer than 1e-4 mm) with its side, and the number of edges within
+// `radius` of it.  A point p of the cell is on the reference point's side unless
+// listed edges cross the segment from it to p, and a ray from p meets no
+// unlisted edge within radius - |p - ref|, so the kernels test a handful of
+// edges instead of every edge there.  Cells farther from the boundary get no
+// reference point (the distance bound decides them).  Pass 2: the lists, edges
+// in ascending order, each cell's wherever the counter put it.  On the host
+// these took 50 ms for a 128-gon of 35 mm (61 ms with its checks) and as much
+// for every call that sets a field again; 41 000 cells are 0.1 ms here.
+struct EdgeScan {
+    double best;   // smallest squared distance
+    bool in;
+};
+
+__device__ __forceinline__ double edge_dist2(const float2 a, const float2 b, double x, double y) {
+    const double ex = (double)b.x - a.x, ey = (double)b.y - a.y, l2 = ex * ex + ey * ey;
+    double t = l2 > 0.0 ? ((x - a.x) * ex + (y - a.y) * ey) / l2 : 0.0;
+    t = fmin(fmax(t, 0.0), 1.0);
+    const double dx = x - a.x - t * ex, dy = y - a.y - t * ey;
+    return dx * dx + dy * dy;
+}
+
+__device__ EdgeScan scan_edges(const Raster &r, double x, double y, int lane) {
+    double best = 1e300;
+    unsigned long long flips = 0;
+    for (int k0 = 0; k0 < r.nv; k0 += 64) {
+        const int k = k0 + lane;
+        bool flip = false;
+        if (k < r.nv) {
+            const float2 b = r.poly[k], a = r.poly[k ? k - 1 : r.nv - 1];
+            if (((double)a.y > y) != ((double)b.y > y)) {
+                const double xc = a.x + (y - a.y) * ((double)b.x - a.x) / ((double)b.y - a.y);
+                flip = x < xc;
+            }
+            best = fmin(best, edge_dist2(a, b, x, y));
+        }
+        flips += __popcll(__ballot(flip));
+    }
+    for (int o = 32; o > 0; o >>= 1) best = fmin(best, __shfl_xor(best, o, 64));
+    return {best, (flips & 1ull) != 0};
+}
+
+__global__ __launch_bounds__(256) void raster_kernel(Raster r) {
+    const int lane = threadIdx.x & 63;
+    const int c = (int)(blockIdx.x * (blockDim.x >> 6)) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (c >= r.nx * r.ny) return;
+    const int j = c / r.nx, i = c - j * r.nx;
+    const double x = r.x0 + (i + 0.5) * r.h, y = r.y0 + (j + 0.5) * r.h;
+    const EdgeScan s = scan_edges(r, x, y, lane);
+    const float d = (float)(s.in ? sqrt(s.best) : -sqrt(s.best));
+    uint2 cell = make_uint2(0u, 0u);
+    float2 q = make_float2(0.0f, 0.0f);
+    if (fabs((double)d) <= r.radius + r.h) {
+        q = make_float2((float)x, (float)y);
+        EdgeScan e{0.0, false};
+        for (int tries = 0; tries < 8; ++tries) {
+            e = scan_edges(r, q.x, q.y, lane);
+            if (sqrt(e.best) > 1e-4) break;
+            q = make_float2(q.x + 0.0013f, q.y + 0.0009f);
+        }
+        e = scan_edges(r, q.x, q.y, lane);
+        unsigned n = 0;
+        for (int k0 = 0; k0 < r.nv; k0 += 64) {
+            const int k = k0 + lane;
+            n += (unsigned)__popcll(__ballot(k < r.nv && sqrt(edge_dist2(r.poly[min(k, r.nv - 1)], r.poly[k + 1 < r.nv ? k + 1 : 0],
+                                                                         q.x, q.y)) <= r.radius));
+        }
+        cell = make_uint2(0x40000000u | (e.in ? 0x80000000u : 0u), n);
+        if (lane == 0 && n) atomicAdd(r.count, (unsigned long long)n);
+    }
+    if (lane == 0) {
+        r.d[c] = d;
+        r.cell[c] = cell;
+        r.ref[c] = q;
+    }
+}
+
+__global__ __launch_bounds__(256) void raster_lists_kernel(Raster r) {
+    const int lane = threadIdx.x & 63;
+    const int c = (int)(blockIdx.x * (blockDim.x >> 6)) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (c >= r.nx * r.ny) return;
+    const uint2 cell = r.cell[c];
+    if (!(cell.x & 0x40000000u)) return;
+    const float2 q = r.ref[c];
+    unsigned long long at = 0;
+    if (lane == 0) at = atomicAdd(r.count + 1, (unsigned long long)cell.y);
+    uint32_t o = __builtin_amdgcn_readfirstlane((uint32_t)at);
+    const uint32_t first = o;
+    for (int k0 = 0; k0 < r.nv; k0 += 64) {
+        const int k = k0 + lane;
+        const bool near = k < r.nv && sqrt(edge_dist2(r.poly[min(k, r.nv - 1)], r.poly[k + 1 < r.nv ? k + 1 : 0], q.x,
+                                                      q.y)) <= r.radius;
+        const unsigned long long m = __ballot(near);
+        if (near) r.edge[o + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)k;
+        o += (uint32_t)__popcll(m);
+    }
+    if (lane == 0) r.cell[c] = make_uint2(cell.x | first, o);
+}
+
 // ------------------------------------------------------------ batches, dose
 // fold nb batches, in order: total += q_b, sum of squares += q_b^2 (FP64), clear q_b
 __global__ void fold_batch_kernel(unsigned long long *qb, int nb, long long *qt, double *s2, size_t n) {
@@ -2926,6 +3031,16 @@ int queue_tile_cap(unsigned physics, int threads) {
 }
 
 size_t queue_static_lds(unsigned physics) { return (tab_hi_floats(3) + (physics == 0 ? tab_lo_floats(3) : 4)) * 4 + 256; }
+
+hipError_t launch_raster(const Raster &r, hipStream_t s) {
+    hipLaunchKernelGGL(raster_kernel, dim3((unsigned)((r.nx * r.ny + 3) / 4)), dim3(256), 0, s, r);
+    return hipGetLastError();
+}
+
+hipError_t launch_raster_lists(const Raster &r, hipStream_t s) {
+    hipLaunchKernelGGL(raster_lists_kernel, dim3((unsigned)((r.nx * r.ny + 3) / 4)), dim3(256), 0, s, r);
+    return hipGetLastError();
+}
 
 hipError_t launch_derive_tables(float *blob, hipStream_t s) {
     hipLaunchKernelGGL(derive_tables_kernel, dim3(NMAT), dim3(NE), 0, s, blob);
