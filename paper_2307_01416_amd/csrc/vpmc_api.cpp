@@ -2509,30 +2509,48 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
     const bool dev = (flags & VPMC_DEVICE_PTRS) != 0;
     const int nvox = (int)c->nvox;
     std::vector<int64_t> rp((size_t)n_rows + 1);
-    std::vector<int32_t> cmap((size_t)nvox);
+    std::vector<int32_t> cstart;
+    int ends[2] = {0, 0};   // the map's first and last cell
+    unsigned bad = ~0u;     // first voxel at which it does not grow by 0 or 1
+    int rc;
     if (dev) {
+        // the map stays where it is: one pass over it on the device checks it
+        // and finds each cell's first voxel (42 MB of map both ways over the
+        // link and two host loops over 10.5 M voxels were 15 ms a call)
         if (c->device < 0) return fail(VPMC_E_STATE, "validation-only context has no device");
         HIP_TRY(hipSetDevice(c->device));
+        if (n_cells > nvox) return fail(VPMC_E_ARG, "cell map must start at 0 and end at n_cells - 1");
+        if ((rc = ensure(c, c->cl_start, ((size_t)n_cells + 1) * 4, 0))) return rc;
+        if ((rc = ensure(c, c->flags, 4 * sizeof(unsigned), 0))) return rc;
+        HIP_TRY(launch_cell_map(cell_of_voxel, nvox, n_cells, (int32_t *)c->cl_start.ptr, (unsigned *)c->flags.ptr,
+                                nullptr));
+        unsigned got[4];
+        HIP_TRY(hipMemcpy(got, c->flags.ptr, sizeof got, hipMemcpyDeviceToHost));
         HIP_TRY(hipMemcpy(rp.data(), row_ptr, rp.size() * 8, hipMemcpyDeviceToHost));
-        HIP_TRY(hipMemcpy(cmap.data(), cell_of_voxel, cmap.size() * 4, hipMemcpyDeviceToHost));
+        ends[0] = (int)got[1];
+        ends[1] = (int)got[2];
+        bad = got[3];
     } else {
         memcpy(rp.data(), row_ptr, rp.size() * 8);
-        memcpy(cmap.data(), cell_of_voxel, cmap.size() * 4);
+        const int32_t *m = cell_of_voxel;
+        ends[0] = m[0];
+        ends[1] = m[nvox - 1];
+        if (n_cells > nvox) return fail(VPMC_E_ARG, "cell map must start at 0 and end at n_cells - 1");
+        cstart.assign((size_t)n_cells + 1, nvox);
+        cstart[0] = 0;
+        for (int v = 1; v < nvox && bad == ~0u && ends[0] == 0; ++v) {
+            const long long d = (long long)m[v] - m[v - 1];
+            if (d != 0 && d != 1) bad = (unsigned)v;
+            else if (d == 1 && m[v] < n_cells) cstart[(size_t)m[v]] = v;
+        }
     }
     if (rp[0] < 0) return fail(VPMC_E_ARG, "row_ptr[0] < 0");
     for (size_t r = 0; r + 1 < rp.size(); ++r)
         if (rp[r + 1] < rp[r]) return fail(VPMC_E_ARG, "row_ptr decreases at row %zu", r);
     // cells: runs of consecutive voxels, numbered 0 .. n_cells-1 in order
-    if (cmap[0] != 0 || cmap[(size_t)nvox - 1] != n_cells - 1)
+    if (ends[0] != 0 || ends[1] != n_cells - 1)
         return fail(VPMC_E_ARG, "cell map must start at 0 and end at n_cells - 1");
-    std::vector<int32_t> cstart((size_t)n_cells + 1);
-    cstart[0] = 0;
-    for (int v = 1; v < nvox; ++v) {
-        const int d = cmap[(size_t)v] - cmap[(size_t)v - 1];
-        if (d != 0 && d != 1) return fail(VPMC_E_ARG, "cell map must grow by 0 or 1 from voxel to voxel (voxel %d)", v);
-        if (d == 1) cstart[(size_t)cmap[(size_t)v]] = v;
-    }
-    cstart[(size_t)n_cells] = nvox;
+    if (bad != ~0u) return fail(VPMC_E_ARG, "cell map must grow by 0 or 1 from voxel to voxel (voxel %u)", bad);
     const long long nnz = rp[(size_t)n_rows] - rp[0];
     if (nnz > 0 && (!col || !q)) return fail(VPMC_E_ARG, "col and q are required");
     if (!dev && nnz > 0) {
@@ -2541,10 +2559,9 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
     }
     if (c->device < 0) return fail(VPMC_E_STATE, "validation-only context has no device");
     HIP_TRY(hipSetDevice(c->device));
-    int rc;
     const size_t R = (size_t)n_rows;
     if ((rc = ensure(c, c->cl_rp, (R + 1) * 8, 0))) return rc;
-    if ((rc = ensure(c, c->cl_map, (size_t)nvox * 4, 0))) return rc;
+    if (!dev && (rc = ensure(c, c->cl_map, (size_t)nvox * 4, 0))) return rc;
     if ((rc = ensure(c, c->cl_start, ((size_t)n_cells + 1) * 4, 0))) return rc;
     if ((rc = ensure(c, c->cl_mass, (size_t)n_cells * 8, 0))) return rc;
     // pieces of at most kCellPiece entries, row by row
@@ -2562,8 +2579,12 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
     if ((rc = ensure(c, c->cl_out, (NP + 1) * 8, 0))) return rc;
     if ((rc = ensure(c, c->flags, 4, 0))) return rc;
     HIP_TRY(hipMemcpy(c->cl_rp.ptr, rp.data(), rp.size() * 8, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->cl_map.ptr, cmap.data(), cmap.size() * 4, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(c->cl_start.ptr, cstart.data(), cstart.size() * 4, hipMemcpyHostToDevice));
+    const int32_t *d_map = cell_of_voxel;
+    if (!dev) {
+        HIP_TRY(hipMemcpy(c->cl_map.ptr, cell_of_voxel, (size_t)nvox * 4, hipMemcpyHostToDevice));
+        HIP_TRY(hipMemcpy(c->cl_start.ptr, cstart.data(), cstart.size() * 4, hipMemcpyHostToDevice));
+        d_map = (const int32_t *)c->cl_map.ptr;
+    }
     if (NP) HIP_TRY(hipMemcpy(c->cl_piece.ptr, pcs.data(), NP * sizeof(CellPiece), hipMemcpyHostToDevice));
     const int32_t *d_col = col;
     const long long *d_q = (const long long *)q;
@@ -2578,7 +2599,7 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
     }
     HIP_TRY(hipMemset(c->flags.ptr, 0, 4));
     HIP_TRY(launch_cell_count((const long long *)c->cl_rp.ptr, (const CellPiece *)c->cl_piece.ptr, (long long)NP,
-                              d_col, (const int32_t *)c->cl_map.ptr, nvox, (unsigned long long *)c->cl_cnt.ptr,
+                              d_col, d_map, nvox, (unsigned long long *)c->cl_cnt.ptr,
                               (unsigned *)c->flags.ptr, nullptr));
     std::vector<unsigned long long> cnt(std::max<size_t>(NP, 1));
     unsigned err = 0;
@@ -2609,7 +2630,7 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
         oval = val_out ? (float *)c->cl_oval.ptr : nullptr;
     }
     HIP_TRY(launch_cell_emit((const long long *)c->cl_rp.ptr, (const CellPiece *)c->cl_piece.ptr, (long long)NP, d_col,
-                             d_q, (const int32_t *)c->cl_map.ptr, (const long long *)c->cl_out.ptr,
+                             d_q, d_map, (const long long *)c->cl_out.ptr,
                              (const double *)c->cl_mass.ptr, ldexp(MEV_TO_J, -k),
                              ocell, oq, oval, nullptr));
     HIP_TRY(hipDeviceSynchronize());

@@ -341,6 +341,7 @@ struct CellPiece {
     int len;
     int row;
 };
+hipError_t launch_cell_map(const int32_t *cmap, int nvox, int n_cells, int32_t *cstart, unsigned *st, hipStream_t s);
 hipError_t launch_cell_mass(const GeomDev &g, const int32_t *cstart, int n_cells, double *mass, hipStream_t s);
 hipError_t launch_cell_count(const long long *rp, const CellPiece *pcs, long long n_pieces, const int32_t *col,
                              const int32_t *cmap, int nvox, unsigned long long *cnt, unsigned *err, hipStream_t s);

@@ -2410,6 +2410,29 @@ __global__ void csr_values_kernel(const int32_t *col, const long long *qv, size_
 // voxels for organs at risk, Methods C): a cell is a run of consecutive
 // voxels given by a non-decreasing voxel -> cell map, cstart[c] its first
 // voxel.  Cell mass (kg) = the sum of its voxels' masses, in voxel order.
+//
+// The map's check and the cells' first voxels in one pass over it.  st[1],
+// st[2]: its first and last cell; st[3] (preset to ~0): the first voxel at
+// which it does not grow by 0 or 1.  cstart is whole only if the check passes.
+__global__ __launch_bounds__(256) void cell_map_kernel(const int32_t *cmap, int nvox, int n_cells, int32_t *cstart,
+                                                       unsigned *st) {
+    unsigned bad = ~0u;
+    for (size_t v = blockIdx.x * (size_t)blockDim.x + threadIdx.x; v < (size_t)nvox; v += (size_t)gridDim.x * blockDim.x) {
+        const int c = cmap[v];
+        if (v == 0) {
+            st[1] = (unsigned)c;
+            cstart[0] = 0;
+            cstart[n_cells] = nvox;
+        } else {
+            const long long d = (long long)c - cmap[v - 1];
+            if (d != 0 && d != 1) bad = min(bad, (unsigned)v);
+            if (d == 1 && c >= 0 && c < n_cells) cstart[c] = (int32_t)v;
+        }
+        if (v + 1 == (size_t)nvox) st[2] = (unsigned)c;
+    }
+    if (bad != ~0u) atomicMin(st + 3, bad);
+}
+
 __global__ void cell_mass_kernel(GeomDev g, const int32_t *cstart, int n_cells, double *mass) {
     const double vol_kg = (double)g.sp[0] * (double)g.sp[1] * (double)g.sp[2] * 1e-6;
     for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n_cells; c += gridDim.x * blockDim.x) {
@@ -3166,6 +3189,14 @@ hipError_t launch_csr_values(const int32_t *col, const long long *qv, size_t n, 
     return hipGetLastError();
 }
 
+
+hipError_t launch_cell_map(const int32_t *cmap, int nvox, int n_cells, int32_t *cstart, unsigned *st, hipStream_t s) {
+    const hipError_t e = launch_fill_u64((unsigned long long *)st, 2, ~0ull, s);
+    if (e != hipSuccess) return e;
+    const int blocks = std::max(1, std::min((nvox + 255) / 256, 8192));
+    hipLaunchKernelGGL(cell_map_kernel, dim3(blocks), dim3(256), 0, s, cmap, nvox, n_cells, cstart, st);
+    return hipGetLastError();
+}
 
 hipError_t launch_cell_mass(const GeomDev &g, const int32_t *cstart, int n_cells, double *mass, hipStream_t s) {
     const int blocks = std::max(1, std::min((n_cells + 255) / 256, 8192));
