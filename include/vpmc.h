@@ -419,7 +419,8 @@ typedef struct {
  * the final x.  Pointer kind of every array per p->flags.  n_spots <= 2^20.
  * Scratch, kept for VPMC_OPT_REUSE: 16 B per entry in a structure voxel,
  * with dose_gy also 8 B per entry of the used rows (a bucketed copy of the
- * whole rows), plus about 4 B x n_scen x nvox and 32 B per spot and scenario.
+ * whole rows), plus about 2.3 B per voxel, 4 B x n_scen per structure voxel and
+ * 60 B per spot and scenario.
  * VPMC_OPT_REUSE also requires identical structure masks (checked).  Errors:
  * VPMC_E_ARG (dims, parameters, flags, row_ptr decreasing, a column out of
  * range or a value not finite), VPMC_E_STATE (validation-only context;

@@ -120,16 +120,16 @@ struct vpmc_ctx {
         bool valid = false;
     } opt_broi, opt_bfull;
     DevBuf opt_rp, opt_col, opt_val, opt_roi, opt_amax, opt_cnt, opt_rcnt, opt_crp, opt_ccol, opt_cval, opt_piece,
-        opt_poff, opt_resid, opt_fpart, opt_gpart, opt_vec, opt_scal, opt_err, opt_hist, opt_dose, opt_sidx,
+        opt_poff, opt_fpart, opt_gpart, opt_vec, opt_scal, opt_err, opt_hist, opt_dose, opt_mask, opt_sroi,
         opt_rstruct;
+    DevBuf opt_keep;   // the index's structure masks (not counted against max_device_bytes)
     long long opt_npieces = 0;
-    int opt_nstruct = 0;
+    int opt_nstruct = 0, opt_bits = 0;
     // dynamic voxel spacing (vpmc_csr_cells)
     DevBuf cl_rp, cl_map, cl_start, cl_mass, cl_cnt, cl_out, cl_col, cl_q, cl_ocell, cl_oq, cl_oval, cl_piece;
     bool opt_valid = false;
     int opt_dims[5] = {0, 0, 0, 0, 0};   // n_scen, n_spots, row_stride, row_offset, nvox
     std::vector<int64_t> opt_rp_host;
-    std::vector<uint8_t> opt_roi_host;
     const void *opt_col_src = nullptr, *opt_val_src = nullptr;
     float sur_dfb = 3.0f, sur_plo = 0.02f, sur_phi = 0.98f;
 };
@@ -1130,8 +1130,8 @@ void vpmc_destroy(vpmc_ctx *c) {
                           &c->mlp_io, &c->mlp_dx, &c->mlp_dy, &c->mlp_dt, &c->mlp_idx, &c->sur_rec,
                           &c->sur_cnt, &c->sur_out, &c->opt_rp, &c->opt_col, &c->opt_val, &c->opt_roi, &c->opt_amax,
                           &c->opt_cnt, &c->opt_rcnt, &c->opt_crp, &c->opt_ccol, &c->opt_cval, &c->opt_piece,
-                          &c->opt_poff, &c->opt_resid, &c->opt_fpart, &c->opt_gpart, &c->opt_vec, &c->opt_scal,
-                          &c->opt_err, &c->opt_hist, &c->opt_dose, &c->opt_sidx, &c->opt_rstruct,
+                          &c->opt_poff, &c->opt_fpart, &c->opt_gpart, &c->opt_vec, &c->opt_scal,
+                          &c->opt_err, &c->opt_hist, &c->opt_dose, &c->opt_mask, &c->opt_sroi, &c->opt_keep, &c->opt_rstruct,
                           &c->opt_broi.off, &c->opt_broi.key,
                           &c->opt_broi.val, &c->opt_broi.work, &c->opt_bfull.off, &c->opt_bfull.key,
                           &c->opt_bfull.val, &c->opt_bfull.work, &c->cl_rp, &c->cl_map, &c->cl_start,
@@ -2252,16 +2252,10 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
     if (c->device < 0) return fail(VPMC_E_STATE, "validation-only context has no device");
     HIP_TRY(hipSetDevice(c->device));
     hipStream_t st = (hipStream_t)p->hip_stream;
-    const int nchunks = (int)((nvox + (long long)kOptChunk - 1) / kOptChunk);
-    const size_t nlist = (size_t)n_scen * nchunks;
     const int dims[5] = {n_scen, n_spots, stride, p->row_offset, nvox};
     const bool same = c->opt_valid && memcmp(dims, c->opt_dims, sizeof dims) == 0 && c->opt_rp_host == rp &&
                       (!dev || (c->opt_col_src == col && c->opt_val_src == val));
-    // structure masks on the host (chunks that hold structure voxels; reuse check)
-    std::vector<uint8_t> roi_h((size_t)nvox);
-    HIP_TRY(hipMemcpy(roi_h.data(), roi, (size_t)nvox, dev ? hipMemcpyDeviceToHost : hipMemcpyHostToHost));
-    if (reuse && (!same || roi_h != c->opt_roi_host))
-        return fail(VPMC_E_STATE, "VPMC_OPT_REUSE without a matching index (rows, columns or structures changed)");
+    if (reuse && !same) return fail(VPMC_E_STATE, "VPMC_OPT_REUSE without a matching index (rows or columns changed)");
     int rc;
     // CSR on the device: the library's own row pointer (validated), caller's or copied arrays
     if ((rc = ensure(c, c->opt_rp, rp.size() * 8, 0))) return rc;
@@ -2281,17 +2275,34 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
         d_val = (const float *)c->opt_val.ptr;
         d_roi = (const uint8_t *)c->opt_roi.ptr;
     }
+    if ((rc = ensure(c, c->opt_err, 4, 0))) return rc;
+    if (reuse) {
+        HIP_TRY(hipMemsetAsync(c->opt_err.ptr, 0, 4, st));
+        HIP_TRY(opt_roi_same(d_roi, (const uint8_t *)c->opt_keep.ptr, nvox, (unsigned *)c->opt_err.ptr, st));
+        unsigned differ = 0;
+        HIP_TRY(hipMemcpyAsync(&differ, c->opt_err.ptr, 4, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        if (differ) return fail(VPMC_E_STATE, "VPMC_OPT_REUSE without a matching index (structures changed)");
+    }
+    const size_t n_words = ((size_t)nvox + 63) / 64, n_vblk = ((size_t)nvox + 4095) / 4096;
+    const int n_part = (int)std::min<long long>(kOptParts, (n_spots + 3ll) / 4);
     if ((rc = ensure(c, c->opt_amax, (size_t)n_rows * 4, 0))) return rc;
-    if ((rc = ensure(c, c->opt_cnt, nlist * 8, 0))) return rc;
-    if ((rc = ensure(c, c->opt_rcnt, (size_t)n_rows * 8, 0))) return rc;
+    if ((rc = ensure(c, c->opt_rcnt, (size_t)n_rows * kRoiParts * 4, 0))) return rc;
     if ((rc = ensure(c, c->opt_crp, ((size_t)n_rows + 1) * 8, 0))) return rc;
     if ((rc = ensure(c, c->opt_poff, ((size_t)n_rows + 1) * 8, 0))) return rc;
-    if ((rc = ensure(c, c->opt_resid, (size_t)n_scen * nvox * 4, 0))) return rc;
-    if ((rc = ensure(c, c->opt_fpart, nlist * 8, 0))) return rc;
+    if ((rc = ensure(c, c->opt_mask, n_words * sizeof(OptMask) + (2 * n_vblk + 1) * 8, 0))) return rc;
+    if ((rc = ensure(c, c->opt_sroi, (size_t)nvox, 0))) return rc;
     if ((rc = ensure(c, c->opt_vec, (size_t)n_spots * 4 * 8, 0))) return rc;
-    if ((rc = ensure(c, c->opt_scal, ((size_t)2 * n_scen + 2) * 8, 0))) return rc;
-    if ((rc = ensure(c, c->opt_err, 4, 0))) return rc;
+    if ((rc = ensure(c, c->opt_scal, (2 + (size_t)(n_scen + 2) * n_part) * 8, 0))) return rc;
     if ((rc = ensure(c, c->opt_hist, ((size_t)p->iters + 1) * 8, 0))) return rc;
+    if (c->opt_keep.cap < (size_t)nvox) {
+        c->opt_valid = false;
+        release(c->opt_keep);
+        HIP_TRY(hipMalloc(&c->opt_keep.ptr, (size_t)nvox));
+        c->opt_keep.cap = (size_t)nvox;
+    }
+    OptMask *mask = (OptMask *)c->opt_mask.ptr;
+    unsigned long long *vcnt = (unsigned long long *)(mask + n_words), *voff = vcnt + n_vblk;
     // the whole layout (validation, bound of every row, dose output) ...
     OptDev F{};
     F.row_ptr = (const long long *)c->opt_rp.ptr;
@@ -2303,24 +2314,26 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
     F.row_stride = stride;
     F.row_offset = p->row_offset;
     F.nvox = nvox;
-    F.nchunks = nchunks;
+    F.bits = kOptChunkBits;
+    F.nchunks = (int)(((long long)nvox + (1 << F.bits) - 1) >> F.bits);
     F.d_presc = p->d_presc;
     F.w_target = p->w_target;
     F.d_max = p->d_max;
     F.w_oar = p->w_oar;
     F.amax = (float *)c->opt_amax.ptr;
-    F.resid = (float *)c->opt_resid.ptr;
-    F.fpart = (double *)c->opt_fpart.ptr;
     double *vec = (double *)c->opt_vec.ptr;
     F.x = vec;
     F.y = vec + n_spots;
     F.z = vec + 2 * (size_t)n_spots;
     F.gvec = vec + 3 * (size_t)n_spots;
-    F.scale = (double *)c->opt_scal.ptr;
-    F.scal = F.scale + 2 * (size_t)n_scen;
+    F.scal = (double *)c->opt_scal.ptr;
+    F.sq = F.scal + 2;
+    F.bpart = F.sq + 2 * (size_t)n_part;
+    F.n_part = n_part;
     F.piece_off = (const long long *)c->opt_poff.ptr;
     // ... and its rows restricted to the structure voxels (the iterations)
     OptDev O = F;
+    O.roi = (const uint8_t *)c->opt_sroi.ptr;
     O.row_ptr = (const long long *)c->opt_crp.ptr;
     O.row_stride = n_spots;
     O.row_offset = 0;
@@ -2331,99 +2344,109 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
         D.work = (const uint32_t *)B.work.ptr;
         D.n_work = B.n_work;
     };
-    // bucketed copy of the rows of D: lists (scenario, chunk) over the chunks
-    // with keep[chunk] (all when keep is empty), heaviest first in the work list
-    auto build_buckets = [&](OptDev &D, vpmc_ctx::OptBuckets &B, const std::vector<char> &keep,
-                             long long expect) -> int {
+    // bucketed copy of the rows of D: lists (scenario, chunk), heaviest first
+    // in the work list
+    std::vector<unsigned long long> boff;
+    std::vector<uint32_t> work;
+    auto build_buckets = [&](OptDev &D, vpmc_ctx::OptBuckets &B, long long expect) -> int {
         B.valid = false;
         int rc2;
+        const size_t nlist = (size_t)n_scen * D.nchunks;
+        if ((rc2 = ensure(c, c->opt_cnt, std::max<size_t>(nlist, 1) * 8, 0))) return rc2;
+        if ((rc2 = ensure(c, c->opt_fpart, std::max<size_t>(nlist, 1) * 8, 0))) return rc2;
         if ((rc2 = ensure(c, B.off, (nlist + 1) * 8, 0))) return rc2;
         if ((rc2 = ensure(c, B.work, std::max<size_t>(nlist, 1) * 4, 0))) return rc2;
+        if ((rc2 = ensure(c, B.key, (size_t)std::max(expect, 1ll) * 4, 0))) return rc2;
+        if ((rc2 = ensure(c, B.val, (size_t)std::max(expect, 1ll) * 4, 0))) return rc2;
         HIP_TRY(hipMemsetAsync(c->opt_cnt.ptr, 0, nlist * 8, st));
         HIP_TRY(hipMemsetAsync(c->opt_err.ptr, 0, 4, st));
         HIP_TRY(opt_build_count(D, (unsigned long long *)c->opt_cnt.ptr, (unsigned *)c->opt_err.ptr, st));
         HIP_TRY(opt_build_scan((unsigned long long *)c->opt_cnt.ptr, (unsigned long long *)B.off.ptr, nlist, st));
-        std::vector<unsigned long long> boff(nlist + 1);
+        HIP_TRY(opt_build_emit(D, (const unsigned long long *)B.off.ptr, (unsigned long long *)c->opt_cnt.ptr,
+                               (uint32_t *)B.key.ptr, (float *)B.val.ptr, st));
+        boff.resize(nlist + 1);
         HIP_TRY(hipMemcpyAsync(boff.data(), B.off.ptr, (nlist + 1) * 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         if ((long long)boff[nlist] != expect)
             return fail(VPMC_E_DEVICE, "entry count %llu of the chunk lists differs from the rows' %lld", boff[nlist],
                         expect);
-        std::vector<uint32_t> work;
-        for (size_t k = 0; k < nlist; ++k)
-            if (keep.empty() || keep[k % (size_t)nchunks]) work.push_back((uint32_t)k);
+        work.resize(nlist);
+        for (size_t k = 0; k < nlist; ++k) work[k] = (uint32_t)k;
         std::stable_sort(work.begin(), work.end(), [&](uint32_t a, uint32_t b) {
             return boff[a + 1] - boff[a] > boff[b + 1] - boff[b];
         });
-        if (!work.empty())
-            HIP_TRY(hipMemcpyAsync(B.work.ptr, work.data(), work.size() * 4, hipMemcpyHostToDevice, st));
-        if ((rc2 = ensure(c, B.key, (size_t)std::max(expect, 1ll) * 4, 0))) return rc2;
-        if ((rc2 = ensure(c, B.val, (size_t)std::max(expect, 1ll) * 4, 0))) return rc2;
-        HIP_TRY(opt_build_emit(D, (const unsigned long long *)B.off.ptr, (unsigned long long *)c->opt_cnt.ptr,
-                               (uint32_t *)B.key.ptr, (float *)B.val.ptr, st));
-        HIP_TRY(hipStreamSynchronize(st));   // the host vectors outlive the copies
-        B.n_work = (long long)work.size();
+        if (nlist) HIP_TRY(hipMemcpyAsync(B.work.ptr, work.data(), nlist * 4, hipMemcpyHostToDevice, st));
+        B.n_work = (long long)nlist;
         B.valid = true;
         return VPMC_OK;
     };
+    auto set_space = [&](OptDev &D, int ns, int bits) {   // the iterations' voxels
+        D.nvox = ns;
+        D.bits = bits;
+        D.nchunks = (int)(((long long)ns + (1 << bits) - 1) >> bits);
+    };
+    std::vector<long long> crp, poff;
+    std::vector<OptPiece> pieces;
+    struct Drain {
+        hipStream_t st;
+        ~Drain() { (void)hipStreamSynchronize(st); }
+    } drain{st};   // also where the call ends early, the copies before the vectors
     if (!reuse) {
         c->opt_valid = false;
         c->opt_bfull.valid = false;
         HIP_TRY(hipMemcpyAsync(c->opt_rp.ptr, rp.data(), rp.size() * 8, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemsetAsync(c->opt_err.ptr, 0, 4, st));
-        HIP_TRY(opt_roi_count(F, (unsigned long long *)c->opt_rcnt.ptr, (unsigned *)c->opt_err.ptr, st));
-        std::vector<unsigned long long> rcnt((size_t)n_rows);
+        HIP_TRY(opt_structures(d_roi, nvox, mask, vcnt, voff, (uint8_t *)c->opt_keep.ptr,
+                               (uint8_t *)c->opt_sroi.ptr, st));
+        HIP_TRY(opt_roi_count(F, mask, (unsigned *)c->opt_rcnt.ptr, (unsigned *)c->opt_err.ptr, st));
+        std::vector<unsigned> rcnt((size_t)n_rows * kRoiParts);
         unsigned err = 0;
-        HIP_TRY(hipMemcpyAsync(rcnt.data(), c->opt_rcnt.ptr, (size_t)n_rows * 8, hipMemcpyDeviceToHost, st));
+        unsigned long long ns = 0;
+        HIP_TRY(hipMemcpyAsync(rcnt.data(), c->opt_rcnt.ptr, rcnt.size() * 4, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipMemcpyAsync(&err, c->opt_err.ptr, 4, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(&ns, voff + n_vblk, 8, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         if (err & 1u) return fail(VPMC_E_ARG, "a column index is outside [0, nvox)");
         if (err & 2u) return fail(VPMC_E_ARG, "a value is not finite");
-        // structure-restricted CSR and its gradient pieces of at most kOptPiece entries
-        std::vector<long long> crp((size_t)n_rows + 1), poff((size_t)n_rows + 1);
-        std::vector<OptPiece> pieces;
+        // structure-restricted CSR and its pieces of at most kOptPiece entries
+        crp.resize((size_t)n_rows + 1);
+        poff.resize((size_t)n_rows + 1);
         crp[0] = 0;
-        for (long long r = 0; r < n_rows; ++r) {
-            crp[(size_t)r + 1] = crp[(size_t)r] + (long long)rcnt[(size_t)r];
-            poff[(size_t)r] = (long long)pieces.size();
-            for (long long q = crp[(size_t)r]; q < crp[(size_t)r + 1]; q += kOptPiece)
-                pieces.push_back(OptPiece{q, (int)std::min<long long>(kOptPiece, crp[(size_t)r + 1] - q), (int)r});
+        for (size_t r = 0; r < (size_t)n_rows; ++r) {
+            long long n = 0;
+            for (int w = 0; w < kRoiParts; ++w) n += rcnt[r * kRoiParts + w];
+            crp[r + 1] = crp[r] + n;
+            poff[r] = (long long)pieces.size();
+            for (long long q = crp[r]; q < crp[r + 1]; q += kOptPiece)
+                pieces.push_back(OptPiece{q, (int)std::min<long long>(kOptPiece, crp[r + 1] - q), (int)r});
         }
         poff[(size_t)n_rows] = (long long)pieces.size();
         const long long kept = crp[(size_t)n_rows];
+        int bits = kOptMaxBits;
+        while (bits > kOptMinBits && (long long)n_scen * (((long long)ns + (1 << bits) - 1) >> bits) < kOptLists) --bits;
         if ((rc = ensure(c, c->opt_ccol, (size_t)std::max(kept, 1ll) * 4, 0))) return rc;
         if ((rc = ensure(c, c->opt_cval, (size_t)std::max(kept, 1ll) * 4, 0))) return rc;
         if ((rc = ensure(c, c->opt_piece, std::max<size_t>(pieces.size(), 1) * sizeof(OptPiece), 0))) return rc;
         if ((rc = ensure(c, c->opt_gpart, std::max<size_t>(pieces.size(), 1) * 8, 0))) return rc;
+        if ((rc = ensure(c, c->opt_rstruct, (size_t)n_scen * std::max<size_t>(ns, 1) * 4, 0))) return rc;
         HIP_TRY(hipMemcpyAsync(c->opt_crp.ptr, crp.data(), crp.size() * 8, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(c->opt_poff.ptr, poff.data(), poff.size() * 8, hipMemcpyHostToDevice, st));
         if (!pieces.empty())
             HIP_TRY(hipMemcpyAsync(c->opt_piece.ptr, pieces.data(), pieces.size() * sizeof(OptPiece),
                                    hipMemcpyHostToDevice, st));
-        HIP_TRY(opt_roi_copy(F, (const long long *)c->opt_crp.ptr, (int32_t *)c->opt_ccol.ptr,
-                             (float *)c->opt_cval.ptr, st));
+        HIP_TRY(opt_roi_copy(F, mask, (const unsigned *)c->opt_rcnt.ptr, (const long long *)c->opt_crp.ptr,
+                             (int32_t *)c->opt_ccol.ptr, (float *)c->opt_cval.ptr, st));
         c->opt_npieces = (long long)pieces.size();
+        c->opt_nstruct = (int)ns;
+        c->opt_bits = bits;
         O.col = (const int32_t *)c->opt_ccol.ptr;
         O.val = (const float *)c->opt_cval.ptr;
-        std::vector<char> keep((size_t)nchunks, 0);
-        for (int v = 0; v < nvox; ++v)
-            if (roi_h[(size_t)v]) keep[(size_t)(v / kOptChunk)] = 1;
-        if ((rc = build_buckets(O, c->opt_broi, keep, kept))) return rc;
-        // the buckets hold voxel keys; the gradient's columns become indices
-        // among the structure voxels, its residual a compact array
-        std::vector<int32_t> sidx((size_t)nvox, -1);
-        int ns = 0;
-        for (int v = 0; v < nvox; ++v)
-            if (roi_h[(size_t)v]) sidx[(size_t)v] = ns++;
-        if ((rc = ensure(c, c->opt_sidx, (size_t)nvox * 4, 0))) return rc;
-        if ((rc = ensure(c, c->opt_rstruct, (size_t)n_scen * std::max(ns, 1) * 4, 0))) return rc;
-        HIP_TRY(hipMemcpyAsync(c->opt_sidx.ptr, sidx.data(), (size_t)nvox * 4, hipMemcpyHostToDevice, st));
-        HIP_TRY(opt_renumber((int32_t *)c->opt_ccol.ptr, kept, (const int32_t *)c->opt_sidx.ptr, nvox, st));
-        HIP_TRY(hipStreamSynchronize(st));   // the host vector outlives the copy
-        c->opt_nstruct = ns;
+        O.units = (const OptPiece *)c->opt_piece.ptr;
+        O.n_units = c->opt_npieces;
+        set_space(O, c->opt_nstruct, bits);
+        if ((rc = build_buckets(O, c->opt_broi, kept))) return rc;
         memcpy(c->opt_dims, dims, sizeof dims);
         c->opt_rp_host.swap(rp);
-        c->opt_roi_host.swap(roi_h);
         c->opt_col_src = dev ? (const void *)col : nullptr;
         c->opt_val_src = dev ? (const void *)val : nullptr;
         c->opt_valid = true;
@@ -2434,11 +2457,7 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
     O.n_pieces = c->opt_npieces;
     O.gpart = (double *)c->opt_gpart.ptr;
     O.rstruct = (float *)c->opt_rstruct.ptr;
-    O.sidx = (const int32_t *)c->opt_sidx.ptr;
-    O.nstruct = c->opt_nstruct;
-    F.piece = O.piece;
-    F.n_pieces = O.n_pieces;
-    F.gpart = O.gpart;
+    set_space(O, c->opt_nstruct, c->opt_bits);
     set_buckets(O, c->opt_broi);
     if (dose_gy && !c->opt_bfull.valid) {
         long long used = 0;
@@ -2446,8 +2465,9 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
             const long long crow = (r / n_spots) * stride + p->row_offset + r % n_spots;
             used += c->opt_rp_host[(size_t)crow + 1] - c->opt_rp_host[(size_t)crow];
         }
-        if ((rc = build_buckets(F, c->opt_bfull, std::vector<char>(), used))) return rc;
+        if ((rc = build_buckets(F, c->opt_bfull, used))) return rc;
     }
+    O.fpart = F.fpart = (double *)c->opt_fpart.ptr;
     HIP_TRY(hipMemcpyAsync(O.x, x, (size_t)n_spots * 8, dev ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, st));
     double *hist = (double *)c->opt_hist.ptr;
     HIP_TRY(opt_update(O, kOptPowerInit, 0.0, 0, hist, st));
@@ -2455,6 +2475,7 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
         HIP_TRY(opt_forward(O, O.z, 1, nullptr, st));
         HIP_TRY(opt_gradient(O, st));
         HIP_TRY(opt_update(O, kOptPower, 0.0, 0, hist, st));
+        HIP_TRY(opt_update(O, kOptPowerNorm, 0.0, 0, hist, st));
     }
     HIP_TRY(opt_update(O, kOptFistaInit, 0.0, 0, hist, st));
     double t = 1.0;

@@ -350,15 +350,28 @@ hipError_t launch_cell_emit(const long long *rp, const CellPiece *pcs, long long
                             double mev_scale, int32_t *ocell, long long *oq, float *oval, hipStream_t s);
 
 // ------------------------------------------------- spot-weight optimiser
-#ifndef VPMC_OPT_CHUNK_BITS
-#define VPMC_OPT_CHUNK_BITS 9
-#endif
-constexpr int kOptChunkBits = VPMC_OPT_CHUNK_BITS;
-constexpr int kOptChunk = 1 << kOptChunkBits;   // voxels per forward workgroup (int64 LDS sums)
-enum { kOptPowerInit = 0, kOptPower = 1, kOptFistaInit = 2, kOptFista = 3, kOptFinalPrep = 4, kOptFinal = 5 };
+// Voxels per forward workgroup (int64 LDS sums): 2^bits.  Over the structure
+// voxels of the iterations the largest of 2^5 .. 2^11 that leaves kOptLists
+// lists (three workgroups a CU): more lists sum too few entries each (2^9 voxels
+// of the whole grid per list: 12 500 lists of 590 entries, 46 us a sweep; 2^11
+// structure voxels: 1000 of 7300, 19 us), fewer leave CUs idle.  The sweep of
+// whole rows for the dose output takes kOptChunkBits.
+constexpr int kOptChunkBits = 9, kOptMinBits = 5, kOptMaxBits = 11;
+constexpr long long kOptLists = 768;
+enum { kOptPowerInit, kOptPower, kOptPowerNorm, kOptFistaInit, kOptFista, kOptFinalPrep, kOptFinal };
 enum { kOptLam = 0, kOptL = 1 };   // device scalars
 
-constexpr int kOptPiece = 4096;   // entries per gradient wavefront
+// Entries per gradient wavefront: four steps of 256 (4096 made the longest
+// rows a chain of 16 steps, 29 us for 7.3 M entries).
+constexpr int kOptPiece = 1024;
+constexpr int kRoiParts = 8;       // wavefronts of a row in the passes that restrict the rows
+constexpr int kOptParts = 512;     // workgroups of the update at most
+
+// 64 voxels: which have a structure bit, and the structure voxels before them
+struct OptMask {
+    unsigned long long bits;
+    uint32_t before, pad;
+};
 
 // at most kOptPiece consecutive entries of one row
 struct OptPiece {
@@ -372,10 +385,11 @@ struct OptDev {
     const int32_t *col;             // voxel indices per row
     const float *val;               // Gy per unit spot weight
     const uint8_t *roi;             // [nvox] bit 0 target, bit 1 organ at risk
-    int n_scen, n_spots, row_stride, row_offset, nvox, nchunks;
+    int n_scen, n_spots, row_stride, row_offset;
+    int nvox, nchunks, bits;        // voxels (of the iterations: structure voxels), chunks of 2^bits
     double d_presc, w_target, d_max, w_oar;
     // chunk-bucketed copy of the entries: list (s, chunk) holds entries
-    // boff[list] .. boff[list + 1], key = spot << kOptChunkBits | voxel - chunk base
+    // boff[list] .. boff[list + 1], key = spot << bits | voxel - chunk base
     const unsigned long long *boff; // [n_scen * nchunks + 1]
     const uint32_t *bkey;
     const float *bval;
@@ -385,21 +399,25 @@ struct OptDev {
     long long n_pieces;
     const long long *piece_off;     // [n_scen * n_spots + 1] first piece of each compact row
     float *amax;                    // [n_scen * n_spots] largest |a| of each row
-    float *resid;                   // [n_scen][nvox] residual of the last forward sweep
-    float *rstruct;                 // [n_scen][nstruct] the same on the structure voxels only (or NULL)
-    const int32_t *sidx;            // [nvox] index among the structure voxels, -1 elsewhere
-    int nstruct;                    // structure voxels
+    const OptPiece *units;          // row pieces of the index passes (NULL: whole rows)
+    long long n_units;
+    float *rstruct;                 // [n_scen][nvox] residual of the last forward sweep (or NULL)
     double *fpart;                  // [n_work] objective partials
     double *gpart;                  // [n_pieces] piece products with the residual
     double *x, *y, *z, *gvec;       // [n_spots]
-    double *scale;                  // [2 * n_scen] 2^m, 2^-m of the next forward sweep
+    int n_part;                     // workgroups of the update (without the objective's)
+    double *bpart;                  // [n_scen][n_part] their parts of the next sweep's bounds
+    double *sq;                     // [2][n_part] and of |g|^2, |z|^2
     double *scal;                   // device scalars (kOptLam, kOptL)
 };
 
 hipError_t opt_build_count(const OptDev &O, unsigned long long *cnt, unsigned *err, hipStream_t st);
-hipError_t opt_roi_count(const OptDev &O, unsigned long long *rcnt, unsigned *err, hipStream_t st);
-hipError_t opt_roi_copy(const OptDev &O, const long long *rptr, int32_t *ccol, float *cval, hipStream_t st);
-hipError_t opt_renumber(int32_t *ccol, long long n, const int32_t *sidx, int nvox, hipStream_t st);
+hipError_t opt_structures(const uint8_t *roi, int nvox, OptMask *mask, unsigned long long *cnt,
+                          unsigned long long *off, uint8_t *keep, uint8_t *sroi, hipStream_t st);
+hipError_t opt_roi_same(const uint8_t *a, const uint8_t *b, int nvox, unsigned *err, hipStream_t st);
+hipError_t opt_roi_count(const OptDev &O, const OptMask *mask, unsigned *rcnt, unsigned *err, hipStream_t st);
+hipError_t opt_roi_copy(const OptDev &O, const OptMask *mask, const unsigned *rcnt, const long long *rptr,
+                        int32_t *ccol, float *cval, hipStream_t st);
 hipError_t opt_build_scan(unsigned long long *cnt, unsigned long long *off, size_t n, hipStream_t st);
 hipError_t opt_build_emit(const OptDev &O, const unsigned long long *off, unsigned long long *cur, uint32_t *bkey,
                           float *bval, hipStream_t st);

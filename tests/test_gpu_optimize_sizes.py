@@ -1,0 +1,59 @@
+"""Spot-weight optimiser at the sizes where its launch shapes change, against
+the FP64 oracle with test_gpu_optimize.py's tolerances (the residual is FP32:
+1e-5 on weights and objective, 1e-6 on the step constant): voxel counts around
+a block of 4096, one structure voxel to all of them, one scenario and more than
+a wavefront has lanes, one spot and more than 512 workgroups of four hold, rows
+from empty to longer than the eight parts' first round.  Device arrays give the
+host arrays' bits, and an index is not reused for other structures."""
+import numpy as np
+import pytest
+
+from paper_2307_01416_amd import inputs as I
+from test_gpu_optimize import PAR, check, ctx, gpu, orc  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+def problem(nvox, n_struct, n_scen, n_spots, longest, seed=0):
+    rng = np.random.default_rng(seed)
+    lens = np.minimum(rng.integers(0, longest + 1, n_scen * n_spots), nvox)
+    lens[rng.integers(0, len(lens))] = min(longest, nvox)
+    col = np.concatenate([np.sort(rng.choice(nvox, n, replace=False)) for n in lens] + [[]]).astype(np.int32)
+    val = (1e-3 * rng.uniform(0.5, 1.5, len(col))).astype(np.float32)
+    roi = np.zeros(nvox, np.uint8)
+    at = rng.choice(nvox, n_struct, replace=False)
+    roi[at] = rng.integers(1, 4, n_struct)
+    rp = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    return I.OptProblem((nvox, 1, 1), n_scen, n_spots, rp, col, val, roi)
+
+
+CASES = [(4095, 1, 1, 1, 40), (4096, 64, 3, 5, 700), (4097, 65, 2, 4, 3000), (20000, 20000, 1, 9, 20000),
+         (9000, 4500, 65, 3, 1500), (700, 300, 2, 2100, 12), (60000, 33000, 13, 6, 9000)]
+
+
+@pytest.mark.parametrize("nvox,n_struct,n_scen,n_spots,longest", CASES)
+def test_sizes(ctx, nvox, n_struct, n_scen, n_spots, longest):  # noqa: F811
+    import torch
+    from paper_2307_01416_amd import vpmc as V
+    P = problem(nvox, n_struct, n_scen, n_spots, longest)
+    x0 = np.full(n_spots, 20.0)
+    xg, hg, Lg, dg = gpu(ctx, P, x0, 12, n_power=8, dose=True)
+    xo, ho, Lo, A = orc(P, x0, 12, n_power=8)
+    check(xg, hg, Lg, xo, ho, Lo)
+    for s in range(n_scen):
+        do = A[s].T @ xo
+        np.testing.assert_allclose(dg[s], do, rtol=0, atol=1e-5 * max(do.max(), 1e-30))
+    t = lambda a: torch.from_numpy(a).cuda()  # noqa: E731
+    xd, rp, col, val, roi = (t(a) for a in (x0, P.row_ptr, P.col, P.val, P.roi))
+    run = lambda m, flags: V.vpmc_optimize(ctx, rp, col, val, n_scen, n_spots, nvox, m, xd, iters=12,  # noqa: E731
+                                           n_power=8, flags=V.DEVICE_PTRS | flags, **PAR)
+    assert run(roi, 0) == Lg
+    np.testing.assert_array_equal(xd.cpu().numpy(), xg)
+    other = P.roi.copy()
+    other[-1] ^= 2
+    with pytest.raises(V.VpmcError) as ex:
+        run(t(other), V.OPT_REUSE)
+    assert ex.value.code == V.E_STATE
+    xd.copy_(t(x0))
+    assert run(roi, V.OPT_REUSE) == Lg
+    np.testing.assert_array_equal(xd.cpu().numpy(), xg)
