@@ -108,9 +108,9 @@ struct vpmc_ctx {
     hipStream_t cap_stream = nullptr;   // private stream for graph capture
     // aperture surrogate
     DevBuf mlp_w, mlp_wb, mlp_m, mlp_v, mlp_g, mlp_act, mlp_io, mlp_dx, mlp_dy, mlp_dt, mlp_idx;
+    DevBuf mlp_part;   // weight fragments and partial gradients (not counted against max_device_bytes)
     bool mlp_ready = false;
     int mlp_step = 0;
-    int mlp_batch_cap = 0;
     DevBuf sur_rec, sur_cnt, sur_out;
     // spot-weight optimiser: structure-restricted rows, bucketed copies and
     // gradient pieces (kept for VPMC_OPT_REUSE), work buffers
@@ -136,7 +136,7 @@ struct vpmc_ctx {
 
 namespace {
 
-int mlp_buffers(vpmc_ctx *c, int cap, MlpBuffers *b);
+int mlp_buffers(vpmc_ctx *c, int cap, MlpStep *S);
 
 int ensure(vpmc_ctx *c, DevBuf &b, size_t bytes, size_t cap_limit) {
     if (bytes <= b.cap) return VPMC_OK;
@@ -822,34 +822,38 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     return VPMC_OK;
 }
 
-// carve the activation buffers of a batch of up to `cap` samples
-int mlp_buffers(vpmc_ctx *c, int cap, MlpBuffers *b) {
-    const size_t H = MLP_HIDDEN;
-    const size_t bytes = (size_t)cap * (MLP_IN * 2 + 4 * H * 2 + 4 * H * 4 + MLP_OUT * 4 * 2 + MLP_OUT_LD * 2 +
-                                        H * 2 * 2 + 4) +
-                         (size_t)kMlpSplit * H * H * 4 + ((size_t)cap / 32 + 1) * H * 4 +
-                         32 * 256;   // 17 carvings, each rounded up to 256 B
-    if (c->mlp_batch_cap < cap) {
-        int rc = ensure(c, c->mlp_act, bytes, 0);
-        if (rc) return rc;
-        c->mlp_batch_cap = cap;
+// the buffers of a step of up to `cap` samples
+int mlp_buffers(vpmc_ctx *c, int cap, MlpStep *S) {
+    const size_t H = MLP_HIDDEN, np = (size_t)mlp_param_count(), n = ((size_t)cap + 31) / 32 * 32;
+    const size_t bytes = n * (2 * 32 * 2 + 8 * H * 2 + MLP_OUT * 4 + 4) + n / 32 * 4 * H * 4 + 32 * 256;
+    int rc = ensure(c, c->mlp_act, bytes, 0);
+    if (rc) return rc;
+    const size_t part = mlp_frag_bytes() + (size_t)kMlpSplit * np * 4;
+    if (c->mlp_part.cap < part) {
+        HIP_TRY(hipMalloc(&c->mlp_part.ptr, part));
+        c->mlp_part.cap = part;
     }
     char *p = (char *)c->mlp_act.ptr;
     char *const end = p + c->mlp_act.cap;
-    auto take = [&](size_t n) { char *q = p; p += (n + 255) & ~(size_t)255; return (void *)q; };
-    b->w = (float *)c->mlp_w.ptr;
-    b->wb = (__bf16 *)c->mlp_wb.ptr;
-    b->x = (__bf16 *)take((size_t)cap * MLP_IN * 2);
-    for (int i = 0; i < 4; ++i) b->h[i] = (__bf16 *)take((size_t)cap * H * 2);
-    for (int i = 0; i < 4; ++i) b->z[i] = (float *)take((size_t)cap * H * 4);
-    b->out = (float *)take((size_t)cap * MLP_OUT * 4);
-    b->dout = (float *)take((size_t)cap * MLP_OUT * 4);
-    b->dout_b = (__bf16 *)take((size_t)cap * MLP_OUT_LD * 2);
-    b->dzb_a = (__bf16 *)take((size_t)cap * H * 2);
-    b->dzb_b = (__bf16 *)take((size_t)cap * H * 2);
-    b->wpart = (float *)take((size_t)kMlpSplit * H * H * 4);
-    b->bpart = (float *)take(((size_t)cap / 32 + 1) * H * 4);
-    b->loss = (float *)take((size_t)cap * 4);
+    auto take = [&](size_t k) { char *q = p; p += (k + 255) & ~(size_t)255; return (void *)q; };
+    *S = MlpStep{};
+    S->np = (int)np;
+    S->w = (float *)c->mlp_w.ptr;
+    S->m = (float *)c->mlp_m.ptr;
+    S->v = (float *)c->mlp_v.ptr;
+    S->wb = (__bf16 *)c->mlp_wb.ptr;
+    S->fwd = (__bf16 *)c->mlp_part.ptr;
+    S->bwd = S->fwd + MLP_FWD_ELEMS;
+    S->part = (float *)((char *)c->mlp_part.ptr + mlp_frag_bytes());
+    S->xf = (__bf16 *)take(n * 32 * 2);
+    S->dof = (__bf16 *)take(n * 32 * 2);
+    for (int i = 0; i < 4; ++i) {
+        S->hf[i] = (__bf16 *)take(n * H * 2);
+        S->df[i] = (__bf16 *)take(n * H * 2);
+        S->bpart[i] = (float *)take(n / 32 * H * 4);
+    }
+    S->dout = (float *)take(n * MLP_OUT * 4);
+    S->loss = (float *)take(n * 4);
     if (p > end) return fail(VPMC_E_OOM, "surrogate activation buffer too small");
     return VPMC_OK;
 }
@@ -1002,8 +1006,8 @@ int vpmc_surrogate_loss_grad(vpmc_ctx *c, const float *x, const float *y, const 
     if (rc) return rc;
     if (!x || !y || !trans || !grad || n < 1 || n > MLP_MAX_BATCH)
         return fail(VPMC_E_ARG, "need 1..%d samples and all buffers", MLP_MAX_BATCH);
-    MlpBuffers b;
-    if ((rc = mlp_buffers(c, n, &b))) return rc;
+    MlpStep S;
+    if ((rc = mlp_buffers(c, n, &S))) return rc;
     if ((rc = ensure(c, c->mlp_io, (size_t)n * (MLP_IN + 4) * 4 + 64, 0))) return rc;
     double *dl = (double *)c->mlp_io.ptr;
     float *dx = (float *)(dl + 2), *dy = dx + (size_t)n * MLP_IN, *dt = dy + (size_t)n * 3;
@@ -1011,8 +1015,15 @@ int vpmc_surrogate_loss_grad(vpmc_ctx *c, const float *x, const float *y, const 
     HIP_TRY(hipMemcpy(dx, x, (size_t)n * MLP_IN * 4, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(dy, y, (size_t)n * 3 * 4, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(dt, trans, (size_t)n * 4, hipMemcpyHostToDevice));
-    HIP_TRY(mlp_to_bf16(dx, b.x, (size_t)n * MLP_IN, nullptr));
-    HIP_TRY(mlp_loss_grad(b, dy, dt, n, (float *)c->mlp_g.ptr, dl, nullptr));
+    S.x = dx;
+    S.y = dy;
+    S.t = dt;
+    S.n = n;
+    S.inv_n = 1.0f / n;
+    S.loss_acc = dl;
+    S.grad = (float *)c->mlp_g.ptr;
+    HIP_TRY(mlp_pack(S, nullptr));
+    HIP_TRY(mlp_step(S, 0.0f, 1, nullptr));
     double lmean = 0.0;
     HIP_TRY(hipMemcpy(&lmean, dl, sizeof(double), hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(grad, c->mlp_g.ptr, (size_t)mlp_param_count() * 4, hipMemcpyDeviceToHost));
@@ -1026,8 +1037,8 @@ int vpmc_surrogate_train(vpmc_ctx *c, const float *x, const float *y, const floa
     if (rc) return rc;
     if (!x || !y || !trans || n < 1 || epochs < 1 || batch < 16 || batch > MLP_MAX_BATCH || !(lr > 0.0f))
         return fail(VPMC_E_ARG, "bad training arguments");
-    MlpBuffers b;
-    if ((rc = mlp_buffers(c, batch, &b))) return rc;
+    MlpStep S;
+    if ((rc = mlp_buffers(c, batch, &S))) return rc;
     if ((rc = ensure(c, c->mlp_dx, (size_t)n * MLP_IN * 4, 0)) || (rc = ensure(c, c->mlp_dy, (size_t)n * 3 * 4, 0)) ||
         (rc = ensure(c, c->mlp_dt, (size_t)n * 4, 0)) || (rc = ensure(c, c->mlp_idx, (size_t)n * 4, 0)) ||
         (rc = ensure(c, c->mlp_io, (size_t)batch * 4 * 4 + 64, 0)))
@@ -1035,32 +1046,35 @@ int vpmc_surrogate_train(vpmc_ctx *c, const float *x, const float *y, const floa
     HIP_TRY(hipMemcpy(c->mlp_dx.ptr, x, (size_t)n * MLP_IN * 4, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->mlp_dy.ptr, y, (size_t)n * 3 * 4, hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(c->mlp_dt.ptr, trans, (size_t)n * 4, hipMemcpyHostToDevice));
-    double *bl = (double *)c->mlp_io.ptr;   // sum over the epoch's batches of the batch-mean loss
-    float *by = (float *)(bl + 2), *bt = by + (size_t)batch * 3;
+    S.x = (const float *)c->mlp_dx.ptr;
+    S.y = (const float *)c->mlp_dy.ptr;
+    S.t = (const float *)c->mlp_dt.ptr;
+    S.n = batch;
+    S.inv_n = 1.0f / batch;
+    S.loss_acc = (double *)c->mlp_io.ptr;   // sum over the epoch's batches of the batch-mean loss
+    HIP_TRY(mlp_pack(S, nullptr));
     std::vector<int> perm(n);
     uint64_t st = seed ^ 0x9E3779B97F4A7C15ull;
-    const int np = mlp_param_count();
-    for (int ep = 0; ep < epochs; ++ep) {
+    auto shuffle = [&]() {
         for (int i = 0; i < n; ++i) perm[i] = i;
         for (int i = n - 1; i > 0; --i) {   // Fisher-Yates with xorshift64*
             st ^= st >> 12; st ^= st << 25; st ^= st >> 27;
             const int j = (int)(((st * 0x2545F4914F6CDD1Dull) >> 11) % (uint64_t)(i + 1));
             std::swap(perm[i], perm[j]);
         }
+    };
+    shuffle();
+    for (int ep = 0; ep < epochs; ++ep) {
         HIP_TRY(hipMemcpy(c->mlp_idx.ptr, perm.data(), (size_t)n * 4, hipMemcpyHostToDevice));
-        HIP_TRY(hipMemsetAsync(bl, 0, sizeof(double), nullptr));
+        HIP_TRY(launch_fill_u64((unsigned long long *)S.loss_acc, 1, 0ull, nullptr));
         int nb = 0;
         for (int s0 = 0; s0 + batch <= n; s0 += batch, ++nb) {
-            const int *idx = (const int *)c->mlp_idx.ptr + s0;
-            HIP_TRY(mlp_gather((const float *)c->mlp_dx.ptr, idx, batch, MLP_IN, b.x, nullptr, nullptr));
-            HIP_TRY(mlp_gather((const float *)c->mlp_dy.ptr, idx, batch, 3, nullptr, by, nullptr));
-            HIP_TRY(mlp_gather((const float *)c->mlp_dt.ptr, idx, batch, 1, nullptr, bt, nullptr));
-            HIP_TRY(mlp_loss_grad(b, by, bt, batch, (float *)c->mlp_g.ptr, bl, nullptr));
-            HIP_TRY(mlp_adam((float *)c->mlp_w.ptr, (const float *)c->mlp_g.ptr, (float *)c->mlp_m.ptr,
-                             (float *)c->mlp_v.ptr, (__bf16 *)c->mlp_wb.ptr, np, lr, ++c->mlp_step, nullptr));
+            S.idx = (const int *)c->mlp_idx.ptr + s0;
+            HIP_TRY(mlp_step(S, lr, ++c->mlp_step, nullptr));
         }
+        if (ep + 1 < epochs) shuffle();   // while the GPU works on this epoch
         double lsum = 0.0;
-        HIP_TRY(hipMemcpy(&lsum, bl, sizeof(double), hipMemcpyDeviceToHost));
+        HIP_TRY(hipMemcpy(&lsum, S.loss_acc, sizeof(double), hipMemcpyDeviceToHost));
         if (loss_per_epoch) loss_per_epoch[ep] = nb ? (float)(lsum / nb) : 0.0f;
     }
     return VPMC_OK;
@@ -1126,7 +1140,7 @@ void vpmc_destroy(vpmc_ctx *c) {
                           &c->stage_dose, &c->stage_sigma, &c->stats, &c->slot_grid, &c->slot_mark, &c->slot_cnt,
                           &c->slot_coff, &c->slot_rowcnt, &c->q_stage, &c->q_ctl, &c->rows, &c->grp_off, &c->heads, &c->row_off, &c->row_nnz, &c->used,
                           &c->flags, &c->fields_tab, &c->poly_off, &c->polys, &c->scen_tab, &c->csr_col,
-                          &c->csr_q, &c->mlp_w, &c->mlp_wb, &c->mlp_m, &c->mlp_v, &c->mlp_g, &c->mlp_act,
+                          &c->csr_q, &c->mlp_w, &c->mlp_wb, &c->mlp_m, &c->mlp_v, &c->mlp_g, &c->mlp_act, &c->mlp_part,
                           &c->mlp_io, &c->mlp_dx, &c->mlp_dy, &c->mlp_dt, &c->mlp_idx, &c->sur_rec,
                           &c->sur_cnt, &c->sur_out, &c->opt_rp, &c->opt_col, &c->opt_val, &c->opt_roi, &c->opt_amax,
                           &c->opt_cnt, &c->opt_rcnt, &c->opt_crp, &c->opt_ccol, &c->opt_cval, &c->opt_piece,

@@ -274,24 +274,26 @@ constexpr int MLP_LAYERS = 5;
 constexpr int MLP_IN = 8;
 constexpr int MLP_OUT = 29;
 constexpr int MLP_HIDDEN = 256;
-constexpr int MLP_OUT_LD = 32;   // row pitch of the BF16 output gradient
 constexpr int kMlpSplit = 16;    // K split of the weight-gradient products
 constexpr int MLP_MAX_BATCH = 16384;
 constexpr unsigned long long kSurMaxRecords = 1ull << 22;   // surrogate queue (64 B each)
 
-struct MlpBuffers {
-    float *w;            // FP32 master parameters
-    __bf16 *wb;          // BF16 parameters
-    __bf16 *x;           // [n][8] inputs
-    __bf16 *h[4];        // [n][256] hidden activations
-    float *z[4];         // [n][256] hidden pre-activations
-    float *out;          // [n][29]
-    float *dout;         // [n][29] d loss / d out (batch mean)
-    __bf16 *dout_b;      // [n][MLP_OUT_LD], zero padded
-    __bf16 *dzb_a, *dzb_b;  // [n][256] d loss / d Z of a hidden layer
-    float *wpart;        // [kMlpSplit][256 * 256] split-K partial weight gradients
-    float *bpart;        // [(n + 31) / 32][256] 32-row partial bias gradients
-    float *loss;         // [n] per-sample loss
+// One training (or gradient) step's operands; *f are MFMA fragments.
+struct MlpStep {
+    const float *x, *y, *t;   // samples: [][8] inputs, [][3] targets, [] outcome
+    const int *idx;           // which of them (NULL: 0 .. n-1)
+    int n, np;                // samples, parameters
+    float inv_n;
+    float *w, *m, *v;         // FP32 master parameters, Adam moments
+    __bf16 *wb, *fwd, *bwd;   // BF16 parameters, as fragments of both directions
+    __bf16 *xf, *hf[4];       // inputs and hidden activations
+    __bf16 *dof, *df[4];      // d loss / d outputs and pre-activations
+    float *dout;              // [29][n] d loss / d outputs (batch mean)
+    float *bpart[4];          // [(n + 31) / 32][256] 32-sample sums of d loss / d pre-activations
+    float *part;              // [kMlpSplit][np] partial weight gradients
+    float *loss;              // [n] per-sample loss
+    double *loss_acc;         // += the batch-mean loss
+    float *grad;              // the gradient instead of an update (or NULL)
 };
 
 hipError_t launch_sur_resume(const GeomDev &g, const FieldDev &f, const LaunchDev &L, const DeferRec *rec,
@@ -301,21 +303,17 @@ hipError_t launch_sur_resume_csr(const GeomDev &g, const QueueDev &Q, const Defe
 hipError_t launch_surrogate_sample(const FieldDev &f, const float *entries, int n, uint32_t key0, uint32_t key1,
                                    unsigned physics, const float *tables, float *x, float *y, float *t, hipStream_t s);
 int mlp_param_count();
-int mlp_param_offset(int layer);
-int mlp_dim(int i);
-hipError_t mlp_forward(const MlpBuffers &b, int n, hipStream_t s);
+size_t mlp_frag_bytes();   // both directions' weight fragments, the forward ones' share first
+constexpr int MLP_FWD_ELEMS = (8 + 3 * 128 + 16) * 512;
 // fused inference of n samples: inputs x [n][8] FP32, or (rec != NULL) the
 // features of deferred-VP records; outputs out [n][29] FP32
 hipError_t mlp_infer(const float *x, const DeferRec *rec, int n, const __bf16 *wb, const float *wf, float *out,
                      hipStream_t s);
-// forward + backward of n samples: gradient of the batch-mean loss into
-// grad; *loss_acc += the batch-mean loss
-hipError_t mlp_loss_grad(const MlpBuffers &b, const float *y, const float *trans, int n, float *grad,
-                         double *loss_acc, hipStream_t s);
-hipError_t mlp_gather(const float *x, const int *idx, int n, int cols, __bf16 *xb, float *xf, hipStream_t s);
+// S.fwd, S.bwd from S.wb; forward, loss, backward and update (or gradient) of
+// S.n samples
+hipError_t mlp_pack(const MlpStep &S, hipStream_t s);
+hipError_t mlp_step(const MlpStep &S, float lr, int step, hipStream_t s);
 hipError_t mlp_to_bf16(const float *x, __bf16 *y, size_t n, hipStream_t s);
-hipError_t mlp_adam(float *p, const float *g, float *m, float *v, __bf16 *pb, int np, float lr, int step,
-                    hipStream_t s);
 hipError_t launch_csr_count(const QueueDev &Q, unsigned int *cnt, hipStream_t s);
 hipError_t launch_csr_chunk_scan(const unsigned int *cnt, unsigned int *coff, unsigned int *rowcnt, int n_rows,
                                  size_t nchunk, hipStream_t s);

@@ -20,143 +20,6 @@ __device__ __forceinline__ float dsilu_f(float z) {
     return s * (1.0f + z * (1.0f - s));
 }
 
-// C[m][n] = sum_k A(m,k) B(k,n) over one K range, A(m,k) = AT ? A[k*lda+m] :
-// A[m*lda+k], B(k,n) = BT ? B[n*ldb+k] : B[k*ldb+n].  Workgroup tile 64x64,
-// four waves each own a 32x32 block computed with v_mfma_f32_32x32x16_bf16,
-// K advancing 64 per LDS stage (next stage's 16-byte global loads in flight
-// in registers during the current stage's MFMAs).  The operand whose
-// contiguous dimension is K is copied to LDS as is; the other is transposed
-// on the way in, so each lane's eight K values are contiguous in LDS.  Loads
-// are 8 elements wide: pitches and pointers are multiples of 8 elements and
-// the contiguous dimension of each operand is readable up to the next
-// multiple of 8 (elements past M or N only reach masked outputs; elements
-// past K are zeroed).  blockIdx.z selects the K range [z*kchunk, ...) for a
-// split-K product; its partial goes to C + z*czs.
-//   EPI_F32:   C = acc (+ bias[n])                                   (FP32)
-//   EPI_SILU:  C = z = acc + bias[n], Cb = bf16(silu(z))             (forward)
-//   EPI_DSILU: d = acc * silu'(aux[m*ldc+n]), Cb = bf16(d), and the sum of d
-//              over each 32-row block into C[(m/32)*ldc + n]          (backward)
-// For a given element the k16 MFMAs run in ascending K order into one
-// accumulator, as in the fused inference kernel below.
-enum { EPI_F32 = 0, EPI_SILU = 1, EPI_DSILU = 2 };
-constexpr int kGT = 64, kGK = 64, kGLd = kGK + 8;
-
-template <bool AT>
-__device__ __forceinline__ void gemm_fetch(const __bf16 *__restrict__ P, int ld, int rows, int r0, int k0, int kend,
-                                           int t, uint4 (&r)[2]) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int c = t + 256 * h, outer = c >> 3, inner = (c & 7) * 8;
-        uint4 v = make_uint4(0u, 0u, 0u, 0u);
-        if (!AT) {   // rows of the tile, K contiguous
-            const int row = r0 + outer, k = k0 + inner;
-            if (row < rows && k < kend) {
-                v = *(const uint4 *)(P + (size_t)row * ld + k);
-                if (k + 8 > kend) {   // zero the elements past K
-                    unsigned int w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                    for (int j = 0; j < 8; ++j)
-                        if (k + j >= kend) w[j >> 1] &= (j & 1) ? 0x0000FFFFu : 0xFFFF0000u;
-                    v = make_uint4(w[0], w[1], w[2], w[3]);
-                }
-            }
-        } else {     // K rows, tile rows contiguous
-            const int k = k0 + outer, row = r0 + inner;
-            if (k < kend && row < rows) v = *(const uint4 *)(P + (size_t)k * ld + row);
-        }
-        r[h] = v;
-    }
-}
-
-template <bool AT>
-__device__ __forceinline__ void gemm_stash(unsigned short *L, int t, const uint4 (&r)[2]) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const int c = t + 256 * h, outer = c >> 3, inner = (c & 7) * 8;
-        if (!AT) {
-            *(uint4 *)(L + outer * kGLd + inner) = r[h];
-        } else {
-            const unsigned int w[4] = {r[h].x, r[h].y, r[h].z, r[h].w};
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                L[(inner + j) * kGLd + outer] = (unsigned short)(w[j >> 1] >> (16 * (j & 1)));
-        }
-    }
-}
-
-template <bool AT, bool BT, int EPI>
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(const __bf16 *__restrict__ A, int lda,
-                                                        const __bf16 *__restrict__ B, int ldb,
-                                                        const float *__restrict__ bias, const float *__restrict__ aux,
-                                                        float *C, int ldc, size_t czs, __bf16 *Cb, int ldcb, int M,
-                                                        int N, int K, int kchunk) {
-    __shared__ __attribute__((aligned(16))) unsigned short As[kGT * kGLd];
-    __shared__ __attribute__((aligned(16))) unsigned short Bs[kGT * kGLd];
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const int m0 = blockIdx.y * kGT, n0 = blockIdx.x * kGT;
-    const int wr = (w >> 1) * 32, wc = (w & 1) * 32;
-    const int kbeg = blockIdx.z * kchunk, kend = min(K, kbeg + kchunk);
-    f32x16 acc;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-    uint4 ra[2], rb[2];
-    gemm_fetch<AT>(A, lda, M, m0, kbeg, kend, t, ra);
-    gemm_fetch<!BT>(B, ldb, N, n0, kbeg, kend, t, rb);
-    const int kb = 8 * (lane >> 5);
-    for (int k0 = kbeg; k0 < kend; k0 += kGK) {
-        gemm_stash<AT>(As, t, ra);
-        gemm_stash<!BT>(Bs, t, rb);
-        __syncthreads();
-        if (k0 + kGK < kend) {
-            gemm_fetch<AT>(A, lda, M, m0, k0 + kGK, kend, t, ra);
-            gemm_fetch<!BT>(B, ldb, N, n0, k0 + kGK, kend, t, rb);
-        }
-#pragma unroll
-        for (int kk = 0; kk < kGK / 16; ++kk) {
-            if (k0 + 16 * kk >= kend) break;
-            const uint4 av = *(const uint4 *)(As + (wr + (lane & 31)) * kGLd + 16 * kk + kb);
-            const uint4 bv = *(const uint4 *)(Bs + (wc + (lane & 31)) * kGLd + 16 * kk + kb);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, av),
-                                                          __builtin_bit_cast(bf16x8, bv), acc, 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    const int n = n0 + wc + (lane & 31);
-    float csum = 0.0f;
-    C += (size_t)blockIdx.z * czs;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int m = m0 + wr + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-        if (m < M && n < N) {
-            if (EPI == EPI_F32) {
-                C[(size_t)m * ldc + n] = acc[i] + (bias ? bias[n] : 0.0f);
-            } else if (EPI == EPI_SILU) {
-                const float z = acc[i] + bias[n];
-                C[(size_t)m * ldc + n] = z;
-                Cb[(size_t)m * ldcb + n] = (__bf16)silu_f(z);
-            } else {
-                const float d = acc[i] * dsilu_f(aux[(size_t)m * ldc + n]);
-                Cb[(size_t)m * ldcb + n] = (__bf16)d;
-                csum += d;
-            }
-        }
-    }
-    if (EPI == EPI_DSILU) {
-        csum += __shfl_xor(csum, 32, 64);
-        const int mb = (m0 + wr) >> 5;
-        if (lane < 32 && n < N && m0 + wr < M) C[(size_t)mb * ldc + n] = csum;
-    }
-}
-
-// out[i] = sum over p < parts of in[p*stride + i], in order of p
-__global__ void sum_parts_kernel(const float *__restrict__ in, int parts, size_t stride, size_t n, float *out) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        float s = 0.0f;
-        for (int p = 0; p < parts; ++p) s += in[(size_t)p * stride + i];
-        out[i] = s;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Fused inference: one workgroup (4 waves) carries 64 samples through all
 // five layers.  The activations stay in LDS (two BF16 buffers of 64 x 256,
@@ -164,8 +27,8 @@ __global__ void sum_parts_kernel(const float *__restrict__ in, int parts, size_t
 // columns of a hidden layer as 2 x 2 tiles of v_mfma_f32_32x32x16_bf16, its B
 // fragments (eight consecutive K of one output unit, W[out][in] row-major)
 // read straight from the L2-resident BF16 weights.  The K order and the
-// instruction are those of gemm_bf16_kernel, so the outputs equal the
-// layer-by-layer forward pass bit for bit.  REC: the inputs are computed from
+// instruction are those of mlp_chain_kernel, so the outputs equal the training
+// pass's bit for bit.  REC: the inputs are computed from
 // the deferred-VP records (same encoding as the training data) instead of
 // read as FP32 rows of 8.
 constexpr int kInfRows = 64;
@@ -282,30 +145,115 @@ __global__ void to_bf16_kernel(const float *__restrict__ x, __bf16 *__restrict__
         y[i] = (__bf16)x[i];
 }
 
-// gather rows of x (n_cols wide) by index, converting to BF16
-__global__ void gather_rows_kernel(const float *__restrict__ x, const int *__restrict__ idx, int n, int cols,
-                                   __bf16 *xb, float *xf) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n * cols; i += gridDim.x * blockDim.x) {
-        const int r = i / cols, c = i - r * cols;
-        const float v = x[(size_t)idx[r] * cols + c];
-        if (xb) xb[i] = (__bf16)v;
-        if (xf) xf[i] = v;
+// ---------------------------------------------------------------------------
+// Training step: three launches (chain, weight gradients, update).  A layer by
+// layer step was 30 launches of 4 to 12 us, 230 us for 4096 samples.
+//
+// Fragments: 64 lanes x 8 BF16 (16 bytes a lane, 1 KB, one load of a
+// wavefront) as v_mfma_f32_32x32x16_bf16 takes an operand: lane & 31 is the
+// row (A) or column (B), 8 (lane >> 5) + j the K index.  The weights are kept a
+// second time as fragments of both directions (frag_fwd, frag_bwd: layer by
+// layer, 32 outputs (inputs) by 16 K); the activations and their gradients are
+// written as fragments with the samples along K (per 32 samples: 32 features,
+// two halves of 16 samples), which is what the weight gradients contract.
+constexpr int kFrag = 512;                          // elements of a fragment
+constexpr int kFwdFrags = MLP_FWD_ELEMS / kFrag, kBwdFrags = 3 * 128 + 16;
+
+__host__ __device__ constexpr int fwd_base(int l) { return l == 0 ? 0 : 8 + 128 * (l - 1); }   // in fragments
+__host__ __device__ constexpr int bwd_base(int l) { return 128 * (l - 1); }
+__device__ __forceinline__ int frag_at(int row, int k, int steps) {
+    return (((row >> 5) * steps + (k >> 4)) * 64 + (row & 31) + 32 * ((k >> 3) & 1)) * 8 + (k & 7);
+}
+// where the weight W[o][i] of layer l stands in both fragment buffers
+__device__ __forceinline__ int frag_fwd(int l, int o, int i) {
+    return fwd_base(l) * kFrag + frag_at(o, i, l == 0 ? 1 : 16);
+}
+__device__ __forceinline__ int frag_bwd(int l, int o, int i) {
+    return bwd_base(l) * kFrag + frag_at(i, o, l == MLP_LAYERS - 1 ? 2 : 16);
+}
+
+// layer, output and input of the e-th weight (biases not counted), and its
+// index among the parameters
+__device__ __forceinline__ int weight_at(int e, int &l, int &o, int &i) {
+    constexpr int n0 = MLP_HIDDEN * MLP_IN, nh = MLP_HIDDEN * MLP_HIDDEN;
+    l = e < n0 ? 0 : 1 + (e - n0) / nh;
+    const int r = l == 0 ? e : e - n0 - (l - 1) * nh;
+    o = l == 0 ? r / MLP_IN : r / MLP_HIDDEN;
+    i = l == 0 ? r % MLP_IN : r % MLP_HIDDEN;
+    return e + MLP_HIDDEN * l;
+}
+constexpr int kWeights = MLP_HIDDEN * (MLP_IN + 3 * MLP_HIDDEN + MLP_OUT);
+
+// both fragment buffers (one behind the other) from the BF16 parameters
+__global__ void mlp_pack_kernel(const __bf16 *__restrict__ wb, __bf16 *fwd, __bf16 *bwd) {
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < kWeights; e += gridDim.x * blockDim.x) {
+        int l, o, i;
+        const __bf16 w = wb[weight_at(e, l, o, i)];
+        fwd[frag_fwd(l, o, i)] = w;
+        if (l > 0) bwd[frag_bwd(l, o, i)] = w;
     }
 }
 
-// Per-sample loss and its gradient with respect to the 29 outputs (scaled
-// by 1/n for the batch mean), written as FP32 [n][29] and as BF16 rows of
-// MLP_OUT_LD with zero padding.
-__global__ void loss_head_kernel(const float *__restrict__ out, const float *__restrict__ y,
-                                 const float *__restrict__ trans, int n, float inv_n, float *dout,
-                                 __bf16 *dout_b, float *loss) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    const float *o = out + (size_t)s * 29;
+// rows of `in` x the fragments b, K in steps of 16
+template <int T>
+__device__ __forceinline__ f32x16 chain_mm(const __bf16 (*in)[kInfLd], const uint4 (&b)[16]) {
+    const int lane = threadIdx.x & 63;
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+            *reinterpret_cast<const bf16x8 *>(&in[lane & 31][16 * t + 8 * (lane >> 5)]),
+            __builtin_bit_cast(bf16x8, b[t]), acc, 0, 0, 0);
+    return acc;
+}
+
+template <int T>
+__device__ __forceinline__ void chain_load(uint4 (&b)[16], const __bf16 *frags) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) b[t] = *((const uint4 *)(frags + (size_t)t * kFrag) + (threadIdx.x & 63));
+}
+
+// A 32 x 32 block of values (accumulator layout: sample 8 (i >> 2) + 4 (lane >> 5)
+// + (i & 3), feature lane & 31) as two fragments with the samples along K.
+__device__ __forceinline__ void put_frags(const unsigned short (&v)[16], __bf16 *to) {
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        unsigned g[2][2], r[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                g[q][k] = (unsigned)v[8 * t + 4 * q + 2 * k] | (unsigned)v[8 * t + 4 * q + 2 * k + 1] << 16;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) r[k] = (unsigned)__shfl_xor((int)(h ? g[0][k] : g[1][k]), 32);
+        const uint4 f = h ? make_uint4(r[0], r[1], g[1][0], g[1][1]) : make_uint4(g[0][0], g[0][1], r[0], r[1]);
+        *((uint4 *)(to + t * kFrag) + lane) = f;
+    }
+}
+
+// the same from rows of samples in LDS (features past `cols` are zero)
+__device__ __forceinline__ void put_rows(const __bf16 (*in)[kInfLd], int cols, __bf16 *to) {
+    const int lane = threadIdx.x & 63, f = lane & 31;
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        bf16x8 v;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = f < cols ? in[16 * t + 8 * (lane >> 5) + j][f] : (__bf16)0.0f;
+        *((uint4 *)(to + t * kFrag) + lane) = __builtin_bit_cast(uint4, v);
+    }
+}
+
+// Per-sample loss and its gradient with respect to the 29 outputs (scaled by
+// inv_n for the batch mean): FP32 in dout (an output every `pitch`), BF16 in db.
+__device__ __forceinline__ float loss_head(const float *o, const float (&y)[3], float tr, float inv_n,
+                                           float *__restrict__ dout, int pitch, __bf16 *db) {
     float g[29];
 #pragma unroll
     for (int j = 0; j < 29; ++j) g[j] = 0.0f;
-    const float lt = o[0], tr = trans[s];
+    const float lt = o[0];
     float L = fmaxf(lt, 0.0f) - lt * tr + log1pf(__expf(-fabsf(lt)));
     g[0] = 1.0f / (1.0f + __expf(-lt)) - tr;
     if (tr > 0.5f) {
@@ -324,7 +272,7 @@ __global__ void loss_head_kernel(const float *__restrict__ out, const float *__r
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const float mu = o[5 + 3 * c + j], ls = o[17 + 3 * c + j];
-                const float r = (y[(size_t)s * 3 + j] - mu) * __expf(-ls);
+                const float r = (y[j] - mu) * __expf(-ls);
                 acc += -0.5f * r * r - ls - 0.91893853320467274f;
             }
             lp[c] = lw[c] + acc;
@@ -342,7 +290,7 @@ __global__ void loss_head_kernel(const float *__restrict__ out, const float *__r
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const float mu = o[5 + 3 * c + j], ls = o[17 + 3 * c + j];
-                const float iv = __expf(-2.0f * ls), d = y[(size_t)s * 3 + j] - mu;
+                const float iv = __expf(-2.0f * ls), d = y[j] - mu;
                 g[5 + 3 * c + j] += -gam * d * iv;
                 g[17 + 3 * c + j] += -gam * (d * d * iv - 1.0f);
             }
@@ -350,56 +298,276 @@ __global__ void loss_head_kernel(const float *__restrict__ out, const float *__r
     }
 #pragma unroll
     for (int j = 0; j < 29; ++j) {
-        dout[(size_t)s * 29 + j] = g[j] * inv_n;
-        dout_b[(size_t)s * MLP_OUT_LD + j] = (__bf16)(g[j] * inv_n);
+        dout[(size_t)j * pitch] = g[j] * inv_n;
+        db[j] = (__bf16)(g[j] * inv_n);
     }
+    return L;
+}
+
+// Forward, loss and backward of 32 samples by one workgroup of eight
+// wavefronts, each on 32 features of every layer.  What bounds it is the chain
+// of ten products, not their arithmetic (4096 samples: 128 workgroups): the
+// activations stay in LDS, the pre-activations in the registers that the
+// backward pass needs them in (the same 32 x 32 block), and the weights of a
+// layer, which do not wait for anything, are loaded as fragments while the
+// layer before it is finished.  27 us for 4096 samples: the ten products and
+// their barriers 14, silu and its derivative 7, loss 2, the fragments' stores
+// and loads 4 (25 launches of the layer by layer step: 120 us).  K runs in
+// ascending steps of 16 into one accumulator.  Rows past n are zero in all that
+// the other kernels read.
+__global__ __launch_bounds__(512) void mlp_chain_kernel(MlpStep S) {
+    __shared__ __attribute__((aligned(16))) __bf16 H[2][32][kInfLd];
+    __shared__ float out[32][MLP_OUT];
+    const int t = threadIdx.x, lane = t & 63, w = __builtin_amdgcn_readfirstlane(t >> 6), h = lane >> 5;
+    const int row0 = blockIdx.x * 32, col = 32 * w + (lane & 31);
+    const int rows = min(32, S.n - row0);
+    uint4 b[16];
+    chain_load<1>(b, S.fwd + (size_t)(fwd_base(0) + w) * kFrag);
+    float bias[4];
 #pragma unroll
-    for (int j = 29; j < MLP_OUT_LD; ++j) dout_b[(size_t)s * MLP_OUT_LD + j] = (__bf16)0.0f;
-    loss[s] = L;
-}
-
-// bias gradient: column sums of dZ [n x cols]
-__global__ void colsum_kernel(const float *__restrict__ dz, int n, int cols, float *gb) {
-    const int c = blockIdx.x;
-    float s = 0.0f;
-    for (int r = threadIdx.x; r < n; r += blockDim.x) s += dz[(size_t)r * cols + c];
-    __shared__ float red[256];
-    red[threadIdx.x] = s;
+    for (int l = 0; l < 4; ++l) bias[l] = S.w[(l == 0 ? MLP_HIDDEN * MLP_IN : MLP_HIDDEN * (MLP_IN + 1) +
+                                               l * MLP_HIDDEN * MLP_HIDDEN + (l - 1) * MLP_HIDDEN) + col];
+    float y[3] = {0.0f, 0.0f, 0.0f}, tr = 0.0f;
+    if (t < 32) {
+        bf16x8 v, zero;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = zero[j] = (__bf16)0.0f;
+        if (t < rows) {
+            const size_t src = S.idx ? (size_t)S.idx[row0 + t] : (size_t)(row0 + t);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = (__bf16)S.x[src * MLP_IN + j];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) y[j] = S.y[src * 3 + j];
+            tr = S.t[src];
+        }
+        *reinterpret_cast<bf16x8 *>(&H[0][t][0]) = v;
+        *reinterpret_cast<bf16x8 *>(&H[0][t][8]) = zero;
+    }
     __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    if (w == 7) put_rows(H[0], MLP_IN, S.xf + (size_t)blockIdx.x * 2 * kFrag);
+    float z[4][16];
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+        const f32x16 acc = l == 0 ? chain_mm<1>(H[0], b) : chain_mm<16>(H[l & 1], b);
+        if (l < 3) chain_load<16>(b, S.fwd + (size_t)(fwd_base(l + 1) + 16 * w) * kFrag);
+        else if (w == 0) chain_load<16>(b, S.fwd + (size_t)fwd_base(4) * kFrag);
+        else chain_load<2>(b, S.bwd + (size_t)(bwd_base(4) + 2 * w) * kFrag);
+        unsigned short v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int m = 8 * (i >> 2) + 4 * h + (i & 3);
+            z[l][i] = acc[i] + bias[l];
+            const __bf16 a = m < rows ? (__bf16)silu_f(z[l][i]) : (__bf16)0.0f;
+            H[(l + 1) & 1][m][col] = a;
+            v[i] = __builtin_bit_cast(unsigned short, a);
+        }
+        put_frags(v, S.hf[l] + ((size_t)blockIdx.x * 8 + w) * 2 * kFrag);
         __syncthreads();
     }
-    if (threadIdx.x == 0) gb[c] = red[0];
-}
-
-// Adam (Kingma and Ba) on FP32 master weights, refreshing the BF16 copy
-__global__ void adam_kernel(float *p, const float *__restrict__ g, float *m, float *v, __bf16 *pb, int np,
-                            float lr, float b1, float b2, float eps, float c1, float c2) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < np; i += gridDim.x * blockDim.x) {
-        const float gi = g[i];
-        const float mi = b1 * m[i] + (1.0f - b1) * gi;
-        const float vi = b2 * v[i] + (1.0f - b2) * gi * gi;
-        m[i] = mi;
-        v[i] = vi;
-        const float pi = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-        p[i] = pi;
-        pb[i] = (__bf16)pi;
+    if (w == 0) {
+        const f32x16 acc = chain_mm<16>(H[0], b);
+        chain_load<2>(b, S.bwd + (size_t)bwd_base(4) * kFrag);
+        const float bo = lane % 32 < MLP_OUT ? S.w[MLP_HIDDEN * (MLP_IN + 1) + 3 * MLP_HIDDEN * (MLP_HIDDEN + 1) +
+                                                   MLP_HIDDEN * MLP_OUT + (lane & 31)] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if ((lane & 31) < MLP_OUT) out[8 * (i >> 2) + 4 * h + (i & 3)][lane & 31] = acc[i] + bo;
     }
-}
-
-// *out += (sum of x[0..n)) * scale, in FP64
-__global__ void reduce_sum_kernel(const float *__restrict__ x, int n, double scale, double *out) {
-    __shared__ float red[256];
-    float s = 0.0f;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) s += x[i];
-    red[threadIdx.x] = s;
     __syncthreads();
-    for (int o = blockDim.x / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+    if (t < 32) {
+        __bf16 *db = H[1][t];
+#pragma unroll
+        for (int j = 0; j < 32; j += 8) {
+            bf16x8 zero;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) zero[k] = (__bf16)0.0f;
+            *reinterpret_cast<bf16x8 *>(db + j) = zero;
+        }
+        if (t < rows)
+            S.loss[row0 + t] = loss_head(out[t], y, tr, S.inv_n, S.dout + row0 + t, S.n, db);
+    }
+    __syncthreads();
+    if (w == 7) put_rows(H[1], MLP_OUT, S.dof + (size_t)blockIdx.x * 2 * kFrag);
+#pragma unroll
+    for (int l = 4; l >= 1; --l) {   // dZ of layer l-1 = (dZ of layer l . W_l) * silu'(Z of layer l-1)
+        const f32x16 acc = l == 4 ? chain_mm<2>(H[1], b) : chain_mm<16>(H[l & 1 ? 0 : 1], b);
+        if (l > 1) chain_load<16>(b, S.bwd + (size_t)(bwd_base(l - 1) + 16 * w) * kFrag);
+        unsigned short v[16];
+        float csum = 0.0f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int m = 8 * (i >> 2) + 4 * h + (i & 3);
+            __bf16 a = (__bf16)0.0f;
+            if (m < rows) {
+                const float d = acc[i] * dsilu_f(z[l - 1][i]);
+                a = (__bf16)d;
+                csum += d;
+            }
+            if (l > 1) H[l & 1 ? 1 : 0][m][col] = a;
+            v[i] = __builtin_bit_cast(unsigned short, a);
+        }
+        put_frags(v, S.df[l - 1] + ((size_t)blockIdx.x * 8 + w) * 2 * kFrag);
+        csum += __shfl_xor(csum, 32, 64);
+        if (h == 0) S.bpart[l - 1][(size_t)blockIdx.x * MLP_HIDDEN + col] = csum;
         __syncthreads();
     }
-    if (threadIdx.x == 0) *out += (double)red[0] * scale;
+}
+
+// Weight gradients dW = dZ^T . H_in of all layers in one launch: a wavefront per
+// 32 x 32 block and K range [z kchunk, ...), partials to part[z][parameter].
+// The operands are fragments, read once per wavefront straight from L2 in 1 KB
+// loads; a workgroup is 2 x 2 blocks of a hidden layer, or four blocks of the
+// first or last.  The K range is the workgroup's number modulo the ranges:
+// workgroups go to the XCDs in turn, so each XCD's L2 fetches an eighth of the
+// samples (11.8 us with the range as the slow index, 10.5 so).
+__global__ __launch_bounds__(256) void mlp_wgrad_kernel(MlpStep S, int kchunk, int split) {
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int kr = (int)blockIdx.x % split, g = (int)blockIdx.x / split;
+    int l, mt, nt;
+    if (g < 48) {
+        l = 1 + g / 16;
+        mt = 2 * (g % 16 / 4) + (w >> 1);
+        nt = 2 * (g % 4) + (w & 1);
+    } else {
+        const int k = 4 * (g & 1) + w;
+        l = g < 50 ? 0 : 4;
+        mt = l == 0 ? k : 0;
+        nt = l == 0 ? 0 : k;
+    }
+    const __bf16 *A = l == 4 ? S.dof : S.df[l] + (size_t)mt * 2 * kFrag;
+    const __bf16 *B = l == 0 ? S.xf : S.hf[l - 1] + (size_t)nt * 2 * kFrag;
+    const size_t da = (l == 4 ? 2 : 16) * kFrag, db = (l == 0 ? 2 : 16) * kFrag;   // per 32 samples
+    const int kbeg = kr * kchunk, kend = min(S.n, kbeg + kchunk);
+    f32x16 acc;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+    constexpr int kFlight = 4;   // blocks of 32 samples in flight
+    for (int k = kbeg; k < kend; k += 32 * kFlight) {
+        uint4 a[kFlight][2], b[kFlight][2];
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            if (k + 32 * u >= kend) break;
+            const uint4 *pa = (const uint4 *)(A + (size_t)((k >> 5) + u) * da) + lane;
+            const uint4 *pb = (const uint4 *)(B + (size_t)((k >> 5) + u) * db) + lane;
+            a[u][0] = pa[0];
+            a[u][1] = pa[64];
+            b[u][0] = pb[0];
+            b[u][1] = pb[64];
+        }
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            if (k + 32 * u >= kend) break;
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a[u][j]),
+                                                              __builtin_bit_cast(bf16x8, b[u][j]), acc, 0, 0, 0);
+        }
+    }
+    const int ni = l == 0 ? MLP_IN : MLP_HIDDEN, no = l == 4 ? MLP_OUT : MLP_HIDDEN;
+    const int off = l == 0 ? 0 : MLP_HIDDEN * (MLP_IN + 1) + (l - 1) * MLP_HIDDEN * (MLP_HIDDEN + 1);
+    float *C = S.part + (size_t)kr * S.np + off;
+    const int n = 32 * nt + (lane & 31);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int m = 32 * mt + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+        if (m < no && n < ni) C[(size_t)m * ni + n] = acc[i];
+    }
+}
+
+// Sum over x[r * stride], r < n: 256 strided sums, then a tree.  By a workgroup
+// (WG, a sum per thread) for a value per sample, by a wavefront (four sums a
+// lane) for one per 32 samples; the same bits.  Up to 16 loads of a thread are
+// in flight: what the sums cost is the rounds to memory.
+template <bool WG>
+__device__ __forceinline__ float strided_sum(const float *__restrict__ x, int n, size_t stride, float *red) {
+    constexpr int per = WG ? 1 : 4, step = WG ? 256 : 64;
+    const int t = WG ? (int)threadIdx.x : (int)(threadIdx.x & 63);
+    float s[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    for (int r = t; r < n; r += step * 16) {
+        float v[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) v[u] = r + step * u < n ? x[(size_t)(r + step * u) * stride] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+            if (r + step * u < n) s[u % per] += v[u];
+    }
+    if (WG) {
+        red[t] = s[0];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) s[q] = red[(t & 63) + 64 * q];
+    }
+    float a = (s[0] + s[2]) + (s[1] + s[3]);
+    for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o);
+    return a;   // lane 0
+}
+
+// The gradient of every parameter, finished, and its Adam step (Kingma and Ba)
+// on the FP32 master with its BF16 copies refreshed; with S.grad the gradient
+// goes there instead.  Workgroups: one for the loss and one per output bias (the
+// longest sums, first), a wavefront per hidden bias (sums of dZ), 256 weights
+// each (their K ranges' partials in order).
+constexpr int kWeightBlocks = (kWeights + 255) / 256;
+constexpr int kUpdateBlocks = 1 + MLP_OUT + MLP_HIDDEN + kWeightBlocks;
+
+__global__ __launch_bounds__(256) void mlp_update_kernel(MlpStep S, int parts, float lr, float b1, float b2, float eps,
+                                                         float c1, float c2) {
+    __shared__ float red[256];
+    int l = 0, o = 0, i = -1, p;
+    float gi = 0.0f, m = 0.0f, v = 0.0f, w = 0.0f;
+    int g = (int)blockIdx.x;
+    if (g == 0) {
+        const float s = strided_sum<true>(S.loss, S.n, 1, red);
+        if (threadIdx.x == 0) *S.loss_acc += (double)s * (1.0 / S.n);
+        return;
+    }
+    g -= 1;
+    if (g < MLP_OUT) {
+        p = MLP_HIDDEN * (MLP_IN + 1) + 3 * MLP_HIDDEN * (MLP_HIDDEN + 1) + MLP_OUT * MLP_HIDDEN + g;
+        gi = strided_sum<true>(S.dout + (size_t)g * S.n, S.n, 1, red);
+        if (threadIdx.x) return;
+    } else if ((g -= MLP_OUT) < MLP_HIDDEN) {
+        const int c = 4 * g + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        l = c / MLP_HIDDEN;
+        o = c % MLP_HIDDEN;
+        p = l == 0 ? MLP_HIDDEN * MLP_IN + o
+                   : MLP_HIDDEN * (MLP_IN + 1) + (l - 1) * MLP_HIDDEN * (MLP_HIDDEN + 1) + MLP_HIDDEN * MLP_HIDDEN + o;
+        gi = strided_sum<false>(S.bpart[l] + o, (S.n + 31) / 32, MLP_HIDDEN, red);
+        if (threadIdx.x & 63) return;
+    } else {
+        const int e = (g - MLP_HIDDEN) * 256 + (int)threadIdx.x;
+        if (e >= kWeights) return;
+        p = weight_at(e, l, o, i);
+        float part[kMlpSplit];
+#pragma unroll
+        for (int k = 0; k < kMlpSplit; ++k) part[k] = k < parts ? S.part[(size_t)k * S.np + p] : 0.0f;
+        m = S.m[p];
+        v = S.v[p];
+        w = S.w[p];
+#pragma unroll
+        for (int k = 0; k < kMlpSplit; ++k)
+            if (k < parts) gi += part[k];
+    }
+    if (i < 0) {
+        m = S.m[p];
+        v = S.v[p];
+        w = S.w[p];
+    }
+    if (S.grad) {
+        S.grad[p] = gi;
+        return;
+    }
+    const float mi = b1 * m + (1.0f - b1) * gi;
+    const float vi = b2 * v + (1.0f - b2) * gi * gi;
+    S.m[p] = mi;
+    S.v[p] = vi;
+    const float pi = w - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
+    S.w[p] = pi;
+    const __bf16 pb = (__bf16)pi;
+    S.wb[p] = pb;
+    if (i < 0) return;
+    S.fwd[frag_fwd(l, o, i)] = pb;
+    if (l > 0) S.bwd[frag_bwd(l, o, i)] = pb;
 }
 
 int grid_for(size_t n) { return (int)std::min<size_t>((n + 255) / 256, 4096); }
@@ -415,97 +583,33 @@ int mlp_param_count() {
     return n;
 }
 
-int mlp_param_offset(int layer) {
-    int n = 0;
-    for (int l = 0; l < layer; ++l) n += kDims[l + 1] * kDims[l] + kDims[l + 1];
-    return n;
-}
+size_t mlp_frag_bytes() { return (size_t)(kFwdFrags + kBwdFrags) * kFrag * sizeof(__bf16); }
 
-int mlp_dim(int i) { return kDims[i]; }
-
-// C = A.B over the whole K range.  With `part` (room for kMlpSplit products
-// of M x N) and a product too small to fill the chip, K is split over up to
-// kMlpSplit workgroup layers whose partials are then summed in order.
-static hipError_t mlp_gemm(bool at, bool bt, int epi, const __bf16 *A, int lda, const __bf16 *B, int ldb,
-                           const float *bias, const float *aux, float *C, int ldc, __bf16 *Cb, int ldcb, int M, int N,
-                           int K, float *part, hipStream_t s) {
-    const int tiles = ((N + kGT - 1) / kGT) * ((M + kGT - 1) / kGT);
-    int split = 1;
-    if (part && epi == EPI_F32 && !bias && ldc == N && K >= 4 * kGK)
-        split = std::max(1, std::min({kMlpSplit, 256 / tiles, K / (2 * kGK)}));
-    const int kchunk = split > 1 ? ((K + split - 1) / split + kGK - 1) / kGK * kGK : K;
-    split = (K + kchunk - 1) / kchunk;
-    float *dst = split > 1 ? part : C;
-    const int ldd = split > 1 ? N : ldc;
-    const size_t czs = (size_t)M * N;
-    dim3 grid((N + kGT - 1) / kGT, (M + kGT - 1) / kGT, split), block(256);
-#define VPMC_GEMM(AT_, BT_, E_)                                                                                   \
-    hipLaunchKernelGGL((gemm_bf16_kernel<AT_, BT_, E_>), grid, block, 0, s, A, lda, B, ldb, bias, aux, dst, ldd, \
-                       czs, Cb, ldcb, M, N, K, kchunk)
-    if (!at && bt && epi == EPI_SILU) VPMC_GEMM(false, true, EPI_SILU);
-    else if (!at && bt && epi == EPI_F32) VPMC_GEMM(false, true, EPI_F32);
-    else if (!at && !bt && epi == EPI_DSILU) VPMC_GEMM(false, false, EPI_DSILU);
-    else if (at && !bt && epi == EPI_F32) VPMC_GEMM(true, false, EPI_F32);
-    else return hipErrorInvalidValue;
-#undef VPMC_GEMM
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || split == 1) return e;
-    hipLaunchKernelGGL(sum_parts_kernel, dim3(grid_for(czs)), dim3(256), 0, s, part, split, czs, czs, C);
+hipError_t mlp_pack(const MlpStep &S, hipStream_t s) {
+    // the fragments' places past the inputs and outputs hold zeros
+    hipError_t e = launch_fill_u64((unsigned long long *)S.fwd, mlp_frag_bytes() / 8, 0ull, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(mlp_pack_kernel, dim3(grid_for(kWeights)), dim3(256), 0, s, S.wb, S.fwd, S.bwd);
     return hipGetLastError();
 }
 
-hipError_t mlp_forward(const MlpBuffers &b, int n, hipStream_t s) {
-    // layer inputs: X (BF16 n x 8), H1..H4 (BF16 n x 256); pre-activations Z1..Z4 and OUT (FP32)
-    hipError_t e = hipSuccess;
-    for (int l = 0; l < MLP_LAYERS && e == hipSuccess; ++l) {
-        const int ni = kDims[l], no = kDims[l + 1];
-        const __bf16 *in = l == 0 ? b.x : b.h[l - 1];
-        const __bf16 *W = b.wb + mlp_param_offset(l);
-        const float *bias = b.w + mlp_param_offset(l) + no * ni;
-        const bool last = l == MLP_LAYERS - 1;
-        e = mlp_gemm(false, true, last ? EPI_F32 : EPI_SILU, in, ni, W, ni, bias, nullptr, last ? b.out : b.z[l], no,
-                     last ? nullptr : b.h[l], no, n, no, ni, nullptr, s);
-    }
-    return e;
+// K ranges of the weight gradients: up to kMlpSplit of at least 128 samples
+static int wgrad_split(int n, int *kchunk) {
+    const int split = n >= 256 ? std::max(1, std::min(kMlpSplit, n / 128)) : 1;
+    *kchunk = split > 1 ? ((n + split - 1) / split + 63) / 64 * 64 : (n + 63) / 64 * 64;
+    return (n + *kchunk - 1) / *kchunk;
 }
 
-hipError_t mlp_loss_grad(const MlpBuffers &b, const float *y, const float *trans, int n, float *grad,
-                         double *loss_acc, hipStream_t s) {
-    hipError_t e = mlp_forward(b, n, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(loss_head_kernel, dim3((n + 255) / 256), dim3(256), 0, s, b.out, y, trans, n, 1.0f / n,
-                       b.dout, b.dout_b, b.loss);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(reduce_sum_kernel, dim3(1), dim3(256), 0, s, b.loss, n, 1.0 / n, loss_acc);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // backward through the layers; dZ of the current layer in BF16 (dcur, row
-    // pitch ldd) and its bias gradient from FP32 values
-    const __bf16 *dcur = b.dout_b;
-    int ldd = MLP_OUT_LD;
-    for (int l = MLP_LAYERS - 1; l >= 0; --l) {
-        const int ni = kDims[l], no = kDims[l + 1];
-        const __bf16 *in = l == 0 ? b.x : b.h[l - 1];
-        float *gW = grad + mlp_param_offset(l), *gb = gW + no * ni;
-        // dW = dZ^T . H_in   (M = no, N = ni, K = n)
-        if ((e = mlp_gemm(true, false, EPI_F32, dcur, ldd, in, ni, nullptr, nullptr, gW, ni, nullptr, 0, no, ni, n,
-                          b.wpart, s)) != hipSuccess)
-            return e;
-        if (l == MLP_LAYERS - 1)   // output layer: column sums of the FP32 dOUT
-            hipLaunchKernelGGL(colsum_kernel, dim3(no), dim3(256), 0, s, b.dout, n, no, gb);
-        else                       // 32-row partial sums left by the dZ epilogue
-            hipLaunchKernelGGL(colsum_kernel, dim3(no), dim3(256), 0, s, b.bpart, (n + 31) / 32, no, gb);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (l == 0) break;
-        // dZ_in = (dZ . W) * silu'(Z_in)   (M = n, N = ni, K = no)
-        const __bf16 *W = b.wb + mlp_param_offset(l);
-        __bf16 *dzb = (l & 1) ? b.dzb_a : b.dzb_b;
-        if ((e = mlp_gemm(false, false, EPI_DSILU, dcur, ldd, W, ni, nullptr, b.z[l - 1], b.bpart, ni, dzb, ni, n,
-                          ni, no, nullptr, s)) != hipSuccess)
-            return e;
-        dcur = dzb;
-        ldd = ni;
-    }
-    return hipSuccess;
+hipError_t mlp_step(const MlpStep &S, float lr, int step, hipStream_t s) {
+    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
+    const float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
+    int kchunk;
+    const int split = wgrad_split(S.n, &kchunk);
+    hipLaunchKernelGGL(mlp_chain_kernel, dim3((S.n + 31) / 32), dim3(512), 0, s, S);
+    hipLaunchKernelGGL(mlp_wgrad_kernel, dim3(52 * split), dim3(256), 0, s, S, kchunk, split);
+    hipLaunchKernelGGL(mlp_update_kernel, dim3(kUpdateBlocks), dim3(256), 0, s, S, split, lr, b1, b2, eps,
+                       c1, c2);
+    return hipGetLastError();
 }
 
 hipError_t mlp_infer(const float *x, const DeferRec *rec, int n, const __bf16 *wb, const float *wf, float *out,
@@ -517,22 +621,8 @@ hipError_t mlp_infer(const float *x, const DeferRec *rec, int n, const __bf16 *w
     return hipGetLastError();
 }
 
-hipError_t mlp_gather(const float *x, const int *idx, int n, int cols, __bf16 *xb, float *xf, hipStream_t s) {
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(grid_for((size_t)n * cols)), dim3(256), 0, s, x, idx, n, cols, xb, xf);
-    return hipGetLastError();
-}
-
 hipError_t mlp_to_bf16(const float *x, __bf16 *y, size_t n, hipStream_t s) {
     hipLaunchKernelGGL(to_bf16_kernel, dim3(grid_for(n)), dim3(256), 0, s, x, y, n);
-    return hipGetLastError();
-}
-
-hipError_t mlp_adam(float *p, const float *g, float *m, float *v, __bf16 *pb, int np, float lr, int step,
-                    hipStream_t s) {
-    const float b1 = 0.9f, b2 = 0.999f, eps = 1e-8f;
-    const float c1 = 1.0f - powf(b1, (float)step), c2 = 1.0f - powf(b2, (float)step);
-    hipLaunchKernelGGL(adam_kernel, dim3(grid_for((size_t)np)), dim3(256), 0, s, p, g, m, v, pb, np, lr, b1, b2, eps,
-                       c1, c2);
     return hipGetLastError();
 }
 
