@@ -2352,16 +2352,15 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
     O.row_stride = n_spots;
     O.row_offset = 0;
     auto set_buckets = [](OptDev &D, const vpmc_ctx::OptBuckets &B) {
-        D.boff = (const unsigned long long *)B.off.ptr;
         D.bkey = (const uint32_t *)B.key.ptr;
         D.bval = (const float *)B.val.ptr;
-        D.work = (const uint32_t *)B.work.ptr;
+        D.work = (const OptWork *)B.work.ptr;
         D.n_work = B.n_work;
     };
     // bucketed copy of the rows of D: lists (scenario, chunk), heaviest first
     // in the work list
     std::vector<unsigned long long> boff;
-    std::vector<uint32_t> work;
+    std::vector<OptWork> work;
     auto build_buckets = [&](OptDev &D, vpmc_ctx::OptBuckets &B, long long expect) -> int {
         B.valid = false;
         int rc2;
@@ -2369,7 +2368,7 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
         if ((rc2 = ensure(c, c->opt_cnt, std::max<size_t>(nlist, 1) * 8, 0))) return rc2;
         if ((rc2 = ensure(c, c->opt_fpart, std::max<size_t>(nlist, 1) * 8, 0))) return rc2;
         if ((rc2 = ensure(c, B.off, (nlist + 1) * 8, 0))) return rc2;
-        if ((rc2 = ensure(c, B.work, std::max<size_t>(nlist, 1) * 4, 0))) return rc2;
+        if ((rc2 = ensure(c, B.work, std::max<size_t>(nlist, 1) * sizeof(OptWork), 0))) return rc2;
         if ((rc2 = ensure(c, B.key, (size_t)std::max(expect, 1ll) * 4, 0))) return rc2;
         if ((rc2 = ensure(c, B.val, (size_t)std::max(expect, 1ll) * 4, 0))) return rc2;
         HIP_TRY(hipMemsetAsync(c->opt_cnt.ptr, 0, nlist * 8, st));
@@ -2385,11 +2384,11 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
             return fail(VPMC_E_DEVICE, "entry count %llu of the chunk lists differs from the rows' %lld", boff[nlist],
                         expect);
         work.resize(nlist);
-        for (size_t k = 0; k < nlist; ++k) work[k] = (uint32_t)k;
-        std::stable_sort(work.begin(), work.end(), [&](uint32_t a, uint32_t b) {
-            return boff[a + 1] - boff[a] > boff[b + 1] - boff[b];
-        });
-        if (nlist) HIP_TRY(hipMemcpyAsync(B.work.ptr, work.data(), nlist * 4, hipMemcpyHostToDevice, st));
+        for (size_t k = 0; k < nlist; ++k)
+            work[k] = OptWork{(long long)boff[k], (long long)(boff[k + 1] - boff[k]), (uint32_t)k};
+        std::stable_sort(work.begin(), work.end(), [](const OptWork &a, const OptWork &b) { return a.len > b.len; });
+        if (nlist)
+            HIP_TRY(hipMemcpyAsync(B.work.ptr, work.data(), nlist * sizeof(OptWork), hipMemcpyHostToDevice, st));
         B.n_work = (long long)nlist;
         B.valid = true;
         return VPMC_OK;
@@ -2422,20 +2421,23 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
         HIP_TRY(hipStreamSynchronize(st));
         if (err & 1u) return fail(VPMC_E_ARG, "a column index is outside [0, nvox)");
         if (err & 2u) return fail(VPMC_E_ARG, "a value is not finite");
-        // structure-restricted CSR and its pieces of at most kOptPiece entries
+        // structure-restricted CSR and its pieces
         crp.resize((size_t)n_rows + 1);
         poff.resize((size_t)n_rows + 1);
         crp[0] = 0;
         for (size_t r = 0; r < (size_t)n_rows; ++r) {
-            long long n = 0;
-            for (int w = 0; w < kRoiParts; ++w) n += rcnt[r * kRoiParts + w];
-            crp[r + 1] = crp[r] + n;
+            crp[r + 1] = crp[r];
+            for (int w = 0; w < kRoiParts; ++w) crp[r + 1] += rcnt[r * kRoiParts + w];
+        }
+        const long long kept = crp[(size_t)n_rows];
+        int piece = kOptMaxPiece;
+        while (piece > kOptMinPiece && kept / piece < kOptWaves) piece /= 2;
+        for (size_t r = 0; r < (size_t)n_rows; ++r) {
             poff[r] = (long long)pieces.size();
-            for (long long q = crp[r]; q < crp[r + 1]; q += kOptPiece)
-                pieces.push_back(OptPiece{q, (int)std::min<long long>(kOptPiece, crp[r + 1] - q), (int)r});
+            for (long long q = crp[r]; q < crp[r + 1]; q += piece)
+                pieces.push_back(OptPiece{q, (int)std::min<long long>(piece, crp[r + 1] - q), (int)r});
         }
         poff[(size_t)n_rows] = (long long)pieces.size();
-        const long long kept = crp[(size_t)n_rows];
         int bits = kOptMaxBits;
         while (bits > kOptMinBits && (long long)n_scen * (((long long)ns + (1 << bits) - 1) >> bits) < kOptLists) --bits;
         if ((rc = ensure(c, c->opt_ccol, (size_t)std::max(kept, 1ll) * 4, 0))) return rc;

@@ -359,9 +359,12 @@ constexpr long long kOptLists = 768;
 enum { kOptPowerInit, kOptPower, kOptPowerNorm, kOptFistaInit, kOptFista, kOptFinalPrep, kOptFinal };
 enum { kOptLam = 0, kOptL = 1 };   // device scalars
 
-// Entries per gradient wavefront: four steps of 256 (4096 made the longest
-// rows a chain of 16 steps, 29 us for 7.3 M entries).
-constexpr int kOptPiece = 1024;
+// Entries per gradient wavefront: the largest of 256 .. 1024 that leaves
+// kOptWaves wavefronts.  Long pieces are chains of loads (4096 entries: 29 us for
+// 7.3 M, 1024: 20, 512: 18; 38 000 entries: 5.6 us at 1024, 4.2 at 256), short
+// ones more partials for the update to add.
+constexpr int kOptMinPiece = 256, kOptMaxPiece = 1024;
+constexpr long long kOptWaves = 8192;
 constexpr int kRoiParts = 8;       // wavefronts of a row in the passes that restrict the rows
 constexpr int kOptParts = 512;     // workgroups of the update at most
 
@@ -371,11 +374,17 @@ struct OptMask {
     uint32_t before, pad;
 };
 
-// at most kOptPiece consecutive entries of one row
+// consecutive entries of one row
 struct OptPiece {
     long long begin;   // first entry (CSR index)
     int len;
     int row;           // compact row s * n_spots + j
+};
+
+// a list of the forward sweep: scenario * chunks + chunk, its entries
+struct OptWork {
+    long long begin, len;
+    uint32_t list;
 };
 
 struct OptDev {
@@ -386,12 +395,10 @@ struct OptDev {
     int n_scen, n_spots, row_stride, row_offset;
     int nvox, nchunks, bits;        // voxels (of the iterations: structure voxels), chunks of 2^bits
     double d_presc, w_target, d_max, w_oar;
-    // chunk-bucketed copy of the entries: list (s, chunk) holds entries
-    // boff[list] .. boff[list + 1], key = spot << bits | voxel - chunk base
-    const unsigned long long *boff; // [n_scen * nchunks + 1]
+    // chunk-bucketed copy of the entries by list (s, chunk): key = spot << bits | voxel - chunk base
     const uint32_t *bkey;
     const float *bval;
-    const uint32_t *work;           // [n_work] lists to sweep, in decreasing entry count
+    const OptWork *work;            // [n_work] lists to sweep, in decreasing entry count
     long long n_work;
     const OptPiece *piece;          // gradient pieces, row-major
     long long n_pieces;

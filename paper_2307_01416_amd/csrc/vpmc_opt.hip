@@ -372,8 +372,8 @@ __device__ __forceinline__ int scale_exp(double bnd) {
 __global__ void __launch_bounds__(kFwdThreads) opt_forward_kernel(OptDev O, const double *w, int mode, float *dose_out) {
     __shared__ unsigned long long acc[1 << kOptMaxBits];
     __shared__ double red[kFwdThreads / 64];
-    const unsigned item = O.work[blockIdx.x];
-    const int s = (int)(item / (unsigned)O.nchunks), c = (int)(item - (unsigned)s * O.nchunks);
+    const OptWork item = O.work[blockIdx.x];
+    const int s = (int)(item.list / (unsigned)O.nchunks), c = (int)(item.list - (unsigned)s * O.nchunks);
     const int chunk = 1 << O.bits;
     const long long base = (long long)c << O.bits;
     const int nv = (int)(O.nvox - base < chunk ? O.nvox - base : chunk);
@@ -384,8 +384,7 @@ __global__ void __launch_bounds__(kFwdThreads) opt_forward_kernel(OptDev O, cons
     bnd = block_sum<kFwdThreads>(bnd, red);
     const int m2 = scale_exp(bnd);
     const double sc = ldexp(1.0, m2), isc = ldexp(1.0, -m2);
-    const size_t list = (size_t)s * O.nchunks + c;
-    const long long e0 = (long long)O.boff[list], e1 = (long long)O.boff[list + 1];
+    const long long e0 = item.begin, e1 = item.begin + item.len;
     const uint32_t *bk = O.bkey;
     const float *bv = O.bval;
     const uint32_t low = (uint32_t)chunk - 1u;
@@ -407,11 +406,22 @@ __global__ void __launch_bounds__(kFwdThreads) opt_forward_kernel(OptDev O, cons
             }
         }
     }
-    for (; e < e1; e += kFwdThreads) {
-        const uint32_t k = bk[e], j = k >> O.bits;
-        if (j < (uint32_t)O.n_spots) {
-            const double t = rint(w[j] * sc * (double)bv[e]);
-            atomicAdd(&acc[k & low], (unsigned long long)(long long)t);
+    if (e < e1) {   // the rest in one step, not one load after the other
+        uint32_t k[3];
+        float a[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const bool in = e + u * kFwdThreads < e1;
+            k[u] = in ? bk[e + u * kFwdThreads] : ~0u;
+            a[u] = in ? bv[e + u * kFwdThreads] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const uint32_t j = k[u] >> O.bits;
+            if (e + u * kFwdThreads < e1 && j < (uint32_t)O.n_spots) {
+                const double t = rint(w[j] * sc * (double)a[u]);
+                atomicAdd(&acc[k[u] & low], (unsigned long long)(long long)t);
+            }
         }
     }
     __syncthreads();
@@ -445,7 +455,7 @@ __global__ void __launch_bounds__(kFwdThreads) opt_forward_kernel(OptDev O, cons
     if (threadIdx.x == 0) O.fpart[blockIdx.x] = f;
 }
 
-// Gradient sweep: a wavefront per piece (at most kOptPiece consecutive
+// Gradient sweep: a wavefront per piece (at most kOptMaxPiece consecutive
 // entries of one row), FP64 products of FP32 values (exact) summed per lane
 // in entry order, then over lanes by a fixed butterfly; pieces of a row are
 // summed in order by the update.
@@ -478,24 +488,38 @@ __global__ void __launch_bounds__(kOptThreads) opt_grad_kernel(OptDev O) {
         a2 = fma((double)v[2], (double)rr[2], a2);
         a3 = fma((double)v[3], (double)rr[3], a3);
     }
-    for (; i < e; i += 64) {
-        const int c0 = O.col[i];
-        const float r0 = (unsigned)c0 < (unsigned)O.nvox ? res[c0] : 0.0f;
-        a0 = fma((double)O.val[i], (double)r0, a0);
+    if (i < e) {   // the rest in one step, not one load after the other
+        int c[3];
+        float v[3], rr[3];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) {
+            const bool in = i + 64 * u < e;
+            c[u] = in ? O.col[i + 64 * u] : -1;
+            v[u] = in ? O.val[i + 64 * u] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u) rr[u] = (unsigned)c[u] < (unsigned)O.nvox ? res[c[u]] : 0.0f;
+        a0 = fma((double)v[0], (double)rr[0], a0);
+        a1 = fma((double)v[1], (double)rr[1], a1);
+        a2 = fma((double)v[2], (double)rr[2], a2);
     }
     double a = (a0 + a1) + (a2 + a3);
     for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o);
     if (lane == 0) O.gpart[p] = a;
 }
 
-// sum over scenarios of A_s[j,:] r_s by one wavefront: a lane per row sums the
-// row's pieces in order, a fixed butterfly the lanes
+// Sum over scenarios of A_s[j,:] r_s by one wavefront, the same in every lane:
+// 64 >> shift lanes' groups of 2^shift take a row each, their lanes every
+// 2^shift-th of its pieces, and a fixed butterfly sums the lanes.
 __device__ double row_gradient(const OptDev &O, int j) {
+    const int shift = O.n_scen <= 4 ? 4 : O.n_scen <= 16 ? 2 : 0;
+    const int lane = lane_id();
     double g = 0.0;
-    for (int s = lane_id(); s < O.n_scen; s += 64) {
+    for (int s = lane >> shift; s < O.n_scen; s += 64 >> shift) {
         const size_t r = (size_t)s * O.n_spots + j;
         const long long p1 = O.piece_off[r + 1];
-        for (long long p = O.piece_off[r]; p < p1; ++p) g += O.gpart[p];
+#pragma unroll 4
+        for (long long p = O.piece_off[r] + (lane & ((1 << shift) - 1)); p < p1; p += 1 << shift) g += O.gpart[p];
     }
     for (int o = 32; o > 0; o >>= 1) g += __shfl_xor(g, o);
     return g;
@@ -563,37 +587,42 @@ __global__ void __launch_bounds__(kOptThreads) opt_update_kernel(OptDev O, int m
     }
     if (mode == kOptFistaInit && blockIdx.x == 0 && threadIdx.x == 0) O.scal[kOptL] = 1.05 * O.scal[kOptLam];
     const double L = mode == kOptFista ? O.scal[kOptL] : 0.0;
-    for (int j = j0; j < n; j += dj) {
-        const double g = mode == kOptFista ? row_gradient(O, j) * g_scale : 0.0;
-        if (lane) continue;
-        if (mode == kOptPowerInit) O.z[j] = 1.0;
-        if (mode == kOptPowerNorm && gn > 0.0) O.z[j] = O.gvec[j] / gn;
-        if (mode == kOptFistaInit) {
-            const double x = O.x[j] > 0.0 ? O.x[j] : 0.0;
-            O.x[j] = x;
-            O.y[j] = x;
-        }
+    double bnd = 0.0;   // of scenario `lane`
+    for (int j = j0; j < n; j += dj) {   // every lane has the spot's values
+        const double am = lane < O.n_scen ? (double)O.amax[(size_t)lane * n + j] : 0.0;
+        const double x = O.x[j], y = O.y[j];
+        double wj = x;
+        if (mode == kOptPowerInit) wj = 1.0;
+        if (mode == kOptPowerNorm) wj = gn > 0.0 ? O.gvec[j] / gn : O.z[j];
+        if (mode == kOptFistaInit) wj = x > 0.0 ? x : 0.0;
         if (mode == kOptFista) {
-            double xn = L > 0.0 ? O.y[j] - g / L : O.y[j];
+            const double g = row_gradient(O, j) * g_scale;
+            double xn = L > 0.0 ? y - g / L : y;
             xn = xn > 0.0 ? xn : 0.0;
-            O.y[j] = xn + beta * (xn - O.x[j]);
-            O.x[j] = xn;
+            wj = xn + beta * (xn - x);
+            if (lane == 0) O.x[j] = xn;
         }
+        if (lane == 0) {
+            if (mode == kOptPowerInit || mode == kOptPowerNorm) O.z[j] = wj;
+            if (mode == kOptFistaInit) O.x[j] = wj;
+            if (mode == kOptFistaInit || mode == kOptFista) O.y[j] = wj;
+        }
+        bnd += fabs(wj) * am;
     }
-    __syncthreads();   // the other lanes read what lane 0 wrote
-    for (int s0 = 0; s0 < O.n_scen; s0 += 64) {
+    __shared__ double wb[kOptThreads / 64][64];
+    for (int s0 = 0;;) {
         const int s = s0 + lane;
-        double bnd = 0.0;
-        if (s < O.n_scen)
-            for (int j = j0; j < n; j += dj) bnd += fabs(w[j]) * (double)O.amax[(size_t)s * n + j];
-        __shared__ double wb[kOptThreads / 64][64];
         wb[wave][lane] = bnd;
-        __syncthreads();
+        __syncthreads();   // also: the other lanes may read what lane 0 wrote
         if (wave == 0 && s < O.n_scen) {
             for (int q = 1; q < kOptThreads / 64; ++q) bnd += wb[q][lane];
             O.bpart[(size_t)s * O.n_part + blockIdx.x] = bnd;
         }
+        if ((s0 += 64) >= O.n_scen) break;
         __syncthreads();
+        bnd = 0.0;
+        if (s0 + lane < O.n_scen)
+            for (int j = j0; j < n; j += dj) bnd += fabs(w[j]) * (double)O.amax[(size_t)(s0 + lane) * n + j];
     }
 }
 
