@@ -2098,7 +2098,7 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
         acc.steps = acc.hist = 0;
         Lane v;
         v.k0 = Q.key0;
-        v.k1 = Q.seed_hi ^ row.field_id;
+        v.k1 = __builtin_amdgcn_readfirstlane(Q.seed_hi ^ row.field_id);
         v.spot = row.spot;
         v.physics = Q.physics;
         bool active = false;
@@ -2131,6 +2131,10 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
                 active = true;
             }
             if (refill) next = min(end, next + nidle);
+            // (opaque here: the round keys are made from these by scalar adds
+            // in each step; hoisted out of the loop they overflow the scalar
+            // registers and come back as 32 v_readlane a step)
+            asm volatile("" : "+s"(v.k0), "+s"(v.k1));
             if (active) {
                 active = patient_step<TileSink<!DENSE, LET>, X, P>(v, acc, scale, T, g, sc.range_scale, sink, ps);
                 if (!active) acc.steps += v.nsteps;
