@@ -1537,8 +1537,12 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
         std::vector<Round> rounds;
     };
     std::vector<Part> parts;
-    const size_t grids = std::max<size_t>(1, kBatchGridBytes / (nvox * 8));
-    if (B == 1) {
+    // grids that the folds read: of batches, and with LET of any run (dose and
+    // LET numerator side by side)
+    const size_t grid_bytes = nvox * (want_let ? 16 : 8);
+    const bool folded = B > 1 || want_let;
+    const size_t grids = std::max<size_t>(1, kBatchGridBytes / grid_bytes);
+    if (!folded) {
         parts.push_back({0, n_scen, 0, 1, {}, {}, {}});
     } else if (grids >= (size_t)B) {
         const int ns = (int)std::min<size_t>((size_t)n_scen, grids / (size_t)B);
@@ -1575,7 +1579,7 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
         max_rows = std::max(max_rows, p.rows.size());
         n_grids = std::max(n_grids, (size_t)(p.s1 - p.s0) * (size_t)(p.b1 - p.b0));
     }
-    const bool whole = B > 1 && parts.front().b1 == B;   // every batch of a scenario in one launch
+    const bool whole = folded && parts.front().b1 == B;   // every batch of a scenario in one launch
     // device buffers
     unsigned long long stage_n = 0;
     if ((rc = stage_buffer(c, max_groups, queue_stage_min(shape.blocks, shape.threads, 1), 0, &stage_n))) return rc;
@@ -1604,9 +1608,9 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
         (!dev_out && dose_gy && (rc = ensure(c, c->stage_dose, nvox * 4, 0))) ||
         (!dev_out && sigma_gy && (rc = ensure(c, c->stage_sigma, nvox * 4, 0))))
         return rc;
-    if (B > 1) {
+    if (folded) {
         const size_t had = c->qbatch.cap;
-        if ((rc = ensure(c, c->qbatch, n_grids * nvox * 8, 0))) return rc;
+        if ((rc = ensure(c, c->qbatch, n_grids * grid_bytes, 0))) return rc;
         if (c->qbatch.cap != had) c->qbatch_zero = 0;
         if (!whole && (rc = ensure(c, c->s2, nvox * 8, 0))) return rc;
     }
@@ -1631,10 +1635,10 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
     HIP_TRY(hipMemsetAsync(c->flags.ptr, 0, 8, st));
     // tallies: written whole by the fold of all batches, else summed into
     if (!whole) HIP_TRY(hipMemsetAsync(c->tallies.ptr, 0, (size_t)n_scen * nvox * 8, st));
-    if (want_let) HIP_TRY(hipMemsetAsync(c->let_tallies.ptr, 0, (size_t)n_scen * nvox * 8, st));
-    if (B > 1) {
-        // the batch grids are left zero by the folds
-        if (c->qbatch_zero < n_grids * nvox * 8) HIP_TRY(hipMemsetAsync(c->qbatch.ptr, 0, n_grids * nvox * 8, st));
+    if (want_let && !whole) HIP_TRY(hipMemsetAsync(c->let_tallies.ptr, 0, (size_t)n_scen * nvox * 8, st));
+    if (folded) {
+        // the folds leave their grids zero
+        if (c->qbatch_zero < n_grids * grid_bytes) HIP_TRY(hipMemsetAsync(c->qbatch.ptr, 0, n_grids * grid_bytes, st));
         c->qbatch_zero = 0;   // (known again once every batch is folded)
     }
 
@@ -1651,7 +1655,7 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
     Q.n_batches = B;
     Q.item_off = (const unsigned long long *)c->offsets.ptr;
     Q.spot_order = (const uint32_t *)c->spot_order.ptr;
-    Q.let = want_let ? (unsigned long long *)c->let_tallies.ptr : nullptr;
+    Q.let = want_let ? 1 : 0;
     Q.fields = (const FieldDev *)c->fields_tab.ptr;
     Q.poly_off = (const int *)c->poly_off.ptr;
     Q.polys = (const float2 *)c->polys.ptr;
@@ -1675,7 +1679,7 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
     for (size_t pi = 0; pi < parts.size(); ++pi) {
         const Part &p = parts[pi];
         long long *const tally0 = (long long *)c->tallies.ptr + (size_t)p.s0 * nvox;
-        Q.grid = B > 1 ? (unsigned long long *)c->qbatch.ptr : (unsigned long long *)tally0;
+        Q.grid = folded ? (unsigned long long *)c->qbatch.ptr : (unsigned long long *)tally0;
         if (B > 1 && !whole && p.b0 == 0) HIP_TRY(hipMemsetAsync(c->s2.ptr, 0, nvox * 8, st));
         HIP_TRY(hipEventRecord(c->events[2 + 2 * pi], st));
         if (!p.rows.empty()) {
@@ -1691,11 +1695,13 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
             long long *tally = (long long *)c->tallies.ptr + (size_t)s * nvox;
             float *dd = dose_gy ? (dev_out ? dose_gy + (size_t)s * nvox : (float *)c->stage_dose.ptr) : nullptr;
             float *ss = sigma_gy ? (dev_out ? sigma_gy + (size_t)s * nvox : (float *)c->stage_sigma.ptr) : nullptr;
-            unsigned long long *qb = (unsigned long long *)c->qbatch.ptr + (size_t)(s - p.s0) * (size_t)(p.b1 - p.b0) * nvox;
+            unsigned long long *qb = (unsigned long long *)c->qbatch.ptr +
+                                     (size_t)(s - p.s0) * (size_t)(p.b1 - p.b0) * (grid_bytes / 8);
+            long long *let = want_let ? (long long *)c->let_tallies.ptr + (size_t)s * nvox : nullptr;
             if (whole) {
-                HIP_TRY(launch_fold_dose(qb, B, tally, c->geom, mev_scale, dd, ss, nvox, st));
+                HIP_TRY(launch_fold_dose(qb, B, tally, let, c->geom, mev_scale, dd, ss, nvox, st));
             } else {
-                if (B > 1) HIP_TRY(launch_fold_batch(qb, p.b1 - p.b0, tally, (double *)c->s2.ptr, nvox, st));
+                if (folded) HIP_TRY(launch_fold_batch(qb, p.b1 - p.b0, tally, (double *)c->s2.ptr, let, nvox, st));
                 if (p.b1 < B) continue;   // more batches of this scenario to come
                 if (dd || ss)
                     HIP_TRY(launch_dose(tally, B > 1 ? (const double *)c->s2.ptr : nullptr, B, c->geom, mev_scale, dd,
@@ -1713,7 +1719,7 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
     HIP_TRY(hipMemcpyAsync(stv, c->stats.ptr, sizeof stv, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipEventRecord(c->events[1], st));
     HIP_TRY(hipStreamSynchronize(st));
-    if (B > 1) c->qbatch_zero = n_grids * nvox * 8;
+    if (folded) c->qbatch_zero = n_grids * grid_bytes;
     vpmc_stats S{};
     float ms = 0.0f;
     for (size_t i = 0; i < parts.size(); ++i) {
@@ -1902,7 +1908,7 @@ int vpmc_run_spots(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spot
             HIP_TRY(hipEventRecord(c->events[3 + 2 * n_launch], st));
             ++n_launch;
             if (B > 1)
-                HIP_TRY(launch_fold_batch((unsigned long long *)c->qbatch.ptr, 1, tally, (double *)c->s2.ptr, nvox, st));
+                HIP_TRY(launch_fold_batch((unsigned long long *)c->qbatch.ptr, 1, tally, (double *)c->s2.ptr, nullptr, nvox, st));
         }
         float *dd = dose_gy ? (dev_out ? dose_gy + (size_t)sc * nvox : (float *)c->stage_dose.ptr) : nullptr;
         float *ss = sigma_gy ? (dev_out ? sigma_gy + (size_t)sc * nvox : (float *)c->stage_sigma.ptr) : nullptr;
@@ -2012,7 +2018,7 @@ int vpmc_run_spots_noalloc(vpmc_ctx *c, int field_id, const vpmc_spot *spots, in
                                        items, b, B, B > 1 ? qb : (unsigned long long *)tally, nullptr,
                                        led_d + (size_t)sc * NLEDGER, stats_d, c->d_tables);
             HIP_TRY(launch_transport(c->geom, fd, L, dense_blocks(c, o, items, threads), threads, st));
-            if (B > 1) HIP_TRY(launch_fold_batch(qb, 1, tally, s2, nvox, st));
+            if (B > 1) HIP_TRY(launch_fold_batch(qb, 1, tally, s2, nullptr, nvox, st));
         }
         float *dd = dose_gy ? dose_gy + (size_t)sc * nvox : nullptr;
         float *ss = sigma_gy ? sigma_gy + (size_t)sc * nvox : nullptr;

@@ -219,7 +219,7 @@ struct QueueDev {
     int dense, n_spots, n_batches;
     const unsigned long long *item_off;
     const uint32_t *spot_order;
-    unsigned long long *let;              // [n_scen][gstride] LET numerators, or null
+    int let;                              // dense grids hold (dose, LET numerator) pairs
     const FieldDev *fields;
     const int *poly_off;                  // per field: offset into polys
     const float2 *polys;
@@ -433,9 +433,9 @@ hipError_t opt_update(const OptDev &O, int mode, double beta, int it, double *hi
 // launchers (vpmc_kernels.hip)
 hipError_t launch_transport(const GeomDev &g, const FieldDev &f, const LaunchDev &L, int blocks,
                             int threads, hipStream_t s);
-hipError_t launch_fold_batch(unsigned long long *q_batch, int nb, long long *q_total, double *s2, size_t n,
+hipError_t launch_fold_batch(unsigned long long *q_batch, int nb, long long *q_total, double *s2, long long *let, size_t n,
                              hipStream_t s);
-hipError_t launch_fold_dose(unsigned long long *q_batch, int n_batches, long long *q_total, const GeomDev &g,
+hipError_t launch_fold_dose(unsigned long long *q_batch, int n_batches, long long *q_total, long long *let, const GeomDev &g,
                             double mev_scale, float *dose, float *sigma, size_t n, hipStream_t s);
 hipError_t launch_dose(const long long *q, const double *s2, int n_batches, const GeomDev &g,
                        double mev_scale, float *dose, float *sigma, size_t n, hipStream_t s);
