@@ -85,6 +85,7 @@ struct vpmc_ctx {
     DevBuf tallies, qbatch, s2, ledger, spots, offsets, stage_dose, stage_sigma, stats, let_tallies;
     bool last_let = false;   // the last dense run tallied the LET numerator
     size_t qbatch_zero = 0;  // leading bytes of qbatch known to be zero
+    bool uncapped = false;   // a run without a cap on device memory has grown its scratch
     DevBuf spot_order;
     size_t bytes = 0;
     // last run
@@ -367,7 +368,23 @@ int stage_buffer(vpmc_ctx *c, unsigned long long groups, unsigned long long stag
         n = std::max(stage_min, n / 2 / 64 * 64);
     }
     *stage_n = n;
+    c->uncapped = c->uncapped || !cap;
     return rc;
+}
+
+// Before a run with a cap on device memory: scratch that runs without one grew
+// for their speed alone (staging, queue tables, grids of batches) does not
+// count against it.
+int trim_scratch(vpmc_ctx *c) {
+    if (!c->uncapped) return VPMC_OK;
+    for (DevBuf *b : {&c->q_stage, &c->q_ctl, &c->rows, &c->grp_off, &c->heads, &c->spot_order, &c->qbatch}) {
+        if (b->ptr) HIP_TRY(hipFree(b->ptr));
+        c->bytes -= b->cap;
+        *b = DevBuf{};
+    }
+    c->qbatch_zero = 0;
+    c->uncapped = false;
+    return VPMC_OK;
 }
 
 // Beam line, tile boxes and patient transport of one round (Q: of its rows'
@@ -398,6 +415,10 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     const size_t nvox = c->nvox;
     const bool dev_out = (o->flags & VPMC_DEVICE_PTRS) != 0;
     const size_t cap = o->max_device_bytes;
+    if (cap) {
+        const int trc = trim_scratch(c);
+        if (trc) return trc;
+    }
     hipStream_t st = (hipStream_t)o->hip_stream;
     // histories per lane: the caller's, else the one tuned for a field, else
     // the last tuned one, else 1 (per epoch: the field with most of its rows)
@@ -1804,12 +1825,13 @@ int vpmc_run_spots(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spot
     // scratch): those run batch by batch, one history per lane at a time.
     // Batch by batch / through the queue, 16 batches: pencil beam of 1e5
     // histories in 2 mm water 3.1 / 0.50 ms, water layer of 1e7 45.9 / 13.5 ms,
-    // head field of 9.5e6 49.2 / 17.7 ms; LET, 3 scenarios of 2.9e6: 87 / 44 ms.
+    // head field of 9.5e6 49.2 / 17.4 ms; LET, 3 scenarios of 2.9e6: 87 / 31 ms.
     if (!use_sur && !cap) {
         rc = run_dense_queue(c, field_id, spots, n_spots, scen, n_scen, o, k, B, dose_gy, sigma_gy, ledger_mev);
         if (rc != VPMC_E_OOM) return rc;
         (void)hipGetLastError();
     }
+    if (cap && (rc = trim_scratch(c))) return rc;
     c->qbatch_zero = 0;
     if ((rc = ensure(c, c->tallies, (size_t)n_scen * nvox * sizeof(long long), cap))) return rc;
     const bool want_let = (o->flags & VPMC_LET) != 0;
