@@ -2193,21 +2193,22 @@ int vpmc_copy_csr(vpmc_ctx *c, int32_t *col, float *val, int64_t *q_raw) {
     const size_t n = c->csr_total;
     if (n == 0) return VPMC_OK;
     const bool dev = (c->csr_flags & VPMC_DEVICE_PTRS) != 0;
-    const hipMemcpyKind kind = dev ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
     HIP_TRY(hipSetDevice(c->device));
-    if (col) HIP_TRY(hipMemcpy(col, c->csr_col.ptr, n * 4, kind));
-    if (q_raw) HIP_TRY(hipMemcpy(q_raw, c->csr_q.ptr, n * 8, kind));
-    if (val) {
-        float *dst = val;
-        if (!dev) {
-            int rc = ensure(c, c->stage_dose, n * sizeof(float), 0);
-            if (rc) return rc;
-            dst = (float *)c->stage_dose.ptr;
-        }
-        HIP_TRY(launch_csr_values((const int32_t *)c->csr_col.ptr, (const long long *)c->csr_q.ptr, n, c->geom,
-                                  ldexp(MEV_TO_J, -c->last_k), dst, nullptr));
+    const int32_t *scol = (const int32_t *)c->csr_col.ptr;
+    const long long *sq = (const long long *)c->csr_q.ptr;
+    const double scale = ldexp(MEV_TO_J, -c->last_k);
+    if (dev) {
+        HIP_TRY(launch_csr_export(scol, sq, n, c->geom, scale, col, val, (long long *)q_raw, nullptr));
         HIP_TRY(hipDeviceSynchronize());
-        if (!dev) HIP_TRY(hipMemcpy(val, dst, n * 4, hipMemcpyDeviceToHost));
+        return VPMC_OK;
+    }
+    if (col) HIP_TRY(hipMemcpy(col, scol, n * 4, hipMemcpyDeviceToHost));
+    if (q_raw) HIP_TRY(hipMemcpy(q_raw, sq, n * 8, hipMemcpyDeviceToHost));
+    if (val) {
+        int rc = ensure(c, c->stage_dose, n * sizeof(float), 0);
+        if (rc) return rc;
+        HIP_TRY(launch_csr_export(scol, sq, n, c->geom, scale, nullptr, (float *)c->stage_dose.ptr, nullptr, nullptr));
+        HIP_TRY(hipMemcpy(val, c->stage_dose.ptr, n * 4, hipMemcpyDeviceToHost));
     }
     return VPMC_OK;
 }

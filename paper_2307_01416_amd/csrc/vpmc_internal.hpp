@@ -328,8 +328,8 @@ hipError_t launch_atomic_rate(unsigned long long *grid, int nx, int ny, int nz, 
                               float sigma, uint32_t seed, hipStream_t s);
 hipError_t launch_csr_scatter(const int32_t *col, const long long *qv, unsigned long long begin,
                               unsigned long long end, unsigned long long *dense, hipStream_t s);
-hipError_t launch_csr_values(const int32_t *col, const long long *qv, size_t n, const GeomDev &g,
-                             double mev_scale, float *val, hipStream_t s);
+hipError_t launch_csr_export(const int32_t *col, const long long *qv, size_t n, const GeomDev &g, double mev_scale,
+                             int32_t *ocol, float *val, long long *oq, hipStream_t s);
 // dynamic voxel spacing: merge influence-matrix rows into cells (runs of
 // consecutive voxels of a non-decreasing voxel -> cell map), a wavefront per
 // piece of at most kCellPiece entries of one row

@@ -2430,14 +2430,58 @@ __global__ void csr_scatter_kernel(const int32_t *col, const long long *qv, unsi
         atomicAdd(dense + col[i], (unsigned long long)qv[i]);
 }
 
-__global__ void csr_values_kernel(const int32_t *col, const long long *qv, size_t n, GeomDev g, double mev_scale,
-                                  float *val) {
-    const float vol_kg = g.sp[0] * g.sp[1] * g.sp[2] * 1e-6f;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        float rho = 1.0f;
-        int m;
-        if (g.kind == 1) hu_material(g.hu[col[i]], m, rho);
-        val[i] = (float)qv[i] * ((float)mev_scale / (rho * vol_kg));
+// Rows handed out: any of columns, values (Gy per unit weight) and energies in
+// one pass, four entries a thread (the library's arrays are 256-byte aligned;
+// VEC: so are the outputs to 16 bytes, else they are stored one by one).
+// HBM-bound: 12 bytes an entry read, up to 16 written.  As a copy per array and a
+// value pass of one entry a thread, columns and values of 1.03e9 entries took
+// 15.8 ms (the copies at 1 TB/s); in this pass 6.8.
+template <bool VEC>
+__global__ __launch_bounds__(256) void csr_export_kernel(const int32_t *col, const long long *qv, size_t n, GeomDev g,
+                                                         double mev_scale, int32_t *ocol, float *val, long long *oq) {
+    const float vol_kg = g.sp[0] * g.sp[1] * g.sp[2] * 1e-6f, ms = (float)mev_scale;
+    for (size_t i = 4 * (blockIdx.x * (size_t)blockDim.x + threadIdx.x); i < n; i += 4 * (size_t)gridDim.x * blockDim.x) {
+        int c[4];
+        long long q[4];
+        float v[4];
+        const int m = (int)min((size_t)4, n - i);
+        if (m == 4) {
+            const int4 c4 = *reinterpret_cast<const int4 *>(col + i);
+            const longlong2 q0 = reinterpret_cast<const longlong2 *>(qv + i)[0], q1 = reinterpret_cast<const longlong2 *>(qv + i)[1];
+            c[0] = c4.x; c[1] = c4.y; c[2] = c4.z; c[3] = c4.w;
+            q[0] = q0.x; q[1] = q0.y; q[2] = q1.x; q[3] = q1.y;
+        } else {
+            for (int j = 0; j < 4; ++j) {
+                c[j] = col[i + (j < m ? j : 0)];
+                q[j] = qv[i + (j < m ? j : 0)];
+            }
+        }
+        if (val) {
+            int hu[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) hu[j] = g.kind == 1 ? (int)g.hu[c[j]] : 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                float rho = 1.0f;
+                int mat;
+                if (g.kind == 1) hu_material(hu[j], mat, rho);
+                v[j] = (float)q[j] * (ms / (rho * vol_kg));
+            }
+        }
+        if (VEC && m == 4) {
+            if (ocol) *reinterpret_cast<int4 *>(ocol + i) = make_int4(c[0], c[1], c[2], c[3]);
+            if (val) *reinterpret_cast<float4 *>(val + i) = make_float4(v[0], v[1], v[2], v[3]);
+            if (oq) {
+                reinterpret_cast<longlong2 *>(oq + i)[0] = make_longlong2(q[0], q[1]);
+                reinterpret_cast<longlong2 *>(oq + i)[1] = make_longlong2(q[2], q[3]);
+            }
+        } else {
+            for (int j = 0; j < m; ++j) {
+                if (ocol) ocol[i + j] = c[j];
+                if (val) val[i + j] = v[j];
+                if (oq) oq[i + j] = q[j];
+            }
+        }
     }
 }
 
@@ -3203,11 +3247,14 @@ hipError_t launch_queue(const GeomDev &g, const QueueDev &Q, int blocks, int thr
 }
 
 // workgroups (4 waves each) of the compaction passes: one wave per group of
-// kCsrGroup (row, chunk) pairs up to 4096 workgroups, the waves striding over
-// the rest
+// kCsrGroup (row, chunk) pairs up to 16384 workgroups, the waves striding over
+// the rest.  Few chunks hold most of a row, so what an early wave finds is
+// uneven: 494 rows of 256 x 256 x 160 voxels (41 M entries) took 761 (count) and
+// 1267 us (emit) with 4096 workgroups, 640 and 1045 with 16384, 667 and 1152
+// without a limit.
 static unsigned csr_pass_blocks(const QueueDev &Q) {
     const size_t ngroup = ((size_t)Q.n_rows * Q.nchunk + kCsrGroup - 1) / kCsrGroup;
-    return (unsigned)std::max<size_t>(1, std::min<size_t>((ngroup + 3) / 4, 4096));
+    return (unsigned)std::max<size_t>(1, std::min<size_t>((ngroup + 3) / 4, 16384));
 }
 
 hipError_t launch_csr_count(const QueueDev &Q, unsigned int *cnt, hipStream_t s) {
@@ -3257,13 +3304,15 @@ hipError_t launch_csr_scatter(const int32_t *col, const long long *qv, unsigned 
     return hipGetLastError();
 }
 
-hipError_t launch_csr_values(const int32_t *col, const long long *qv, size_t n, const GeomDev &g,
-                             double mev_scale, float *val, hipStream_t s) {
-    const int blocks = (int)((n + 255) / 256 < 8192 ? (n + 255) / 256 : 8192);
-    if (blocks > 0) hipLaunchKernelGGL(csr_values_kernel, dim3(blocks), dim3(256), 0, s, col, qv, n, g, mev_scale, val);
+hipError_t launch_csr_export(const int32_t *col, const long long *qv, size_t n, const GeomDev &g, double mev_scale,
+                             int32_t *ocol, float *val, long long *oq, hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    const int blocks = (int)std::min<size_t>((n + 1023) / 1024, 65536);
+    const bool vec = (((uintptr_t)ocol | (uintptr_t)val | (uintptr_t)oq) & 15u) == 0;
+    if (vec) hipLaunchKernelGGL(csr_export_kernel<true>, dim3(blocks), dim3(256), 0, s, col, qv, n, g, mev_scale, ocol, val, oq);
+    else hipLaunchKernelGGL(csr_export_kernel<false>, dim3(blocks), dim3(256), 0, s, col, qv, n, g, mev_scale, ocol, val, oq);
     return hipGetLastError();
 }
-
 
 hipError_t launch_cell_map(const int32_t *cmap, int nvox, int n_cells, int32_t *cstart, unsigned *st, hipStream_t s) {
     const hipError_t e = launch_fill_u64((unsigned long long *)st, 2, ~0ull, s);
