@@ -2626,25 +2626,28 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
     if (c->device < 0) return fail(VPMC_E_STATE, "validation-only context has no device");
     HIP_TRY(hipSetDevice(c->device));
     const size_t R = (size_t)n_rows;
-    if ((rc = ensure(c, c->cl_rp, (R + 1) * 8, 0))) return rc;
+    // (behind the row pointers: each row's first piece and, for host arrays, its output offset)
+    if ((rc = ensure(c, c->cl_rp, 3 * (R + 1) * 8, 0))) return rc;
+    long long *d_first = (long long *)c->cl_rp.ptr + (R + 1), *d_rpo = d_first + (R + 1);
     if (!dev && (rc = ensure(c, c->cl_map, (size_t)nvox * 4, 0))) return rc;
     if ((rc = ensure(c, c->cl_start, ((size_t)n_cells + 1) * 4, 0))) return rc;
     if ((rc = ensure(c, c->cl_mass, (size_t)n_cells * 8, 0))) return rc;
     // pieces of at most kCellPiece entries, row by row
     std::vector<CellPiece> pcs;
-    std::vector<size_t> first_piece(R + 1);
+    std::vector<long long> first_piece(R + 1);
     for (size_t r = 0; r < R; ++r) {
-        first_piece[r] = pcs.size();
+        first_piece[r] = (long long)pcs.size();
         for (long long q0 = rp[r]; q0 < rp[r + 1]; q0 += kCellPiece)
             pcs.push_back(CellPiece{q0, (int)std::min<long long>(kCellPiece, rp[r + 1] - q0), (int)r});
     }
-    first_piece[R] = pcs.size();
+    first_piece[R] = (long long)pcs.size();
     const size_t NP = pcs.size();
     if ((rc = ensure(c, c->cl_piece, std::max<size_t>(NP, 1) * sizeof(CellPiece), 0))) return rc;
     if ((rc = ensure(c, c->cl_cnt, std::max<size_t>(NP, 1) * 8, 0))) return rc;
     if ((rc = ensure(c, c->cl_out, (NP + 1) * 8, 0))) return rc;
     if ((rc = ensure(c, c->flags, 4, 0))) return rc;
     HIP_TRY(hipMemcpy(c->cl_rp.ptr, rp.data(), rp.size() * 8, hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(d_first, first_piece.data(), (R + 1) * 8, hipMemcpyHostToDevice));
     const int32_t *d_map = cell_of_voxel;
     if (!dev) {
         HIP_TRY(hipMemcpy(c->cl_map.ptr, cell_of_voxel, (size_t)nvox * 4, hipMemcpyHostToDevice));
@@ -2667,21 +2670,23 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
     HIP_TRY(launch_cell_count((const long long *)c->cl_rp.ptr, (const CellPiece *)c->cl_piece.ptr, (long long)NP,
                               d_col, d_map, nvox, (unsigned long long *)c->cl_cnt.ptr,
                               (unsigned *)c->flags.ptr, nullptr));
-    std::vector<unsigned long long> cnt(std::max<size_t>(NP, 1));
+    // output offsets: per piece (its own runs) and per row
+    HIP_TRY(opt_build_scan((unsigned long long *)c->cl_cnt.ptr, (unsigned long long *)c->cl_out.ptr, NP, nullptr));
     unsigned err = 0;
-    if (NP) HIP_TRY(hipMemcpy(cnt.data(), c->cl_cnt.ptr, NP * 8, hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(&err, c->flags.ptr, 4, hipMemcpyDeviceToHost));
     if (err & 1u) return fail(VPMC_E_ARG, "a column index is outside [0, nvox)");
     if (err & 2u) return fail(VPMC_E_ARG, "columns are not ascending within a row");
-    // output offsets: per piece (its own runs) and per row
-    std::vector<int64_t> pout(NP + 1), op(R + 1);
-    pout[0] = 0;
-    for (size_t k = 0; k < NP; ++k) pout[k + 1] = pout[k] + (int64_t)cnt[k];
-    for (size_t r = 0; r <= R; ++r) op[r] = pout[first_piece[r]];
-    HIP_TRY(hipMemcpy(row_ptr_out, op.data(), op.size() * 8, dev ? hipMemcpyHostToDevice : hipMemcpyHostToHost));
-    const long long nout = op[R];
-    if (!cell_out && !q_out && !val_out) return VPMC_OK;
-    HIP_TRY(hipMemcpy(c->cl_out.ptr, pout.data(), pout.size() * 8, hipMemcpyHostToDevice));
+    long long nout = 0;
+    HIP_TRY(launch_cell_rows(d_first, (const long long *)c->cl_out.ptr, R + 1, dev ? (long long *)row_ptr_out : d_rpo,
+                             nullptr));
+    if (!dev) {
+        HIP_TRY(hipMemcpy(row_ptr_out, d_rpo, (R + 1) * 8, hipMemcpyDeviceToHost));
+        nout = row_ptr_out[R];
+    }
+    if (!cell_out && !q_out && !val_out) {
+        HIP_TRY(hipDeviceSynchronize());
+        return VPMC_OK;
+    }
     HIP_TRY(launch_cell_mass(c->geom, (const int32_t *)c->cl_start.ptr, n_cells, (double *)c->cl_mass.ptr, nullptr));
     int32_t *ocell = cell_out;
     long long *oq = (long long *)q_out;

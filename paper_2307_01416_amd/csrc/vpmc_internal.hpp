@@ -343,6 +343,8 @@ hipError_t launch_cell_map(const int32_t *cmap, int nvox, int n_cells, int32_t *
 hipError_t launch_cell_mass(const GeomDev &g, const int32_t *cstart, int n_cells, double *mass, hipStream_t s);
 hipError_t launch_cell_count(const long long *rp, const CellPiece *pcs, long long n_pieces, const int32_t *col,
                              const int32_t *cmap, int nvox, unsigned long long *cnt, unsigned *err, hipStream_t s);
+hipError_t launch_cell_rows(const long long *first_piece, const long long *pout, size_t n, long long *rp_out,
+                            hipStream_t s);
 hipError_t launch_cell_emit(const long long *rp, const CellPiece *pcs, long long n_pieces, const int32_t *col,
                             const long long *q, const int32_t *cmap, const long long *pout, const double *mass,
                             double mev_scale, int32_t *ocell, long long *oq, float *oval, hipStream_t s);
