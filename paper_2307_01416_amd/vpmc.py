@@ -230,13 +230,16 @@ def vpmc_set_divergence(ctx, field_id: int, vsad_mm: float, focus_mm: float) -> 
 
 
 def spot_array(spots: np.ndarray):
-    arr = (vpmc_spot * max(1, len(spots)))()
-    for i in range(len(spots)):
-        s = arr[i]
-        s.x_mm, s.y_mm = float(spots["x_mm"][i]), float(spots["y_mm"][i])
-        s.energy_mev, s.sigma_mm = float(spots["energy_mev"][i]), float(spots["sigma_mm"][i])
-        s.energy_sigma_mev, s.weight = float(spots["energy_sigma_mev"][i]), float(spots["weight"][i])
-        s.n_histories = int(spots["n_histories"][i])
+    # column by column (a spot at a time, 950 spots took 0.85 ms)
+    arr, n = (vpmc_spot * max(1, len(spots)))(), len(spots)
+    out = np.frombuffer(arr, dtype=np.dtype(vpmc_spot))
+    with np.errstate(over="ignore"):   # (to infinity, which the library refuses)
+        for name in ("x_mm", "y_mm", "energy_mev", "sigma_mm", "energy_sigma_mev", "weight"):
+            out[name][:n] = spots[name]
+    hist = np.asarray(spots["n_histories"])
+    if hist.dtype.kind not in "iub":   # as int() takes them
+        hist = np.array([int(h) & 0xFFFFFFFF for h in hist], np.uint32)
+    out["n_histories"][:n] = hist.astype(np.uint32)
     return arr
 
 
