@@ -2468,7 +2468,8 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
         }
         poff[(size_t)n_rows] = (long long)pieces.size();
         int bits = kOptMaxBits;
-        while (bits > kOptMinBits && (long long)n_scen * (((long long)ns + (1 << bits) - 1) >> bits) < kOptLists) --bits;
+        auto lists = [&]() { return (long long)n_scen * (((long long)ns + (1 << bits) - 1) >> bits); };
+        while (bits > kOptMinBits && (lists() < kOptLists || kept / lists() > kOptListLen)) --bits;
         if ((rc = ensure(c, c->opt_ccol, (size_t)std::max(kept, 1ll) * 4, 0))) return rc;
         if ((rc = ensure(c, c->opt_cval, (size_t)std::max(kept, 1ll) * 4, 0))) return rc;
         if ((rc = ensure(c, c->opt_piece, std::max<size_t>(pieces.size(), 1) * sizeof(OptPiece), 0))) return rc;

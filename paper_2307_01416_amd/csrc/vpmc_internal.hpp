@@ -352,12 +352,14 @@ hipError_t launch_cell_emit(const long long *rp, const CellPiece *pcs, long long
 // ------------------------------------------------- spot-weight optimiser
 // Voxels per forward workgroup (int64 LDS sums): 2^bits.  Over the structure
 // voxels of the iterations the largest of 2^5 .. 2^11 that leaves kOptLists
-// lists (three workgroups a CU): more lists sum too few entries each (2^9 voxels
-// of the whole grid per list: 12 500 lists of 590 entries, 46 us a sweep; 2^11
-// structure voxels: 1000 of 7300, 19 us), fewer leave CUs idle.  The sweep of
-// whole rows for the dose output takes kOptChunkBits.
+// lists (three workgroups a CU) of at most kOptListLen entries on average: more
+// lists sum too few entries each (2^9 voxels of the whole grid per list: 12 500
+// lists of 590 entries, 46 us a sweep; 2^11 structure voxels: 1000 of 7300, 19
+// us), fewer leave CUs idle, and long ones want several a CU to even out
+// (1040 lists of 95 600: 203 us, 2080 of 47 800: 169).  The sweep of whole rows
+// for the dose output takes kOptChunkBits.
 constexpr int kOptChunkBits = 9, kOptMinBits = 5, kOptMaxBits = 11;
-constexpr long long kOptLists = 768;
+constexpr long long kOptLists = 768, kOptListLen = 65536;
 enum { kOptPowerInit, kOptPower, kOptPowerNorm, kOptFistaInit, kOptFista, kOptFinalPrep, kOptFinal };
 enum { kOptLam = 0, kOptL = 1 };   // device scalars
 

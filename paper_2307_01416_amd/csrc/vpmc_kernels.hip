@@ -1959,13 +1959,16 @@ __global__ __launch_bounds__(256) void tile_box_kernel(GeomDev g, QueueDev Q, Ro
 // that did not get it deposit straight into the slot grid.
 // Draws are of one wavefull by default: more keep waves longer on rows other
 // than the tile's (0.4 cc head matrix, transport of all epochs: 137, 123 and
-// 114 ms at 256, 128 and 64 records a draw).  Bound by VALU issue (384
-// instructions a wave-step; 89 % of the launch) and next by the memory-side
-// atomics (1.4e10 of 2.0e10 per second).  Measured on the 13-scenario matrices,
-// 0.4 cc / 8 cc head: 110 / 546 ms as one kernel with source and beam line, a
-// drain after every chunk and int64 tile entries; 71.5 / 399 ms with staged
-// draws, 32-bit entries and the tile joined in flight; 57 / 311 ms with the
-// step rewritten for instruction count and exhausted rows leaving the tile.
+// 114 ms at 256, 128 and 64 records a draw).  Bound by VALU issue (431
+// instructions a wave-step, 0.87 of its lanes with a particle, 0.78 of the
+// issued lanes at work; 93 % of the launch at 4 clocks each, and the 64-bit
+// products and transcendentals take more), then by the memory-side atomics
+// (1.1e10 of 2.0e10 per second).  Measured on the 13-scenario matrices, 0.4 cc /
+// 8 cc head: 110 / 546 ms as one kernel with source and beam line, a drain
+// after every chunk and int64 tile entries; 71.5 / 399 ms with staged draws,
+// 32-bit entries and the tile joined in flight; 57 / 311 ms with the step
+// rewritten for instruction count and exhausted rows leaving the tile; 56 / 306
+// ms with the round keys made in the step.
 // Each history's arithmetic and random stream are those of a lane running it
 // alone, and the tallies are integer sums: the result does not depend on
 // the schedule.  The only waits between waves are for the wave that is
