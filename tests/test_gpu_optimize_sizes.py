@@ -1,7 +1,7 @@
 """Spot-weight optimiser at the sizes where its launch shapes change, against
 the FP64 oracle with test_gpu_optimize.py's tolerances (the residual is FP32:
 1e-5 on weights and objective, 1e-6 on the step constant): voxel counts around
-a block of 4096, one structure voxel to all of them, one scenario and more than
+a block of 4096, no structure voxel to all of them, one scenario and more than
 a wavefront has lanes, one spot and more than 512 workgroups of four hold, rows
 from empty to longer than the eight parts' first round.  Device arrays give the
 host arrays' bits, and an index is not reused for other structures."""
@@ -27,7 +27,7 @@ def problem(nvox, n_struct, n_scen, n_spots, longest, seed=0):
     return I.OptProblem((nvox, 1, 1), n_scen, n_spots, rp, col, val, roi)
 
 
-CASES = [(4095, 1, 1, 1, 40), (4096, 64, 3, 5, 700), (4097, 65, 2, 4, 3000), (20000, 20000, 1, 9, 20000),
+CASES = [(500, 0, 2, 3, 100), (4095, 1, 1, 1, 40), (4096, 64, 3, 5, 700), (4097, 65, 2, 4, 3000), (20000, 20000, 1, 9, 20000),
          (9000, 4500, 65, 3, 1500), (700, 300, 2, 2100, 12), (60000, 33000, 13, 6, 9000)]
 
 
