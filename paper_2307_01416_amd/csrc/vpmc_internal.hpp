@@ -80,6 +80,14 @@ struct GeomDev {
     const float *rho;
 };
 
+// Linear index of the voxel behind a face, stride (1, nx or nx * ny) from vox
+// up or down.  Behind the grid's own faces it runs from -nx * ny to
+// voxels + nx * ny - 1, for grids near the limit of 2^31 - 1 voxels more than 32
+// signed bits hold.
+__host__ __device__ inline int64_t voxel_behind(uint32_t vox, int stride, bool up) {
+    return (int64_t)vox + (up ? stride : -stride);
+}
+
 struct FieldDev {
     float iso[3], ex[3], ey[3], ez[3];
     int has_block, nv;

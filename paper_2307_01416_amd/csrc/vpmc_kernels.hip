@@ -1348,7 +1348,7 @@ __device__ __forceinline__ bool patient_step(Lane &v, Acc &acc, float scale, con
     // what lies behind the face this step may cross is fetched now, so its
     // latency overlaps the step's arithmetic
     const int stride = is2 ? g.nx * g.ny : is1 ? g.nx : 1;
-    const int nvox = up ? (int)ps.vox + stride : (int)ps.vox - stride;
+    const int64_t nvox = voxel_behind(ps.vox, stride, up);
     uint32_t ncell = ps.cell;
     if (g.kind == 1) {
         if constexpr (X) {
