@@ -88,7 +88,8 @@ int vpmc_version(void);
  * VPMC_GEOM_HU copies nx*ny*nz int16 CT numbers (host pointer, or device
  * pointer with VPMC_DEVICE_PTRS).  nx*ny*nz must be < 2^31.  On a
  * validation-only context only the grid's shape is kept (for the checks of
- * later calls) and hu is not read. */
+ * later calls) and hu is not read.  A load that fails after its argument
+ * checks (VPMC_E_OOM, VPMC_E_DEVICE) leaves the context without a geometry. */
 int vpmc_load_geometry(vpmc_ctx *ctx, int kind, const int16_t *hu, int nx, int ny, int nz,
                        const float spacing_mm[3], const float origin_mm[3], unsigned flags);
 

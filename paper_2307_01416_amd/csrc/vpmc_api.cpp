@@ -1251,6 +1251,10 @@ int vpmc_load_geometry(vpmc_ctx *c, int kind, const int16_t *hu, int nx, int ny,
     }
     HIP_TRY(hipSetDevice(c->device));
     if (kind == VPMC_GEOM_HU) {
+        // the buffers of the geometry before are about to be overwritten or
+        // released: if that ends early, there is no geometry
+        c->has_geom = false;
+        c->last_nscen = 0;
         int rc = ensure(c, c->hu_buf, nvox * sizeof(int16_t), 0);
         if (rc) return rc;
         HIP_TRY(hipMemcpy(c->hu_buf.ptr, hu, nvox * sizeof(int16_t),

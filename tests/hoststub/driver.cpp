@@ -1,0 +1,164 @@
+// Failing device allocations on the CPU (test tooling): this program defines
+// the HIP runtime calls that libvpmc makes, so the library's host code runs
+// with "device" memory from calloc, kernels that do nothing, and allocations
+// that fail where a case says so.  One case per run (argv[1]); each compares
+// return codes with the documented ones.  Exit status 0 when all agree.
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <map>
+#include <vector>
+
+#include "../../include/vpmc.h"
+
+// ------------------------------------------------------------- HIP runtime
+static const int kOutOfMemory = 2;
+static std::map<void *, size_t> g_live;   // allocations
+static size_t g_bytes = 0;                // their sum
+static size_t g_room = ~(size_t)0;        // device memory: what does not fit is refused
+static int g_last = 0;                    // what hipGetLastError has to say
+static unsigned long long g_launches = 0;
+struct Dim3 {
+    unsigned x, y, z;
+};
+static Dim3 g_grid, g_block;
+static size_t g_shared;
+static void *g_stream;
+
+extern "C" {
+int hipMalloc(void **p, size_t n) {
+    if (n > g_room - (g_bytes < g_room ? g_bytes : g_room)) return g_last = kOutOfMemory;
+    *p = calloc(1, n ? n : 1);
+    g_live[*p] = n;
+    g_bytes += n;
+    return 0;
+}
+int hipFree(void *p) {
+    auto it = g_live.find(p);
+    if (it == g_live.end()) return g_last = 1;
+    g_bytes -= it->second;
+    g_live.erase(it);
+    free(p);
+    return 0;
+}
+int hipMemcpy(void *d, const void *s, size_t n, int) {
+    if (n && (!d || !s)) return g_last = 1;
+    if (n) memcpy(d, s, n);
+    return 0;
+}
+int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *) { return hipMemcpy(d, s, n, k); }
+int hipMemset(void *d, int v, size_t n) {
+    if (n && !d) return g_last = 1;
+    if (n) memset(d, v, n);
+    return 0;
+}
+int hipMemsetAsync(void *d, int v, size_t n, void *) { return hipMemset(d, v, n); }
+int hipLaunchKernel(const void *, Dim3 g, Dim3 b, void **, size_t, void *) {
+    // the hardware's limit on a launch
+    if ((unsigned long long)g.x * b.x >= 1ull << 32) return g_last = 9;
+    ++g_launches;
+    return 0;
+}
+int __hipPushCallConfiguration(Dim3 g, Dim3 b, size_t shared, void *stream) {
+    g_grid = g;
+    g_block = b;
+    g_shared = shared;
+    g_stream = stream;
+    return 0;
+}
+int __hipPopCallConfiguration(Dim3 *g, Dim3 *b, size_t *shared, void **stream) {
+    *g = g_grid;
+    *b = g_block;
+    *shared = g_shared;
+    *stream = g_stream;
+    return 0;
+}
+int hipGetLastError() {
+    const int e = g_last;
+    g_last = 0;
+    return e;
+}
+const char *hipGetErrorString(int e) { return e == kOutOfMemory ? "out of memory" : "error"; }
+int hipGetDevice(int *d) { return *d = 0; }
+int hipGetDeviceCount(int *n) { return *n = 1, 0; }
+int hipSetDevice(int) { return 0; }
+int hipGetDevicePropertiesR0600(void *, int) { return 1; }   // (the library then takes its defaults)
+int hipMemGetInfo(size_t *f, size_t *t) { return *f = *t = (size_t)1 << 30, 0; }
+int hipGetSymbolAddress(void **p, const void *) {
+    static void *scratch = calloc(1, (size_t)32 << 20);
+    return *p = scratch, 0;
+}
+int hipDeviceSynchronize() { return 0; }
+int hipStreamSynchronize(void *) { return 0; }
+int hipStreamCreateWithFlags(void **s, unsigned) { return *s = malloc(1), 0; }
+int hipStreamDestroy(void *s) { return free(s), 0; }
+int hipEventCreate(void **e) { return *e = malloc(1), 0; }
+int hipEventDestroy(void *e) { return free(e), 0; }
+int hipEventRecord(void *, void *) { return 0; }
+int hipEventSynchronize(void *) { return 0; }
+int hipEventElapsedTime(float *ms, void *, void *) { return *ms = 1.0f, 0; }
+}
+
+// ------------------------------------------------------------- cases
+static int fails = 0;
+#define EXPECT(call, code)                                                                       \
+    do {                                                                                         \
+        const int rc_ = (call);                                                                  \
+        if (rc_ != (code)) {                                                                     \
+            fprintf(stderr, "line %d: %s returned %d, expected %d (%s)\n", __LINE__, #call, rc_, \
+                    (code), vpmc_last_error(nullptr));                                           \
+            fails++;                                                                             \
+        }                                                                                        \
+    } while (0)
+
+static const float kSp[3] = {2.0f, 2.0f, 2.0f}, kOrg[3] = {-32.0f, -32.0f, 0.0f};
+static const vpmc_beam kBeam = {{0, 0, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
+static const vpmc_spot kSpots[2] = {{0, 0, 150.0f, 3.0f, 0.0f, 1.0f, 1000}, {2.5f, 0, 140.0f, 3.0f, 0.0f, 1.0f, 500}};
+static const vpmc_scenario kScen = {{0, 0, 0}, 1.0f};
+
+static int load(vpmc_ctx *c, int n) {
+    std::vector<int16_t> hu((size_t)n * n * n, 0);
+    return vpmc_load_geometry(c, VPMC_GEOM_HU, hu.data(), n, n, n, kSp, kOrg, 0);
+}
+
+static int dense(vpmc_ctx *c, int n, size_t cap = 0, int batches = 0, int blocks = 0) {
+    std::vector<float> dose((size_t)n * n * n);
+    vpmc_opts o{};
+    o.physics = VPMC_PHYS_ALL;
+    o.max_device_bytes = cap;
+    o.n_batches = batches;
+    o.grid_blocks = blocks;
+    return vpmc_run_spots(c, 0, kSpots, 2, &kScen, 1, &o, dose.data(), nullptr, nullptr, nullptr);
+}
+
+// a CT grid whose density array does not fit: the context has no geometry
+// until one loads, and no run reads what the failed call released
+static void geometry(vpmc_ctx *c) {
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, nullptr, 0, nullptr, nullptr), VPMC_OK);
+    EXPECT(load(c, 8), VPMC_OK);
+    EXPECT(dense(c, 8), VPMC_OK);
+    g_room = g_bytes + 80000;   // 32^3: CT numbers of 66 kB fit, densities of 139 kB do not
+    EXPECT(load(c, 32), VPMC_E_OOM);
+    g_room = ~(size_t)0;
+    (void)hipGetLastError();
+    EXPECT(dense(c, 8), VPMC_E_STATE);
+    EXPECT(load(c, 32), VPMC_OK);
+    EXPECT(dense(c, 32), VPMC_OK);
+}
+
+int main(int argc, char **argv) {
+    vpmc_ctx *c = nullptr;
+    EXPECT(vpmc_create(&c, 0), VPMC_OK);
+    const char *name = argc > 1 ? argv[1] : "";
+    if (!strcmp(name, "geometry")) geometry(c);
+    else return 2;
+    vpmc_destroy(c);
+    if (!g_live.empty()) {
+        fprintf(stderr, "%zu allocations left\n", g_live.size());
+        fails++;
+    }
+    if (fails) return 1;
+    printf("%s: ok\n", name);
+    return 0;
+}

@@ -1,0 +1,31 @@
+"""Device allocations that fail, on the CPU: tests/hoststub/driver.cpp runs the
+library's host code over a HIP runtime of its own (memory from calloc, kernels
+that do nothing, allocations refused where a case says so) and compares return
+codes with the documented ones."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_2307_01416_amd")
+CASES = ["geometry"]
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    from paper_2307_01416_amd import build
+    if not os.path.exists(build.LIB):
+        build.build()
+    exe = str(tmp_path_factory.mktemp("hoststub") / "driver")
+    # -rdynamic: the library's HIP calls resolve to the program's
+    subprocess.run(["g++", "-O1", "-g", "-std=c++17", "-rdynamic", "-o", exe,
+                    os.path.join(ROOT, "tests", "hoststub", "driver.cpp"), "-L" + PKG, "-l:libvpmc.so",
+                    "-Wl,-rpath," + PKG], check=True, timeout=300)
+    return exe
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_failed_allocations(driver, case):
+    r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, f"{r.returncode}\n{r.stdout}\n{r.stderr}"
