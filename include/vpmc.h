@@ -123,7 +123,8 @@ typedef struct {
  * block == NULL: no aperture block.  block != NULL and n_vertices == 0:
  * closed block (no opening).  rs == NULL: no range shifter.
  * Errors: VPMC_E_ARG (bad numbers, field id), VPMC_E_POLYGON (fewer than 3
- * vertices but not 0, zero area, self-intersection, > VPMC_MAX_VERTICES). */
+ * vertices but not 0, zero area, self-intersection, > VPMC_MAX_VERTICES): the
+ * field stays as it was.  VPMC_E_OOM, VPMC_E_DEVICE: it may be unset. */
 int vpmc_set_aperture(vpmc_ctx *ctx, int field_id, const vpmc_beam *beam, const float *xy_mm,
                       int n_vertices, const vpmc_block *block, const vpmc_rs *rs);
 

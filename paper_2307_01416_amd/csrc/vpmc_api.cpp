@@ -1354,6 +1354,9 @@ int vpmc_set_aperture(vpmc_ctx *c, int field_id, const vpmc_beam *beam, const fl
     }
     if (c->device >= 0 && !poly.empty()) {
         HIP_TRY(hipSetDevice(c->device));
+        // the buffers of the field before are about to be overwritten or
+        // released: if that ends early, the field is not set
+        f.set = false;
         if ((rc = ensure(c, f.poly_buf, poly.size() * sizeof(float2), 0))) return rc;
         HIP_TRY(hipMemcpy(f.poly_buf.ptr, poly.data(), poly.size() * sizeof(float2), hipMemcpyHostToDevice));
         if (ras.nx > 0) {

@@ -3,6 +3,7 @@
 // with "device" memory from calloc, kernels that do nothing, and allocations
 // that fail where a case says so.  One case per run (argv[1]); each compares
 // return codes with the documented ones.  Exit status 0 when all agree.
+#include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -147,11 +148,40 @@ static void geometry(vpmc_ctx *c) {
     EXPECT(dense(c, 32), VPMC_OK);
 }
 
+static std::vector<float> circle(int n, float r) {
+    std::vector<float> p(2 * n);
+    for (int i = 0; i < n; ++i) {
+        p[2 * i] = r * cosf(6.2831853f * (i + 0.5f) / n);
+        p[2 * i + 1] = r * sinf(6.2831853f * (i + 0.5f) / n);
+    }
+    return p;
+}
+
+// an opening whose raster does not fit: the field is not set until a call
+// succeeds, and no run reads the polygon or raster that the failed call released
+static void aperture(vpmc_ctx *c) {
+    const vpmc_block blk = {30.0f, 8.5f, 50.0f};
+    const std::vector<float> small = circle(16, 5.0f), large = circle(1000, 90.0f);
+    EXPECT(load(c, 8), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, small.data(), 16, &blk, nullptr), VPMC_OK);
+    EXPECT(dense(c, 8), VPMC_OK);
+    g_room = g_bytes + 20000;
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, large.data(), 1000, &blk, nullptr), VPMC_E_OOM);
+    g_room = ~(size_t)0;
+    (void)hipGetLastError();
+    EXPECT(dense(c, 8), VPMC_E_STATE);
+    // what the argument checks refuse leaves the field as it is
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, large.data(), 1000, &blk, nullptr), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, large.data(), 2, &blk, nullptr), VPMC_E_POLYGON);
+    EXPECT(dense(c, 8), VPMC_OK);
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
     const char *name = argc > 1 ? argv[1] : "";
     if (!strcmp(name, "geometry")) geometry(c);
+    else if (!strcmp(name, "aperture")) aperture(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {
