@@ -501,6 +501,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     if (G < 1) return fail(VPMC_E_OOM, "no room for one influence-matrix slot (%zu bytes)", slot_bytes);
     if (c->n_slots < G || c->slot_nvox != nvox || c->slots_dirty) {
         const int Ga = std::max(G, c->slot_nvox == nvox ? c->n_slots : 0);
+        c->n_slots = 0;   // (none until all of them are there)
         if ((rc = ensure(c, c->slot_grid, (size_t)Ga * gstride * 8, cap))) return rc;
         if ((rc = ensure(c, c->slot_mark, (size_t)Ga * mstride, cap))) return rc;
         if ((rc = ensure(c, c->slot_cnt, (size_t)Ga * nchunk * 4, cap))) return rc;

@@ -176,12 +176,41 @@ static void aperture(vpmc_ctx *c) {
     EXPECT(dense(c, 8), VPMC_OK);
 }
 
+static int matrix(vpmc_ctx *c, int n_spots, int hist = 100) {
+    std::vector<vpmc_spot> sp(n_spots, kSpots[0]);
+    for (vpmc_spot &s : sp) s.n_histories = (uint32_t)hist;
+    std::vector<int64_t> rp(n_spots + 1);
+    vpmc_opts o{};
+    o.physics = VPMC_PHYS_ALL;
+    o.output = VPMC_OUT_CSR;
+    return vpmc_run_spots(c, 0, sp.data(), n_spots, &kScen, 1, &o, nullptr, nullptr, nullptr, rp.data());
+}
+
+// more row slots than fit: the slots that were there are gone, and the next
+// run allocates its own
+static void slots(vpmc_ctx *c) {
+    EXPECT(load(c, 8), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, nullptr, 0, nullptr, nullptr), VPMC_OK);
+    EXPECT(matrix(c, 2), VPMC_OK);
+    g_room = g_bytes + 100000;   // 60 slots of 4 KB do not fit
+    EXPECT(matrix(c, 60), VPMC_E_OOM);
+    g_room = ~(size_t)0;
+    (void)hipGetLastError();
+    const size_t before = g_bytes;
+    EXPECT(matrix(c, 2), VPMC_OK);
+    if (g_bytes < before + 2 * 512 * 8) {
+        fprintf(stderr, "the run after the failed one has no row slots\n");
+        fails++;
+    }
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
     const char *name = argc > 1 ? argv[1] : "";
     if (!strcmp(name, "geometry")) geometry(c);
     else if (!strcmp(name, "aperture")) aperture(c);
+    else if (!strcmp(name, "slots")) slots(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {
