@@ -327,7 +327,9 @@ int vpmc_surrogate_train(vpmc_ctx *ctx, const float *x, const float *y, const fl
 /* After a CSR run: column (voxel) indices in ascending order per row and FP32
  * values (Gy per unit spot weight, converted from the int64 tally); q_raw
  * (optional) receives the int64 tallies themselves.  Buffers must hold
- * row_ptr[last] entries; pointer kind follows the run's flags. */
+ * row_ptr[last] entries; pointer kind follows the run's flags.  Values are made
+ * from the loaded geometry's densities: VPMC_E_STATE for val_gy when none is
+ * loaded or it has another number of voxels than the run's. */
 int vpmc_copy_csr(vpmc_ctx *ctx, int32_t *col_voxel, float *val_gy, int64_t *q_raw);
 
 /* After a dense run: copy the int64 tally of scenario `scen_index` and the

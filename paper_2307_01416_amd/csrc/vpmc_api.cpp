@@ -101,6 +101,7 @@ struct vpmc_ctx {
     unsigned long long csr_cap = 0, csr_total = 0, csr_cap_hint = 0;
     int csr_rows = 0;
     bool csr_valid = false;
+    size_t csr_nvox = 0;   // voxels of the grid that its columns index
     unsigned csr_flags = 0;
     // autotuned launch shapes (0 = not tuned)
     int tuned_csr_hpl = 0, tuned_csr_blocks = 0, tuned_dense_blocks = 0;
@@ -806,6 +807,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     c->csr_total = used_host;
     c->csr_rows = R;
     c->csr_valid = true;
+    c->csr_nvox = nvox;
     c->csr_flags = o->flags;
     c->csr_cap_hint = used_host;
     c->last_k = k;
@@ -2219,6 +2221,9 @@ int vpmc_copy_csr(vpmc_ctx *c, int32_t *col, float *val, int64_t *q_raw) {
     if (!col && !val && !q_raw) return fail(VPMC_E_ARG, "no output");
     const size_t n = c->csr_total;
     if (n == 0) return VPMC_OK;
+    // values need the densities at the run's columns
+    if (val && !(c->has_geom && c->nvox == c->csr_nvox))
+        return fail(VPMC_E_STATE, "the geometry of the CSR run is no longer loaded");
     const bool dev = (c->csr_flags & VPMC_DEVICE_PTRS) != 0;
     HIP_TRY(hipSetDevice(c->device));
     const int32_t *scol = (const int32_t *)c->csr_col.ptr;
