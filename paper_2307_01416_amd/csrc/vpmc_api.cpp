@@ -102,6 +102,7 @@ struct vpmc_ctx {
     int csr_rows = 0;
     bool csr_valid = false;
     size_t csr_nvox = 0;   // voxels of the grid that its columns index
+    int csr_k = 0;         // exponent of its energies (last_k may be a later dense run's)
     unsigned csr_flags = 0;
     // autotuned launch shapes (0 = not tuned)
     int tuned_csr_hpl = 0, tuned_csr_blocks = 0, tuned_dense_blocks = 0;
@@ -808,6 +809,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     c->csr_rows = R;
     c->csr_valid = true;
     c->csr_nvox = nvox;
+    c->csr_k = k;
     c->csr_flags = o->flags;
     c->csr_cap_hint = used_host;
     c->last_k = k;
@@ -2228,7 +2230,7 @@ int vpmc_copy_csr(vpmc_ctx *c, int32_t *col, float *val, int64_t *q_raw) {
     HIP_TRY(hipSetDevice(c->device));
     const int32_t *scol = (const int32_t *)c->csr_col.ptr;
     const long long *sq = (const long long *)c->csr_q.ptr;
-    const double scale = ldexp(MEV_TO_J, -c->last_k);
+    const double scale = ldexp(MEV_TO_J, -c->csr_k);
     if (dev) {
         HIP_TRY(launch_csr_export(scol, sq, n, c->geom, scale, col, val, (long long *)q_raw, nullptr));
         HIP_TRY(hipDeviceSynchronize());

@@ -1,6 +1,6 @@
 """Rows copied out after something else has happened on the context: another
 grid loaded (columns and energies as before, values refused), the run's own
-grid again (everything as before)."""
+grid again, a dense run of another fixed-point exponent (everything as before)."""
 import numpy as np
 import pytest
 
@@ -43,4 +43,11 @@ def test_another_grid(run):
     np.testing.assert_array_equal(q, want[2])
     V.vpmc_load_geometry(e.ctx, c.geometry)
     for a, b in zip(copy(V, e, n), want):
+        np.testing.assert_array_equal(a, b)
+
+
+def test_dense_run_of_another_exponent(run):
+    V, e, c, want = run
+    e.run_dose(c, 0, n_batches=0, sigma=False, fixed_point_bits=30)
+    for a, b in zip(copy(V, e, len(want[0])), want):
         np.testing.assert_array_equal(a, b)
