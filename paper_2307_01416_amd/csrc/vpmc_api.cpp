@@ -374,9 +374,9 @@ int stage_buffer(vpmc_ctx *c, unsigned long long groups, unsigned long long stag
     return rc;
 }
 
-// Before a run with a cap on device memory: scratch that runs without one grew
-// for their speed alone (staging, queue tables, grids of batches) does not
-// count against it.
+// Before a run with a cap on device memory, and where the device has no more:
+// scratch that runs without a cap grew for their speed alone (staging, queue
+// tables, grids of batches) goes back.
 int trim_scratch(vpmc_ctx *c) {
     if (!c->uncapped) return VPMC_OK;
     for (DevBuf *b : {&c->q_stage, &c->q_ctl, &c->rows, &c->grp_off, &c->heads, &c->dense_args, &c->qbatch}) {
@@ -1614,7 +1614,19 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
         n_grids = std::max(n_grids, (size_t)(p.s1 - p.s0) * (size_t)(p.b1 - p.b0));
     }
     const bool whole = folded && parts.front().b1 == B;   // every batch of a scenario in one launch
-    // device buffers
+    // device buffers: results and grids, then the staging in what is left
+    if ((rc = ensure(c, c->tallies, (size_t)n_scen * nvox * 8, 0)) ||
+        (want_let && (rc = ensure(c, c->let_tallies, (size_t)n_scen * nvox * 8, 0))) ||
+        (!dev_out && dose_gy && (rc = ensure(c, c->stage_dose, nvox * 4, 0))) ||
+        (!dev_out && sigma_gy && (rc = ensure(c, c->stage_sigma, nvox * 4, 0))))
+        return rc;
+    if (folded) {
+        const size_t had = c->qbatch.cap;
+        c->uncapped = true;   // (what trim_scratch gives back)
+        if ((rc = ensure(c, c->qbatch, n_grids * grid_bytes, 0))) return rc;
+        if (c->qbatch.cap != had) c->qbatch_zero = 0;
+        if (!whole && (rc = ensure(c, c->s2, nvox * 8, 0))) return rc;
+    }
     unsigned long long stage_n = 0;
     if ((rc = stage_buffer(c, max_groups, queue_stage_min(shape.blocks, shape.threads, 1), 0, &stage_n))) return rc;
     size_t n_rounds = 1;
@@ -1648,18 +1660,7 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
     const size_t a_part = args_bytes;
     const size_t a_rows = place(max_rows * sizeof(RowDev)), a_goff = place((max_rows + 1) * 8);
     const size_t a_heads = place(n_rounds * 8), a_ctl = place(max_rows * sizeof(RowCtl));
-    if ((rc = ensure(c, c->tallies, (size_t)n_scen * nvox * 8, 0)) ||
-        (want_let && (rc = ensure(c, c->let_tallies, (size_t)n_scen * nvox * 8, 0))) ||
-        (rc = ensure(c, c->dense_args, args_bytes, 0)) ||
-        (!dev_out && dose_gy && (rc = ensure(c, c->stage_dose, nvox * 4, 0))) ||
-        (!dev_out && sigma_gy && (rc = ensure(c, c->stage_sigma, nvox * 4, 0))))
-        return rc;
-    if (folded) {
-        const size_t had = c->qbatch.cap;
-        if ((rc = ensure(c, c->qbatch, n_grids * grid_bytes, 0))) return rc;
-        if (c->qbatch.cap != had) c->qbatch_zero = 0;
-        if (!whole && (rc = ensure(c, c->s2, nvox * 8, 0))) return rc;
-    }
+    if ((rc = ensure(c, c->dense_args, args_bytes, 0))) return rc;
     while (c->events.size() < 2 * parts.size() + 2) {
         hipEvent_t e;
         HIP_TRY(hipEventCreate(&e));
@@ -1861,6 +1862,8 @@ int vpmc_run_spots(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spot
         rc = run_dense_queue(c, field_id, spots, n_spots, scen, n_scen, o, k, B, dose_gy, sigma_gy, ledger_mev);
         if (rc != VPMC_E_OOM) return rc;
         (void)hipGetLastError();
+        // batch by batch in what that needs: what the attempt grew goes back
+        if ((rc = trim_scratch(c))) return rc;
     }
     if (cap && (rc = trim_scratch(c))) return rc;
     c->qbatch_zero = 0;

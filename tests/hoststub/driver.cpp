@@ -204,6 +204,20 @@ static void slots(vpmc_ctx *c) {
     }
 }
 
+// a dense run whose batch grids and staging do not fit together: it runs batch
+// by batch in the room that a run batch by batch needs
+static void fallback(vpmc_ctx *c) {
+    const size_t n = 32, nvox = n * n * n;
+    EXPECT(load(c, (int)n), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, nullptr, 0, nullptr, nullptr), VPMC_OK);
+    // tally, batch grid, squares, staged dose and small tables; the queue
+    // wants 16 batch grids, or the staging of 1500 particles beside these
+    g_room = g_bytes + nvox * (8 + 8 + 8 + 4) + 16384;
+    EXPECT(dense(c, (int)n, 0, 16), VPMC_OK);
+    g_room = ~(size_t)0;
+    EXPECT(dense(c, (int)n, 0, 16), VPMC_OK);
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
@@ -211,6 +225,7 @@ int main(int argc, char **argv) {
     if (!strcmp(name, "geometry")) geometry(c);
     else if (!strcmp(name, "aperture")) aperture(c);
     else if (!strcmp(name, "slots")) slots(c);
+    else if (!strcmp(name, "fallback")) fallback(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {
