@@ -29,12 +29,17 @@ int fail(int code, const char *fmt, ...) {
     return code;
 }
 
-#define HIP_TRY(expr)                                                                     \
-    do {                                                                                  \
-        hipError_t e_ = (expr);                                                           \
-        if (e_ != hipSuccess)                                                             \
-            return fail(e_ == hipErrorOutOfMemory ? VPMC_E_OOM : VPMC_E_DEVICE, "%s: %s", \
-                        #expr, hipGetErrorString(e_));                                    \
+// A reported error is also taken from the runtime, whose last error the
+// launches of the next call would report again.
+int hip_fail(const char *what, hipError_t e) {
+    (void)hipGetLastError();
+    return fail(e == hipErrorOutOfMemory ? VPMC_E_OOM : VPMC_E_DEVICE, "%s: %s", what, hipGetErrorString(e));
+}
+
+#define HIP_TRY(expr)                                       \
+    do {                                                    \
+        hipError_t e_ = (expr);                             \
+        if (e_ != hipSuccess) return hip_fail(#expr, e_);   \
     } while (0)
 
 bool finite3(const float *v) { return isfinite(v[0]) && isfinite(v[1]) && isfinite(v[2]); }
@@ -366,7 +371,6 @@ int stage_buffer(vpmc_ctx *c, unsigned long long groups, unsigned long long stag
     for (;;) {
         rc = ensure(c, c->q_stage, n * kStageFields * sizeof(float), cap);
         if (rc != VPMC_E_OOM || cap || n <= stage_min) break;
-        (void)hipGetLastError();
         n = std::max(stage_min, n / 2 / 64 * 64);
     }
     *stage_n = n;
@@ -1133,6 +1137,7 @@ int vpmc_create(vpmc_ctx **out, int hip_device) {
             (e = launch_derive_tables(c->d_tables, nullptr)) != hipSuccess ||
             (e = hipStreamSynchronize(nullptr)) != hipSuccess) {
             if (c->d_tables) (void)hipFree(c->d_tables);
+            (void)hipGetLastError();
             delete c;
             return fail(VPMC_E_DEVICE, "table upload failed: %s", hipGetErrorString(e));
         }
@@ -1140,6 +1145,7 @@ int vpmc_create(vpmc_ctx **out, int hip_device) {
         // the static scratch's device address on this device (current here)
         if ((e = scratch_device_ptr(hip_device, &c->scratch)) != hipSuccess) {
             (void)hipFree(c->d_tables);
+            (void)hipGetLastError();
             delete c;
             return fail(VPMC_E_DEVICE, "scratch address lookup failed: %s", hipGetErrorString(e));
         }
@@ -1861,7 +1867,6 @@ int vpmc_run_spots(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spot
     if (!use_sur && !cap) {
         rc = run_dense_queue(c, field_id, spots, n_spots, scen, n_scen, o, k, B, dose_gy, sigma_gy, ledger_mev);
         if (rc != VPMC_E_OOM) return rc;
-        (void)hipGetLastError();
         // batch by batch in what that needs: what the attempt grew goes back
         if ((rc = trim_scratch(c))) return rc;
     }

@@ -142,7 +142,6 @@ static void geometry(vpmc_ctx *c) {
     g_room = g_bytes + 80000;   // 32^3: CT numbers of 66 kB fit, densities of 139 kB do not
     EXPECT(load(c, 32), VPMC_E_OOM);
     g_room = ~(size_t)0;
-    (void)hipGetLastError();
     EXPECT(dense(c, 8), VPMC_E_STATE);
     EXPECT(load(c, 32), VPMC_OK);
     EXPECT(dense(c, 32), VPMC_OK);
@@ -168,7 +167,6 @@ static void aperture(vpmc_ctx *c) {
     g_room = g_bytes + 20000;
     EXPECT(vpmc_set_aperture(c, 0, &kBeam, large.data(), 1000, &blk, nullptr), VPMC_E_OOM);
     g_room = ~(size_t)0;
-    (void)hipGetLastError();
     EXPECT(dense(c, 8), VPMC_E_STATE);
     // what the argument checks refuse leaves the field as it is
     EXPECT(vpmc_set_aperture(c, 0, &kBeam, large.data(), 1000, &blk, nullptr), VPMC_OK);
@@ -195,7 +193,6 @@ static void slots(vpmc_ctx *c) {
     g_room = g_bytes + 100000;   // 60 slots of 4 KB do not fit
     EXPECT(matrix(c, 60), VPMC_E_OOM);
     g_room = ~(size_t)0;
-    (void)hipGetLastError();
     const size_t before = g_bytes;
     EXPECT(matrix(c, 2), VPMC_OK);
     if (g_bytes < before + 2 * 512 * 8) {
@@ -218,6 +215,28 @@ static void fallback(vpmc_ctx *c) {
     EXPECT(dense(c, (int)n, 0, 16), VPMC_OK);
 }
 
+// a call refused for memory does not fail the next one (launches report the
+// runtime's last error)
+static void next_call(vpmc_ctx *c) {
+    EXPECT(load(c, 8), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, nullptr, 0, nullptr, nullptr), VPMC_OK);
+    EXPECT(dense(c, 8), VPMC_OK);
+    EXPECT(matrix(c, 2), VPMC_OK);
+    g_room = g_bytes + 100000;
+    EXPECT(matrix(c, 60), VPMC_E_OOM);
+    EXPECT(dense(c, 8), VPMC_OK);
+    EXPECT(load(c, 32), VPMC_E_OOM);
+    EXPECT(load(c, 8), VPMC_OK);
+    std::vector<float> w(vpmc_surrogate_param_count(), 0.01f), x(8 * 64, 0.1f), y(3 * 64, 0.1f), t(64, 1.0f);
+    EXPECT(vpmc_surrogate_set_weights(c, w.data(), (int)w.size()), VPMC_E_OOM);
+    g_room = ~(size_t)0;
+    EXPECT(vpmc_surrogate_set_weights(c, w.data(), (int)w.size()), VPMC_OK);
+    g_room = g_bytes + 100000;   // the fragments and partial gradients do not fit
+    EXPECT(vpmc_surrogate_loss_grad(c, x.data(), y.data(), t.data(), 64, w.data(), nullptr), VPMC_E_OOM);
+    g_room = ~(size_t)0;
+    EXPECT(vpmc_surrogate_loss_grad(c, x.data(), y.data(), t.data(), 64, w.data(), nullptr), VPMC_OK);
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
@@ -226,6 +245,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(name, "aperture")) aperture(c);
     else if (!strcmp(name, "slots")) slots(c);
     else if (!strcmp(name, "fallback")) fallback(c);
+    else if (!strcmp(name, "next_call")) next_call(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {
