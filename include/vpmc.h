@@ -169,8 +169,8 @@ typedef struct {
     void *hip_stream;       /* hipStream_t or NULL (default stream) */
     size_t max_device_bytes;/* 0 = no cap; scratch above the cap -> VPMC_E_OOM */
     int block_threads;      /* 0 = tuned default; else 256 or 512, for CSR output also 768 or 1024
-                               (the CSR queue runs at most 1024 threads in physics mode, 768 in
-                               straight mode, and its LDS tile shrinks with the workgroup) */
+                               (the work queue, CSR and dense, runs 1024 threads by default in physics
+                               mode, 768 in straight mode, and its LDS tile shrinks with the workgroup) */
     int grid_blocks;        /* 0 = tuned default */
     int hist_per_lane;      /* CSR work queue: a wavefront draws 64 * min(hist_per_lane, 32) particles of its
                                row at a time; 0 = default 1 */
@@ -258,8 +258,12 @@ int vpmc_run_batched(vpmc_ctx *ctx, const int *field_ids, const vpmc_spot *const
  * Candidates (CSR): hist_per_lane in {1,2,3,4,6,8} x workgroups of 1024 or
  * 512 threads (768 or 512
  * in straight mode), as many as fill every CU at its full wave occupancy;
- * (dense): {4,8,16,32} x CUs x 256 threads of work per launch in workgroups of
- * 256 or 512 threads. */
+ * (dense, base without VPMC_SURROGATE and max_device_bytes: runs through the
+ * work queue): the untuned default, which leaves grid_blocks and block_threads
+ * of *best at 0, and workgroups of 512 or 256 threads that fill every CU;
+ * (dense, base with one of them: runs batch by batch, whose tuned shape
+ * vpmc_run_spots_noalloc uses too): {4,8,16,32} x CUs x 256 threads of work per
+ * launch in workgroups of 256 or 512 threads. */
 int vpmc_autotune(vpmc_ctx *ctx, int field_id, const vpmc_spot *spots, int n_spots,
                   const vpmc_scenario *scen, const vpmc_opts *base, uint64_t sample_histories,
                   vpmc_opts *best);

@@ -113,6 +113,7 @@ struct vpmc_ctx {
     int tuned_csr_hpl = 0, tuned_csr_blocks = 0, tuned_dense_blocks = 0;
     int tuned_csr_hpl_field[VPMC_MAX_FIELDS] = {};   // per field (CSR), 0 = not tuned
     int tuned_csr_threads = 0, tuned_dense_threads = 0;
+    int tuned_dq_blocks = 0, tuned_dq_threads = 0;   // dense runs through the queue (tuned_dense_*: batch by batch)
     hipStream_t cap_stream = nullptr;   // private stream for graph capture
     // aperture surrogate
     DevBuf mlp_w, mlp_wb, mlp_m, mlp_v, mlp_g, mlp_act, mlp_io, mlp_dx, mlp_dy, mlp_dt, mlp_idx;
@@ -1567,8 +1568,8 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
 
     const QueueShape shape = queue_shape(c, o->physics,
                                          o->block_threads ? o->block_threads
-                                                          : (c->tuned_dense_threads ? c->tuned_dense_threads : 1024),
-                                         o->grid_blocks ? o->grid_blocks : c->tuned_dense_blocks);
+                                                          : (c->tuned_dq_threads ? c->tuned_dq_threads : 1024),
+                                         o->grid_blocks ? o->grid_blocks : c->tuned_dq_blocks);
     // launches: scenarios [s0, s1) x batches [b0, b1)
     struct Part {
         int s0, s1, b0, b1;
@@ -2164,16 +2165,34 @@ int vpmc_autotune(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spots
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, c->device) == hipSuccess) cus = prop.multiProcessorCount;
     const bool csr = base->output == VPMC_OUT_CSR;
+    // dense: the route that such runs take (vpmc_run_spots)
+    const bool queue = !csr && !(base->flags & VPMC_SURROGATE) && !base->max_device_bytes;
     struct Cand { int hpl, blocks, threads; };
     std::vector<Cand> cand;
+    // one resident set of workgroups: 16 waves per CU (12 in double-float mode)
+    const int waves_cu = base->physics == 0 ? 12 : 16;
+    // (put back unless the call succeeds)
+    struct Tuned {
+        vpmc_ctx *c;
+        int blocks, threads;
+        ~Tuned() {
+            c->tuned_dq_blocks = blocks;
+            c->tuned_dq_threads = threads;
+        }
+    } tuned{c, c->tuned_dq_blocks, c->tuned_dq_threads};
     if (csr) {
-        // one resident set of workgroups: 16 waves per CU (12 in double-float mode)
-        const int waves_cu = base->physics == 0 ? 12 : 16;
         for (int h : {1, 2, 3, 4, 6, 8})
             for (int t : {1024, 512}) {
                 const int tt = queue_threads(base->physics, t);
                 cand.push_back({h, std::max(1, cus * waves_cu / (tt / 64)), tt});
             }
+    } else if (queue) {
+        // the default shape (its LDS tile is the largest: water layer of 4e6
+        // histories and 16 batches 6.1 ms, 8.6 ms in workgroups of 512), then
+        // sets of the smaller workgroups that dense runs accept
+        c->tuned_dq_blocks = c->tuned_dq_threads = 0;
+        cand.push_back({0, 0, 0});
+        for (int t : {512, 256}) cand.push_back({0, std::max(1, cus * waves_cu / (t / 64)), t});
     } else {
         for (int m : {4, 8, 16, 32})
             for (int t : {256, 512}) cand.push_back({0, m * cus * 256 / t, t});
@@ -2217,6 +2236,9 @@ int vpmc_autotune(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spots
         c->tuned_csr_hpl_field[field_id] = pick.hist_per_lane;
         c->tuned_csr_blocks = pick.grid_blocks;
         c->tuned_csr_threads = pick.block_threads;
+    } else if (queue) {
+        tuned.blocks = pick.grid_blocks;
+        tuned.threads = pick.block_threads;
     } else {
         c->tuned_dense_blocks = pick.grid_blocks;
         c->tuned_dense_threads = pick.block_threads;

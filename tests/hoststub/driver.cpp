@@ -1,8 +1,9 @@
-// Failing device allocations on the CPU (test tooling): this program defines
-// the HIP runtime calls that libvpmc makes, so the library's host code runs
-// with "device" memory from calloc, kernels that do nothing, and allocations
-// that fail where a case says so.  One case per run (argv[1]); each compares
-// return codes with the documented ones.  Exit status 0 when all agree.
+// The library's host code on the CPU (test tooling): this program defines
+// the HIP runtime calls that libvpmc makes, so the host code runs with "device"
+// memory from calloc, kernels that do nothing, allocations that fail and
+// launches that are quicker where a case says so.  One case per run (argv[1]);
+// each compares return codes and launches with the documented ones.  Exit
+// status 0 when all agree.
 #include <math.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -19,7 +20,8 @@ static std::map<void *, size_t> g_live;   // allocations
 static size_t g_bytes = 0;                // their sum
 static size_t g_room = ~(size_t)0;        // device memory: what does not fit is refused
 static int g_last = 0;                    // what hipGetLastError has to say
-static unsigned long long g_launches = 0;
+static unsigned long long g_launches = 0, g_launches512 = 0;   // (those of 512 threads a workgroup)
+static bool g_quick512 = false;                                // events take half the time around such launches
 struct Dim3 {
     unsigned x, y, z;
 };
@@ -59,6 +61,7 @@ int hipLaunchKernel(const void *, Dim3 g, Dim3 b, void **, size_t, void *) {
     // the hardware's limit on a launch
     if ((unsigned long long)g.x * b.x >= 1ull << 32) return g_last = 9;
     ++g_launches;
+    g_launches512 += b.x == 512;
     return 0;
 }
 int __hipPushCallConfiguration(Dim3 g, Dim3 b, size_t shared, void *stream) {
@@ -94,11 +97,14 @@ int hipDeviceSynchronize() { return 0; }
 int hipStreamSynchronize(void *) { return 0; }
 int hipStreamCreateWithFlags(void **s, unsigned) { return *s = malloc(1), 0; }
 int hipStreamDestroy(void *s) { return free(s), 0; }
-int hipEventCreate(void **e) { return *e = malloc(1), 0; }
+int hipEventCreate(void **e) { return *e = calloc(1, sizeof g_launches512), 0; }
 int hipEventDestroy(void *e) { return free(e), 0; }
-int hipEventRecord(void *, void *) { return 0; }
+int hipEventRecord(void *e, void *) { return *(unsigned long long *)e = g_launches512, 0; }
 int hipEventSynchronize(void *) { return 0; }
-int hipEventElapsedTime(float *ms, void *, void *) { return *ms = 1.0f, 0; }
+int hipEventElapsedTime(float *ms, void *a, void *b) {
+    *ms = g_quick512 && *(unsigned long long *)a != *(unsigned long long *)b ? 0.5f : 1.0f;
+    return 0;
+}
 }
 
 // ------------------------------------------------------------- cases
@@ -237,6 +243,54 @@ static void next_call(vpmc_ctx *c) {
     EXPECT(vpmc_surrogate_loss_grad(c, x.data(), y.data(), t.data(), 64, w.data(), nullptr), VPMC_OK);
 }
 
+static int noalloc(vpmc_ctx *c) {
+    vpmc_opts o{};
+    o.physics = VPMC_PHYS_ALL;
+    o.flags = VPMC_DEVICE_PTRS;
+    double led[VPMC_NLEDGER];
+    return vpmc_run_spots_noalloc(c, 0, kSpots, 2, &kScen, 1, &o, nullptr, nullptr, led);
+}
+
+// Dense runs tuned through the work queue: the untuned default is a candidate
+// (and wins where nothing is faster), smaller workgroups come as resident sets,
+// and the pick does not shape the batch-by-batch kernel, which has its own.
+static void autotune(vpmc_ctx *c) {
+    EXPECT(load(c, 16), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, nullptr, 0, nullptr, nullptr), VPMC_OK);
+    vpmc_opts base{}, best{};
+    base.physics = VPMC_PHYS_ALL;
+    auto tune = [&](int threads, int blocks) {
+        EXPECT(vpmc_autotune(c, 0, kSpots, 2, &kScen, &base, 1000, &best), VPMC_OK);
+        EXPECT(best.block_threads, threads);
+        EXPECT(best.grid_blocks, blocks);
+        EXPECT(dense(c, 16), VPMC_OK);
+        std::vector<float> dose(16 * 16 * 16);
+        EXPECT(vpmc_run_spots(c, 0, kSpots, 2, &kScen, 1, &best, dose.data(), nullptr, nullptr, nullptr), VPMC_OK);
+    };
+    tune(0, 0);
+    g_quick512 = true;
+    tune(512, 256 * 16 / 8);
+    unsigned long long n = g_launches512;
+    EXPECT(dense(c, 16), VPMC_OK);
+    EXPECT(g_launches512 > n, true);
+    n = g_launches512;
+    EXPECT(noalloc(c), VPMC_OK);
+    EXPECT(dense(c, 16, (size_t)1 << 30), VPMC_OK);
+    EXPECT(g_launches512 == n, true);
+    g_quick512 = false;
+    tune(0, 0);
+    // the batch-by-batch route, by a cap on device memory
+    g_quick512 = true;
+    base.max_device_bytes = (size_t)1 << 30;
+    tune(512, 4 * 256 * 256 / 512);
+    n = g_launches512;
+    EXPECT(noalloc(c), VPMC_OK);
+    EXPECT(g_launches512 > n, true);
+    n = g_launches512;
+    EXPECT(dense(c, 16), VPMC_OK);
+    EXPECT(g_launches512 == n, true);
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
@@ -246,6 +300,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(name, "slots")) slots(c);
     else if (!strcmp(name, "fallback")) fallback(c);
     else if (!strcmp(name, "next_call")) next_call(c);
+    else if (!strcmp(name, "autotune")) autotune(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {

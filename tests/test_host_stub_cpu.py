@@ -1,7 +1,8 @@
-"""Device allocations that fail, on the CPU: tests/hoststub/driver.cpp runs the
-library's host code over a HIP runtime of its own (memory from calloc, kernels
-that do nothing, allocations refused where a case says so) and compares return
-codes with the documented ones."""
+"""The library's host code on the CPU: tests/hoststub/driver.cpp runs it over a
+HIP runtime of its own (memory from calloc, kernels that do nothing, allocations
+refused and launches timed as a case says) and compares return codes and
+launches with the documented ones: device allocations that fail, and the shapes
+that tuning picks."""
 import os
 import subprocess
 
@@ -9,7 +10,7 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2307_01416_amd")
-CASES = ["geometry", "aperture", "slots", "fallback", "next_call"]
+CASES = ["geometry", "aperture", "slots", "fallback", "next_call", "autotune"]
 
 
 @pytest.fixture(scope="module")
@@ -26,6 +27,6 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case", CASES)
-def test_failed_allocations(driver, case):
+def test_host_code(driver, case):
     r = subprocess.run([driver, case], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, f"{r.returncode}\n{r.stdout}\n{r.stderr}"
