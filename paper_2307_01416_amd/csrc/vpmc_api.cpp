@@ -1566,10 +1566,11 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
     }
     auto items_of = [&](int b) { return off[(size_t)b * (n_spots + 1) + n_spots]; };
 
-    const QueueShape shape = queue_shape(c, o->physics,
-                                         o->block_threads ? o->block_threads
-                                                          : (c->tuned_dq_threads ? c->tuned_dq_threads : 1024),
-                                         o->grid_blocks ? o->grid_blocks : c->tuned_dq_blocks);
+    const int threads = o->block_threads ? o->block_threads : (c->tuned_dq_threads ? c->tuned_dq_threads : 1024);
+    QueueShape shape = queue_shape(c, o->physics, threads, 0);   // as many workgroups as run at once
+    // (more only wait their turn: a million of 256 threads took a run of 3 ms to 16)
+    const int blocks = o->grid_blocks ? o->grid_blocks : c->tuned_dq_blocks;
+    if (blocks) shape.blocks = std::min(shape.blocks, blocks);
     // launches: scenarios [s0, s1) x batches [b0, b1)
     struct Part {
         int s0, s1, b0, b1;

@@ -291,6 +291,15 @@ static void autotune(vpmc_ctx *c) {
     EXPECT(g_launches512 == n, true);
 }
 
+// any grid_blocks that the argument checks accept: a dense run launches no more
+// workgroups than run at once (what a launch can hold, with their staging)
+static void blocks(vpmc_ctx *c) {
+    EXPECT(load(c, 16), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, nullptr, 0, nullptr, nullptr), VPMC_OK);
+    for (int b : {1, 37, 1 << 20, 1 << 24, 0x7fffffff}) EXPECT(dense(c, 16, 0, 0, b), VPMC_OK);
+    for (int b : {1, 37, 1 << 20, 1 << 24, 0x7fffffff}) EXPECT(dense(c, 16, (size_t)1 << 30, 0, b), VPMC_OK);
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
@@ -301,6 +310,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(name, "fallback")) fallback(c);
     else if (!strcmp(name, "next_call")) next_call(c);
     else if (!strcmp(name, "autotune")) autotune(c);
+    else if (!strcmp(name, "blocks")) blocks(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {
