@@ -1537,6 +1537,7 @@ std::vector<uint32_t> spatial_order(const vpmc_spot *spots, int n) {
 
 constexpr size_t kBatchGridBytes = (size_t)8 << 30;   // batch tallies resident at once
 constexpr int kDenseTile = 16384;                     // items of a dense row, at most
+constexpr unsigned long long kDenseRows = 1ull << 20;  // ... up to this many rows (64 MB of them)
 
 // Dense run through the work queue: rows are ranges of a batch's items in one
 // scenario, and all batches (as many as kBatchGridBytes of tallies hold) and
@@ -1599,9 +1600,11 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
         unsigned long long tot = 0;
         for (int b = p.b0; b < p.b1; ++b) tot += items_of(b);
         tot *= (unsigned long long)(p.s1 - p.s0);
-        // about two rows per workgroup, of 512 to kDenseTile items
+        // about two rows per workgroup, of 512 to kDenseTile items; longer ones
+        // where there would be more than kDenseRows
         const unsigned long long want = tot / (2ull * (unsigned long long)shape.blocks);
-        const unsigned long long T = std::min<unsigned long long>(kDenseTile, std::max<unsigned long long>(512, (want + 63) / 64 * 64));
+        unsigned long long T = std::min<unsigned long long>(kDenseTile, std::max<unsigned long long>(512, (want + 63) / 64 * 64));
+        T = std::max(T, std::min(0xffffffc0ull, (tot / kDenseRows + 63) / 64 * 64));
         p.goff.push_back(0);
         for (int s = p.s0; s < p.s1; ++s)
             for (int b = p.b0; b < p.b1; ++b)

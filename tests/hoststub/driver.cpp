@@ -8,6 +8,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
+#include <sys/resource.h>
 
 #include <map>
 #include <vector>
@@ -300,6 +301,25 @@ static void blocks(vpmc_ctx *c) {
     for (int b : {1, 37, 1 << 20, 1 << 24, 0x7fffffff}) EXPECT(dense(c, 16, (size_t)1 << 30, 0, b), VPMC_OK);
 }
 
+// 1.1e12 histories in one dense run: the host's tables stay small
+static void many_histories(vpmc_ctx *c) {
+    EXPECT(load(c, 8), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, nullptr, 0, nullptr, nullptr), VPMC_OK);
+    std::vector<vpmc_spot> sp(256, kSpots[0]);
+    for (vpmc_spot &s : sp) s.n_histories = 0xffffffffu;
+    std::vector<float> dose(8 * 8 * 8);
+    vpmc_opts o{};
+    o.physics = VPMC_PHYS_ALL;
+    g_room = g_bytes + ((size_t)256 << 20);
+    EXPECT(vpmc_run_spots(c, 0, sp.data(), 256, &kScen, 1, &o, dose.data(), nullptr, nullptr, nullptr), VPMC_OK);
+    struct rusage u;
+    getrusage(RUSAGE_SELF, &u);
+    if (u.ru_maxrss > 1 << 20) {   // (kB)
+        fprintf(stderr, "the run took %ld MB of host memory\n", u.ru_maxrss / 1024);
+        fails++;
+    }
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
@@ -311,6 +331,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(name, "next_call")) next_call(c);
     else if (!strcmp(name, "autotune")) autotune(c);
     else if (!strcmp(name, "blocks")) blocks(c);
+    else if (!strcmp(name, "many_histories")) many_histories(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {
