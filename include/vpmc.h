@@ -175,7 +175,8 @@ typedef struct {
     int hist_per_lane;      /* CSR work queue: a wavefront draws 64 * min(hist_per_lane, 32) particles of its
                                row at a time; 0 = default 1 */
     int max_slots;          /* CSR rows resident at once (<= 1024); 0 = sized from memory */
-    uint64_t queue_cap;     /* CSR work queue: iterations (draws, row picks, waits) a
+    uint64_t queue_cap;     /* CSR work queue: iterations (draws, a default one counting as a
+                               quarter, row picks, waits) a
                                wavefront may make before it gives up and the run returns
                                VPMC_E_ABORTED with no rows written; 0 = 2^40 (no practical cap) */
 } vpmc_opts;

@@ -428,11 +428,12 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     }
     hipStream_t st = (hipStream_t)o->hip_stream;
     // histories per lane: the caller's, else the one tuned for a field, else
-    // the last tuned one, else 1 (per epoch: the field with most of its rows)
+    // the last tuned one, else 0 for the default (per epoch: the field with most
+    // of its rows)
     auto field_hpl = [&](uint32_t field_id) {
         if (o->hist_per_lane > 0) return o->hist_per_lane;
         if (field_id < VPMC_MAX_FIELDS && c->tuned_csr_hpl_field[field_id]) return c->tuned_csr_hpl_field[field_id];
-        return c->tuned_csr_hpl ? c->tuned_csr_hpl : 1;
+        return c->tuned_csr_hpl;
     };
     int rc;
 
@@ -658,7 +659,10 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
         QueueDev Qe = Q;
         Qe.row_begin = e * G;
         Qe.n_rows = std::min(R, (e + 1) * G) - e * G;
-        Qe.hist_per_lane = ep_hpl[e];
+        Qe.hist_per_lane = std::max(1, ep_hpl[e]);
+        // a default draw (64 records) is a quarter of an iteration: callers
+        // choose queue_cap by chunks of 256 histories
+        Qe.draw_mask = ep_hpl[e] ? 0u : 3u;
         return Qe;
     };
     // beam line and patient transport of an epoch, round by round

@@ -1996,10 +1996,12 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
     RowCtl *const ctl = Q.ctl + Q.row_begin;
     const uint32_t draw_n = 64u * (uint32_t)min(Q.hist_per_lane, kStageHpl);   // (few enough for the 32-bit counters)
     unsigned long long iters = 0;
+    uint32_t drawn = 0;
+    auto drew = [&]() { iters += (++drawn & Q.draw_mask) == 0u ? 1 : 0; };
     for (;;) {
         // ---- bounded queue: a wavefront that has made iter_cap iterations
-        // (draws, row picks, waits) leaves and reports it; it holds no row
-        // pick and no tile here, so the other waves finish as before
+        // (draws by drew(), row picks, waits) leaves and reports it; it holds
+        // no row pick and no tile here, so the other waves finish as before
         if (++iters > Q.iter_cap) {
             if (lane == 0) atomicOr(Q.flags, kFlagAborted);
             break;
@@ -2064,6 +2066,8 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
             }
             continue;
         }
+        --iters;   // (not a pick or a wait)
+        drew();
         const uint32_t rl = cur;
         const RowDev row = Q.rows[Q.row_begin + rl];
         float scale = DENSE ? 0.0f : Q.spots[row.spot_global].scale;   // (dense rows: per lane)
@@ -2141,11 +2145,12 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
             const unsigned long long idle = __ballot(!active);
             const uint32_t nidle = (uint32_t)__popcll(idle);
             if (next >= end && end < n_staged && nidle >= (uint32_t)Q.refill_min) {
-                if (++iters > Q.iter_cap) {   // no further draw: the lanes in flight finish, then the wave leaves
+                if (iters >= Q.iter_cap) {   // no further draw: the lanes in flight finish, then the wave leaves
                     n_staged = end;
                 } else {
                     draw();
                     if (next >= end) n_staged = end = next = 0;   // the row is exhausted
+                    else drew();
                 }
             }
             // a wave that started beside the previous row's stragglers gets
