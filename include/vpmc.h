@@ -167,7 +167,12 @@ typedef struct {
     int fixed_point_bits;   /* 0: automatic; else k in [1, 62] */
     unsigned flags;         /* VPMC_DEVICE_PTRS */
     void *hip_stream;       /* hipStream_t or NULL (default stream) */
-    size_t max_device_bytes;/* 0 = no cap; scratch above the cap -> VPMC_E_OOM */
+    size_t max_device_bytes;/* 0 = no cap; scratch above the cap -> VPMC_E_OOM.  Held against it: tables, CT
+                               numbers, apertures, network and what runs, the optimiser and the cell merge
+                               keep on the context; not the densities made from the CT numbers (4 B per
+                               voxel and two slabs), 4 B per cell of an aperture's raster, the structure
+                               masks kept for VPMC_OPT_REUSE (1 B per voxel) and the training step's
+                               weight fragments and partial gradients (14 MB) */
     int block_threads;      /* 0 = tuned default; else 256 or 512, for CSR output also 768 or 1024
                                (the work queue, CSR and dense, runs 1024 threads by default in physics
                                mode, 768 in straight mode, and its LDS tile shrinks with the workgroup) */

@@ -46,7 +46,7 @@ bool finite3(const float *v) { return isfinite(v[0]) && isfinite(v[1]) && isfini
 
 struct DevBuf {
     void *ptr = nullptr;
-    size_t cap = 0;
+    size_t cap = 0, counted = 0;   // bytes, and those that max_device_bytes is held against
 };
 
 struct FieldState {
@@ -83,7 +83,7 @@ struct vpmc_ctx {
     bool has_geom = false;
     GeomDev geom{};
     DevBuf hu_buf;
-    DevBuf rho_buf;   // densities derived from the CT numbers (not counted against max_device_bytes)
+    DevBuf rho_buf;   // densities derived from the CT numbers (not counted)
     size_t nvox = 0;
     FieldState fields[VPMC_MAX_FIELDS];
     // scratch (grow-only)
@@ -117,7 +117,7 @@ struct vpmc_ctx {
     hipStream_t cap_stream = nullptr;   // private stream for graph capture
     // aperture surrogate
     DevBuf mlp_w, mlp_wb, mlp_m, mlp_v, mlp_g, mlp_act, mlp_io, mlp_dx, mlp_dy, mlp_dt, mlp_idx;
-    DevBuf mlp_part;   // weight fragments and partial gradients (not counted against max_device_bytes)
+    DevBuf mlp_part;   // weight fragments and partial gradients (not counted)
     bool mlp_ready = false;
     int mlp_step = 0;
     DevBuf sur_rec, sur_cnt, sur_out;
@@ -131,7 +131,7 @@ struct vpmc_ctx {
     DevBuf opt_rp, opt_col, opt_val, opt_roi, opt_amax, opt_cnt, opt_rcnt, opt_crp, opt_ccol, opt_cval, opt_piece,
         opt_poff, opt_fpart, opt_gpart, opt_vec, opt_scal, opt_err, opt_hist, opt_dose, opt_mask, opt_sroi,
         opt_rstruct;
-    DevBuf opt_keep;   // the index's structure masks (not counted against max_device_bytes)
+    DevBuf opt_keep;   // the index's structure masks (not counted)
     long long opt_npieces = 0;
     int opt_nstruct = 0, opt_bits = 0;
     // dynamic voxel spacing (vpmc_csr_cells)
@@ -147,28 +147,28 @@ namespace {
 
 int mlp_buffers(vpmc_ctx *c, int cap, MlpStep *S);
 
-int ensure(vpmc_ctx *c, DevBuf &b, size_t bytes, size_t cap_limit) {
+int ensure(vpmc_ctx *c, DevBuf &b, size_t bytes, size_t cap_limit, size_t counted) {
     if (bytes <= b.cap) return VPMC_OK;
-    const size_t grow = bytes - b.cap;
-    if (cap_limit && c->bytes + grow > cap_limit)
-        return fail(VPMC_E_OOM, "scratch of %zu bytes exceeds max_device_bytes=%zu", c->bytes + grow,
+    if (cap_limit && c->bytes - b.counted + counted > cap_limit)
+        return fail(VPMC_E_OOM, "scratch of %zu bytes exceeds max_device_bytes=%zu", c->bytes - b.counted + counted,
                     cap_limit);
     if (b.ptr) {
         HIP_TRY(hipFree(b.ptr));
-        c->bytes -= b.cap;
-        b.ptr = nullptr;
-        b.cap = 0;
+        c->bytes -= b.counted;
+        b = DevBuf{};
     }
     HIP_TRY(hipMalloc(&b.ptr, bytes));
     b.cap = bytes;
-    c->bytes += bytes;
+    b.counted = counted;
+    c->bytes += counted;
     return VPMC_OK;
 }
 
+int ensure(vpmc_ctx *c, DevBuf &b, size_t bytes, size_t cap_limit) { return ensure(c, b, bytes, cap_limit, bytes); }
+
 void release(DevBuf &b) {
     if (b.ptr) (void)hipFree(b.ptr);
-    b.ptr = nullptr;
-    b.cap = 0;
+    b = DevBuf{};
 }
 
 double cross2(double ax, double ay, double bx, double by) { return ax * by - ay * bx; }
@@ -308,7 +308,7 @@ struct BatchField {
 
 int grow_keep(vpmc_ctx *c, DevBuf &b, size_t keep_bytes, size_t bytes, size_t cap_limit, hipStream_t st) {
     if (bytes <= b.cap) return VPMC_OK;
-    if (cap_limit && c->bytes + (bytes - b.cap) > cap_limit)
+    if (cap_limit && c->bytes - b.counted + bytes > cap_limit)
         return fail(VPMC_E_OOM, "CSR storage of %zu bytes exceeds max_device_bytes", bytes);
     void *p = nullptr;
     HIP_TRY(hipMalloc(&p, bytes));
@@ -316,10 +316,10 @@ int grow_keep(vpmc_ctx *c, DevBuf &b, size_t keep_bytes, size_t bytes, size_t ca
         if (keep_bytes) HIP_TRY(hipMemcpyAsync(p, b.ptr, keep_bytes, hipMemcpyDeviceToDevice, st));
         HIP_TRY(hipStreamSynchronize(st));
         HIP_TRY(hipFree(b.ptr));
-        c->bytes -= b.cap;
+        c->bytes -= b.counted;
     }
     b.ptr = p;
-    b.cap = bytes;
+    b.cap = b.counted = bytes;
     c->bytes += bytes;
     return VPMC_OK;
 }
@@ -386,7 +386,7 @@ int trim_scratch(vpmc_ctx *c) {
     if (!c->uncapped) return VPMC_OK;
     for (DevBuf *b : {&c->q_stage, &c->q_ctl, &c->rows, &c->grp_off, &c->heads, &c->dense_args, &c->qbatch}) {
         if (b->ptr) HIP_TRY(hipFree(b->ptr));
-        c->bytes -= b->cap;
+        c->bytes -= b->counted;
         *b = DevBuf{};
     }
     c->qbatch_zero = 0;
@@ -865,10 +865,7 @@ int mlp_buffers(vpmc_ctx *c, int cap, MlpStep *S) {
     int rc = ensure(c, c->mlp_act, bytes, 0);
     if (rc) return rc;
     const size_t part = mlp_frag_bytes() + (size_t)kMlpSplit * np * 4;
-    if (c->mlp_part.cap < part) {
-        HIP_TRY(hipMalloc(&c->mlp_part.ptr, part));
-        c->mlp_part.cap = part;
-    }
+    if ((rc = ensure(c, c->mlp_part, part, 0, 0))) return rc;
     char *p = (char *)c->mlp_act.ptr;
     char *const end = p + c->mlp_act.cap;
     auto take = [&](size_t k) { char *q = p; p += (k + 255) & ~(size_t)255; return (void *)q; };
@@ -1277,11 +1274,7 @@ int vpmc_load_geometry(vpmc_ctx *c, int kind, const int16_t *hu, int nx, int ny,
                           (flags & VPMC_DEVICE_PTRS) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice));
         g.hu = (const int16_t *)c->hu_buf.ptr;
         const size_t margin = (size_t)nx * ny, total = nvox + 2 * margin;
-        if (c->rho_buf.cap < total * sizeof(float)) {
-            release(c->rho_buf);
-            HIP_TRY(hipMalloc(&c->rho_buf.ptr, total * sizeof(float)));
-            c->rho_buf.cap = total * sizeof(float);
-        }
+        if ((rc = ensure(c, c->rho_buf, total * sizeof(float), 0, 0))) return rc;
         float *rho = (float *)c->rho_buf.ptr;
         HIP_TRY(hipMemset(rho, 0, margin * sizeof(float)));
         HIP_TRY(hipMemset(rho + margin + nvox, 0, margin * sizeof(float)));
@@ -1377,12 +1370,11 @@ int vpmc_set_aperture(vpmc_ctx *c, int field_id, const vpmc_beam *beam, const fl
         HIP_TRY(hipMemcpy(f.poly_buf.ptr, poly.data(), poly.size() * sizeof(float2), hipMemcpyHostToDevice));
         if (ras.nx > 0) {
             const size_t cells = (size_t)ras.nx * ras.ny;
-            const size_t had = f.cell_buf.cap;   // the two counters stand behind the cells
+            // (the two counters stand behind the cells; one offset a cell is counted)
             if ((rc = ensure(c, f.sdf_buf, cells * sizeof(float), 0)) ||
-                (rc = ensure(c, f.cell_buf, (cells + 2) * sizeof(uint2), 0)))
+                (rc = ensure(c, f.cell_buf, (cells + 2) * sizeof(uint2), 0, (cells + 2) * sizeof(uint32_t))) ||
+                (rc = ensure(c, f.cell_ref_buf, cells * sizeof(float2), 0)))
                 return rc;
-            c->bytes -= (f.cell_buf.cap - had) / 2;   // max_device_bytes counts one offset a cell
-            if ((rc = ensure(c, f.cell_ref_buf, cells * sizeof(float2), 0))) return rc;
             ras.poly = (const float2 *)f.poly_buf.ptr;
             ras.nv = (int)poly.size();
             ras.radius = kListRadius;
@@ -2412,9 +2404,7 @@ int vpmc_optimize(vpmc_ctx *c, const int64_t *row_ptr, const int32_t *col, const
     if ((rc = ensure(c, c->opt_hist, ((size_t)p->iters + 1) * 8, 0))) return rc;
     if (c->opt_keep.cap < (size_t)nvox) {
         c->opt_valid = false;
-        release(c->opt_keep);
-        HIP_TRY(hipMalloc(&c->opt_keep.ptr, (size_t)nvox));
-        c->opt_keep.cap = (size_t)nvox;
+        if ((rc = ensure(c, c->opt_keep, (size_t)nvox, 0, 0))) return rc;
     }
     OptMask *mask = (OptMask *)c->opt_mask.ptr;
     unsigned long long *vcnt = (unsigned long long *)(mask + n_words), *voff = vcnt + n_vblk;

@@ -320,6 +320,36 @@ static void many_histories(vpmc_ctx *c) {
     }
 }
 
+// smallest max_device_bytes that lets a dense run through
+static size_t least_cap(vpmc_ctx *c, int n) {
+    for (size_t cap = (size_t)n * n * n * 8; cap < (size_t)64 << 20; cap += 256)
+        if (dense(c, n, cap) == VPMC_OK) return cap;
+    return 0;
+}
+
+// what max_device_bytes is held against does not drift with allocations that
+// failed before
+static void counted(vpmc_ctx *c) {
+    const vpmc_block blk = {30.0f, 8.5f, 50.0f};
+    const std::vector<float> small = circle(16, 30.0f), large = circle(1000, 90.0f);
+    EXPECT(load(c, 8), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, small.data(), 16, &blk, nullptr), VPMC_OK);
+    g_room = g_bytes + 1200000;   // the distances of the larger raster fit, its cells do not
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, large.data(), 1000, &blk, nullptr), VPMC_E_OOM);
+    g_room = ~(size_t)0;
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, large.data(), 1000, &blk, nullptr), VPMC_OK);
+    vpmc_ctx *d = nullptr;
+    EXPECT(vpmc_create(&d, 0), VPMC_OK);
+    EXPECT(load(d, 8), VPMC_OK);
+    EXPECT(vpmc_set_aperture(d, 0, &kBeam, large.data(), 1000, &blk, nullptr), VPMC_OK);
+    const size_t a = least_cap(c, 8), b = least_cap(d, 8);
+    if (!a || a != b) {
+        fprintf(stderr, "least cap %zu after a failed call, %zu without one\n", a, b);
+        fails++;
+    }
+    vpmc_destroy(d);
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
@@ -332,6 +362,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(name, "autotune")) autotune(c);
     else if (!strcmp(name, "blocks")) blocks(c);
     else if (!strcmp(name, "many_histories")) many_histories(c);
+    else if (!strcmp(name, "counted")) counted(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {

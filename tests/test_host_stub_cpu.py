@@ -10,7 +10,8 @@ import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PKG = os.path.join(ROOT, "paper_2307_01416_amd")
-CASES = ["geometry", "aperture", "slots", "fallback", "next_call", "autotune", "blocks", "many_histories"]
+CASES = ["geometry", "aperture", "slots", "fallback", "next_call", "autotune", "blocks", "many_histories",
+         "counted"]
 
 
 @pytest.fixture(scope="module")
