@@ -1757,8 +1757,9 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
             long long *tally = (long long *)c->tallies.ptr + (size_t)s * nvox;
             float *dd = dose_gy ? (dev_out ? dose_gy + (size_t)s * nvox : (float *)c->stage_dose.ptr) : nullptr;
             float *ss = sigma_gy ? (dev_out ? sigma_gy + (size_t)s * nvox : (float *)c->stage_sigma.ptr) : nullptr;
-            unsigned long long *qb = (unsigned long long *)c->qbatch.ptr +
-                                     (size_t)(s - p.s0) * (size_t)(p.b1 - p.b0) * (grid_bytes / 8);
+            unsigned long long *qb =
+                folded ? (unsigned long long *)c->qbatch.ptr + (size_t)(s - p.s0) * (size_t)(p.b1 - p.b0) * (grid_bytes / 8)
+                       : nullptr;
             long long *let = want_let ? (long long *)c->let_tallies.ptr + (size_t)s * nvox : nullptr;
             if (whole) {
                 HIP_TRY(launch_fold_dose(qb, B, tally, let, c->geom, mev_scale, dd, ss, nvox, st));

@@ -350,6 +350,42 @@ static void counted(vpmc_ctx *c) {
     vpmc_destroy(d);
 }
 
+// dense and matrix runs of every choice of batches, scenarios, outputs and
+// processes, from no spots on (for the sanitizers)
+static void outputs(vpmc_ctx *c) {
+    const vpmc_block blk = {30.0f, 8.5f, 50.0f};
+    const std::vector<float> poly = circle(16, 5.0f);
+    EXPECT(load(c, 8), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, poly.data(), 16, &blk, nullptr), VPMC_OK);
+    const std::vector<vpmc_scenario> sc(5, kScen);
+    for (int n : {0, 1, 65})
+        for (int batches : {0, 2, 16, 1024})
+            for (int S : {5, 1})
+                for (unsigned flags : {0u, (unsigned)VPMC_LET, (unsigned)VPMC_DEVICE_PTRS})
+                    for (unsigned physics : {0u, (unsigned)VPMC_PHYS_ALL}) {
+                        std::vector<vpmc_spot> sp(n, kSpots[0]);
+                        for (int i = 0; i < n; ++i) {
+                            sp[i].n_histories = (uint32_t)(i * 37 % 300);
+                            sp[i].x_mm = i == 3 ? 1e30f : i * 7.0f - 200.0f;
+                        }
+                        std::vector<float> dose(512 * S), sigma(512 * S);
+                        std::vector<double> led(VPMC_NLEDGER * S);
+                        std::vector<int64_t> rp((size_t)n * S + 1);
+                        vpmc_opts o{};
+                        o.physics = physics;
+                        o.n_batches = batches;
+                        o.flags = flags;
+                        EXPECT(vpmc_run_spots(c, 0, sp.data(), n, sc.data(), S, &o, dose.data(),
+                                              batches ? sigma.data() : nullptr, led.data(), nullptr), VPMC_OK);
+                        o.flags &= ~VPMC_LET;
+                        o.n_batches = 0;
+                        o.output = VPMC_OUT_CSR;
+                        o.max_slots = batches ? 3 : 0;
+                        EXPECT(vpmc_run_spots(c, 0, sp.data(), n, sc.data(), S, &o, nullptr, nullptr, led.data(),
+                                              rp.data()), VPMC_OK);
+                    }
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
@@ -363,6 +399,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(name, "blocks")) blocks(c);
     else if (!strcmp(name, "many_histories")) many_histories(c);
     else if (!strcmp(name, "counted")) counted(c);
+    else if (!strcmp(name, "outputs")) outputs(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {
