@@ -194,6 +194,12 @@ typedef struct {
  *   sigma_gy  [n_scen][nvox] FP32 standard error (needs n_batches >= 2) or NULL
  *   ledger_mev[n_scen][6]    FP64 energy balance (weighted MeV) or NULL; always
  *                            host memory
+ *   Without a cap on device memory (and without VPMC_SURROGATE) such a run
+ *   stages its particles (up to 2 GiB) and keeps a grid per batch and scenario
+ *   (up to 8 GiB); both stay on the context, for the next run, until a run with
+ *   max_device_bytes or vpmc_destroy gives them back.  With a cap, however
+ *   large, it runs batch by batch in the least memory, three to eight times
+ *   slower.
  * CSR mode: row_ptr [n_scen*n_spots + 1] (row = scen*n_spots + spot) is
  *   filled; the total number of non-zeros is row_ptr[n_scen*n_spots]; then
  *   call vpmc_copy_csr.  dose_gy/sigma_gy may be NULL.

@@ -2,8 +2,9 @@
 //
 // One lane carries one VP history at a time (Methods A: every VP, primary or
 // secondary, follows the same model, so lanes of a wavefront run the same
-// code).  Per launch each workgroup stages the 32 KiB of physics tables and
-// the aperture polygon in LDS.  The step loop is FP32; the VP energy is kept
+// code).  Each workgroup stages the physics tables of the materials it meets
+// (17 to 51 KB by kernel) and, where the beam line runs, the aperture polygon in
+// LDS.  The step loop is FP32; the VP energy is kept
 // as an unevaluated FP32 pair so per-step losses telescope without drift;
 // every deposit is converted to int64 fixed point and added with a 64-bit
 // atomic, which makes the tally independent of execution order.
@@ -229,12 +230,6 @@ __device__ __forceinline__ float node_lerp(const float *y, NodePos p) {
     return fmaf(p.f, y[p.i + 1] - y[p.i], y[p.i]);
 }
 
-// Energy lost while traversing r (density x mm), starting at E = E_i + x in
-// segment i of the piecewise-linear CSDA relation E(R), whose range within
-// the segment is rem = x / slope_i.  Whole segments crossed contribute their
-// exact energy width; the last partial segment r * slope_j.  All in pairs.
-
-
 __device__ __forceinline__ void rotate_dir(Lane &v, float ax, float ay) {
     const float th2 = ax * ax + ay * ay;
     if (th2 == 0.0f) return;
@@ -345,6 +340,10 @@ __device__ __forceinline__ void sub_energy(Lane &v, DF dE) {
     v.Elo = e.l;
 }
 
+// Energy lost while traversing r (density x mm), starting at E = E_i + x in
+// segment i of the piecewise-linear CSDA relation E(R), whose range within
+// the segment is rem = x / slope_i.  Whole segments crossed contribute their
+// exact energy width; the last partial segment r * slope_j.  All in pairs.
 // tm: the material's high tables, tl: its low tables (read only when X).  The
 // walk ends at the latest at index -1, whose width is infinite and slope zero.
 template <bool X>
@@ -1975,8 +1974,8 @@ __global__ __launch_bounds__(256) void tile_box_kernel(GeomDev g, QueueDev Q, Ro
 // replacing the current row, which does so without waiting on anyone.
 template <bool X, int P, bool DENSE, bool LET>
 // Physics mode: up to 1024 threads (16 waves at <= 128 VGPRs, one workgroup
-// per CU with a ~120 KiB tile); double-float mode: up to 768 (12 waves at
-// <= 168 VGPRs).
+// per CU with a ~120 KiB tile); double-float mode: up to 768 (12 waves; its 99 to
+// 110 VGPRs would leave room for 16).
 __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueDev Q) {
     __shared__ __attribute__((aligned(16))) float hi[tab_hi_floats(3)], lo[X ? tab_lo_floats(3) : 4];
     __shared__ unsigned long long s_row;    // current row (high word; kRowNone while replaced)
@@ -3242,8 +3241,10 @@ hipError_t launch_tile_box(const GeomDev &g, const QueueDev &Q, RowDev *rows, hi
     return hipGetLastError();
 }
 
-// beam line of a round: a resident set of workgroups (3 of 256 threads per
-// CU), each wave striding over runs of Q.beam_groups groups
+// beam line of a round: up to 3 workgroups of 256 threads per CU, which is a
+// resident set in physics mode (52 to 54 KB of LDS each; with the low tables of
+// the double-float mode it is 60 to 62, two fit and the third runs behind them),
+// each wave striding over runs of Q.beam_groups groups
 hipError_t launch_beam(const GeomDev &g, QueueDev Q, int cus, hipStream_t s) {
     const unsigned long long groups = Q.g_end - Q.g_begin;
     if (groups == 0) return hipSuccess;
