@@ -1440,10 +1440,21 @@ __device__ __forceinline__ int find_spot(const unsigned long long *off, int n, u
     return lo;
 }
 
+// LDS of the kernels that run a whole history, all tables and the aperture's
+// vertices: the vertices are allocated by the launch, as many as there are.  With
+// up to 256 of them four workgroups of 256 threads fit a CU in physics mode and
+// three in double-float mode; with room for 1024 in every workgroup it was three
+// and two, and a run of 1.5e5 to 2.6e5 histories took a second round of them
+// (10 mm opening: 2.3e5 histories 1.13 ms against 0.83, without processes 1.5e5
+// 0.77 against 0.50).
+constexpr int whole_lds(bool x) { return (TAB_HI_FLOATS + (x ? tab_lo_floats(NMAT) : 0)) * 4; }
+static_assert(4 * (whole_lds(false) + 256 * 8) <= 160 * 1024, "four workgroups a CU");
+static_assert(3 * (whole_lds(true) + 256 * 8) <= 160 * 1024, "three workgroups a CU");
+
 template <bool X>
 __global__ __launch_bounds__(512) void transport_kernel(GeomDev g, FieldDev f, LaunchDev L) {
-    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS], lo[X ? tab_lo_floats(NMAT) : 4];
-    __shared__ float2 poly[POLY_LDS];
+    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS], lo[X ? tab_lo_floats(NMAT) : 1];
+    extern __shared__ __attribute__((aligned(16))) float2 poly[];   // f.nv with a block
     stage_tables<X, NMAT>(hi, lo, L.tables, 0);
     const Tabs T{hi, lo, DM_PMMA, DM_BRASS};
     if (f.has_block)
@@ -2854,8 +2865,8 @@ template <bool X>
 __global__ __launch_bounds__(256) void sur_resume_kernel(GeomDev g, FieldDev f, LaunchDev L, const DeferRec *rec,
                                                          const float *out, unsigned long long n, float p_lo,
                                                          float p_hi) {
-    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS], lo[X ? tab_lo_floats(NMAT) : 4];
-    __shared__ float2 poly[POLY_LDS];
+    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS], lo[X ? tab_lo_floats(NMAT) : 1];
+    extern __shared__ __attribute__((aligned(16))) float2 poly[];
     stage_tables<X, NMAT>(hi, lo, L.tables, 0);
     const Tabs T{hi, lo, DM_PMMA, DM_BRASS};
     for (int i = threadIdx.x; i < f.nv; i += blockDim.x) poly[i] = f.poly[i];
@@ -2882,8 +2893,8 @@ template <bool X>
 __global__ __launch_bounds__(256) void sur_resume_csr_kernel(GeomDev g, QueueDev Q, const DeferRec *rec,
                                                              const float *out, unsigned long long n, float p_lo,
                                                              float p_hi) {
-    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS], lo[X ? tab_lo_floats(NMAT) : 4];
-    __shared__ float2 poly[POLY_LDS];
+    __shared__ __attribute__((aligned(16))) float hi[TAB_HI_FLOATS], lo[X ? tab_lo_floats(NMAT) : 1];
+    extern __shared__ __attribute__((aligned(16))) float2 poly[];
     stage_tables<X, NMAT>(hi, lo, Q.tables, 0);
     const Tabs T{hi, lo, DM_PMMA, DM_BRASS};
     for (int i = threadIdx.x; i < Q.n_poly_total; i += blockDim.x) poly[i] = Q.polys[i];
@@ -3190,9 +3201,10 @@ __global__ __launch_bounds__(256) void fold_dose_kernel(unsigned long long *qb, 
 hipError_t launch_transport(const GeomDev &g, const FieldDev &f, const LaunchDev &L, int blocks,
                             int threads, hipStream_t s) {
     if (threads != 256 && threads != 512) threads = kThreads;
+    const size_t lds = f.has_block ? (size_t)f.nv * sizeof(float2) : 0;
     // deterministic mode: the double-float instantiation
-    if (L.physics == 0) hipLaunchKernelGGL(transport_kernel<true>, dim3(blocks), dim3(threads), 0, s, g, f, L);
-    else hipLaunchKernelGGL(transport_kernel<false>, dim3(blocks), dim3(threads), 0, s, g, f, L);
+    if (L.physics == 0) hipLaunchKernelGGL(transport_kernel<true>, dim3(blocks), dim3(threads), lds, s, g, f, L);
+    else hipLaunchKernelGGL(transport_kernel<false>, dim3(blocks), dim3(threads), lds, s, g, f, L);
     return hipGetLastError();
 }
 
@@ -3398,20 +3410,22 @@ hipError_t launch_cell_emit(const long long *rp, const CellPiece *pcs, long long
 hipError_t launch_sur_resume(const GeomDev &g, const FieldDev &f, const LaunchDev &L, const DeferRec *rec,
                              const float *out, unsigned long long n, float p_lo, float p_hi, hipStream_t s) {
     const int blocks = (int)std::max<unsigned long long>(1, std::min<unsigned long long>((n + 255) / 256, 4096));
+    const size_t lds = (size_t)f.nv * sizeof(float2);
     if (L.physics == 0)
-        hipLaunchKernelGGL(sur_resume_kernel<true>, dim3(blocks), dim3(256), 0, s, g, f, L, rec, out, n, p_lo, p_hi);
+        hipLaunchKernelGGL(sur_resume_kernel<true>, dim3(blocks), dim3(256), lds, s, g, f, L, rec, out, n, p_lo, p_hi);
     else
-        hipLaunchKernelGGL(sur_resume_kernel<false>, dim3(blocks), dim3(256), 0, s, g, f, L, rec, out, n, p_lo, p_hi);
+        hipLaunchKernelGGL(sur_resume_kernel<false>, dim3(blocks), dim3(256), lds, s, g, f, L, rec, out, n, p_lo, p_hi);
     return hipGetLastError();
 }
 
 hipError_t launch_sur_resume_csr(const GeomDev &g, const QueueDev &Q, const DeferRec *rec, const float *out,
                                  unsigned long long n, float p_lo, float p_hi, hipStream_t s) {
     const int blocks = (int)std::max<unsigned long long>(1, std::min<unsigned long long>((n + 255) / 256, 4096));
+    const size_t lds = (size_t)Q.n_poly_total * sizeof(float2);
     if (Q.physics == 0)
-        hipLaunchKernelGGL(sur_resume_csr_kernel<true>, dim3(blocks), dim3(256), 0, s, g, Q, rec, out, n, p_lo, p_hi);
+        hipLaunchKernelGGL(sur_resume_csr_kernel<true>, dim3(blocks), dim3(256), lds, s, g, Q, rec, out, n, p_lo, p_hi);
     else
-        hipLaunchKernelGGL(sur_resume_csr_kernel<false>, dim3(blocks), dim3(256), 0, s, g, Q, rec, out, n, p_lo, p_hi);
+        hipLaunchKernelGGL(sur_resume_csr_kernel<false>, dim3(blocks), dim3(256), lds, s, g, Q, rec, out, n, p_lo, p_hi);
     return hipGetLastError();
 }
 
