@@ -113,6 +113,7 @@ struct vpmc_ctx {
     int tuned_csr_hpl = 0, tuned_csr_blocks = 0, tuned_dense_blocks = 0;
     int tuned_csr_hpl_field[VPMC_MAX_FIELDS] = {};   // per field (CSR), 0 = not tuned
     int tuned_csr_threads = 0, tuned_dense_threads = 0;
+    bool tuning = false;   // the autotuner is timing the queue
     int tuned_dq_blocks = 0, tuned_dq_threads = 0;   // dense runs through the queue (tuned_dense_*: batch by batch)
     hipStream_t cap_stream = nullptr;   // private stream for graph capture
     // aperture surrogate
@@ -1531,6 +1532,27 @@ std::vector<uint32_t> spatial_order(const vpmc_spot *spots, int n) {
     return ord;
 }
 
+// Whether a dense run of one tally grid (no batches, one scenario) is better off
+// batch by batch, where each history has a lane of its own at once and the run
+// takes as long as its longest one; the queue's boxes, draws and beam line only
+// come on top, until its tile's share of the deposits outweighs them.  Behind a
+// block many particles end early and deposit nothing, so that is later.  Batch by
+// batch / through the queue, ms: pencil beam of 4e4 histories 0.36 / 0.42, of 1e5
+// 0.64 / 0.48; 40 mm opening of 1.0e5 0.66 / 0.86, of 1.6e5 0.97 / 0.95, of 2.0e5
+// 1.10 / 0.99 (10 mm 0.74 / 0.82; behind a range shifter of 1.0e5 0.66 / 0.92);
+// without processes, 40 mm, of 2.0e5 0.79 / 0.81, of 2.3e5 (more than the lanes
+// resident at once) 1.04 / 0.92.  A launch shape that is asked for is one of the
+// queue.
+constexpr unsigned long long kFewOpen = 3ull << 14, kFewBlock = 5ull << 15, kFewStraight = 3ull << 16;
+
+bool few_histories(const vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spots, int n_scen, const vpmc_opts *o,
+                   int B) {
+    if (B > 1 || n_scen > 1 || o->grid_blocks || o->block_threads || c->tuning) return false;
+    unsigned long long n = 0;
+    for (int i = 0; i < n_spots; ++i) n += spots[i].n_histories;
+    return n <= (!c->fields[field_id].dev.has_block ? kFewOpen : o->physics ? kFewBlock : kFewStraight);
+}
+
 constexpr size_t kBatchGridBytes = (size_t)8 << 30;   // batch tallies resident at once
 constexpr int kDenseTile = 16384;                     // items of a dense row, at most
 constexpr unsigned long long kDenseRows = 1ull << 20;  // ... up to this many rows (64 MB of them)
@@ -1861,19 +1883,19 @@ int vpmc_run_spots(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spot
     hipStream_t st = (hipStream_t)o->hip_stream;
     HIP_TRY(hipSetDevice(c->device));
     // The work queue, except with the surrogate (its record buffer is per
-    // batch) or a cap on device memory (staging and batch tallies need
-    // scratch): those run batch by batch, one history per lane at a time.
+    // batch), a cap on device memory (staging and batch tallies need scratch) or
+    // few histories: those run batch by batch, one history per lane at a time.
     // Batch by batch / through the queue, 16 batches: pencil beam of 1e5
     // histories in 2 mm water 3.1 / 0.50 ms, water layer of 1e7 45.9 / 13.5 ms,
     // head field of 9.5e6 49.2 / 17.4 ms; LET, 3 scenarios of 2.9e6: 87 / 31 ms.
-    if (!use_sur && !cap) {
+    if (!use_sur && !cap && !few_histories(c, field_id, spots, n_spots, n_scen, o, B)) {
         rc = run_dense_queue(c, field_id, spots, n_spots, scen, n_scen, o, k, B, dose_gy, sigma_gy, ledger_mev);
         if (rc != VPMC_E_OOM) return rc;
         // batch by batch in what that needs: what the attempt grew goes back
         if ((rc = trim_scratch(c))) return rc;
     }
     if (cap && (rc = trim_scratch(c))) return rc;
-    c->qbatch_zero = 0;
+    if (B > 1) c->qbatch_zero = 0;
     if ((rc = ensure(c, c->tallies, (size_t)n_scen * nvox * sizeof(long long), cap))) return rc;
     const bool want_let = (o->flags & VPMC_LET) != 0;
     if (want_let && (rc = ensure(c, c->let_tallies, (size_t)n_scen * nvox * sizeof(long long), cap))) return rc;
@@ -2179,6 +2201,7 @@ int vpmc_autotune(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spots
         ~Tuned() {
             c->tuned_dq_blocks = blocks;
             c->tuned_dq_threads = threads;
+            c->tuning = false;
         }
     } tuned{c, c->tuned_dq_blocks, c->tuned_dq_threads};
     if (csr) {
@@ -2192,6 +2215,7 @@ int vpmc_autotune(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spots
         // histories and 16 batches 6.1 ms, 8.6 ms in workgroups of 512), then
         // sets of the smaller workgroups that dense runs accept
         c->tuned_dq_blocks = c->tuned_dq_threads = 0;
+        c->tuning = true;
         cand.push_back({0, 0, 0});
         for (int t : {512, 256}) cand.push_back({0, std::max(1, cus * waves_cu / (t / 64)), t});
     } else {

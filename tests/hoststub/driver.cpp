@@ -272,7 +272,7 @@ static void autotune(vpmc_ctx *c) {
     g_quick512 = true;
     tune(512, 256 * 16 / 8);
     unsigned long long n = g_launches512;
-    EXPECT(dense(c, 16), VPMC_OK);
+    EXPECT(dense(c, 16, 0, 2), VPMC_OK);   // (with batches: through the queue at any size)
     EXPECT(g_launches512 > n, true);
     n = g_launches512;
     EXPECT(noalloc(c), VPMC_OK);
@@ -288,7 +288,7 @@ static void autotune(vpmc_ctx *c) {
     EXPECT(noalloc(c), VPMC_OK);
     EXPECT(g_launches512 > n, true);
     n = g_launches512;
-    EXPECT(dense(c, 16), VPMC_OK);
+    EXPECT(dense(c, 16, 0, 2), VPMC_OK);
     EXPECT(g_launches512 == n, true);
 }
 
@@ -386,6 +386,22 @@ static void outputs(vpmc_ctx *c) {
                     }
 }
 
+// a dense run of few histories is one transport and one conversion; with
+// batches, or a launch shape that is asked for, it goes through the queue (beam
+// line, boxes, queue, fold or conversion)
+static void few(vpmc_ctx *c) {
+    EXPECT(load(c, 16), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, nullptr, 0, nullptr, nullptr), VPMC_OK);
+    auto launches = [&](int batches, int blocks) {
+        const unsigned long long n = g_launches;
+        EXPECT(dense(c, 16, 0, batches, blocks), VPMC_OK);
+        return (int)(g_launches - n);
+    };
+    EXPECT(launches(0, 0), 2);
+    EXPECT(launches(2, 0), 4);
+    EXPECT(launches(0, 8), 4);
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
@@ -400,6 +416,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(name, "many_histories")) many_histories(c);
     else if (!strcmp(name, "counted")) counted(c);
     else if (!strcmp(name, "outputs")) outputs(c);
+    else if (!strcmp(name, "few")) few(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {
