@@ -9,6 +9,7 @@
 #include <stdlib.h>
 #include <string.h>
 #include <sys/resource.h>
+#include <time.h>
 
 #include <map>
 #include <vector>
@@ -402,6 +403,38 @@ static void few(vpmc_ctx *c) {
     EXPECT(launches(0, 8), 4);
 }
 
+// 2e5 spots: what the host does for a run through the queue stays within six
+// times what it does batch by batch (the quickest of three calls each)
+static void many_spots(vpmc_ctx *c) {
+    EXPECT(load(c, 8), VPMC_OK);
+    EXPECT(vpmc_set_aperture(c, 0, &kBeam, nullptr, 0, nullptr, nullptr), VPMC_OK);
+    std::vector<vpmc_spot> sp(200000, kSpots[0]);
+    unsigned r = 1;
+    auto rnd = [&]() { return (float)((r = r * 1664525u + 1013904223u) >> 8) / (1 << 24); };
+    for (vpmc_spot &s : sp) {
+        s.x_mm = 150.0f * rnd();
+        s.y_mm = 150.0f * rnd();
+        s.energy_mev = 70.0f + 150.0f * rnd();
+        s.n_histories = 5;
+    }
+    std::vector<float> dose(512);
+    double ms[2] = {1e30, 1e30};
+    for (int pass = 0; pass < 6; ++pass) {
+        vpmc_opts o{};
+        o.physics = VPMC_PHYS_ALL;
+        const int queue = pass / 3;
+        o.max_device_bytes = queue ? 0 : (size_t)1 << 30;
+        timespec a, b;
+        clock_gettime(CLOCK_MONOTONIC, &a);
+        EXPECT(vpmc_run_spots(c, 0, sp.data(), (int)sp.size(), &kScen, 1, &o, dose.data(), nullptr, nullptr, nullptr),
+               VPMC_OK);
+        clock_gettime(CLOCK_MONOTONIC, &b);
+        ms[queue] = fmin(ms[queue], (b.tv_sec - a.tv_sec) * 1e3 + (b.tv_nsec - a.tv_nsec) * 1e-6);
+    }
+    printf("host time batch by batch %.2f ms, queue %.2f ms\n", ms[0], ms[1]);
+    EXPECT(ms[1] <= 6.0 * ms[0], true);
+}
+
 int main(int argc, char **argv) {
     vpmc_ctx *c = nullptr;
     EXPECT(vpmc_create(&c, 0), VPMC_OK);
@@ -417,6 +450,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(name, "counted")) counted(c);
     else if (!strcmp(name, "outputs")) outputs(c);
     else if (!strcmp(name, "few")) few(c);
+    else if (!strcmp(name, "many_spots")) many_spots(c);
     else return 2;
     vpmc_destroy(c);
     if (!g_live.empty()) {

@@ -14,7 +14,7 @@ HIPCC = "/opt/rocm/bin/hipcc"
 PKG = os.path.join(ROOT, "paper_2307_01416_amd")
 ENV = dict(os.environ, ASAN_OPTIONS="detect_leaks=0", UBSAN_OPTIONS="halt_on_error=1:print_stacktrace=1")
 CASES = ["geometry", "aperture", "slots", "fallback", "next_call", "autotune", "blocks", "many_histories",
-         "counted", "outputs", "few"]
+         "counted", "outputs", "few", "many_spots"]
 
 
 @pytest.fixture(scope="module")
