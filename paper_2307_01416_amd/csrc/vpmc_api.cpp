@@ -1277,9 +1277,7 @@ int vpmc_load_geometry(vpmc_ctx *c, int kind, const int16_t *hu, int nx, int ny,
         const size_t margin = (size_t)nx * ny, total = nvox + 2 * margin;
         if ((rc = ensure(c, c->rho_buf, total * sizeof(float), 0, 0))) return rc;
         float *rho = (float *)c->rho_buf.ptr;
-        HIP_TRY(hipMemset(rho, 0, margin * sizeof(float)));
-        HIP_TRY(hipMemset(rho + margin + nvox, 0, margin * sizeof(float)));
-        HIP_TRY(launch_density(g.hu, rho + margin, nvox, nullptr));
+        HIP_TRY(launch_density(g.hu, rho, margin, nvox, nullptr));
         HIP_TRY(hipStreamSynchronize(nullptr));   // runs may use any stream
         g.rho = rho + margin;
     }

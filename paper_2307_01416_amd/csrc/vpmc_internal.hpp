@@ -266,7 +266,7 @@ inline unsigned long long queue_stage_min(int blocks, int threads, int hist_per_
     return (unsigned long long)blocks * (unsigned long long)((threads + 63) / 64) * 64ull * (unsigned long long)hps;
 }
 hipError_t launch_derive_tables(float *blob, hipStream_t s);
-hipError_t launch_density(const int16_t *hu, float *rho, size_t n, hipStream_t s);
+hipError_t launch_density(const int16_t *hu, float *rho, size_t margin, size_t n, hipStream_t s);
 hipError_t launch_tile_box(const GeomDev &g, const QueueDev &Q, RowDev *rows, hipStream_t s);
 hipError_t launch_beam(const GeomDev &g, QueueDev Q, int cus, hipStream_t s);
 hipError_t launch_queue(const GeomDev &g, const QueueDev &Q, int blocks, int threads, hipStream_t s);

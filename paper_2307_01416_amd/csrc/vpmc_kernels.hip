@@ -2964,10 +2964,11 @@ __global__ void derive_tables_kernel(float *blob) {
     tm[T_RS * NE + i] = rcp_nr(tm[T_SH * NE + i]);
 }
 
-__global__ void density_kernel(const int16_t *hu, float *rho, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+// densities of n voxels between two margins of zeros
+__global__ void density_kernel(const int16_t *hu, float *rho, size_t margin, size_t n) {
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n + 2 * margin; i += (size_t)gridDim.x * blockDim.x) {
         int m;
-        rho[i] = hu_density<false>((int)hu[i], m).h;
+        rho[i] = i - margin < n ? hu_density<false>((int)hu[i - margin], m).h : 0.0f;
     }
 }
 
@@ -3241,9 +3242,9 @@ hipError_t launch_derive_tables(float *blob, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_density(const int16_t *hu, float *rho, size_t n, hipStream_t s) {
-    const int blocks = (int)std::min<size_t>((n + 255) / 256, 8192);
-    hipLaunchKernelGGL(density_kernel, dim3(blocks), dim3(256), 0, s, hu, rho, n);
+hipError_t launch_density(const int16_t *hu, float *rho, size_t margin, size_t n, hipStream_t s) {
+    const int blocks = (int)std::min<size_t>((n + 2 * margin + 255) / 256, 8192);
+    hipLaunchKernelGGL(density_kernel, dim3(blocks), dim3(256), 0, s, hu, rho, margin, n);
     return hipGetLastError();
 }
 
