@@ -2746,15 +2746,17 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
     if (c->device < 0) return fail(VPMC_E_STATE, "validation-only context has no device");
     HIP_TRY(hipSetDevice(c->device));
     const size_t R = (size_t)n_rows;
-    // (behind the row pointers: each row's first piece and, for host arrays, its output offset)
-    if ((rc = ensure(c, c->cl_rp, 3 * (R + 1) * 8, 0))) return rc;
-    long long *d_first = (long long *)c->cl_rp.ptr + (R + 1), *d_rpo = d_first + (R + 1);
+    // row pointers, and behind them each row's first piece
+    if ((rc = ensure(c, c->cl_rp, 2 * (R + 1) * 8, 0))) return rc;
+    long long *const d_first = (long long *)c->cl_rp.ptr + (R + 1);
     if (!dev && (rc = ensure(c, c->cl_map, (size_t)nvox * 4, 0))) return rc;
     if ((rc = ensure(c, c->cl_start, ((size_t)n_cells + 1) * 4, 0))) return rc;
     if ((rc = ensure(c, c->cl_mass, (size_t)n_cells * 8, 0))) return rc;
     // pieces of at most kCellPiece entries, row by row
     std::vector<CellPiece> pcs;
-    std::vector<long long> first_piece(R + 1);
+    std::vector<long long> rows(2 * (R + 1));
+    std::copy(rp.begin(), rp.end(), rows.begin());
+    long long *const first_piece = rows.data() + (R + 1);
     for (size_t r = 0; r < R; ++r) {
         first_piece[r] = (long long)pcs.size();
         for (long long q0 = rp[r]; q0 < rp[r + 1]; q0 += kCellPiece)
@@ -2766,8 +2768,7 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
     if ((rc = ensure(c, c->cl_cnt, std::max<size_t>(NP, 1) * 8, 0))) return rc;
     if ((rc = ensure(c, c->cl_out, (NP + 1) * 8, 0))) return rc;
     if ((rc = ensure(c, c->flags, 4, 0))) return rc;
-    HIP_TRY(hipMemcpy(c->cl_rp.ptr, rp.data(), rp.size() * 8, hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(d_first, first_piece.data(), (R + 1) * 8, hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(c->cl_rp.ptr, rows.data(), rows.size() * 8, hipMemcpyHostToDevice));
     const int32_t *d_map = cell_of_voxel;
     if (!dev) {
         HIP_TRY(hipMemcpy(c->cl_map.ptr, cell_of_voxel, (size_t)nvox * 4, hipMemcpyHostToDevice));
@@ -2797,10 +2798,12 @@ int vpmc_csr_cells(vpmc_ctx *c, const int64_t *row_ptr, int n_rows, const int32_
     if (err & 1u) return fail(VPMC_E_ARG, "a column index is outside [0, nvox)");
     if (err & 2u) return fail(VPMC_E_ARG, "columns are not ascending within a row");
     long long nout = 0;
-    HIP_TRY(launch_cell_rows(d_first, (const long long *)c->cl_out.ptr, R + 1, dev ? (long long *)row_ptr_out : d_rpo,
-                             nullptr));
-    if (!dev) {
-        HIP_TRY(hipMemcpy(row_ptr_out, d_rpo, (R + 1) * 8, hipMemcpyDeviceToHost));
+    if (dev) {
+        HIP_TRY(launch_cell_rows(d_first, (const long long *)c->cl_out.ptr, R + 1, (long long *)row_ptr_out, nullptr));
+    } else {
+        std::vector<long long> pout(NP + 1);
+        HIP_TRY(hipMemcpy(pout.data(), c->cl_out.ptr, pout.size() * 8, hipMemcpyDeviceToHost));
+        for (size_t r = 0; r <= R; ++r) row_ptr_out[r] = pout[(size_t)first_piece[r]];
         nout = row_ptr_out[R];
     }
     if (!cell_out && !q_out && !val_out) {
