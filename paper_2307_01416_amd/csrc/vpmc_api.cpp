@@ -631,7 +631,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     Q.ledger = (unsigned long long *)c->ledger.ptr;
     Q.stats = (unsigned long long *)c->stats.ptr;
     Q.tables = c->d_tables;
-    Q.iter_cap = o->queue_cap ? (unsigned long long)o->queue_cap : kDefaultQueueCap;
+    Q.iter_cap = 4ull * (o->queue_cap ? std::min<unsigned long long>(o->queue_cap, 1ull << 61) : kDefaultQueueCap);
     Q.flags = (unsigned int *)c->flags.ptr;
 
     if ((rc = ensure(c, c->q_ctl, (size_t)std::max(R, 1) * sizeof(RowCtl), cap))) return rc;
@@ -663,7 +663,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
         Qe.hist_per_lane = std::max(1, ep_hpl[e]);
         // a default draw (64 records) is a quarter of an iteration: callers
         // choose queue_cap by chunks of 256 histories
-        Qe.draw_mask = ep_hpl[e] ? 0u : 3u;
+        Qe.draw_cost = ep_hpl[e] ? 4u : 1u;
         return Qe;
     };
     // beam line and patient transport of an epoch, round by round
@@ -807,7 +807,7 @@ int run_csr(vpmc_ctx *c, const std::vector<BatchField> &bf, const vpmc_scenario 
     c->slots_dirty = false;   // every launched epoch was compacted, which clears its slots
     if (fl & kFlagAborted)
         return fail(VPMC_E_ABORTED, "a wavefront reached the work-queue cap of %llu iterations; no rows written",
-                    (unsigned long long)Q.iter_cap);
+                    Q.iter_cap / 4);
     std::vector<int64_t> rp((size_t)R + 1);
     for (int r = 0; r < R; ++r) rp[r] = (int64_t)roff[r];
     rp[R] = (int64_t)used_host;
@@ -1769,7 +1769,8 @@ int run_dense_queue(vpmc_ctx *c, int field_id, const vpmc_spot *spots, int n_spo
     Q.ledger = (unsigned long long *)(base + a_led);
     Q.stats = Q.ledger + n_led;
     Q.tables = c->d_tables;
-    Q.iter_cap = kDefaultQueueCap;
+    Q.iter_cap = 4ull * kDefaultQueueCap;
+    Q.draw_cost = 4;
     Q.flags = (unsigned int *)(Q.stats + 2);
 
     const double mev_scale = ldexp(MEV_TO_J, -k);

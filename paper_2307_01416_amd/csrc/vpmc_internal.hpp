@@ -245,8 +245,8 @@ struct QueueDev {
     unsigned long long *stats;            // [2]
     const float *tables;
     SurDev sur;                           // surrogate queue (enabled = 0: off)
-    unsigned long long iter_cap;          // work-queue iterations a wavefront may make
-    uint32_t draw_mask;                   // draws that count as one of them, less one (0 or 3)
+    unsigned long long iter_cap;          // quarters of work-queue iterations a wavefront may make
+    uint32_t draw_cost;                   // those of a draw (4, or 1 of the default size)
     unsigned int *flags;                  // bit 2 (value 4) set when a wavefront reached iter_cap
 };
 constexpr unsigned long long kDefaultQueueCap = 1ull << 40;   // far above any run's chunk count

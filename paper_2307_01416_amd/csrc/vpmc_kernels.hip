@@ -2005,14 +2005,13 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
     const unsigned long long below = (1ull << lane) - 1ull;
     RowCtl *const ctl = Q.ctl + Q.row_begin;
     const uint32_t draw_n = 64u * (uint32_t)min(Q.hist_per_lane, kStageHpl);   // (few enough for the 32-bit counters)
-    unsigned long long iters = 0;
-    uint32_t drawn = 0;
-    auto drew = [&]() { iters += (++drawn & Q.draw_mask) == 0u ? 1 : 0; };
+    unsigned long long iters = 0;   // in quarters
     for (;;) {
         // ---- bounded queue: a wavefront that has made iter_cap iterations
-        // (draws by drew(), row picks, waits) leaves and reports it; it holds
-        // no row pick and no tile here, so the other waves finish as before
-        if (++iters > Q.iter_cap) {
+        // (draws, row picks, waits) leaves and reports it; it holds no row
+        // pick and no tile here, so the other waves finish as before
+        iters += 4;
+        if (iters > Q.iter_cap) {
             if (lane == 0) atomicOr(Q.flags, kFlagAborted);
             break;
         }
@@ -2076,8 +2075,7 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
             }
             continue;
         }
-        --iters;   // (not a pick or a wait)
-        drew();
+        iters -= 4u - Q.draw_cost;   // (not a pick or a wait)
         const uint32_t rl = cur;
         const RowDev row = Q.rows[Q.row_begin + rl];
         float scale = DENSE ? 0.0f : Q.spots[row.spot_global].scale;   // (dense rows: per lane)
@@ -2160,7 +2158,7 @@ __global__ __launch_bounds__(X ? 768 : 1024) void queue_kernel(GeomDev g, QueueD
                 } else {
                     draw();
                     if (next >= end) n_staged = end = next = 0;   // the row is exhausted
-                    else drew();
+                    else iters += Q.draw_cost;
                 }
             }
             // a wave that started beside the previous row's stragglers gets
