@@ -1530,7 +1530,9 @@ int dense_blocks(const vpmc_ctx *c, const vpmc_opts *o, unsigned long long items
 // 5.0 so.
 std::vector<uint32_t> spatial_order(const vpmc_spot *spots, int n) {
     std::vector<uint64_t> a((size_t)n), b((size_t)n);
-    auto square = [](float x) { return (int32_t)(std::min(std::max(x * 0.1f, -1e6f), 1e6f) + 0x1p20f); };
+    auto square = [](float x) {   // floor(x / 10), from 2^20 on
+        return (int32_t)(std::min(std::max(x / 10.0, -1e6), 1e6) + 0x1p20);
+    };
     int32_t lo[2] = {1 << 30, 1 << 30}, hi[2] = {0, 0};
     for (int i = 0; i < n; ++i) {
         const int32_t x = square(spots[i].x_mm), y = square(spots[i].y_mm);
